@@ -1320,37 +1320,16 @@ fosb_status fosb_lowrank_create(fosb_context* ctx, const fosb_level* const* leve
   check_device_memory(*ctx, (int64_t)max_rank * nc * 8 + 7 * nc * 8, "the low-rank factor");
   hipStream_t s = ctx->stream;
   DevBuf X((size_t)3 * nc * sizeof(double)), Nn((size_t)3 * nc * sizeof(double)), d((size_t)nc * sizeof(double));
-  DevBuf pv(2 * sizeof(double));
   lr->L.alloc((size_t)max_rank * nc * sizeof(double));
   for (int32_t i = 0; i < n_levels; ++i)
     lr_candidates(s, *levels[i], lr->off[i], nc, X.as<double>(), Nn.as<double>());
   lr_diag(s, Nn.as<double>(), nc, *cov, d.as<double>());
-  // Greedy pivoted Cholesky: the host reads each pivot (its remaining diagonal
-  // entry decides termination) and launches the column update.
   constexpr double kTie = 1e-9;
-  double dmax0 = -1.0, last = 0.0;
-  for (int32_t j = 0; j < max_rank; ++j) {
-    double h[2];
-    lr_pivot(s, d.as<double>(), nc, kTie, pv.as<double>());
-    FOSB_HIP(hipMemcpyAsync(h, pv.p, sizeof(h), hipMemcpyDeviceToHost, s));
-    FOSB_HIP(hipStreamSynchronize(s));
-    if (j == 0) dmax0 = h[0];
-    last = h[0];
-    if (!(h[0] > tol * dmax0) || !(h[0] > 0.0)) break;
-    const int64_t p = (int64_t)h[1];
-    lr_column(s, X.as<double>(), Nn.as<double>(), nc, *cov, lr->L.as<double>(), j, p, h[0], d.as<double>());
-    lr->pivots.push_back(p);
-    lr->rank = j + 1;
-  }
-  if (lr->rank == max_rank) {  // the largest remaining diagonal entry after the last column
-    double h[2];
-    lr_pivot(s, d.as<double>(), nc, kTie, pv.as<double>());
-    FOSB_HIP(hipMemcpyAsync(h, pv.p, sizeof(h), hipMemcpyDeviceToHost, s));
-    FOSB_HIP(hipStreamSynchronize(s));
-    last = h[0];
-  }
-  lr->residual = dmax0 > 0 ? last / dmax0 : 0.0;
-  FOSB_HIP(hipStreamSynchronize(s));
+  LrState st{};
+  lr_factor(s, X.as<double>(), Nn.as<double>(), nc, *cov, kTie, tol, max_rank, lr->L.as<double>(), d.as<double>(), st,
+            lr->pivots);
+  lr->rank = st.rank;
+  lr->residual = st.dmax0 > 0 ? st.last / st.dmax0 : 0.0;
   *out = lr.release();
   API_END
 }

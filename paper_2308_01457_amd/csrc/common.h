@@ -494,10 +494,20 @@ void zero_f64(hipStream_t s, double* p, int64_t n);
 // (candidates Xc, Nc: [3][nc]; factor L column-major, L[k * nc + i]).
 void lr_candidates(hipStream_t s, const Level& l, int64_t off, int64_t nc, double* Xc, double* Nc);
 void lr_diag(hipStream_t s, const double* Nc, int64_t nc, const fosb_cov& cov, double* d);
-// out (device, 2 doubles) = {d[p], p}: p the lowest index with d[p] >= (1 - tie) max d
-void lr_pivot(hipStream_t s, const double* d, int64_t nc, double tie, double* out);
-void lr_column(hipStream_t s, const double* Xc, const double* Nc, int64_t nc, const fosb_cov& cov, double* L, int j,
-               int64_t p, double dp, double* d);
+// Greedy pivoted Cholesky of the covariance on the candidates: columns of L
+// until the largest remaining d falls to tol times the first pivot's, or
+// max_rank columns (pivot: the lowest index p with d[p] >= (1 - tie) max d).
+// d (the covariance's diagonal) is consumed; synchronises the stream.
+struct LrState {
+  int32_t rank;     // columns formed
+  int32_t done;
+  double dmax0;     // d of the first pivot
+  double last;      // d of the pivot chosen last (the remainder once done)
+  double dp;        // the current column's pivot value and index
+  long long p;
+};
+void lr_factor(hipStream_t s, const double* Xc, const double* Nc, int64_t nc, const fosb_cov& cov, double tie,
+               double tol, int max_rank, double* L, double* d, LrState& out, std::vector<int64_t>& pivots);
 // M (N x rank) = Wgt_dir L_l with L_l the factor's rows [off, off + 6 nt) (Lr: scratch, 6 nt x rank doubles)
 // the level's rows of the factor, node-major (Q x rank); a real array widened to complex128
 void lr_rows(hipStream_t s, const Level& l, const double* L, int64_t nc, int64_t off, int rank, double* Lr);

@@ -62,67 +62,172 @@ void lr_diag(hipStream_t s, const double* Nc, int64_t nc, const fosb_cov& cov, d
   FOSB_LAUNCH_CHECK();
 }
 
-// One workgroup: the largest d, then the lowest index i with d[i] >= (1 - tie) max,
-// out = {d[i], i}.  The maximum and the first index are order-independent.
-__global__ __launch_bounds__(1024) void k_lr_pivot(const double* __restrict__ d, int64_t nc, double tie,
-                                                   double* __restrict__ out) {
+// The greedy factorisation runs on the device, two launches per column: the
+// pivot kernel and the column kernel, ordered by the stream.  The host only
+// reads the state once per batch of columns, so no column waits for it.
+// pm[b] is the largest d of block b of LR_ROWS consecutive candidates.
+constexpr int LR_ROWS = 64;    // candidates per workgroup of the column kernel: one per lane
+constexpr int LR_SPLIT = 4;    // wavefronts of a workgroup, each summing a share of the previous columns
+
+__device__ __forceinline__ double wave_max_f64(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+  return v;
+}
+
+__global__ __launch_bounds__(64) void k_lr_block_max(const double* __restrict__ d, int64_t nc, double* __restrict__ pm) {
+  const int64_t i = (int64_t)blockIdx.x * LR_ROWS + threadIdx.x;
+  const double m = wave_max_f64(i < nc ? d[i] : -1.0);
+  if (threadIdx.x == 0) pm[blockIdx.x] = m;
+}
+
+// Pivot of column j: p, the lowest index with d[p] >= (1 - tie) max d.  The
+// block maxima give max d and the first block that holds such an index, so one
+// workgroup reads nblk + LR_ROWS values instead of scanning d twice (19.5 us a
+// column over 40320 candidates before, 6 us now).  Row p of the previous
+// columns is gathered into prow for the column kernel.  With j = max_rank, or
+// once d[p] falls to tol times the first pivot's value, the state is done and
+// the launches that follow it return at once.
+__global__ __launch_bounds__(1024) void k_lr_pivot(const double* __restrict__ d, int64_t nc,
+                                                   const double* __restrict__ pm, int nblk, double tie, double tol,
+                                                   int j, int max_rank, const double* __restrict__ L,
+                                                   double* __restrict__ prow, int64_t* __restrict__ piv,
+                                                   LrState* __restrict__ st) {
   __shared__ double sm[1024];
-  __shared__ long long si[1024];
+  __shared__ int sb[1024];
+  __shared__ long long sp;
+  if (st->done) return;
+  const int tid = threadIdx.x;
   double m = -1.0;
-  for (int64_t i = threadIdx.x; i < nc; i += 1024) m = fmax(m, d[i]);
-  sm[threadIdx.x] = m;
+  for (int b = tid; b < nblk; b += 1024) m = fmax(m, pm[b]);
+  sm[tid] = m;
   __syncthreads();
   for (int o = 512; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) sm[threadIdx.x] = fmax(sm[threadIdx.x], sm[threadIdx.x + o]);
+    if (tid < o) sm[tid] = fmax(sm[tid], sm[tid + o]);
     __syncthreads();
   }
   const double thr = (1.0 - tie) * sm[0];
-  __syncthreads();
-  long long best = nc;
-  for (int64_t i = threadIdx.x; i < nc; i += 1024)
-    if (d[i] >= thr) {
-      best = i;
+  int best = nblk;
+  for (int b = tid; b < nblk; b += 1024)
+    if (pm[b] >= thr) {
+      best = b;
       break;
     }
-  si[threadIdx.x] = best;
+  sb[tid] = best;
   __syncthreads();
   for (int o = 512; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) si[threadIdx.x] = min(si[threadIdx.x], si[threadIdx.x + o]);
+    if (tid < o) sb[tid] = min(sb[tid], sb[tid + o]);
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    const long long p = si[0] < nc ? si[0] : 0;
-    out[0] = d[p];
-    out[1] = (double)p;
+  if (tid < 64) {
+    const int64_t i = (int64_t)sb[0] * LR_ROWS + tid;
+    const bool hit = sb[0] < nblk && i < nc && d[i] >= thr;
+    const unsigned long long mask = __ballot(hit);
+    const long long p = mask ? (long long)sb[0] * LR_ROWS + __ffsll(mask) - 1 : 0;
+    if (tid == 0) {
+      const double dp = d[p];
+      if (j == 0) st->dmax0 = dp;
+      st->last = dp;
+      if (j >= max_rank || !(dp > tol * st->dmax0) || !(dp > 0.0)) {
+        st->done = 1;
+      } else {
+        st->rank = j + 1;
+        st->p = p;
+        st->dp = dp;
+        piv[j] = p;
+      }
+      sp = p;
+    }
   }
+  __syncthreads();
+  const int64_t p = sp;
+  for (int k = tid; k < j; k += 1024) prow[k] = L[(int64_t)k * nc + p];
 }
 
-void lr_pivot(hipStream_t s, const double* d, int64_t nc, double tie, double* out) {
-  hipLaunchKernelGGL(k_lr_pivot, dim3(1), dim3(1024), 0, s, d, nc, tie, out);
-  FOSB_LAUNCH_CHECK();
-}
-
-// Column j of the factor (column-major, L[k * nc + i]):
+// Column j of the factor (column-major, L[k * nc + i]) for the pivot of the state:
 //   L[j][i] = (K(x_i, x_p) - sum_{k<j} L[k][i] L[k][p]) / sqrt(dp),  d[i] -= L[j][i]^2,  d[p] = 0.
-__global__ __launch_bounds__(256) void k_lr_column(const double* __restrict__ Xc, const double* __restrict__ Nc,
-                                                   int64_t nc, LrCov cp, double* __restrict__ L, int j, int64_t p,
-                                                   double dp, double* __restrict__ d) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nc) return;
-  const double e0 = Xc[i] - Xc[p], e1 = Xc[nc + i] - Xc[nc + p], e2 = Xc[2 * nc + i] - Xc[2 * nc + p];
-  const double nd = Nc[i] * Nc[p] + Nc[nc + i] * Nc[nc + p] + Nc[2 * nc + i] * Nc[2 * nc + p];
-  double c = lr_cov(cp, e0 * e0 + e1 * e1 + e2 * e2, nd);
-  for (int k = 0; k < j; ++k) c -= L[(int64_t)k * nc + i] * L[(int64_t)k * nc + p];
-  const double v = c / sqrt(dp);
-  L[(int64_t)j * nc + i] = v;
-  d[i] = (i == p) ? 0.0 : d[i] - v * v;
+// Bound by reading the previous columns (8 j nc bytes).  One lane per candidate
+// and one serial sum per lane kept too few loads in flight: 104 us a column on
+// average at nc = 40320, j up to 775 (1.2 TB/s).  The columns are dealt to four
+// wavefronts, each with eight loads in flight, and row p comes from the gathered
+// copy through scalar loads; the four partial sums are added in a fixed order.
+__global__ __launch_bounds__(LR_ROWS * LR_SPLIT) void k_lr_column(const double* __restrict__ Xc,
+                                                                  const double* __restrict__ Nc, int64_t nc, LrCov cp,
+                                                                  double* __restrict__ L,
+                                                                  const double* __restrict__ prow, int j,
+                                                                  double* __restrict__ d, double* __restrict__ pm,
+                                                                  const LrState* __restrict__ st) {
+  __shared__ double part[LR_SPLIT][LR_ROWS];
+  if (st->done) return;
+  const int lane = threadIdx.x & 63;
+  const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i = (int64_t)blockIdx.x * LR_ROWS + lane;
+  const int64_t ir = i < nc ? i : nc - 1;   // lanes past the end read the last candidate and store nothing
+  const int share = (j + LR_SPLIT - 1) / LR_SPLIT;
+  const int k0 = g * share, k1 = min(j, k0 + share);
+  double acc = 0.0;
+  int k = k0;
+  for (; k + 8 <= k1; k += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = L[(int64_t)(k + u) * nc + ir];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc = fma(v[u], prow[k + u], acc);
+  }
+  for (; k < k1; ++k) acc = fma(L[(int64_t)k * nc + ir], prow[k], acc);
+  part[g][lane] = acc;
+  __syncthreads();
+  if (threadIdx.x >= LR_ROWS) return;
+  const int64_t p = st->p;
+  const double e0 = Xc[ir] - Xc[p], e1 = Xc[nc + ir] - Xc[nc + p], e2 = Xc[2 * nc + ir] - Xc[2 * nc + p];
+  const double nd = Nc[ir] * Nc[p] + Nc[nc + ir] * Nc[nc + p] + Nc[2 * nc + ir] * Nc[2 * nc + p];
+  const double c = lr_cov(cp, e0 * e0 + e1 * e1 + e2 * e2, nd) -
+                   ((part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]));
+  const double v = c / sqrt(st->dp);
+  double dn = -1.0;
+  if (i < nc) {
+    L[(int64_t)j * nc + i] = v;
+    dn = (i == p) ? 0.0 : d[i] - v * v;
+    d[i] = dn;
+  }
+  const double m = wave_max_f64(dn);
+  if (lane == 0) pm[blockIdx.x] = m;
 }
 
-void lr_column(hipStream_t s, const double* Xc, const double* Nc, int64_t nc, const fosb_cov& cov, double* L, int j,
-               int64_t p, double dp, double* d) {
-  hipLaunchKernelGGL(k_lr_column, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, Xc, Nc, nc, lr_params(cov),
-                     L, j, p, dp, d);
+// Columns are enqueued in batches of this many between two reads of the state;
+// launches past the last column return at once (a few microseconds each).
+constexpr int LR_BATCH = 32;
+
+void lr_factor(hipStream_t s, const double* Xc, const double* Nc, int64_t nc, const fosb_cov& cov, double tie,
+               double tol, int max_rank, double* L, double* d, LrState& out, std::vector<int64_t>& pivots) {
+  const int64_t nblk = (nc + LR_ROWS - 1) / LR_ROWS;
+  if (nblk > INT32_MAX) fail(FOSB_E_UNSUPPORTED, "low-rank factor over %lld nodes", (long long)nc);
+  DevBuf pm((size_t)nblk * sizeof(double)), prow((size_t)max_rank * sizeof(double));
+  DevBuf piv((size_t)max_rank * sizeof(int64_t)), state(sizeof(LrState));
+  LrState h{};
+  FOSB_HIP(hipMemcpyAsync(state.p, &h, sizeof(h), hipMemcpyHostToDevice, s));
+  hipLaunchKernelGGL(k_lr_block_max, dim3((unsigned)nblk), dim3(64), 0, s, d, nc, pm.as<double>());
   FOSB_LAUNCH_CHECK();
+  for (int j = 0; j <= max_rank; ++j) {   // the pivot of column max_rank only measures the remainder
+    hipLaunchKernelGGL(k_lr_pivot, dim3(1), dim3(1024), 0, s, d, nc, pm.as<double>(), (int)nblk, tie, tol, j, max_rank,
+                       L, prow.as<double>(), piv.as<int64_t>(), state.as<LrState>());
+    FOSB_LAUNCH_CHECK();
+    if (j < max_rank) {
+      hipLaunchKernelGGL(k_lr_column, dim3((unsigned)nblk), dim3(LR_ROWS * LR_SPLIT), 0, s, Xc, Nc, nc, lr_params(cov),
+                         L, prow.as<double>(), j, d, pm.as<double>(), state.as<LrState>());
+      FOSB_LAUNCH_CHECK();
+    }
+    if (j % LR_BATCH == LR_BATCH - 1 || j == max_rank) {
+      FOSB_HIP(hipMemcpyAsync(&h, state.p, sizeof(h), hipMemcpyDeviceToHost, s));
+      FOSB_HIP(hipStreamSynchronize(s));
+      if (h.done) break;
+    }
+  }
+  pivots.resize(h.rank);
+  if (h.rank > 0)
+    FOSB_HIP(hipMemcpyAsync(pivots.data(), piv.p, (size_t)h.rank * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  FOSB_HIP(hipStreamSynchronize(s));
+  out = h;
 }
 
 // Row-major copy of rows [off, off + n) of the column-major factor: Lr[i][k] = L[k][off + i].

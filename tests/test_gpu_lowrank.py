@@ -113,3 +113,29 @@ def test_lowrank_full_size(fz, precision, tol):
           f"solves + far field {t2 - t1:.3f} s, vs oracle dense {e:.2e}", flush=True)
     assert e < tol
     lr.close()
+
+
+@pytest.mark.parametrize("max_rank", [1, 31, 32, 33, 120])
+def test_lowrank_columns_at_batch_edges(fz, max_rank):
+    """The device-side factorisation around its batch of 32 columns, on 120 nodes (no
+    multiple of the 64 candidates of a workgroup), up to full rank: the oracle's
+    pivots, and the factor through Sigma = Y Y^H = Z^{-1} W L L^T W^H Z^{-H}.
+    The last pivots of the full-rank factor are near the rounding of the
+    diagonal, so only those above 1e-6 of the first are compared there."""
+    fosb, ctx, torch = fz
+    from oracle import lowrank, uq
+    V, F = workloads.geodesic_sphere(1)
+    V = V * np.array([0.8, 1.0, 1.2])
+    lv = _levels(fosb, ctx, [(V, F)], 1.0, fosb.FP64)
+    lr = fosb.LowRank(ctx, lv, fosb.make_cov("gaussian", SIG, ELL), max_rank, 0.0)
+    ol = uq.make_level(V, F, 1.0)
+    piv, Lf, res = lowrank.pivoted_cholesky("gaussian", SIG, ELL, ol.X, ol.Nq, max_rank, 0.0)
+    head = int(np.sum(np.square(Lf[piv, np.arange(len(piv))]) > 1e-6 * SIG ** 2))
+    assert np.array_equal(lr.pivots[:head], piv[:head])
+    assert abs(lr.residual - res) <= 1e-12
+    if max_rank <= 33:
+        assert lr.rank == len(piv) == max_rank
+        Y = lr.factor(0)
+        S = (Y @ Y.conj().T).cpu().numpy()
+        M = np.linalg.solve(ol.Z, ol.Wgt @ Lf)
+        assert _rel(S, M @ M.conj().T) < 1e-10
