@@ -73,7 +73,7 @@ static void merge_level_certificate(fosb_stats* dst, const Level& L) {
 // B <- Z^{-1} B (or Z^{-H} B) for a factorised level; MIXED levels refine in FP64.
 // With P Z = L U:  Z^{-1} = U^{-1} L^{-1} P  and  Z^{-H} = P^T L^{-H} U^{-H}.
 void level_solve_inplace(Context& ctx, const Level& L, c128* B, int64_t ldb, int64_t nrhs, fosb_stats* st,
-                         bool adjoint, int max_sweeps) {
+                         bool adjoint, int max_sweeps, double tol_factor) {
   hipStream_t s = ctx.stream;
   const int64_t n = L.n;
   if (nrhs <= 0) return;
@@ -155,7 +155,7 @@ void level_solve_inplace(Context& ctx, const Level& L, c128* B, int64_t ldb, int
     rel = nn[1] > 0 ? std::sqrt(nn[0] / nn[1]) : 0.0;
     est = it == 0 ? 1.0 : rel * rel / prev;
     if (it > 0) sweeps = it;
-    if (est <= L.opts.ir_tol || it >= sweep_limit || (it > 1 && rel >= prev)) break;
+    if (est <= tol_factor * L.opts.ir_tol || it >= sweep_limit || (it > 1 && rel >= prev)) break;
     prev = rel;
     // residual R = Bo - op(Z64) X in FP64 (scratch[5])
     copy_c128(s, Bo, nrhs, Rw, nrhs, n, nrhs);
@@ -365,6 +365,13 @@ static double inverse_norm1_estimate(Context& c, const Level& L) {
   return std::max(est, 2.0 * norm1() / (3.0 * (double)n));
 }
 
+// The first moments enter every right-hand side of their level, so their
+// refinement aims below ir_tol.  With ir_tol = 1e-10 the levels up to N = 7680
+// stop after one sweep or two depending on the last digit of the first
+// correction (estimate 6e-11); one that stopped after one left 7.5e-10 in a
+// Sigma block.  The other sweep costs 0.6 ms there.
+constexpr double kFirstMomentTol = 0.1;
+
 // Factorisation, first moments and RHS weights of one level, on c's stream.
 static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh, double k, int32_t precision,
                                                void* Z, int64_t ldz, void* Zlow, int64_t ldzlow, const double* dirs,
@@ -483,7 +490,7 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
     L->b.alloc((size_t)n * n_dirs * sizeof(c128));
     incident_rhs_pmchwt(s, *mesh, k, ddir.as<double>(), dpol.as<double>(), (int)n_dirs, L->b.as<c128>());
     copy_c128(s, L->b.as<c128>(), n_dirs, L->u.as<c128>(), n_dirs, n, n_dirs);
-    level_solve_inplace(c, *L, L->u.as<c128>(), n_dirs, n_dirs, nullptr);
+    level_solve_inplace(c, *L, L->u.as<c128>(), n_dirs, n_dirs, nullptr, false, -1, kFirstMomentTol);
     if (sd_field >= 0) {  // shape-derivative weights per incidence, and the nodes for the covariance
       const int64_t Q = 6LL * mesh->h.nt;
       L->sd_field = sd_field;
@@ -506,7 +513,7 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
   L->qx.alloc((size_t)3 * 6 * mesh->h.nt * sizeof(double));
   quad_nodes(s, *mesh, L->qx.as<double>());
   incident_rhs(s, *mesh, k, ddir.as<double>(), dpol.as<double>(), (int)n_dirs, L->u.as<c128>());
-  level_solve_inplace(c, *L, L->u.as<c128>(), n_dirs, n_dirs, nullptr);
+  level_solve_inplace(c, *L, L->u.as<c128>(), n_dirs, n_dirs, nullptr, false, -1, kFirstMomentTol);
   L->W.alloc((size_t)n_dirs * mesh->h.nt * 18 * sizeof(c128));
   for (int64_t d = 0; d < n_dirs; ++d)
     rhs_weights(s, *mesh, k, field, L->u.as<c128>() + d, n_dirs, L->W.as<c128>() + d * mesh->h.nt * 18);

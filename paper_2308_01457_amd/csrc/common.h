@@ -158,6 +158,7 @@ struct Context {
   DevBuf norms;       // refinement norms: 2 doubles + per-block partials
   DevBuf splitk;      // partial products of split-K GEMMs
   DevBuf tune_out;    // scratch output of autotuning runs
+  DevBuf pack_a, pack_ma, pack_b, pack_mb, pack_ke;   // split products: packed operands, their maxima, scaling along K
   hipEvent_t tune_ev[2] = {nullptr, nullptr};
   // handles created on this context and not yet destroyed: destroying the
   // context detaches them (their ctx becomes null), so a later destroy of a
@@ -363,6 +364,20 @@ inline int tile_variant_count(int fp64) { return fp64 ? 3 : 4; }
 template <typename T>
 void gemm_ch(Context& ctx, int64_t M, int64_t N, int64_t K, double alpha, const cplx<T>* A, int64_t lda,
              const cplx<T>* B, int64_t ldb, double beta, cplx<T>* C, int64_t ldc);
+// gemm16.hip: C = beta C + alpha A B for complex64 operands on the fp16 matrix
+// cores.  Both operands are packed into the context's buffers first (A, or A^H
+// of a stored K x M matrix; B), then multiplied: rows [row0, row0 + M) of the
+// packed A (row0 a multiple of 32) by the packed B.  diag_nb > 0 leaves out the
+// tiles above the diag_nb-wide diagonal blocks.
+// split_scale (or split_scale_diag, for A = L and B = D L^T with D on the
+// diagonal of the given block) sets the scaling along K before the packing.
+void split_scale(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, const c64* B, int64_t ldb,
+                 int64_t N, int64_t K);
+void split_scale_diag(Context& ctx, const c64* A, int64_t lda, int64_t K);
+void split_pack_a(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K);
+void split_pack_b(Context& ctx, const c64* B, int64_t ldb, int64_t N, int64_t K);
+void split_gemm(Context& ctx, int64_t row0, int64_t M, int64_t N, int64_t K, double alpha, double beta, c64* C,
+                int64_t ldc, int diag_nb);
 // lu.hip
 // invL (optional, complex64 factors): receives the kInvBlock x kInvBlock
 // diagonal-block inverses of L (layout as for upper_block_inverses); the
@@ -517,8 +532,9 @@ void lr_rhs(hipStream_t s, const Level& l, int64_t dir, const double* L, int64_t
 
 // level-wide solves (api.cpp helpers)
 // B <- Z^{-1} B, or B <- Z^{-H} B (adjoint); max_sweeps >= 0 overrides the
-// level's refinement sweep limit (0: the factors' solve alone)
+// level's refinement sweep limit (0: the factors' solve alone).  Refinement
+// aims at tol_factor ir_tol; only missing ir_tol itself is FOSB_E_NOCONV
 void level_solve_inplace(Context& ctx, const Level& L, c128* B, int64_t ldb, int64_t nrhs, fosb_stats* st,
-                         bool adjoint = false, int max_sweeps = -1);
+                         bool adjoint = false, int max_sweeps = -1, double tol_factor = 1.0);
 
 }  // namespace fosb

@@ -458,6 +458,12 @@ static int pick_variant(Context& ctx, int64_t M, int64_t N, int64_t K, const cpl
   return best;
 }
 
+// Complex64 products worth packing for the fp16 matrix cores (gemm16.hip).
+static bool split_pays(const Context& ctx, int64_t M, int64_t N, int64_t K) {
+  if (ctx.no_alloc || ctx.lean_tiles > 0) return false;
+  return N >= 256 && K >= 256 && ((M + 255) / 256) * ((N + 127) / 128) >= ctx.n_cu / 2;
+}
+
 template <typename T, bool CONJ_A>
 static void gemm_launch(Context& ctx, int64_t M, int64_t N, int64_t K, double alpha, const cplx<T>* A, int64_t lda,
                         const cplx<T>* B, int64_t ldb, double beta, cplx<T>* C, int64_t ldc) {
@@ -478,6 +484,16 @@ static void gemm_launch(Context& ctx, int64_t M, int64_t N, int64_t K, double al
     }
   }
   const int64_t Kp = std::max<int64_t>(K, 0);
+  if constexpr (sizeof(T) == 4) {
+    if (split_pays(ctx, M, N, Kp)) {
+      ProfScope prof(ctx, FOSB_K_GEMM_F32, flops, bytes);
+      split_scale(ctx, A, lda, CONJ_A, M, B, ldb, N, Kp);
+      split_pack_a(ctx, A, lda, CONJ_A, M, Kp);
+      split_pack_b(ctx, B, ldb, N, Kp);
+      split_gemm(ctx, 0, M, N, Kp, alpha, beta, C, ldc, 0);
+      return;
+    }
+  }
   // split K when the output has too few tiles to fill the chip and K is long:
   // about two workgroups per CU, each still streaming at least 256 of K.  The
   // decision uses a fixed 64 x 64 reference tile, so it (and the summation

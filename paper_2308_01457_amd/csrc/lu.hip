@@ -431,59 +431,221 @@ __device__ __forceinline__ double lane_value(double v, int l) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Panel without pivoting (the symmetric factorisation below): LU of the
-// panel's top w x w block with the pivots in place, and the same outputs as a
-// tournament root (top block, inverses of both diagonal factors, an empty
-// row-move list, the first exactly zero pivot).  The first wavefront factors
-// the block in registers, lane r holding row r; at step j every lane takes
-// row j's entries from lane j (row j is final once step j starts).
-template <typename T>
-__global__ __launch_bounds__(Node<T>::size) void k_nopiv_root(const cplx<T>* __restrict__ A, int64_t lda, int64_t k,
-                                                              int w, int32_t* __restrict__ moves,
-                                                              int32_t* __restrict__ info, cplx<T>* __restrict__ top,
-                                                              cplx<T>* __restrict__ invL, cplx<T>* __restrict__ invU) {
-  __shared__ cplx<T> lu[NB][NB + 1];
-  __shared__ int win[NB];
-  __shared__ int szc;
-  const int tid = threadIdx.x;
+// Symmetric factorisation without pivoting of a diagonal block of up to
+// kSymBlk = 128 columns, by one workgroup with the block in LDS (FP32):
+// A = L D L^T, U = D L^T.  Writes L \ U over the block, the inverses of the
+// 32 x 32 diagonal blocks of both factors, the inverse of the whole upper factor
+// (Uinv, 128 x 128 row-major: U^{-1} = L^{-T} D^{-1}, so one inversion serves
+// both factors), empty row-move lists and the first exactly zero pivot.
+//
+// Panels of 16 columns: up to three wavefronts factor the 16 x 16 diagonal tile
+// in registers, one row per lane, each on its own copy, with 48 rows below it
+// in the other lanes (so the multipliers need no inverse); the lower tiles to
+// the right are updated by L D L^T on the matrix cores.  The chain of dependent
+// steps is what bounds it.  In place of four 32-column panels with their own
+// root, multiplier, triangular-leaf and product launches, a 128-column step is
+// this launch, one product for the rows below, U12 and one product for the rest
+// of the block column.
+constexpr int kSymBlk = 128;
+constexpr int kSymLd = kSymBlk + 1;
+
+typedef float f4v __attribute__((ext_vector_type(4)));
+
+// 16 x 16 tile of a complex product over K (a multiple of 4) on the FP32 matrix
+// instruction (3M): fa(m, k), fb(k, n); lane l receives rows 4 (l / 16) + v, column l % 16.
+template <typename FA, typename FB>
+__device__ __forceinline__ void tile_product(int K, int lane, FA fa, FB fb, f4v& re, f4v& im) {
+  f4v t1{0, 0, 0, 0}, t2{0, 0, 0, 0}, t3{0, 0, 0, 0};
+  for (int k = 0; k < K; k += 4) {
+    const c64 a = fa(lane & 15, k + (lane >> 4)), b = fb(k + (lane >> 4), lane & 15);
+    t1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.re, b.re, t1, 0, 0, 0);
+    t2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.im, b.im, t2, 0, 0, 0);
+    t3 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.re + a.im, b.re + b.im, t3, 0, 0, 0);
+  }
+  re = t1 - t2;
+  im = t3 - t1 - t2;
+}
+
+__global__ __launch_bounds__(512) void k_sym_diag(c64* __restrict__ A, int64_t lda, int64_t k, int w,
+                                                  int32_t* __restrict__ moves, int32_t* __restrict__ info,
+                                                  c64* __restrict__ dinvL, c64* __restrict__ dinvU,
+                                                  c64* __restrict__ Uinv) {
+  __shared__ c64 T[kSymBlk * kSymLd];       // lower tiles L, then L^{-1}; upper tiles scratch
+  __shared__ c64 d[kSymBlk], rd[kSymBlk];   // D and 1 / D
+  __shared__ int szc;                       // first zero pivot
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   raise_wave_priority();
-  if (tid < NB) win[tid] = (int)(k + tid);
-  if (tid < 64) {
-    const int r = tid;
-    const bool row = r < w;
-    cplx<T> a[NB];
+  c64* Ab = A + k * lda + k;
+  // lower tiles; identity beyond w
+  for (int e = tid; e < kSymBlk * kSymBlk; e += 512) {
+    const int r = e / kSymBlk, c = e % kSymBlk;
+    if ((c >> 4) <= (r >> 4))
+      T[r * kSymLd + c] = (r < w && c < w) ? Ab[(int64_t)r * lda + c] : c64{r == c ? 1.f : 0.f, 0.f};
+  }
+  if (tid == 0) szc = kSymBlk;
+  if (tid < (w + NB - 1) / NB) moves[tid * (1 + 4 * NB)] = 0;
+  __syncthreads();
+  for (int p = 0; p < kSymBlk / 16; ++p) {
+    const int b = 16 * p;
+    const bool works = wave < 3 && (wave == 0 || b + 16 + 48 * wave < kSymBlk);
+    const int row = lane < 16 ? b + lane : b + 48 * wave + lane;   // b + 16 + 48 wave + (lane - 16)
+    const bool live = works && row < kSymBlk;
+    c64 a[16];
 #pragma unroll
-    for (int c = 0; c < NB; ++c) a[c] = (row && c < w) ? A[(k + r) * lda + k + c] : cplx<T>{T(0), T(0)};
-    int zc = -1;
+    for (int c = 0; c < 16; ++c) a[c] = live ? T[row * kSymLd + b + c] : c64{0.f, 0.f};
+    __syncthreads();   // every wavefront has its copy of the diagonal tile before the first one stores it
+    if (works) {
+      int zc = -1;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      if (j < w) {
-        const cplx<T> p{lane_value(a[j].re, j), lane_value(a[j].im, j)};
-        if (zc < 0 && p.re == T(0) && p.im == T(0)) zc = j;
-        // the multiplier, zero on the rows at and above the pivot (their
-        // entries then stay as they are); cinv_panel(0) = 0: an exactly zero
-        // pivot is reported through info
-        const bool below = row && r > j;
-        const cplx<T> l = below ? cmul(a[j], cinv_panel(p)) : cplx<T>{T(0), T(0)};
+      for (int j = 0; j < 16; ++j) {
+        const c64 pv{lane_value(a[j].re, j), lane_value(a[j].im, j)};
+        if (zc < 0 && pv.re == 0.f && pv.im == 0.f) zc = j;
+        const c64 pi = cinv_panel(pv);
+        if (wave == 0 && lane == j) {
+          d[b + j] = pv;
+          rd[b + j] = pi;
+        }
+        // the multiplier, zero on the rows at and above the pivot
+        const bool below = lane > j;
+        const c64 l = below ? cmul(a[j], pi) : c64{0.f, 0.f};
         if (below) a[j] = l;
 #pragma unroll
-        for (int c = j + 1; c < NB; ++c) {
-          const cplx<T> u{lane_value(a[c].re, j), lane_value(a[c].im, j)};
+        for (int c = j + 1; c < 16; ++c) {
+          const c64 u{lane_value(a[c].re, j), lane_value(a[c].im, j)};
           a[c].re -= l.re * u.re - l.im * u.im;
           a[c].im -= l.re * u.im + l.im * u.re;
         }
       }
-    }
-    if (r < NB) {
+      if (live && (lane >= 16 || wave == 0)) {   // the diagonal tile keeps the multipliers below its diagonal
 #pragma unroll
-      for (int c = 0; c < NB; ++c) lu[r][c] = a[c];
+        for (int c = 0; c < 16; ++c)
+          if (lane >= 16 || c < lane) T[row * kSymLd + b + c] = a[c];
+      }
+      if (wave == 0 && lane == 0 && zc >= 0) atomicMin(&szc, b + zc);
     }
-    if (tid == 0) szc = zc;
+    __syncthreads();
+    // lower tiles (I, J), I >= J > p:  T_IJ -= L_I D L_J^T
+    const int q = kSymBlk / 16 - 1 - p;
+    for (int t = wave; t < q * (q + 1) / 2; t += 8) {
+      int i = 0, off = t;
+      while (off > i) off -= ++i;   // row i holds tiles 0 .. i
+      const int ri = b + 16 + 16 * i, rj = b + 16 + 16 * off;
+      f4v re, im;
+      tile_product(
+          16, lane, [&](int m, int kk) { return T[(ri + m) * kSymLd + b + kk]; },
+          [&](int kk, int n) { return cmul(d[b + kk], T[(rj + n) * kSymLd + b + kk]); }, re, im);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        c64& o = T[(ri + 4 * (lane >> 4) + v) * kSymLd + rj + (lane & 15)];
+        o.re -= re[v];
+        o.im -= im[v];
+      }
+    }
+    __syncthreads();
+  }
+  // L \ U to memory
+  for (int e = tid; e < kSymBlk * kSymBlk; e += 512) {
+    const int r = e / kSymBlk, c = e % kSymBlk;
+    if (r < w && c < w)
+      Ab[(int64_t)r * lda + c] = r > c ? T[r * kSymLd + c] : (r == c ? d[r] : cmul(d[r], T[c * kSymLd + r]));
+  }
+  if (tid == 0 && szc < w) atomicMin(info, (int)(k + szc + 1));
+  // L^{-1} in place: the 16 x 16 diagonal tiles (wavefront t inverts tile t,
+  // lane c its column c), then pairs of blocks of 16, 32 and 64:
+  // L21 <- -L22^{-1} (L21 L11^{-1}), the inner product kept in the upper tiles
+  {
+    const int b = 16 * wave, c = lane & 15;
+    c64 x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      c64 v{(i == c) ? 1.f : 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < i; ++j) {
+        const c64 l = T[(b + i) * kSymLd + b + j];
+        v.re -= l.re * x[j].re - l.im * x[j].im;
+        v.im -= l.re * x[j].im + l.im * x[j].re;
+      }
+      x[i] = v;
+    }
+    __syncthreads();
+    if (lane < 16) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) T[(b + i) * kSymLd + b + c] = x[i];
+    }
   }
   __syncthreads();
-  const int zc = szc;
-  panel_root(lu, win, w, w, zc, k, tid, moves, info, top, invL, invU);
+  for (int h = 16; h < kSymBlk; h *= 2) {   // merge blocks of h columns in pairs
+    const int nt = h / 16, tiles = nt * nt, pairs = kSymBlk / (2 * h);
+    for (int t = wave; t < pairs * tiles; t += 8) {   // W = L21 L11^{-1} into the pair's upper block
+      const int o = t / tiles * 2 * h, i = t % tiles / nt * 16, j = t % nt * 16;
+      f4v re, im;
+      tile_product(
+          h, lane, [&](int m, int kk) { return T[(o + h + i + m) * kSymLd + o + kk]; },
+          [&](int kk, int n) { return kk < j ? c64{0.f, 0.f} : T[(o + kk) * kSymLd + o + j + n]; }, re, im);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        T[(o + i + 4 * (lane >> 4) + v) * kSymLd + o + h + j + (lane & 15)] = c64{re[v], im[v]};
+    }
+    __syncthreads();
+    for (int t = wave; t < pairs * tiles; t += 8) {   // L21 = -L22^{-1} W
+      const int o = t / tiles * 2 * h, i = t % tiles / nt * 16, j = t % nt * 16;
+      f4v re, im;
+      tile_product(
+          h, lane,
+          [&](int m, int kk) { return kk >= i + 16 ? c64{0.f, 0.f} : T[(o + h + i + m) * kSymLd + o + h + kk]; },
+          [&](int kk, int n) { return T[(o + kk) * kSymLd + o + h + j + n]; }, re, im);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        T[(o + h + i + 4 * (lane >> 4) + v) * kSymLd + o + j + (lane & 15)] = c64{-re[v], -im[v]};
+    }
+    __syncthreads();
+  }
+  // outputs: Uinv[i][j] = L^{-1}[j][i] / d_j for i <= j
+  for (int e = tid; e < kSymBlk * kSymBlk; e += 512) {
+    const int r = e / kSymBlk, c = e % kSymBlk;
+    Uinv[e] = r <= c ? cmul(T[c * kSymLd + r], rd[c]) : c64{0.f, 0.f};
+    if (r / NB == c / NB && r / NB * NB < w) {
+      const int64_t o = (int64_t)(r / NB) * NB * NB + r % NB * NB + c % NB;
+      dinvL[o] = r >= c ? T[r * kSymLd + c] : c64{0.f, 0.f};
+      dinvU[o] = r <= c ? cmul(T[c * kSymLd + r], rd[c]) : c64{0.f, 0.f};
+    }
+  }
 }
+
+// Rows below a diagonal block of 128 columns: X <- X Uinv, in place (64 rows per
+// workgroup, all 128 columns, so a row's entries are read before any is
+// written).  Uinv is upper triangular: columns 32 j .. take K = 32 (j + 1).
+// Bound by the round trip of the block column through memory.
+__global__ __launch_bounds__(256) void k_sym_mul(c64* X, int64_t ldx, int64_t m, const c64* __restrict__ Uinv) {
+  __shared__ c64 S[64 * kSymLd];
+  __shared__ c64 B[kSymBlk * (NB + 1)];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  raise_wave_priority();
+  const int64_t r0 = (int64_t)blockIdx.x * 64;
+  for (int e = tid; e < 64 * kSymBlk; e += 256) {
+    const int r = e / kSymBlk, c = e % kSymBlk;
+    S[r * kSymLd + c] = r0 + r < m ? X[(r0 + r) * ldx + c] : c64{0.f, 0.f};
+  }
+  for (int j = 0; j < kSymBlk / NB; ++j) {
+    __syncthreads();   // S is loaded; the previous columns' products have read B
+    for (int e = tid; e < NB * (j + 1) * NB; e += 256)
+      B[e / NB * (NB + 1) + e % NB] = Uinv[e / NB * kSymBlk + NB * j + e % NB];
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < NB; h += 16) {
+      f4v re, im;
+      tile_product(
+          NB * (j + 1), lane, [&](int mm, int kk) { return S[(16 * wave + mm) * kSymLd + kk]; },
+          [&](int kk, int n) { return B[kk * (NB + 1) + h + n]; }, re, im);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t r = r0 + 16 * wave + 4 * (lane >> 4) + v;
+        if (r < m) X[r * ldx + NB * j + h + (lane & 15)] = c64{re[v], im[v]};
+      }
+    }
+  }
+}
+
 
 // U12 = D L21^T for a symmetric factorisation without pivoting: rows
 // kj .. kj + wj of columns c0 .. c0 + cn receive d_t A[c][kj + t], d_t the
@@ -932,6 +1094,14 @@ constexpr int64_t kLookaheadMinN = 2048;  // smaller matrices: plain recursion o
 constexpr int64_t kTrailChunk = 16384;     // columns per trailing-update launch (measured: 2048..16384)
 constexpr int64_t kSymChunk = 2048;        // symmetric form: its rows start at the chunk, so narrower chunks waste less
 
+// Symmetric form on the fp16 matrix cores: fewer trailing rows than this keep
+// the FP32 instruction (under 24 tiles, each a chain of 48 K blocks), and an
+// update launch covers this many blocks of columns (level build at N = 30720
+// with the panels not overlapped: 203, 197, 193 and 202 ms with 2, 3, 6 and 12;
+// the panels beside the updates find free compute units between launches).
+constexpr int64_t kSplitMinRows = 1024;
+constexpr int64_t kSplitChunk = 3;
+
 static inline int64_t split_half(int64_t w) { return (int64_t)NB * (((w / NB) + 1) / 2); }
 
 template <typename T>
@@ -941,15 +1111,6 @@ static void panel(LuRun<T>& R, int64_t k, int w) {
   const int64_t blk = k / NB;
   int32_t* moves = R.moves + blk * kMoveStride;
   ProfScope prof(*R.ctx, FOSB_K_PANEL, 0.0, (double)sizeof(cplx<T>) * (double)m * w * 3.0);
-  if (R.sym) {  // pivots in place: factor the top block, then the multipliers below it
-    hipLaunchKernelGGL(k_nopiv_root<T>, dim3(1), dim3(Node<T>::size), 0, s, R.A, R.lda, k, w, moves, R.info, R.top,
-                       R.dinvL + blk * NB * NB, R.dinvU + blk * NB * NB);
-    FOSB_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_panel_finish<T>, dim3((unsigned)((m + 63) / 64)), dim3(256), 0, s, R.A, R.lda, R.n, k, w,
-                       R.top, R.dinvU + blk * NB * NB);
-    FOSB_LAUNCH_CHECK();
-    return;
-  }
   // leaf level over consecutive rows, then FANIN-way merges until one node remains
   constexpr int NODE = Node<T>::size, FANIN = NODE / NB;
   int nodes = (int)((m + NODE - 1) / NODE);
@@ -998,6 +1159,32 @@ static void rec_lu(LuRun<T>& R, int64_t k, int64_t w) {
   gemm<T>(*R.ctx, R.n - k - w1, w - w1, w1, -1.0, A + (k + w1) * lda + k, lda, A + k * lda + (k + w1), lda, 1.0,
           A + (k + w1) * lda + (k + w1), lda);
   rec_lu(R, k + w1, w - w1);
+}
+
+// Columns k .. k + w of a symmetric matrix's block column in steps of kSymBlk:
+// the diagonal block, the multipliers below it, U12 = D L21^T and the product
+// that updates the rest of the block column.
+static void sym_block(LuRun<float>& R, int64_t k, int64_t w) {
+  hipStream_t s = R.ctx->stream;
+  c64* A = R.A;
+  const int64_t lda = R.lda;
+  for (int64_t o = 0; o < w; o += kSymBlk) {
+    const int64_t kk = k + o, ws = std::min<int64_t>(kSymBlk, w - o), k1 = kk + ws, m = R.n - k1, rest = w - o - ws;
+    const int64_t blk = kk / NB;
+    {
+      ProfScope prof(*R.ctx, FOSB_K_PANEL, 0.0, (double)sizeof(c64) * (double)(R.n - kk) * ws * 2.0);
+      hipLaunchKernelGGL(k_sym_diag, dim3(1), dim3(512), 0, s, A, lda, kk, (int)ws, R.moves + blk * kMoveStride,
+                         R.info, R.dinvL + blk * NB * NB, R.dinvU + blk * NB * NB, R.top);
+      FOSB_LAUNCH_CHECK();
+      if (m <= 0) continue;
+      // rows remain below only after a full block: the last block ends the matrix
+      hipLaunchKernelGGL(k_sym_mul, dim3((unsigned)((m + 63) / 64)), dim3(256), 0, s, A + k1 * lda + kk, lda, m, R.top);
+      FOSB_LAUNCH_CHECK();
+    }
+    if (rest <= 0) continue;
+    sym_u12<float>(s, A, lda, kk, ws, k1, rest);
+    gemm<float>(*R.ctx, m, rest, ws, -1.0, A + k1 * lda + kk, lda, A + kk * lda + k1, lda, 1.0, A + k1 * lda + k1, lda);
+  }
 }
 
 // Right-looking blocked LU with a lookahead of one block column, over two
@@ -1053,7 +1240,14 @@ static void blocked_lu(LuRun<T>& R, Context& U, int64_t nb) {
   auto panel_block = [&](int64_t k, int64_t w) {
     R.pc0 = k;
     R.pc1 = k + w;
-    rec_lu(R, k, w);
+    if constexpr (sizeof(T) == 4) {
+      if (R.sym)
+        sym_block(R, k, w);
+      else
+        rec_lu(R, k, w);
+    } else {
+      rec_lu(R, k, w);
+    }
     FOSB_HIP(hipEventRecord(ev_panel, sa));
   };
   panel_block(0, std::min(nb, n));
@@ -1068,8 +1262,8 @@ static void blocked_lu(LuRun<T>& R, Context& U, int64_t nb) {
       cb();
     }
     FOSB_HIP(hipStreamWaitEvent(sb, ev_panel, 0));
-    if (R.invL) block_inverses<T, true>(U, A, n, lda, R.dinvL, R.invL, kj / NL, (wj + NL - 1) / NL);
     if (!R.sym) {
+      if (R.invL) block_inverses<T, true>(U, A, n, lda, R.dinvL, R.invL, kj / NL, (wj + NL - 1) / NL);
       ColRanges cr{{0, kj + wj}, {kj, n}};
       const int64_t width = kj + (n - kj - wj);
       if (width > 0) {
@@ -1081,6 +1275,26 @@ static void blocked_lu(LuRun<T>& R, Context& U, int64_t nb) {
     }
     if (j + 1 == nblk) break;
     const int64_t k1 = kj + wj, w1 = std::min(nb, n - k1);
+    if constexpr (sizeof(T) == 4) {
+      if (R.sym && n - k1 >= kSplitMinRows) {  // as below, the products on the fp16 matrix cores
+        split_scale_diag(U, A + kj * lda + kj, lda, wj);
+        split_pack_a(U, A + k1 * lda + kj, lda, false, n - k1, wj);
+        auto update = [&](int64_t c0, int64_t cn) {
+          sym_u12<T>(sb, A, lda, kj, wj, c0, cn);
+          ProfScope prof(U, FOSB_K_GEMM_F32, 8.0 * (double)(n - c0) * cn * wj,
+                         (double)sizeof(cplx<T>) * ((double)(n - c0) * wj + (double)wj * cn + 2.0 * (double)(n - c0) * cn));
+          split_pack_b(U, A + kj * lda + c0, lda, cn, wj);
+          split_gemm(U, c0 - k1, n - c0, cn, wj, -1.0, 1.0, A + c0 * lda + c0, lda, (int)nb);
+        };
+        update(k1, w1);
+        FOSB_HIP(hipEventRecord(ev_look, sb));
+        FOSB_HIP(hipStreamWaitEvent(sa, ev_look, 0));
+        panel_block(k1, w1);
+        for (int64_t c0 = k1 + w1; c0 < n; c0 += kSplitChunk * nb)
+          update(c0, std::min<int64_t>(kSplitChunk * nb, n - c0));
+        continue;
+      }
+    }
     if (R.sym) {  // symmetric, no pivoting: U12 = D L21^T, trailing updates of the lower triangle only
       sym_u12<T>(sb, A, lda, kj, wj, k1, w1);
       gemm<T>(U, n - k1, w1, wj, -1.0, A + k1 * lda + kj, lda, A + kj * lda + k1, lda, 1.0, A + k1 * lda + k1, lda);
@@ -1128,7 +1342,7 @@ int64_t lu_factor(Context& ctx, cplx<T>* A, int64_t n, int64_t lda, cplx<T>* din
   const int64_t npanel = (n + NB - 1) / NB;
   const size_t n_i32 = (size_t)(2 * maxnodes * NB + npanel * kMoveStride + 1);
   const size_t top_off = (n_i32 * sizeof(int32_t) + 255) / 256 * 256;
-  ctx.small.reserve(top_off + NB * NB * sizeof(cplx<T>));
+  ctx.small.reserve(top_off + kSymBlk * kSymBlk * sizeof(cplx<T>));
   int32_t* base = ctx.small.as<int32_t>();
   LuRun<T> R;
   R.ctx = &ctx;
@@ -1161,7 +1375,12 @@ int64_t lu_factor(Context& ctx, cplx<T>* A, int64_t n, int64_t lda, cplx<T>* din
     // block width: 768 from N = 16384 (measured at N = 30720: symmetric FP32
     // factorisation 0.325 -> 0.319 s, pivoted FP64 1.300 -> 1.293 s against 512;
     // 1024 gained nothing for the symmetric form)
-    blocked_lu(R, U, n >= 16384 ? 768 : 256);
+    // The symmetric form takes 768 at every size: its block column costs one
+    // launch chain per 128 columns, and a wider block halves the passes over
+    // the trailing matrix (N = 7680: level build 16.1 / 14.9 / 14.6 ms at 256 /
+    // 512 / 768; 15870: 77 / 53 / 50; 1024 gained 4% at 7680 and lost 2% at 30720).
+    blocked_lu(R, U, R.sym || n >= 16384 ? 768 : 256);
+    if (R.sym && invL) block_inverses<T, true>(ctx, A, n, lda, dinvL, invL, 0, (n + NL - 1) / NL);
   } else {
     rec_lu(R, 0, n);
     if (invL) block_inverses<T, true>(ctx, A, n, lda, dinvL, invL, 0, (n + NL - 1) / NL);

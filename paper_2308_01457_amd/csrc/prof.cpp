@@ -101,7 +101,7 @@ bool& thread_no_alloc() {
 Context::Context() {
   for (DevBuf& b : scratch) b.home = pool;
   for (DevBuf& b : ss) b.home = pool;
-  for (DevBuf* b : {&solve_tmp, &counters, &small, &norms, &splitk, &tune_out}) b->home = pool;
+  for (DevBuf* b : {&solve_tmp, &counters, &small, &norms, &splitk, &tune_out, &pack_a, &pack_ma, &pack_b, &pack_mb, &pack_ke}) b->home = pool;
 }
 
 static void for_each_context(Context& c, const std::function<void(Context&)>& f) {

@@ -143,3 +143,62 @@ def test_narrow_solves_match_wide_solves(fz):
         print(f"[gpu]   {k} right-hand sides: vs the 5-column solve {rel:.2e}, residual {res:.2e}", flush=True)
         assert rel < 1e-10 and res < 1e-13
     lv.close()
+
+
+@pytest.mark.parametrize("nu", [9, 10, 13])
+def test_symmetric_blocks_and_split_products(fz, nu):
+    """The 128-column diagonal blocks and the split products at sizes that are no
+    multiple of the block widths (N = 2430 = 3 * 768 + 126, 3000 = 3 * 768 + 696,
+    5070 = 6 * 768 + 462), on a complex symmetric matrix whose rows and columns
+    are scaled by powers of two between 2^-20 and 2^20 (S A S with A dominant on
+    the diagonal).  The factors are read back from Zlow: in the unscaled norm
+    ||A - L U||_F <= N 2^-24 ||L||_F ||U||_F, the rounding bound of an FP32
+    elimination of that size, and the refined solve meets the FP64 residual."""
+    fosb, ctx, torch, w, m_, Z_ = fz
+    V, F = workloads.geodesic_sphere(nu)
+    m = fosb.Mesh(ctx, V, F)
+    n = m.n_edges
+    print(f"[gpu] symmetric blocks: N={n}", flush=True)
+    g = torch.Generator(device="cpu").manual_seed(nu)
+    A = torch.randn((n, n), dtype=torch.complex128, generator=g).to(ctx.torch_device)
+    A = (A + A.T) / n ** 0.5 + 4.0 * torch.eye(n, dtype=torch.complex128, device=ctx.torch_device)
+    s = torch.exp2(torch.randint(-20, 21, (n,), generator=g).double()).to(ctx.torch_device)
+    Z = (s[:, None] * A * s[None, :]).contiguous()
+    Zlow = torch.empty((n, n), dtype=torch.complex64, device=ctx.torch_device)
+    lv = fosb.Level(ctx, m, 1.0, Z, fosb.MIXED, w.dirs, w.pols, "radial", _opts(fosb, 0), Zlow=Zlow)
+    assert lv.factorization() == fosb.FACTOR_SYM
+    LU = Zlow.to(torch.complex128) / s[:, None] / s[None, :]      # L and U of A up to S: (S L S^-1)(S U S)
+    U = torch.triu(LU)
+    Lf = torch.tril(Zlow.to(torch.complex128) / s[:, None] * s[None, :], -1)
+    Lf += torch.eye(n, dtype=torch.complex128, device=ctx.torch_device)
+    err = float((A - torch.matmul(Lf, U)).norm() / (Lf.norm() * U.norm()))
+    print(f"[gpu]   ||A - LU|| / (||L|| ||U||) = {err:.2e} (bound {n * 2.0 ** -24:.2e})", flush=True)
+    assert err <= n * 2.0 ** -24
+    B = _rhs(torch, ctx, n, nrhs=3)
+    X = B.clone()
+    lv.solve(X)
+    assert _residual(torch, Z, X, B) < 1e-13
+
+
+@pytest.mark.parametrize("nrhs", [255, 256, 300])
+def test_split_products_in_wide_solves(fz, nrhs):
+    """Refined solves on both sides of the width at which the triangular solves'
+    coupling products turn to the split form (256 columns; 300 ends inside a tile),
+    forward and adjoint, with right-hand sides of magnitudes 1e-12 .. 1e12 by
+    column: the FP64 residual bound of every column."""
+    fosb, ctx, torch, w, m, Z = fz
+    n = m.n_edges
+    lv = fosb.Level(ctx, m, w.k, Z, fosb.MIXED, w.dirs, w.pols, "radial", _opts(fosb, 0))
+    B = _rhs(torch, ctx, n, nrhs=nrhs, seed=nrhs)
+    B = B * torch.logspace(-12, 12, nrhs, dtype=torch.float64, device=B.device)[None, :]
+    zn = Z.norm()
+    for adjoint in (False, True):
+        X = B.clone()
+        if adjoint:
+            lv.solve_adjoint(X)
+        else:
+            lv.solve(X)
+        R = torch.matmul(Z.mH.contiguous() if adjoint else Z, X) - B
+        worst = float((R.norm(dim=0) / (zn * X.norm(dim=0))).max())
+        print(f"[gpu]   {nrhs} columns, adjoint {adjoint}: worst column residual {worst:.1e}", flush=True)
+        assert worst < 1e-9   # refinement stops by the whole block's norm: small columns carry the FP32 solve's accuracy
