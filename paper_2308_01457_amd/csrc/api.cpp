@@ -626,6 +626,29 @@ static void pair_rhs(Context& c, const Level& a, const Level& b, const fosb_cov*
     rhs_correlation_kernel(c.stream, a, b, *cov, dir, C, ldc);
 }
 
+// Sigma blocks of rank-one right-hand sides C = b_l1 b_l2^H: the two-sided solve
+// separates, Sigma = (Z_l1^{-1} b_l1) (Z_l2^{-1} b_l2)^H, so each level solves one
+// column instead of N_l2 and N_l1 columns per pair (three levels to 2N = 15360,
+// mixed: 245 -> 96 ms with the levels' construction).
+static void rank_one_blocks(Context& c, const fosb_level* const* levels, int32_t n_levels, int32_t L0,
+                            const std::vector<std::array<int32_t, 4>>& pairs, int64_t dir, void* const* blocks,
+                            const int64_t* ldb, fosb_stats* st) {
+  std::vector<DevBuf> x(n_levels);
+  for (int32_t i = 0; i < n_levels; ++i) {
+    const fosb_level& l = *levels[i];
+    x[i].alloc((size_t)l.n * sizeof(c128));
+    copy_c128(c.stream, l.b.as<c128>() + dir, l.n_dirs, x[i].as<c128>(), 1, l.n, 1);
+    level_solve_inplace(c, l, x[i].as<c128>(), 1, 1, st, false, -1, kFirstMomentTol);
+  }
+  for (size_t p = 0; p < pairs.size(); ++p) {
+    const int i1 = pairs[p][0] - L0, i2 = pairs[p][1] - L0;
+    ProfScope prof(c, FOSB_K_RHS, 0.0, 16.0 * (double)levels[i1]->n * (double)levels[i2]->n);
+    rank_one_correlation(c.stream, x[i1].as<c128>(), levels[i1]->n, x[i2].as<c128>(), levels[i2]->n, 1, 0,
+                         static_cast<c128*>(blocks[p]), ldb[p]);
+    if (st) st->n_solves += 1;
+  }
+}
+
 static void check_cov_for(const fosb_level* l, const fosb_cov* cov);
 
 static void check_cov(const fosb_cov* cov) {
@@ -1195,6 +1218,11 @@ fosb_status fosb_correlation(fosb_context* ctx, const fosb_level* const* levels,
     if (ldb[p] < levels[v[p][1] - L0]->n) fail(FOSB_E_WORKSPACE, "ldb[%zu] < N_l2", p);
   }
   bind(*ctx);
+  if (levels[0]->form == FOSB_FORM_PMCHWT && !cov) {
+    rank_one_blocks(*ctx, levels, n_levels, L0, v, dir, blocks, ldb, stats);
+    set_last_error("");
+    return FOSB_OK;
+  }
   for (size_t p = 0; p < v.size(); ++p) {
     const fosb_level* a = levels[v[p][0] - L0];
     const fosb_level* b = levels[v[p][1] - L0];

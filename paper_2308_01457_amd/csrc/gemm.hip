@@ -458,7 +458,14 @@ static int pick_variant(Context& ctx, int64_t M, int64_t N, int64_t K, const cpl
   return best;
 }
 
-// Complex64 products worth packing for the fp16 matrix cores (gemm16.hip).
+// A packed operand of a split product takes 12 bytes an entry.  1 GiB: solves
+// with 480 columns at N = 30720 took 196 ms; bounds of 384, 192 and 96 MiB, whose
+// shorter K chunks add more passes over C, 199, 213 and 231 ms.
+constexpr int64_t kSplitPackBytes = (int64_t)1 << 30;
+
+// Complex64 products worth packing for the fp16 matrix cores (gemm16.hip): at
+// least 256 columns and 256 of K, so that reading and packing A (28 bytes an
+// entry) stays below the products saved, and tiles for half the compute units.
 static bool split_pays(const Context& ctx, int64_t M, int64_t N, int64_t K) {
   if (ctx.no_alloc || ctx.lean_tiles > 0) return false;
   return N >= 256 && K >= 256 && ((M + 255) / 256) * ((N + 127) / 128) >= ctx.n_cu / 2;
@@ -487,10 +494,18 @@ static void gemm_launch(Context& ctx, int64_t M, int64_t N, int64_t K, double al
   if constexpr (sizeof(T) == 4) {
     if (split_pays(ctx, M, N, Kp)) {
       ProfScope prof(ctx, FOSB_K_GEMM_F32, flops, bytes);
-      split_scale(ctx, A, lda, CONJ_A, M, B, ldb, N, Kp);
-      split_pack_a(ctx, A, lda, CONJ_A, M, Kp);
-      split_pack_b(ctx, B, ldb, N, Kp);
-      split_gemm(ctx, 0, M, N, Kp, alpha, beta, C, ldc, 0);
+      // K in chunks, so that a packed operand (12 bytes an entry) stays within
+      // kSplitPackBytes; the later chunks add to C
+      const int64_t kc = std::max<int64_t>(256, kSplitPackBytes / (12 * std::max(M, N)) / 256 * 256);
+      for (int64_t k0 = 0; k0 < Kp; k0 += kc) {
+        const int64_t kn = std::min(kc, Kp - k0);
+        const cplx<T>* Ak = CONJ_A ? A + k0 * lda : A + k0;
+        const cplx<T>* Bk = B + k0 * ldb;
+        split_scale(ctx, Ak, lda, CONJ_A, M, Bk, ldb, N, kn);
+        split_pack_a(ctx, Ak, lda, CONJ_A, M, kn);
+        split_pack_b(ctx, Bk, ldb, N, kn);
+        split_gemm(ctx, 0, M, N, kn, alpha, k0 == 0 ? beta : 1.0, C, ldc, 0);
+      }
       return;
     }
   }

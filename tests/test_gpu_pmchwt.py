@@ -308,3 +308,33 @@ def test_pmchwt_symmetric_factorisation(fz):
     assert float((u["sym"] - u["fp64"]).norm() / u["fp64"].norm()) < 1e-10
     for l in lv.values():
         l.close()
+
+
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("mixed", 1e-8)])
+def test_rank_one_blocks_equal_two_sided_solves(fz, precision, tol):
+    """fosb_correlation's separated rank-one blocks against the general route (C
+    formed, solved on both sides) for every pair, the second of two incidences
+    and a row stride beyond the block.  FP64: both are backward stable; mixed:
+    both refine to ir_tol = 1e-10, times a condition number below 100."""
+    fosb, ctx, torch = fz
+    prec = fosb.FP64 if precision == "fp64" else fosb.MIXED
+    dirs = ((1.0, 0.0, 0.0), (0.0, 0.6, 0.8))
+    pols = ((0.0, 0.0, 1.0), (1.0, 0.0, 0.0))
+    lvs = []
+    for s in (1, 2):
+        m = fosb.Mesh(ctx, *workloads.icosphere(s))
+        Z = fosb.assemble_pmchwt(ctx, m, 1.3, 2.1)
+        lvs.append(fosb.Level.pmchwt(ctx, m, 1.3, 2.1, 1.0, Z, prec, dirs, pols))
+    pairs = fosb.ct_pairs(1, 2)
+    wide = [torch.zeros((lvs[a - 1].n, lvs[b - 1].n + 5), dtype=torch.complex128, device=ctx.torch_device)
+            for a, b, _, _ in pairs]
+    st = fosb.Stats()
+    fosb.correlation(ctx, lvs, 1, 2, None, 1, blocks=wide, stats=st)
+    assert st.n_solves == len(pairs)
+    for (a, b, _, _), W in zip(pairs, wide):
+        C = fosb.rhs_correlation(ctx, lvs[a - 1], lvs[b - 1], None, 1)
+        S = fosb.two_sided_solve(ctx, lvs[a - 1], lvs[b - 1], C)
+        n2 = lvs[b - 1].n
+        e = float((W[:, :n2] - S).norm() / S.norm())
+        print(f"[gpu] rank-one block ({a},{b}) {precision}: separated vs two-sided {e:.1e}", flush=True)
+        assert e < tol and float(W[:, n2:].abs().max()) == 0.0
