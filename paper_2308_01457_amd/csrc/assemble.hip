@@ -127,11 +127,60 @@ __device__ __forceinline__ void load_tri(const MeshDev& md, int t, double P[3][3
   for (int q = 0; q < 3; ++q) c[q] = (P[0][q] + P[1][q] + P[2][q]) * (1.0 / 3.0);
 }
 
+// sin and cos of a small phase by N terms each past the first: the Taylor
+// series sum_t (-1)^t x^(2t+1) / (2t+1)! and sum_t (-1)^t x^(2t) / (2t)!,
+// t <= N.  The first omitted term of cos, x^(2N+2) / (2N+2)!, is below half an
+// ulp of one on |x| <= kShortPhase(N).
+template <int N>
+__device__ __forceinline__ void sincos_short(double x, double* sn, double* cs) {
+  constexpr double S[9] = {1.0, -0.16666666666666666, 0.008333333333333333, -0.0001984126984126984,
+                           2.7557319223985893e-06, -2.505210838544172e-08, 1.6059043836821613e-10,
+                           -7.647163731819816e-13, 2.8114572543455206e-15};
+  constexpr double C[9] = {1.0, -0.5, 0.041666666666666664, -0.001388888888888889, 2.48015873015873e-05,
+                           -2.755731922398589e-07, 2.08767569878681e-09, -1.1470745597729725e-11,
+                           4.779477332387385e-14};
+  const double z = x * x;
+  double ps = S[N], pc = C[N];
+#pragma unroll
+  for (int t = N - 1; t > 0; --t) {
+    ps = fma(ps, z, S[t]);
+    pc = fma(pc, z, C[t]);
+  }
+  *sn = fma(ps * z, x, x);
+  *cs = fma(pc, z, 1.0);
+}
+
+// The 6-point rule by its two orbits o of points lambda = b_o + (a_o - b_o) e_v:
+// node offset d[o] = a_o - b_o, moment factors wb[o] = w_o b_o, wd[o] = w_o d[o].
+struct Orbits6 {
+  double d[2], wb[2], wd[2];
+};
+
 // One thread per ordered non-touching triangle pair (i, j0 + jj).
-__global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Rule6 R, double k, int j0, int jc,
+//
+// Bound by FP64 VALU issue, so it is written for few instructions per point
+// pair.  Lengths are in units of 1/k (the phase is the distance).  With
+// R0 the distance of the centroids, e^{ir} = e^{iR0} e^{i(r - R0)}: for
+// NT > 0 the second factor has |r - R0| <= k (h_i + h_j) (h: largest distance
+// of a vertex from its centroid) and is a short series without range reduction,
+// and the first is applied once per pair; NT = 0 takes the general sincos_phase of
+// r.  The centred nodes are d_o times a vertex (the centred vertices add to
+// zero), and the moments are kept barycentric, N[a][b] = sum w w' G lambda_a
+// lambda'_b: per orbit a plain sum and one term more, with the weights applied
+// after it.  The block then needs the dot products of the centred vertices only:
+//   (i/k) alpha_a beta_b (I0 - k^2 M / 4),  M = Ixy - U_b - V_a + D_ab I0,
+//   D_ab = P~_a . Q~_b,  U_b = sum_a' (sum_b' N) D_a'b,  V_a = sum_b' (sum_a' N) D_ab',
+//   Ixy = sum N D,  I0 = sum N.
+// Vector instructions per point pair, all included: 48.7 with NT = 6, 52.6 with
+// NT = 8, 70.1 with NT = 0 (78.6 with sincos_phase on every point pair and
+// moments of the coordinates); at nt = 20480 (N = 30720) the launches of one
+// matrix add up to 42 ms instead of 53 beside the gather, the matrix takes 49.4
+// instead of 61.7.
+template <int NT>
+__global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Orbits6 R, double k, int j0, int jc,
                                                           c128* __restrict__ Zc, int64_t ldc) {
   const int jj = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int i = blockIdx.y * 4 + (threadIdx.x >> 6);
+  const int i = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (threadIdx.x >> 6));
   if (jj >= jc || i >= md.nt) return;
   const int j = j0 + jj;
   const int nt = md.nt;
@@ -142,67 +191,137 @@ __global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Rule6 R, d
         a2 == b2)
       return;  // touching pair: integrated by the singular kernel
   }
-  double Pi[3][3], Pj[3][3], ci[3], cj[3];
-  load_tri(md, i, Pi, ci);
-  load_tri(md, j, Pj, cj);
-  double Li[3][3], Lj[3][3];
-#pragma unroll
-  for (int v = 0; v < 3; ++v)
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      Li[v][q] = Pi[v][q] - ci[q];
-      Lj[v][q] = Pj[v][q] - cj[q];
-    }
-  const double Ai = md.area[i], Aj = md.area[j];
-  double yq[6][3], wq[6];
-#pragma unroll
-  for (int q = 0; q < 6; ++q) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) yq[q][c] = R.l[q][0] * Lj[0][c] + R.l[q][1] * Lj[1][c] + R.l[q][2] * Lj[2][c];
-    wq[q] = R.w[q] * Aj * kInv4Pi;
-  }
-  const double dc0 = ci[0] - cj[0], dc1 = ci[1] - cj[1], dc2 = ci[2] - cj[2];
-  double I0r = 0, I0i = 0, Ixyr = 0, Ixyi = 0;
-  double Ixr[3] = {0, 0, 0}, Ixi[3] = {0, 0, 0}, Iyr[3] = {0, 0, 0}, Iyi[3] = {0, 0, 0};
-#pragma unroll
-  for (int p = 0; p < 6; ++p) {
-    double xp[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) xp[c] = R.l[p][0] * Li[0][c] + R.l[p][1] * Li[1][c] + R.l[p][2] * Li[2][c];
-    const double wp = R.w[p] * Ai;
-    const double e0 = xp[0] + dc0, e1 = xp[1] + dc1, e2 = xp[2] + dc2;
-    double Sr = 0, Si = 0, Syr[3] = {0, 0, 0}, Syi[3] = {0, 0, 0};
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-      const double d0 = e0 - yq[q][0], d1 = e1 - yq[q][1], d2 = e2 - yq[q][2];
-      const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-      const double ir = rsqrt_pos(r2);
-      const double r = r2 * ir;
-      double sn, cs;
-      sincos_phase(k * r, &sn, &cs);
-      const double g = wq[q] * ir;
-      const double gr = cs * g, gi = sn * g;
-      Sr += gr;
-      Si += gi;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        Syr[c] += gr * yq[q][c];
-        Syi[c] += gi * yq[q][c];
-      }
-    }
-    I0r += wp * Sr;
-    I0i += wp * Si;
+  double Li[3][3], Lj[3][3], dc[3];
+  {
+    double ci[3], cj[3];
+    load_tri(md, i, Li, ci);
+    load_tri(md, j, Lj, cj);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      Ixr[c] += wp * Sr * xp[c];
-      Ixi[c] += wp * Si * xp[c];
-      Iyr[c] += wp * Syr[c];
-      Iyi[c] += wp * Syi[c];
+      dc[c] = k * (ci[c] - cj[c]);
+#pragma unroll
+      for (int v = 0; v < 3; ++v) {
+        Li[v][c] = k * (Li[v][c] - ci[c]);
+        Lj[v][c] = k * (Lj[v][c] - cj[c]);
+      }
     }
-    Ixyr += wp * (xp[0] * Syr[0] + xp[1] * Syr[1] + xp[2] * Syr[2]);
-    Ixyi += wp * (xp[0] * Syi[0] + xp[1] * Syi[1] + xp[2] * Syi[2]);
   }
-  write_local_block(md, i, j, jj, k, Li, Lj, I0r, I0i, Ixr, Ixi, Iyr, Iyi, Ixyr, Ixyi, Zc, ldc);
+  double R0 = 0.0;
+  if constexpr (NT > 0) {
+    const double s = dc[0] * dc[0] + dc[1] * dc[1] + dc[2] * dc[2];
+    R0 = s * rsqrt_pos(fmax(s, 1e-300));   // zero where two centroids coincide
+  }
+  double Nr[3][3], Ni[3][3];
+#pragma unroll
+  for (int o = 0; o < 2; ++o) {
+    double Tr[3] = {0, 0, 0}, Ti[3] = {0, 0, 0};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double e0 = fma(R.d[o], Li[a][0], dc[0]), e1 = fma(R.d[o], Li[a][1], dc[1]),
+                   e2 = fma(R.d[o], Li[a][2], dc[2]);
+      double Mr[3], Mi[3];
+      double base_r = 0, base_i = 0;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        double sr = 0, si = 0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          const double d0 = fma(-R.d[u], Lj[b][0], e0), d1 = fma(-R.d[u], Lj[b][1], e1),
+                       d2 = fma(-R.d[u], Lj[b][2], e2);
+          const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+          const double ir = rsqrt_pos(r2);
+          double sn, cs;
+          if constexpr (NT > 0)
+            sincos_short<NT>(fma(r2, ir, -R0), &sn, &cs);
+          else
+            sincos_phase(r2 * ir, &sn, &cs);
+          const double gr = cs * ir, gi = sn * ir;
+          sr = b ? sr + gr : gr;
+          si = b ? si + gi : gi;
+          Mr[b] = u ? fma(R.wd[u], gr, Mr[b]) : R.wd[u] * gr;
+          Mi[b] = u ? fma(R.wd[u], gi, Mi[b]) : R.wd[u] * gi;
+        }
+        base_r = u ? fma(R.wb[u], sr, base_r) : R.wb[u] * sr;
+        base_i = u ? fma(R.wb[u], si, base_i) : R.wb[u] * si;
+      }
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        Mr[b] += base_r;
+        Mi[b] += base_i;
+        Tr[b] += Mr[b];
+        Ti[b] += Mi[b];
+        Nr[a][b] = o ? fma(R.wd[o], Mr[b], Nr[a][b]) : R.wd[o] * Mr[b];
+        Ni[a][b] = o ? fma(R.wd[o], Mi[b], Ni[a][b]) : R.wd[o] * Mi[b];
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        Nr[a][b] = fma(R.wb[o], Tr[b], Nr[a][b]);
+        Ni[a][b] = fma(R.wb[o], Ti[b], Ni[a][b]);
+      }
+  }
+  double D[3][3], Ur[3] = {0, 0, 0}, Ui[3] = {0, 0, 0}, Vr[3] = {0, 0, 0}, Vi[3] = {0, 0, 0};
+  double Ir = 0, Ii = 0, Xr = 0, Xi = 0;
+  double cr[3], cim[3];
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    cr[b] = Nr[0][b] + Nr[1][b] + Nr[2][b];
+    cim[b] = Ni[0][b] + Ni[1][b] + Ni[2][b];
+    Ir += cr[b];
+    Ii += cim[b];
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const double rr = Nr[a][0] + Nr[a][1] + Nr[a][2], ri = Ni[a][0] + Ni[a][1] + Ni[a][2];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      D[a][b] = 0.25 * (Li[a][0] * Lj[b][0] + Li[a][1] * Lj[b][1] + Li[a][2] * Lj[b][2]);
+      Ur[b] = fma(rr, D[a][b], Ur[b]);
+      Ui[b] = fma(ri, D[a][b], Ui[b]);
+      Vr[a] = fma(cr[b], D[a][b], Vr[a]);
+      Vi[a] = fma(cim[b], D[a][b], Vi[a]);
+      Xr = fma(Nr[a][b], D[a][b], Xr);
+      Xi = fma(Ni[a][b], D[a][b], Xi);
+    }
+  }
+  // i / (4 pi) e^{iR0} times the areas
+  double fr, fi;
+  const double sc = md.area[i] * md.area[j] * kInv4Pi;
+  if constexpr (NT > 0) {
+    double sn, cs;
+    sincos_phase(R0, &sn, &cs);
+    fr = -sc * sn;
+    fi = sc * cs;
+  } else {
+    fr = 0.0;
+    fi = sc;
+  }
+  auto turn = [&](double& xr, double& xi) {
+    const double t = fr * xr - fi * xi;
+    xi = fr * xi + fi * xr;
+    xr = t;
+  };
+  Xr = Ir - Xr;
+  Xi = Ii - Xi;
+  turn(Xr, Xi);
+  turn(Ir, Ii);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    turn(Ur[a], Ui[a]);
+    turn(Vr[a], Vi[a]);
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const double al = md.alpha[a * nt + i];
+    c128* row = Zc + (int64_t)(3 * i + a) * ldc + 3 * jj;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const double g = al * md.alpha[b * nt + j];
+      row[b] = c128{g * fma(-D[a][b], Ir, Xr + Ur[b] + Vr[a]), g * fma(-D[a][b], Ii, Xi + Ui[b] + Vi[a])};
+    }
+  }
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -412,6 +531,37 @@ __global__ __launch_bounds__(256) void k_assemble_gather_c64(int ne, const int32
 }
 
 namespace {
+// Terms of the short phase series: six and eight reach half an ulp of one on
+// these ranges (0.43^14 / 14! and 0.95^18 / 18! are below 1e-16), beyond them
+// the general reduction is the cheaper one.
+constexpr double kShortPhase6 = 0.43, kShortPhase8 = 0.95;
+
+// phase: bound of k |r - R0| over the mesh's pairs.
+void launch_regular(hipStream_t s, const MeshDev& md, const Orbits6& R, double k, double phase, int j0, int w,
+                    c128* Zc, int64_t ldc) {
+  const dim3 g((w + 63) / 64, (md.nt + 3) / 4), b(256);
+  if (phase <= kShortPhase6)
+    hipLaunchKernelGGL(k_assemble_regular<6>, g, b, 0, s, md, R, k, j0, w, Zc, ldc);
+  else if (phase <= kShortPhase8)
+    hipLaunchKernelGGL(k_assemble_regular<8>, g, b, 0, s, md, R, k, j0, w, Zc, ldc);
+  else
+    hipLaunchKernelGGL(k_assemble_regular<0>, g, b, 0, s, md, R, k, j0, w, Zc, ldc);
+  FOSB_LAUNCH_CHECK();
+}
+
+Orbits6 orbits6() {
+  double l[6][3], w[6];
+  rule6(l, w);
+  Orbits6 R;
+  for (int o = 0; o < 2; ++o) {
+    const double b = l[3 * o][1];
+    R.d[o] = l[3 * o][0] - b;
+    R.wb[o] = w[3 * o] * b;
+    R.wd[o] = w[3 * o] * R.d[o];
+  }
+  return R;
+}
+
 // Triangle-column bands of the local EFIE blocks.  For each band [j0, j1) of
 // column triangles, the regular and touching-pair kernels fill Zc (3 nt x 3 w
 // local blocks, row stride ldc) and sink(stream, j0, j1, Zc, ldc, cols, ncols)
@@ -427,21 +577,12 @@ void assemble_bands(Context& ctx, const Mesh& m, double k, int n_gauss, int64_t 
   hipStream_t s = ctx.stream;
   const MeshHost& h = m.h;
   const int nt = (int)h.nt, ne = (int)h.ne;
-  {  // every phase k |x - y| stays within the range of sincos_phase
-    double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
-    for (int64_t v = 0; v < h.nv; ++v)
-      for (int q = 0; q < 3; ++q) {
-        lo[q] = std::min(lo[q], h.V[3 * v + q]);
-        hi[q] = std::max(hi[q], h.V[3 * v + q]);
-      }
-    const double diag = std::sqrt((hi[0] - lo[0]) * (hi[0] - lo[0]) + (hi[1] - lo[1]) * (hi[1] - lo[1]) +
-                                  (hi[2] - lo[2]) * (hi[2] - lo[2]));
-    if (!(k * diag <= kTrigPhaseMax))
-      fail(FOSB_E_INVALID, "k * (mesh bounding-box diagonal) = %g exceeds %g", k * diag, kTrigPhaseMax);
-  }
+  // every phase k |x - y| stays within the range of sincos_phase
+  if (!(k * h.diag <= kTrigPhaseMax))
+    fail(FOSB_E_INVALID, "k * (mesh bounding-box diagonal) = %g exceeds %g", k * h.diag, kTrigPhaseMax);
   ensure_ss_table(ctx, n_gauss);
-  Rule6 R;
-  rule6(R.l, R.w);
+  const Orbits6 R = orbits6();
+  const double phase = 2.0 * k * h.hmax;
   int jc = (int)std::max<int64_t>(1, std::min<int64_t>(nt, budget / (9LL * nt * (int64_t)sizeof(c128))));
   if (jc < nt) jc = std::max(64, jc / 64 * 64);
   jc = std::min(jc, nt);
@@ -484,9 +625,7 @@ void assemble_bands(Context& ctx, const Mesh& m, double k, int n_gauss, int64_t 
     const int buf = two ? (bi & 1) : 0;
     c128* Zc = Zbuf[buf];
     if (two && bi >= 2) FOSB_HIP(hipStreamWaitEvent(s, ev.e[2 + buf], 0));   // band bi - 2 consumed
-    dim3 g1((w + 63) / 64, (nt + 3) / 4);
-    hipLaunchKernelGGL(k_assemble_regular, g1, dim3(256), 0, s, md, R, k, j0, w, Zc, ldc);
-    FOSB_LAUNCH_CHECK();
+    launch_regular(s, md, R, k, phase, j0, w, Zc, ldc);
     const int pb = (int)(std::lower_bound(h.tp_j.begin(), h.tp_j.end(), j0) - h.tp_j.begin());
     const int pe = (int)(std::lower_bound(h.tp_j.begin(), h.tp_j.end(), j1) - h.tp_j.begin());
     if (pe > pb) {

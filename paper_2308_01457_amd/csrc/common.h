@@ -243,6 +243,8 @@ struct MeshHost {
   std::vector<double> edge_len;    // ne
   std::vector<int32_t> edge_tri;   // ne*2 (T+, T-)
   std::vector<int32_t> edge_loc;   // ne*2
+  double diag = 0;                 // diagonal of the bounding box
+  double hmax = 0;                 // largest distance of a vertex from the centroid of its triangle
   // touching ordered pairs (i, j), sorted by j then i
   std::vector<int32_t> tp_i, tp_j, tp_kind;   // kind: 0 identical, 1 edge, 2 vertex
   std::vector<int32_t> tp_ord;                // 6 per pair: local slots of (P0,P1,P2) in i, then in j

@@ -26,6 +26,16 @@ void mesh_build_host(const double* V, int64_t nv, const int32_t* F, int64_t nt, 
     if (!std::isfinite(V[i])) fail(FOSB_E_INVALID, "mesh: non-finite vertex coordinate at %lld", (long long)i);
     scale = std::max(scale, std::fabs(V[i]));
   }
+  {
+    double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300}, d2 = 0.0;
+    for (int64_t i = 0; i < 3 * nv; ++i) {
+      lo[i % 3] = std::min(lo[i % 3], V[i]);
+      hi[i % 3] = std::max(hi[i % 3], V[i]);
+    }
+    for (int q = 0; q < 3; ++q) d2 += (hi[q] - lo[q]) * (hi[q] - lo[q]);
+    m.diag = std::sqrt(d2);
+  }
+  m.hmax = 0.0;
   m.area.resize(nt);
   m.normal.resize(3 * nt);
   double vol6 = 0.0;
@@ -43,6 +53,14 @@ void mesh_build_host(const double* V, int64_t nv, const int32_t* F, int64_t nt, 
     double len = std::sqrt(cr[0] * cr[0] + cr[1] * cr[1] + cr[2] * cr[2]);
     if (!(len > 1e-14 * scale * scale)) fail(FOSB_E_INVALID, "mesh: degenerate triangle %lld", (long long)t);
     m.area[t] = 0.5 * len;
+    for (const double* p : {p0, p1, p2}) {
+      double d2 = 0.0;
+      for (int q = 0; q < 3; ++q) {
+        const double d = p[q] - (p0[q] + p1[q] + p2[q]) / 3.0;
+        d2 += d * d;
+      }
+      m.hmax = std::max(m.hmax, std::sqrt(d2));
+    }
     for (int k = 0; k < 3; ++k) m.normal[3 * t + k] = cr[k] / len;
     // p0 . (p1 x p2)
     vol6 += p0[0] * (p1[1] * p2[2] - p1[2] * p2[1]) + p0[1] * (p1[2] * p2[0] - p1[0] * p2[2]) +
