@@ -87,11 +87,12 @@ __device__ __forceinline__ double rsqrt_pos(double x) {
   return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-__device__ __forceinline__ void write_local_block(const MeshDev& md, int i, int j, int jj, double k,
+// blk: first entry of the 3 x 3 block, rows ldc apart.
+__device__ __forceinline__ void write_local_block(const MeshDev& md, int i, int j, double k,
                                                   const double Li[3][3], const double Lj[3][3], double I0r,
                                                   double I0i, const double Ixr[3], const double Ixi[3],
                                                   const double Iyr[3], const double Iyi[3], double Ixyr,
-                                                  double Ixyi, c128* __restrict__ Zc, int64_t ldc) {
+                                                  double Ixyi, c128* __restrict__ blk, int64_t ldc) {
   const int nt = md.nt;
   const double ik = 1.0 / k;
 #pragma unroll
@@ -100,7 +101,7 @@ __device__ __forceinline__ void write_local_block(const MeshDev& md, int i, int 
     const double Pa0 = Li[a][0], Pa1 = Li[a][1], Pa2 = Li[a][2];
     const double PIyr = Pa0 * Iyr[0] + Pa1 * Iyr[1] + Pa2 * Iyr[2];
     const double PIyi = Pa0 * Iyi[0] + Pa1 * Iyi[1] + Pa2 * Iyi[2];
-    c128* row = Zc + (int64_t)(3 * i + a) * ldc + 3 * jj;
+    c128* row = blk + a * ldc;
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
       const double be = md.alpha[b * nt + j];
@@ -156,7 +157,8 @@ struct Orbits6 {
   double d[2], wb[2], wd[2];
 };
 
-// One thread per ordered non-touching triangle pair (i, j0 + jj).
+// One thread per ordered triangle pair (i0 + row, j0 + jj); zeros for touching
+// pairs, whose blocks come from the singular kernel.
 //
 // Bound by FP64 VALU issue, so it is written for few instructions per point
 // pair.  Lengths are in units of 1/k (the phase is the distance).  With
@@ -173,154 +175,175 @@ struct Orbits6 {
 //   Ixy = sum N D,  I0 = sum N.
 // Vector instructions per point pair, all included: 48.7 with NT = 6, 52.6 with
 // NT = 8, 70.1 with NT = 0 (78.6 with sincos_phase on every point pair and
-// moments of the coordinates); at nt = 20480 (N = 30720) the launches of one
-// matrix add up to 42 ms instead of 53 beside the gather, the matrix takes 49.4
-// instead of 61.7.
+// moments of the coordinates).  Alone, on all pairs of nt = 5120: 1.8 ms (issue
+// alone would take 1.2, the blocks' 3.8 GB 0.9); 140 registers leave three
+// wavefronts per SIMD, and four (spilling 52 bytes) are slower.
 template <int NT>
-__global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Orbits6 R, double k, int j0, int jc,
-                                                          c128* __restrict__ Zc, int64_t ldc) {
-  const int jj = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int i = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (threadIdx.x >> 6));
-  if (jj >= jc || i >= md.nt) return;
-  const int j = j0 + jj;
+__global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Orbits6 R, double k, int i0, int j0,
+                                                          int jc, c128* __restrict__ Zc, int64_t ldc) {
+  __shared__ c128 stage[4][3 * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + wave);
+  const int i = i0 + row;
+  if (i >= md.nt) return;
+  const int jj0 = blockIdx.x * 64, j = j0 + min(jj0 + lane, jc - 1);
   const int nt = md.nt;
+  bool touch;
   {
     const int a0 = md.fv[i], a1 = md.fv[nt + i], a2 = md.fv[2 * nt + i];
     const int b0 = md.fv[j], b1 = md.fv[nt + j], b2 = md.fv[2 * nt + j];
-    if (a0 == b0 || a0 == b1 || a0 == b2 || a1 == b0 || a1 == b1 || a1 == b2 || a2 == b0 || a2 == b1 ||
-        a2 == b2)
-      return;  // touching pair: integrated by the singular kernel
+    touch = a0 == b0 || a0 == b1 || a0 == b2 || a1 == b0 || a1 == b1 || a1 == b2 || a2 == b0 || a2 == b1 ||
+            a2 == b2;
   }
-  double Li[3][3], Lj[3][3], dc[3];
-  {
-    double ci[3], cj[3];
-    load_tri(md, i, Li, ci);
-    load_tri(md, j, Lj, cj);
+  c128 out[3][3] = {};
+  if (!touch) {
+    double Li[3][3], Lj[3][3], dc[3];
+    {
+      double ci[3], cj[3];
+      load_tri(md, i, Li, ci);
+      load_tri(md, j, Lj, cj);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      dc[c] = k * (ci[c] - cj[c]);
+      for (int c = 0; c < 3; ++c) {
+        dc[c] = k * (ci[c] - cj[c]);
 #pragma unroll
-      for (int v = 0; v < 3; ++v) {
-        Li[v][c] = k * (Li[v][c] - ci[c]);
-        Lj[v][c] = k * (Lj[v][c] - cj[c]);
+        for (int v = 0; v < 3; ++v) {
+          Li[v][c] = k * (Li[v][c] - ci[c]);
+          Lj[v][c] = k * (Lj[v][c] - cj[c]);
+        }
       }
     }
-  }
-  double R0 = 0.0;
-  if constexpr (NT > 0) {
-    const double s = dc[0] * dc[0] + dc[1] * dc[1] + dc[2] * dc[2];
-    R0 = s * rsqrt_pos(fmax(s, 1e-300));   // zero where two centroids coincide
-  }
-  double Nr[3][3], Ni[3][3];
+    double R0 = 0.0;
+    if constexpr (NT > 0) {
+      const double s = dc[0] * dc[0] + dc[1] * dc[1] + dc[2] * dc[2];
+      R0 = s * rsqrt_pos(fmax(s, 1e-300));   // zero where two centroids coincide
+    }
+    double Nr[3][3], Ni[3][3];
 #pragma unroll
-  for (int o = 0; o < 2; ++o) {
-    double Tr[3] = {0, 0, 0}, Ti[3] = {0, 0, 0};
+    for (int o = 0; o < 2; ++o) {
+      double Tr[3] = {0, 0, 0}, Ti[3] = {0, 0, 0};
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const double e0 = fma(R.d[o], Li[a][0], dc[0]), e1 = fma(R.d[o], Li[a][1], dc[1]),
-                   e2 = fma(R.d[o], Li[a][2], dc[2]);
-      double Mr[3], Mi[3];
-      double base_r = 0, base_i = 0;
+      for (int a = 0; a < 3; ++a) {
+        const double e0 = fma(R.d[o], Li[a][0], dc[0]), e1 = fma(R.d[o], Li[a][1], dc[1]),
+                     e2 = fma(R.d[o], Li[a][2], dc[2]);
+        double Mr[3], Mi[3];
+        double base_r = 0, base_i = 0;
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        double sr = 0, si = 0;
+        for (int u = 0; u < 2; ++u) {
+          double sr = 0, si = 0;
+#pragma unroll
+          for (int b = 0; b < 3; ++b) {
+            const double d0 = fma(-R.d[u], Lj[b][0], e0), d1 = fma(-R.d[u], Lj[b][1], e1),
+                         d2 = fma(-R.d[u], Lj[b][2], e2);
+            const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+            const double ir = rsqrt_pos(r2);
+            double sn, cs;
+            if constexpr (NT > 0)
+              sincos_short<NT>(fma(r2, ir, -R0), &sn, &cs);
+            else
+              sincos_phase(r2 * ir, &sn, &cs);
+            const double gr = cs * ir, gi = sn * ir;
+            sr = b ? sr + gr : gr;
+            si = b ? si + gi : gi;
+            Mr[b] = u ? fma(R.wd[u], gr, Mr[b]) : R.wd[u] * gr;
+            Mi[b] = u ? fma(R.wd[u], gi, Mi[b]) : R.wd[u] * gi;
+          }
+          base_r = u ? fma(R.wb[u], sr, base_r) : R.wb[u] * sr;
+          base_i = u ? fma(R.wb[u], si, base_i) : R.wb[u] * si;
+        }
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-          const double d0 = fma(-R.d[u], Lj[b][0], e0), d1 = fma(-R.d[u], Lj[b][1], e1),
-                       d2 = fma(-R.d[u], Lj[b][2], e2);
-          const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-          const double ir = rsqrt_pos(r2);
-          double sn, cs;
-          if constexpr (NT > 0)
-            sincos_short<NT>(fma(r2, ir, -R0), &sn, &cs);
-          else
-            sincos_phase(r2 * ir, &sn, &cs);
-          const double gr = cs * ir, gi = sn * ir;
-          sr = b ? sr + gr : gr;
-          si = b ? si + gi : gi;
-          Mr[b] = u ? fma(R.wd[u], gr, Mr[b]) : R.wd[u] * gr;
-          Mi[b] = u ? fma(R.wd[u], gi, Mi[b]) : R.wd[u] * gi;
+          Mr[b] += base_r;
+          Mi[b] += base_i;
+          Tr[b] += Mr[b];
+          Ti[b] += Mi[b];
+          Nr[a][b] = o ? fma(R.wd[o], Mr[b], Nr[a][b]) : R.wd[o] * Mr[b];
+          Ni[a][b] = o ? fma(R.wd[o], Mi[b], Ni[a][b]) : R.wd[o] * Mi[b];
         }
-        base_r = u ? fma(R.wb[u], sr, base_r) : R.wb[u] * sr;
-        base_i = u ? fma(R.wb[u], si, base_i) : R.wb[u] * si;
       }
 #pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        Mr[b] += base_r;
-        Mi[b] += base_i;
-        Tr[b] += Mr[b];
-        Ti[b] += Mi[b];
-        Nr[a][b] = o ? fma(R.wd[o], Mr[b], Nr[a][b]) : R.wd[o] * Mr[b];
-        Ni[a][b] = o ? fma(R.wd[o], Mi[b], Ni[a][b]) : R.wd[o] * Mi[b];
-      }
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          Nr[a][b] = fma(R.wb[o], Tr[b], Nr[a][b]);
+          Ni[a][b] = fma(R.wb[o], Ti[b], Ni[a][b]);
+        }
     }
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        Nr[a][b] = fma(R.wb[o], Tr[b], Nr[a][b]);
-        Ni[a][b] = fma(R.wb[o], Ti[b], Ni[a][b]);
-      }
-  }
-  double D[3][3], Ur[3] = {0, 0, 0}, Ui[3] = {0, 0, 0}, Vr[3] = {0, 0, 0}, Vi[3] = {0, 0, 0};
-  double Ir = 0, Ii = 0, Xr = 0, Xi = 0;
-  double cr[3], cim[3];
-#pragma unroll
-  for (int b = 0; b < 3; ++b) {
-    cr[b] = Nr[0][b] + Nr[1][b] + Nr[2][b];
-    cim[b] = Ni[0][b] + Ni[1][b] + Ni[2][b];
-    Ir += cr[b];
-    Ii += cim[b];
-  }
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const double rr = Nr[a][0] + Nr[a][1] + Nr[a][2], ri = Ni[a][0] + Ni[a][1] + Ni[a][2];
+    double D[3][3], Ur[3] = {0, 0, 0}, Ui[3] = {0, 0, 0}, Vr[3] = {0, 0, 0}, Vi[3] = {0, 0, 0};
+    double Ir = 0, Ii = 0, Xr = 0, Xi = 0;
+    double cr[3], cim[3];
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
-      D[a][b] = 0.25 * (Li[a][0] * Lj[b][0] + Li[a][1] * Lj[b][1] + Li[a][2] * Lj[b][2]);
-      Ur[b] = fma(rr, D[a][b], Ur[b]);
-      Ui[b] = fma(ri, D[a][b], Ui[b]);
-      Vr[a] = fma(cr[b], D[a][b], Vr[a]);
-      Vi[a] = fma(cim[b], D[a][b], Vi[a]);
-      Xr = fma(Nr[a][b], D[a][b], Xr);
-      Xi = fma(Ni[a][b], D[a][b], Xi);
+      cr[b] = Nr[0][b] + Nr[1][b] + Nr[2][b];
+      cim[b] = Ni[0][b] + Ni[1][b] + Ni[2][b];
+      Ir += cr[b];
+      Ii += cim[b];
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double rr = Nr[a][0] + Nr[a][1] + Nr[a][2], ri = Ni[a][0] + Ni[a][1] + Ni[a][2];
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        D[a][b] = 0.25 * (Li[a][0] * Lj[b][0] + Li[a][1] * Lj[b][1] + Li[a][2] * Lj[b][2]);
+        Ur[b] = fma(rr, D[a][b], Ur[b]);
+        Ui[b] = fma(ri, D[a][b], Ui[b]);
+        Vr[a] = fma(cr[b], D[a][b], Vr[a]);
+        Vi[a] = fma(cim[b], D[a][b], Vi[a]);
+        Xr = fma(Nr[a][b], D[a][b], Xr);
+        Xi = fma(Ni[a][b], D[a][b], Xi);
+      }
+    }
+    // i / (4 pi) e^{iR0} times the areas
+    double fr, fi;
+    const double sc = md.area[i] * md.area[j] * kInv4Pi;
+    if constexpr (NT > 0) {
+      double sn, cs;
+      sincos_phase(R0, &sn, &cs);
+      fr = -sc * sn;
+      fi = sc * cs;
+    } else {
+      fr = 0.0;
+      fi = sc;
+    }
+    auto turn = [&](double& xr, double& xi) {
+      const double t = fr * xr - fi * xi;
+      xi = fr * xi + fi * xr;
+      xr = t;
+    };
+    Xr = Ir - Xr;
+    Xi = Ii - Xi;
+    turn(Xr, Xi);
+    turn(Ir, Ii);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      turn(Ur[a], Ui[a]);
+      turn(Vr[a], Vi[a]);
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double al = md.alpha[a * nt + i];
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        const double g = al * md.alpha[b * nt + j];
+        out[a][b] = c128{g * fma(-D[a][b], Ir, Xr + Ur[b] + Vr[a]), g * fma(-D[a][b], Ii, Xi + Ui[b] + Vi[a])};
+      }
     }
   }
-  // i / (4 pi) e^{iR0} times the areas
-  double fr, fi;
-  const double sc = md.area[i] * md.area[j] * kInv4Pi;
-  if constexpr (NT > 0) {
-    double sn, cs;
-    sincos_phase(R0, &sn, &cs);
-    fr = -sc * sn;
-    fi = sc * cs;
-  } else {
-    fr = 0.0;
-    fi = sc;
-  }
-  auto turn = [&](double& xr, double& xi) {
-    const double t = fr * xr - fi * xi;
-    xi = fr * xi + fi * xr;
-    xr = t;
-  };
-  Xr = Ir - Xr;
-  Xi = Ii - Xi;
-  turn(Xr, Xi);
-  turn(Ir, Ii);
+  // Row by row through the wavefront's own LDS, so that each store of the wave
+  // is contiguous: 16-byte pieces 48 bytes apart cost three times the requests.
+  c128* st = stage[wave];
+  const int last = 3 * min(64, jc - jj0);
+  c128* dst = Zc + 3LL * row * ldc + 3 * jj0;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    turn(Ur[a], Ui[a]);
-    turn(Vr[a], Vi[a]);
-  }
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const double al = md.alpha[a * nt + i];
-    c128* row = Zc + (int64_t)(3 * i + a) * ldc + 3 * jj;
+    for (int b = 0; b < 3; ++b) st[3 * lane + b] = out[a][b];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      const double g = al * md.alpha[b * nt + j];
-      row[b] = c128{g * fma(-D[a][b], Ir, Xr + Ur[b] + Vr[a]), g * fma(-D[a][b], Ii, Xi + Ui[b] + Vi[a])};
-    }
+    for (int b = 0; b < 3; ++b)
+      if (64 * b + lane < last) dst[a * ldc + 64 * b + lane] = st[64 * b + lane];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -330,7 +353,12 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// One wavefront per touching ordered pair; lanes stride over the Sauter-Schwab points.
+// One wavefront per touching ordered pair p; lanes stride over the Sauter-Schwab
+// points.  The block goes to its place in the band Zc (row stride ldc), or, with
+// ldc = 0, to entry 9 (p - pbeg) of a list of blocks.  NT as for the regular pairs,
+// for the phase itself (no two points of touching triangles are further apart
+// than both diameters, 2 h_i + 2 h_j).
+template <int NT>
 __global__ __launch_bounds__(256) void k_assemble_singular(MeshDev md, const int32_t* __restrict__ tp_i,
                                                            const int32_t* __restrict__ tp_j,
                                                            const int32_t* __restrict__ tp_kind,
@@ -378,10 +406,13 @@ __global__ __launch_bounds__(256) void k_assemble_singular(MeshDev md, const int
     }
     const double d0 = x[0] - y[0] + dc0, d1 = x[1] - y[1] + dc1, d2 = x[2] - y[2] + dc2;
     const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-    const double ir = rsqrt(r2);
+    const double ir = rsqrt_pos(r2);
     const double r = r2 * ir;
     double sn, cs;
-    sincos(k * r, &sn, &cs);
+    if constexpr (NT > 0)
+      sincos_short<NT>(k * r, &sn, &cs);
+    else
+      sincos_phase(k * r, &sn, &cs);
     const double g = w * jac * ir;
     const double gr = cs * g, gi = sn * g;
     I0r += gr;
@@ -408,49 +439,208 @@ __global__ __launch_bounds__(256) void k_assemble_singular(MeshDev md, const int
     Iyr[q] = wave_sum(Iyr[q]);
     Iyi[q] = wave_sum(Iyi[q]);
   }
-  if (lane == 0) write_local_block(md, i, j, j - j0, k, Li, Lj, I0r, I0i, Ixr, Ixi, Iyr, Iyi, Ixyr, Ixyi, Zc, ldc);
+  if (lane == 0)
+    write_local_block(md, i, j, k, Li, Lj, I0r, I0i, Ixr, Ixi, Iyr, Iyi, Ixyr, Ixyi,
+                      ldc ? Zc + 3LL * i * ldc + 3 * (j - j0) : Zc + 9LL * (p - pbeg), ldc ? ldc : 3);
 }
 
-// Z[m][n] for the columns n listed for this band: sum of the (up to) four local
-// blocks of the band; store when the band holds T+ of n, add otherwise.  With
-// Zl, the final entries are also stored rounded to complex64.
-__global__ __launch_bounds__(256) void k_assemble_gather(int ne, const int32_t* __restrict__ edge_tri,
-                                                         const int32_t* __restrict__ edge_loc, int j0, int j1,
-                                                         const int32_t* __restrict__ cols, int ncols,
-                                                         const c128* __restrict__ Zc, int64_t ldc,
-                                                         c128* __restrict__ Z, int64_t ldz,
-                                                         c64* __restrict__ Zl, int64_t ldl) {
-  const int ci = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int m = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (ci >= ncols || m >= ne) return;
-  const int n = cols[ci];
-  const int tp = edge_tri[n], tm = edge_tri[ne + n];
-  const int64_t rp = 3 * (int64_t)edge_tri[m] + edge_loc[m];
-  const int64_t rm = 3 * (int64_t)edge_tri[ne + m] + edge_loc[ne + m];
-  double sr = 0.0, si = 0.0;
-  const bool has_p = tp >= j0 && tp < j1;
-  if (has_p) {
-    const int64_t c = 3 * (int64_t)(tp - j0) + edge_loc[n];
-    const c128 u = Zc[rp * ldc + c], v = Zc[rm * ldc + c];
-    sr += u.re + v.re;
-    si += u.im + v.im;
+// The local blocks of a band of column triangles [j0, j1), rows from triangle
+// j0 on: block (i, j) at row 3 (i - j0), column 3 (j - j0).  The 6-point rule is
+// the same in both triangles, so block (j, i) is the transpose of block (i, j)
+// and the pairs with a row before the band come from that row's own band.
+// The RWG functions on the band's triangles are by_q[0 .. nq) (T- in the band;
+// those with T+ in it as well are skipped here) and e0, e0 + 1, ... (T+ in the
+// band: edges are numbered by their T+, and T+ < T-).
+struct Band {
+  int j0, j1;
+  const int32_t* by_q;
+  int nq, e0, n;
+  const c128* Zc;
+  int64_t ldc;
+};
+
+__device__ __forceinline__ int band_edge(const Band& b, const int32_t* __restrict__ edge_tri, int x) {
+  if (x >= b.n) return -1;
+  if (x >= b.nq) return b.e0 + x - b.nq;
+  const int e = b.by_q[x];
+  return edge_tri[e] >= b.j0 ? -1 : e;
+}
+
+__device__ __forceinline__ void add_to(c128& s, const c128& v) {
+  s.re += v.re;
+  s.im += v.im;
+}
+
+// Z[m][n] = Z[n][m] for n on the band's triangles and m on none of them but on
+// one after the band.  The first band of an entry, that of the lesser of both
+// T+, stores it, later ones add; with Zl the entry is also stored rounded to
+// complex64 once it is final, in the band of the lesser of both T-.  A tile of
+// 32 rows m by 64 columns n is summed and written along n, and written once
+// more along m through the LDS.  Bound by memory: the band's blocks are read
+// once (30 GB over an N = 30720 matrix), Z is written about 1.7 times.
+__global__ __launch_bounds__(256) void k_band_strip(int ne, const int32_t* __restrict__ edge_tri,
+                                                    const int32_t* __restrict__ edge_loc, Band B,
+                                                    c128* __restrict__ Z, int64_t ldz, c64* __restrict__ Zl,
+                                                    int64_t ldl) {
+  constexpr int TM = 32, TN = 64;
+  __shared__ c128 tile[TM][TN + 1];
+  __shared__ int mine[TM], col[TN];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m0 = blockIdx.y * TM;
+  bool on = false;
+  if (threadIdx.x < TM) {
+    const int m = m0 + (int)threadIdx.x;
+    if (m < ne) {
+      const int p = edge_tri[m];
+      on = edge_tri[ne + m] >= B.j1 && (p < B.j0 || p >= B.j1);
+    }
+    mine[threadIdx.x] = on;
   }
-  if (tm >= j0 && tm < j1) {
-    const int64_t c = 3 * (int64_t)(tm - j0) + edge_loc[ne + n];
-    const c128 u = Zc[rp * ldc + c], v = Zc[rm * ldc + c];
-    sr += u.re + v.re;
-    si += u.im + v.im;
+  if (!__syncthreads_or(on)) return;
+  const int n = band_edge(B, edge_tri, blockIdx.x * TN + lane);
+  int tp = 0, tm = 0;
+  bool has_p = false, has_m = false;
+  int64_t cp = 0, cm = 0;
+  if (n >= 0) {
+    tp = edge_tri[n];
+    tm = edge_tri[ne + n];
+    has_p = tp >= B.j0;
+    has_m = tm < B.j1;
+    cp = 3LL * (tp - B.j0) + edge_loc[n];
+    cm = 3LL * (tm - B.j0) + edge_loc[ne + n];
   }
+  // -1: no entry; else 2 n + (final in this band)
+  if (wave == 0) col[lane] = n < 0 ? -1 : 2 * n + (has_m ? 1 : 0);
+  // all loads of four rows are unconditional (absent parts read a present
+  // part's place, absent rows the band's first), so that they are in flight together
+  if (!has_p) cp = has_m ? cm : 0;
+  if (!has_m) cm = cp;
+  for (int g = 0; g < TM; g += 16) {
+    c128 v[4][4], s[4];
+    bool late[4];   // T+ of m after the band, else before it
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = __builtin_amdgcn_readfirstlane(g + 4 * q + wave), m = m0 + r;
+      const bool act = __builtin_amdgcn_readfirstlane(mine[r]);
+      const int mc = act ? m : 0;
+      const int mp = edge_tri[mc], mm = edge_tri[ne + mc];
+      late[q] = act && mp >= B.j1;
+      const c128* rm = B.Zc + (act ? (3LL * (mm - B.j0) + edge_loc[ne + mc]) * B.ldc : 0);
+      const c128* rp = late[q] ? B.Zc + (3LL * (mp - B.j0) + edge_loc[mc]) * B.ldc : rm;
+      v[q][0] = rm[cp];
+      v[q][1] = rp[cp];
+      v[q][2] = rm[cm];
+      v[q][3] = rp[cm];
+      s[q] = c128{0.0, 0.0};
+      if (act && n >= 0 && !(late[q] && has_p)) s[q] = Z[(int64_t)m * ldz + n];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = g + 4 * q + wave, m = m0 + r;
+      if (n < 0 || !mine[r]) continue;
+      if (has_p) {
+        add_to(s[q], v[q][0]);
+        if (late[q]) add_to(s[q], v[q][1]);
+      }
+      if (has_m) {
+        add_to(s[q], v[q][2]);
+        if (late[q]) add_to(s[q], v[q][3]);
+      }
+      Z[(int64_t)m * ldz + n] = s[q];
+      if (Zl && has_m) Zl[(int64_t)m * ldl + n] = c64{(float)s[q].re, (float)s[q].im};
+      tile[r][lane] = s[q];
+    }
+  }
+  __syncthreads();
+  const int r = threadIdx.x & 31;
+  if (!mine[r]) return;
+  for (int c = threadIdx.x >> 5; c < TN; c += 8) {
+    const int v = col[c];
+    if (v < 0) continue;
+    const c128 s = tile[r][c];
+    Z[(int64_t)(v >> 1) * ldz + m0 + r] = s;
+    if (Zl && (v & 1)) Zl[(int64_t)(v >> 1) * ldl + m0 + r] = c64{(float)s.re, (float)s.im};
+  }
+}
+
+// Z[m][n] for m and n both on the band's triangles; store, add and complex64
+// copy as in k_band_strip.
+__global__ __launch_bounds__(256) void k_band_square(int ne, const int32_t* __restrict__ edge_tri,
+                                                     const int32_t* __restrict__ edge_loc, Band B,
+                                                     c128* __restrict__ Z, int64_t ldz, c64* __restrict__ Zl,
+                                                     int64_t ldl) {
+  const int n = band_edge(B, edge_tri, blockIdx.x * 64 + (threadIdx.x & 63));
+  const int m = band_edge(B, edge_tri, blockIdx.y * 4 + (threadIdx.x >> 6));
+  if (n < 0 || m < 0) return;
+  const int tm[2] = {edge_tri[m], edge_tri[ne + m]}, tn[2] = {edge_tri[n], edge_tri[ne + n]};
+  const int lm[2] = {edge_loc[m], edge_loc[ne + m]}, ln[2] = {edge_loc[n], edge_loc[ne + n]};
+  c128 s{0.0, 0.0};
   c128* z = Z + (int64_t)m * ldz + n;
-  c128 out{sr, si};
-  if (!has_p) {
-    const c128 o = *z;
-    out = c128{o.re + sr, o.im + si};
+  if (tm[0] < B.j0 || tn[0] < B.j0) s = *z;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      if (tm[a] < B.j0 || tn[b] < B.j0) continue;
+      const int64_t r = 3LL * (tm[a] - B.j0) + lm[a], c = 3LL * (tn[b] - B.j0) + ln[b];
+      if (tn[b] < B.j1)
+        add_to(s, B.Zc[r * B.ldc + c]);
+      else if (tm[a] < B.j1)
+        add_to(s, B.Zc[c * B.ldc + r]);
+    }
+  *z = s;
+  if (Zl && (tm[1] < B.j1 || tn[1] < B.j1)) Zl[(int64_t)m * ldl + n] = c64{(float)s.re, (float)s.im};
+}
+
+// Adds the touching pairs' blocks S (9 entries per pair, pairs sorted by column
+// triangle, those of triangle j at beg[j] ..) to Z: one wavefront per column n,
+// lanes over the local functions of the triangles that touch T+ or T- of n.  An
+// entry (m, n) belongs to the first touching pair of (T+-(n), T+-(m)), which
+// adds all of them in that order.  The blocks of (i, j) and (j, i) are not the same: the
+// Sauter-Schwab points treat the two triangles differently.
+__global__ __launch_bounds__(256) void k_add_touching(MeshDev md, const int32_t* __restrict__ beg,
+                                                      const int32_t* __restrict__ tp_i, const c128* __restrict__ S,
+                                                      c128* __restrict__ Z, int64_t ldz, c64* __restrict__ Zl,
+                                                      int64_t ldl) {
+  const int n = blockIdx.x * 4 + (threadIdx.x >> 6), ne = md.ne, nt = md.nt;
+  if (n >= ne) return;
+  int b[2], c[2], ln[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int t = md.edge_tri[q * ne + n];
+    b[q] = beg[t];
+    c[q] = beg[t + 1] - b[q];
+    ln[q] = md.edge_loc[q * ne + n];
   }
-  *z = out;
-  // the optional complex64 copy receives the entry once it is final: T- lies
-  // in this band (T+ < T-, so an earlier band held T+ if this one does not)
-  if (Zl && tm < j1) Zl[(int64_t)m * ldl + n] = c64{(float)out.re, (float)out.im};
+  for (int x = threadIdx.x & 63; x < 3 * (c[0] + c[1]); x += 64) {
+    const int q = x >= 3 * c[0], y = x - (q ? 3 * c[0] : 0);
+    const int i = tp_i[(q ? b[1] : b[0]) + y / 3];
+    const int m = md.tri_edge[(y % 3) * nt + i];
+    const int m0 = md.edge_tri[m], m1 = md.edge_tri[ne + m];
+    c128 s{0.0, 0.0};
+    int first = -1;   // 2 (side of n) + (side of m) of the first touching pair
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      int at[2] = {-1, -1};
+      for (int e = b[u]; e < b[u] + c[u]; ++e) {
+        const int t = tp_i[e];
+        if (t == m0) at[0] = e;
+        if (t == m1) at[1] = e;
+      }
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+        if (at[v] >= 0) {
+          if (first < 0) first = 2 * u + v;
+          add_to(s, S[9LL * at[v] + 3 * md.edge_loc[v * ne + m] + ln[u]]);
+        }
+    }
+    if (first != 2 * q + (i == m0 ? 0 : 1)) continue;
+    c128* z = Z + (int64_t)m * ldz + n;
+    c128 o = *z;
+    add_to(o, s);
+    *z = o;
+    if (Zl) Zl[(int64_t)m * ldl + n] = c64{(float)o.re, (float)o.im};
+  }
 }
 
 static void ensure_ss_table(Context& ctx, int n) {
@@ -493,8 +683,10 @@ __global__ __launch_bounds__(256) void k_band_gather_x(int nt, const int32_t* __
   Xt[(int64_t)r * nrhs + c] = X[(int64_t)e * ldx + c];
 }
 
-// As k_assemble_gather, into a complex64 matrix: the first part of a column is
-// rounded and stored, the second added to it in FP64 and rounded again.
+// The columns n listed for a band of column triangles with rows of all triangles,
+// into a complex64 matrix: the sum of the (up to) four local blocks of the band,
+// rounded and stored on the band of T+, added on that of T- (if that is a later
+// one) in FP64 and rounded again.
 __global__ __launch_bounds__(256) void k_assemble_gather_c64(int ne, const int32_t* __restrict__ edge_tri,
                                                              const int32_t* __restrict__ edge_loc, int j0, int j1,
                                                              const int32_t* __restrict__ cols, int ncols,
@@ -537,17 +729,51 @@ namespace {
 constexpr double kShortPhase6 = 0.43, kShortPhase8 = 0.95;
 
 // phase: bound of k |r - R0| over the mesh's pairs.
-void launch_regular(hipStream_t s, const MeshDev& md, const Orbits6& R, double k, double phase, int j0, int w,
-                    c128* Zc, int64_t ldc) {
-  const dim3 g((w + 63) / 64, (md.nt + 3) / 4), b(256);
+void launch_regular(hipStream_t s, const MeshDev& md, const Orbits6& R, double k, double phase, int i0, int j0,
+                    int w, c128* Zc, int64_t ldc) {
+  const dim3 g((w + 63) / 64, (md.nt - i0 + 3) / 4), b(256);
   if (phase <= kShortPhase6)
-    hipLaunchKernelGGL(k_assemble_regular<6>, g, b, 0, s, md, R, k, j0, w, Zc, ldc);
+    hipLaunchKernelGGL(k_assemble_regular<6>, g, b, 0, s, md, R, k, i0, j0, w, Zc, ldc);
   else if (phase <= kShortPhase8)
-    hipLaunchKernelGGL(k_assemble_regular<8>, g, b, 0, s, md, R, k, j0, w, Zc, ldc);
+    hipLaunchKernelGGL(k_assemble_regular<8>, g, b, 0, s, md, R, k, i0, j0, w, Zc, ldc);
   else
-    hipLaunchKernelGGL(k_assemble_regular<0>, g, b, 0, s, md, R, k, j0, w, Zc, ldc);
+    hipLaunchKernelGGL(k_assemble_regular<0>, g, b, 0, s, md, R, k, i0, j0, w, Zc, ldc);
   FOSB_LAUNCH_CHECK();
 }
+
+// Touching pairs [pb, pe); ldc and Zc as in k_assemble_singular.
+void launch_singular(Context& ctx, const Mesh& m, double k, int n_gauss, int pb, int pe, int j0, c128* Zc,
+                     int64_t ldc) {
+  if (pe <= pb) return;
+  const double phase = 4.0 * k * m.h.hmax;
+  const auto kernel = phase <= kShortPhase6   ? k_assemble_singular<6>
+                      : phase <= kShortPhase8 ? k_assemble_singular<8>
+                                              : k_assemble_singular<0>;
+  hipLaunchKernelGGL(kernel, dim3((pe - pb + 3) / 4), dim3(256), 0, ctx.stream, m.dev(),
+                     m.tp_i.as<int32_t>(), m.tp_j.as<int32_t>(), m.tp_kind.as<int32_t>(), m.tp_ord.as<int32_t>(), pb,
+                     pe, ctx.ss[n_gauss].as<double>(), ctx.ss_off[n_gauss][0], ctx.ss_off[n_gauss][1],
+                     ctx.ss_off[n_gauss][2], ctx.ss_cnt[n_gauss][0], ctx.ss_cnt[n_gauss][1], ctx.ss_cnt[n_gauss][2],
+                     k, j0, Zc, ldc);
+  FOSB_LAUNCH_CHECK();
+}
+
+// every phase k |x - y| stays within the range of sincos_phase
+void check_phase(const MeshHost& h, double k) {
+  if (!(k * h.diag <= kTrigPhaseMax))
+    fail(FOSB_E_INVALID, "k * (mesh bounding-box diagonal) = %g exceeds %g", k * h.diag, kTrigPhaseMax);
+}
+
+// Two band buffers in turn: filled on one stream, consumed on another.
+struct BandEvents {
+  hipEvent_t e[4] = {nullptr, nullptr, nullptr, nullptr};   // [0, 1]: buffer filled; [2, 3]: buffer consumed
+  void create() {
+    for (hipEvent_t& x : e) FOSB_HIP(hipEventCreateWithFlags(&x, hipEventDisableTiming));
+  }
+  ~BandEvents() {
+    for (hipEvent_t x : e)
+      if (x) (void)hipEventDestroy(x);
+  }
+};
 
 Orbits6 orbits6() {
   double l[6][3], w[6];
@@ -577,9 +803,7 @@ void assemble_bands(Context& ctx, const Mesh& m, double k, int n_gauss, int64_t 
   hipStream_t s = ctx.stream;
   const MeshHost& h = m.h;
   const int nt = (int)h.nt, ne = (int)h.ne;
-  // every phase k |x - y| stays within the range of sincos_phase
-  if (!(k * h.diag <= kTrigPhaseMax))
-    fail(FOSB_E_INVALID, "k * (mesh bounding-box diagonal) = %g exceeds %g", k * h.diag, kTrigPhaseMax);
+  check_phase(h, k);
   ensure_ss_table(ctx, n_gauss);
   const Orbits6 R = orbits6();
   const double phase = 2.0 * k * h.hmax;
@@ -590,18 +814,12 @@ void assemble_bands(Context& ctx, const Mesh& m, double k, int n_gauss, int64_t 
   const size_t band_bytes = (size_t)(3LL * nt) * ldc * sizeof(c128);
   DevBuf band(band_bytes), band2;
   c128* Zbuf[2] = {band.as<c128>(), nullptr};
-  struct Events {
-    hipEvent_t e[4] = {nullptr, nullptr, nullptr, nullptr};
-    ~Events() {
-      for (hipEvent_t x : e)
-        if (x) (void)hipEventDestroy(x);
-    }
-  } ev;   // [0, 1]: band buffer filled; [2, 3]: band buffer consumed
+  BandEvents ev;
   const bool two = sg != nullptr && nt > jc;
   if (two) {
     band2.alloc(band_bytes);
     Zbuf[1] = band2.as<c128>();
-    for (hipEvent_t& x : ev.e) FOSB_HIP(hipEventCreateWithFlags(&x, hipEventDisableTiming));
+    ev.create();
   }
   // column lists per band (host): edges whose T+ or T- lies in the band
   std::vector<int32_t> cols;
@@ -625,17 +843,8 @@ void assemble_bands(Context& ctx, const Mesh& m, double k, int n_gauss, int64_t 
     const int buf = two ? (bi & 1) : 0;
     c128* Zc = Zbuf[buf];
     if (two && bi >= 2) FOSB_HIP(hipStreamWaitEvent(s, ev.e[2 + buf], 0));   // band bi - 2 consumed
-    launch_regular(s, md, R, k, phase, j0, w, Zc, ldc);
-    const int pb = (int)(std::lower_bound(h.tp_j.begin(), h.tp_j.end(), j0) - h.tp_j.begin());
-    const int pe = (int)(std::lower_bound(h.tp_j.begin(), h.tp_j.end(), j1) - h.tp_j.begin());
-    if (pe > pb) {
-      dim3 g2((pe - pb + 3) / 4);
-      hipLaunchKernelGGL(k_assemble_singular, g2, dim3(256), 0, s, md, m.tp_i.as<int32_t>(), m.tp_j.as<int32_t>(),
-                         m.tp_kind.as<int32_t>(), m.tp_ord.as<int32_t>(), pb, pe, ctx.ss[n_gauss].as<double>(),
-                         ctx.ss_off[n_gauss][0], ctx.ss_off[n_gauss][1], ctx.ss_off[n_gauss][2],
-                         ctx.ss_cnt[n_gauss][0], ctx.ss_cnt[n_gauss][1], ctx.ss_cnt[n_gauss][2], k, j0, Zc, ldc);
-      FOSB_LAUNCH_CHECK();
-    }
+    launch_regular(s, md, R, k, phase, 0, j0, w, Zc, ldc);
+    launch_singular(ctx, m, k, n_gauss, h.tp_beg[j0], h.tp_beg[j1], j0, Zc, ldc);
     const int32_t* bc = dcols.as<int32_t>() + cbeg[bi];
     const int nbc = (int)(cbeg[bi + 1] - cbeg[bi]);
     if (two) {
@@ -653,21 +862,83 @@ void assemble_bands(Context& ctx, const Mesh& m, double k, int n_gauss, int64_t 
 }
 }  // namespace
 
+// Bands of column triangles with rows from the band on (struct Band): half of
+// the triangle pairs, and of the band buffer's traffic, of whole columns.  The
+// width follows the rows left, so that a band holds about kBandBytes; a mesh
+// whose blocks fit one band takes whole columns and its touching pairs'
+// blocks directly.  Two band buffers in turn: band b + 1 is integrated (bound by
+// the vector units) while band b is gathered (bound by memory) on the update stream.
+// N = 30720: 29.2 ms with 512 MiB bands (whole columns in 1 GiB bands: 49.4), 35 with
+// 128, 28.6 with 1024, the same order at N = 7680 (2.9, 2.9 and 3.0; 4.0).
+static constexpr int64_t kBandBytes = (int64_t)512 << 20;
+
 void assemble_efie(Context& ctx, const Mesh& m, double k, int n_gauss, c128* Z, int64_t ldz, c64* Zl,
                    int64_t ldl) {
-  // 1 GiB bands: at nt = 20480 these assembled faster than 256 and 512 MiB ones, and about as fast as 2 GiB
-  const int ne = (int)m.h.ne;
+  hipStream_t s = ctx.stream;
+  const MeshHost& h = m.h;
+  const int nt = (int)h.nt, ne = (int)h.ne;
+  check_phase(h, k);
+  ensure_ss_table(ctx, n_gauss);
+  const Orbits6 R = orbits6();
+  const double phase = 2.0 * k * h.hmax;
   const MeshDev md = m.dev();
-  assemble_bands(
-      ctx, m, k, n_gauss, (int64_t)1024 << 20,
-      [&](hipStream_t st, int j0, int j1, const c128* Zc, int64_t ldc, const int32_t* cols, int nc) {
-        if (nc <= 0) return;
-        dim3 g3((nc + 63) / 64, (ne + 3) / 4);
-        hipLaunchKernelGGL(k_assemble_gather, g3, dim3(256), 0, st, ne, md.edge_tri, md.edge_loc, j0, j1, cols, nc,
-                           Zc, ldc, Z, ldz, Zl, ldl);
+  auto width = [&](int j0) {
+    const int left = nt - j0;
+    const int64_t w = kBandBytes / (9LL * left * (int64_t)sizeof(c128));
+    return w >= left ? left : (int)std::min<int64_t>(left, std::max<int64_t>(64, w / 64 * 64));
+  };
+  const bool one = width(0) == nt;
+  size_t band_bytes = 0;
+  for (int j0 = 0; j0 < nt; j0 += width(j0))
+    band_bytes = std::max(band_bytes, 9 * (size_t)(nt - j0) * width(j0) * sizeof(c128));
+  DevBuf band[2], sing;
+  band[0].alloc(band_bytes);
+  BandEvents ev;
+  hipStream_t sg = s;
+  if (!one) {
+    band[1].alloc(band_bytes);
+    sing.alloc(9 * h.tp_i.size() * sizeof(c128));
+    ev.create();
+    sg = ctx.la_context().stream;
+    launch_singular(ctx, m, k, n_gauss, 0, (int)h.tp_i.size(), 0, sing.as<c128>(), 0);
+  }
+  int bi = 0;
+  for (int j0 = 0; j0 < nt; ++bi) {
+    const int w = width(j0), j1 = j0 + w, buf = bi & 1;
+    const int64_t ldc = 3LL * w;
+    c128* Zc = band[buf].as<c128>();
+    if (bi >= 2) FOSB_HIP(hipStreamWaitEvent(s, ev.e[2 + buf], 0));   // band bi - 2 gathered
+    launch_regular(s, md, R, k, phase, j0, j0, w, Zc, ldc);
+    if (one) {
+      launch_singular(ctx, m, k, n_gauss, 0, (int)h.tp_i.size(), 0, Zc, ldc);
+    } else {
+      FOSB_HIP(hipEventRecord(ev.e[buf], s));
+      FOSB_HIP(hipStreamWaitEvent(sg, ev.e[buf], 0));
+    }
+    const int nq = h.q_beg[j1] - h.q_beg[j0], n = nq + h.e_beg[j1] - h.e_beg[j0];
+    const Band B{j0, j1, m.edge_by_q.as<int32_t>() + h.q_beg[j0], nq, h.e_beg[j0], n, Zc, ldc};
+    if (n > 0) {
+      const unsigned gx = (unsigned)((n + 63) / 64);
+      hipLaunchKernelGGL(k_band_square, dim3(gx, (unsigned)((n + 3) / 4)), dim3(256), 0, sg, ne, md.edge_tri,
+                         md.edge_loc, B, Z, ldz, Zl, ldl);
+      FOSB_LAUNCH_CHECK();
+      if (j1 < nt) {
+        hipLaunchKernelGGL(k_band_strip, dim3(gx, (unsigned)((ne + 31) / 32)), dim3(256), 0, sg, ne, md.edge_tri,
+                           md.edge_loc, B, Z, ldz, Zl, ldl);
         FOSB_LAUNCH_CHECK();
-      },
-      &ctx.la_context());
+      }
+    }
+    if (!one) FOSB_HIP(hipEventRecord(ev.e[2 + buf], sg));
+    j0 = j1;
+  }
+  if (!one) {
+    FOSB_HIP(hipStreamWaitEvent(s, ev.e[2 + ((bi - 1) & 1)], 0));   // the last band gathered
+    hipLaunchKernelGGL(k_add_touching, dim3((unsigned)((ne + 3) / 4)), dim3(256), 0, s, md, m.tp_beg.as<int32_t>(),
+                       m.tp_i.as<int32_t>(), sing.as<c128>(), Z, ldz, Zl, ldl);
+    FOSB_LAUNCH_CHECK();
+  }
+  // the band buffers must live until the kernels ran
+  FOSB_HIP(hipStreamSynchronize(s));
 }
 
 void assemble_efie_c64(Context& ctx, const Mesh& m, double k, int n_gauss, c64* Z, int64_t ldz) {
@@ -838,7 +1109,7 @@ __global__ __launch_bounds__(256) void k_pm_regular(MeshDev md, Rule6 R, double 
     Ixyr += wp * (xp[0] * Syr[0] + xp[1] * Syr[1] + xp[2] * Syr[2]);
     Ixyi += wp * (xp[0] * Syi[0] + xp[1] * Syi[1] + xp[2] * Syi[2]);
   }
-  write_local_block(md, i, j, jj, k, Li, Lj, I0r, I0i, Ixr, Ixi, Iyr, Iyi, Ixyr, Ixyi, Tc, ldc);
+  write_local_block(md, i, j, k, Li, Lj, I0r, I0i, Ixr, Ixi, Iyr, Iyi, Ixyr, Ixyi, Tc + 3LL * i * ldc + 3 * jj, ldc);
   write_local_block_k(md, i, j, jj, Li, Lj, dc, K0r, K0i, Kxr, Kxi, Kyr, Kyi, Kyxr, Kyxi, Kc, ldc);
 }
 
@@ -950,7 +1221,8 @@ __global__ __launch_bounds__(256) void k_pm_singular(MeshDev md, const int32_t* 
     Kyxi[q] = wave_sum(Kyxi[q]);
   }
   if (lane == 0) {
-    write_local_block(md, i, j, j - j0, k, Li, Lj, I0r, I0i, Ixr, Ixi, Iyr, Iyi, Ixyr, Ixyi, Tc, ldc);
+    write_local_block(md, i, j, k, Li, Lj, I0r, I0i, Ixr, Ixi, Iyr, Iyi, Ixyr, Ixyi,
+                      Tc + 3LL * i * ldc + 3 * (j - j0), ldc);
     write_local_block_k(md, i, j, j - j0, Li, Lj, dc, K0r, K0i, Kxr, Kxi, Kyr, Kyi, Kyxr, Kyxi, Kc, ldc);
   }
 }

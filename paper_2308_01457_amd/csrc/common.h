@@ -248,6 +248,10 @@ struct MeshHost {
   // touching ordered pairs (i, j), sorted by j then i
   std::vector<int32_t> tp_i, tp_j, tp_kind;   // kind: 0 identical, 1 edge, 2 vertex
   std::vector<int32_t> tp_ord;                // 6 per pair: local slots of (P0,P1,P2) in i, then in j
+  std::vector<int32_t> tp_beg;                // nt+1: pairs of column triangle j
+  // edges by triangle: T+ = t are e_beg[t] .. (edges are numbered by their T+),
+  // T- = t are edge_by_q[q_beg[t]] .. (ascending)
+  std::vector<int32_t> e_beg, q_beg, edge_by_q;
 };
 
 // Structure-of-arrays device view of a mesh (passed by value to kernels).
@@ -267,7 +271,7 @@ struct Mesh {
   Context* ctx = nullptr;
   MeshHost h;
   DevBuf vtx, area, nrm, alpha, fv, tri_edge, edge_tri, edge_loc;
-  DevBuf tp_i, tp_j, tp_kind, tp_ord;
+  DevBuf tp_i, tp_j, tp_kind, tp_ord, tp_beg, edge_by_q;
   MeshDev dev() const {
     return MeshDev{(int)h.nt, (int)h.ne, vtx.as<double>(), area.as<double>(), nrm.as<double>(),
                    alpha.as<double>(), fv.as<int32_t>(), tri_edge.as<int32_t>(),

@@ -172,6 +172,18 @@ void mesh_touching_pairs(MeshHost& m) {
     m.tp_i[q] = pairs[q].i; m.tp_j[q] = pairs[q].j; m.tp_kind[q] = pairs[q].kind;
     for (int r = 0; r < 6; ++r) m.tp_ord[6 * q + r] = pairs[q].ord[r];
   }
+  // counting sorts: pairs by column triangle, edges by T+ (already in order) and by T-
+  auto offsets = [&](std::vector<int32_t>& beg, size_t n, auto&& key) {
+    beg.assign((size_t)m.nt + 1, 0);
+    for (size_t q = 0; q < n; ++q) ++beg[(size_t)key(q) + 1];
+    for (int64_t t = 0; t < m.nt; ++t) beg[t + 1] += beg[t];
+  };
+  offsets(m.tp_beg, np, [&](size_t q) { return m.tp_j[q]; });
+  offsets(m.e_beg, (size_t)m.ne, [&](size_t e) { return m.edge_tri[2 * e]; });
+  offsets(m.q_beg, (size_t)m.ne, [&](size_t e) { return m.edge_tri[2 * e + 1]; });
+  std::vector<int32_t> at(m.q_beg);
+  m.edge_by_q.resize((size_t)m.ne);
+  for (int64_t e = 0; e < m.ne; ++e) m.edge_by_q[at[m.edge_tri[2 * e + 1]]++] = (int32_t)e;
 }
 
 void mesh_upload(Mesh& mesh) {
@@ -209,6 +221,8 @@ void mesh_upload(Mesh& mesh) {
   upload(mesh.tp_j, m.tp_j, s);
   upload(mesh.tp_kind, m.tp_kind, s);
   upload(mesh.tp_ord, m.tp_ord, s);
+  upload(mesh.tp_beg, m.tp_beg, s);
+  upload(mesh.edge_by_q, m.edge_by_q, s);
   FOSB_HIP(hipStreamSynchronize(s));   // host vectors above are temporaries
 }
 

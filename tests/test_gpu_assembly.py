@@ -30,3 +30,30 @@ def test_phase_series_at_their_limits(phase):
     Z = fosb.assemble(ctx, fosb.Mesh(ctx, V, F), k).cpu().numpy()
     Zo = efie.assemble(mesh.build(V, F), k)
     assert np.abs(Z - Zo).max() / np.abs(Zo).max() < 1e-12
+
+
+@pytest.mark.parametrize("s, shuffled", [(2, True), (3, False), (3, True), (4, True)])
+def test_bands_from_the_diagonal_on(s, shuffled):
+    """One band (s = 2), two (s = 3) and many (s = 4), with triangles in mesh order
+    and in random order (T+ and T- of most edges in different bands): entries
+    from the corners, at random, and of edges that share a vertex (touching pairs)."""
+    from oracle import efie, mesh
+    from paper_2308_01457_amd import fosb
+    V, F = _stretched(s)
+    rng = np.random.default_rng(s)
+    if shuffled:
+        F = F[rng.permutation(len(F))]
+    k = 3.0
+    ctx = fosb.Context(0)
+    Z = fosb.assemble(ctx, fosb.Mesh(ctx, V, F), k).cpu().numpy()
+    m = mesh.build(V, F)
+    assert Z.shape == (m.ne, m.ne)
+    corners = [(a, b) for a in (0, 1, m.ne - 2, m.ne - 1) for b in (0, 1, m.ne - 2, m.ne - 1)]
+    far = list(zip(rng.integers(0, m.ne, 300), rng.integers(0, m.ne, 300)))
+    near = []
+    for v in rng.integers(0, len(V), 40):
+        e = m.tri_edge[np.nonzero((F == v).any(1))[0]].ravel()
+        near += list(zip(rng.choice(e, 10), rng.choice(e, 10)))
+    at = np.array(corners + far + near)
+    Zo = efie.entries(m, k, at[:, 0], at[:, 1])
+    assert np.abs(Z[at[:, 0], at[:, 1]] - Zo).max() / np.abs(Z).max() < 1e-12
