@@ -6,15 +6,16 @@
 //   Re C = T1 - T2,  Im C = T3 - T1 - T2,
 // the operand sums being formed in registers from the staged tiles.
 //
-// Tiling: 256 threads (4 wave64) per workgroup, 128 x 64 output tile, each wave
-// owns a 64 x 32 sub-tile = 4 x 2 MFMA 16x16 blocks; K is staged in slices
-// through double-buffered LDS in planar (re/im) layout, A stored k-major so that a fragment
-// load is 16 consecutive rows.  Operand fragments (16x16x4): lane l holds
+// Tiling: 256 threads (4 wave64) per workgroup, 2 x 2 waves of WM x WN MFMA 16x16
+// blocks each; K is staged in slices through double-buffered LDS (planar for
+// FP32, interleaved for FP64), A stored k-major so that a fragment load is 16
+// consecutive rows.  Operand fragments (16x16x4): lane l holds
 // A[l%16][k0 + l/16] and B[k0 + l/16][l%16]; accumulator element v (0..3) of
 // lane l is D[row][l%16] with row = 4*(l/16) + v for the FP32 instruction and
 // row = l/16 + 4*v for the FP64 one.
 #include <algorithm>
 #include <map>
+#include <type_traits>
 
 #include "common.h"
 
@@ -49,6 +50,44 @@ constexpr int PADA = 4, PADB = 4;
 template <typename T> struct Slice { static constexpr int BK = 16; };
 template <> struct Slice<double> { static constexpr int BK = 8; };
 
+// XCD-aware tile order: workgroup L runs on XCD L % 8, so XCD x is given the
+// contiguous tile range [start(x), start(x) + count(x)), walked in groups of
+// GM tile rows, column by column: the ~64 workgroups resident on one XCD then
+// cover an 8 x 8 block of tiles and share their A rows and B columns in that
+// XCD's L2.
+__device__ __forceinline__ void tile_of_block(int64_t& tm, int64_t& tn) {
+  const int64_t nN = gridDim.x, nM = gridDim.y, ntile = nN * nM;
+  const int64_t L = (int64_t)blockIdx.y * nN + blockIdx.x;
+  const int64_t x = L % NXCD, slot = L / NXCD;
+  const int64_t t = x * (ntile / NXCD) + min(x, ntile % NXCD) + slot;
+  const int64_t group = t / (GM * nN);
+  const int64_t fm = group * GM;
+  const int64_t gs = min<int64_t>(nM - fm, GM);
+  const int64_t in = t - group * GM * nN;
+  tm = fm + in % gs;
+  tn = in / gs;
+}
+
+// One entry of C (or of the split-K partial product) from the three real products.
+template <typename T>
+__device__ __forceinline__ void store_entry(int64_t M, int64_t N, int64_t row, int64_t col, T t1, T t2, T t3, T alpha,
+                                            T beta, cplx<T>* __restrict__ C, int64_t ldc, cplx<T>* __restrict__ P) {
+  if (row >= M || col >= N) return;
+  const T cr = t1 - t2;
+  const T ci = t3 - t1 - t2;
+  if (gridDim.z > 1) {
+    P[(int64_t)blockIdx.z * M * N + row * N + col] = cplx<T>{cr, ci};
+    return;
+  }
+  cplx<T>* p = C + row * ldc + col;
+  if (beta == T(0)) {
+    *p = cplx<T>{alpha * cr, alpha * ci};
+  } else {
+    const cplx<T> o = *p;
+    *p = cplx<T>{beta * o.re + alpha * cr, beta * o.im + alpha * ci};
+  }
+}
+
 // Split K: workgroup z of gridDim.z covers K range [z*kc, min(K, (z+1)*kc)); with
 // gridDim.z > 1 it writes its raw partial product to P + z*M*N (row stride N)
 // and k_gemm_splitk_sum forms C = beta*C + alpha*sum_z P_z in fixed z order.
@@ -75,24 +114,8 @@ __device__ __forceinline__ void gemm_tile(int64_t M, int64_t N, int64_t K, T alp
   const int wave = tid >> 6;
   const int wr = wave >> 1;  // wave row (0..1): rows wr*16*WM ..
   const int wc = wave & 1;   // wave col (0..1): cols wc*16*WN ..
-  // XCD-aware tile order: workgroup L runs on XCD L % 8, so XCD x is given the
-  // contiguous tile range [start(x), start(x) + count(x)), walked in groups of
-  // GM tile rows, column by column: the ~64 workgroups resident on one XCD then
-  // cover an 8 x 8 block of tiles and share their A rows and B columns in that
-  // XCD's L2.
   int64_t tm, tn;
-  {
-    const int64_t nN = gridDim.x, nM = gridDim.y, ntile = nN * nM;
-    const int64_t L = (int64_t)blockIdx.y * nN + blockIdx.x;
-    const int64_t x = L % NXCD, slot = L / NXCD;
-    const int64_t t = x * (ntile / NXCD) + min(x, ntile % NXCD) + slot;
-    const int64_t group = t / (GM * nN);
-    const int64_t fm = group * GM;
-    const int64_t gs = min<int64_t>(nM - fm, GM);
-    const int64_t in = t - group * GM * nN;
-    tm = fm + in % gs;
-    tn = in / gs;
-  }
+  tile_of_block(tm, tn);
   const int64_t m0 = tm * BM;
   const int64_t n0 = tn * BN;
 
@@ -221,21 +244,7 @@ __device__ __forceinline__ void gemm_tile(int64_t M, int64_t N, int64_t K, T alp
       for (int v = 0; v < 4; ++v) {
         const int64_t row = m0 + wr * 16 * WM + i * 16 + Mfma<T>::row(kq, v);
         const int64_t col = n0 + wc * 16 * WN + j * 16 + r16;
-        if (row < M && col < N) {
-          const T cr = t1[i][j][v] - t2[i][j][v];
-          const T ci = t3[i][j][v] - t1[i][j][v] - t2[i][j][v];
-          if (gridDim.z > 1) {
-            P[(int64_t)blockIdx.z * M * N + row * N + col] = cplx<T>{cr, ci};
-            continue;
-          }
-          cplx<T>* p = C + row * ldc + col;
-          if (beta == T(0)) {
-            *p = cplx<T>{alpha * cr, alpha * ci};
-          } else {
-            const cplx<T> o = *p;
-            *p = cplx<T>{beta * o.re + alpha * cr, beta * o.im + alpha * ci};
-          }
-        }
+        store_entry<T>(M, N, row, col, t1[i][j][v], t2[i][j][v], t3[i][j][v], alpha, beta, C, ldc, P);
       }
 }
 
@@ -249,19 +258,168 @@ __global__ __launch_bounds__(256) void k_gemm(FOSB_GEMM_ARGS(T)) {
   gemm_tile<T, CONJ_A, WM, WN>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kc, P);
 }
 
-// The FP64 64 x 32 tile asks for four waves per SIMD: the compiler then keeps its
-// accumulators in VGPRs instead of AGPRs (113 registers, no spills) and the
-// occupancy rises from 3 to 4, which measured 64 -> 78 TFLOP/s on a 30720 x 480
-// x 30720 product.  The larger FP64 tiles would spill under that request.
-template <>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_gemm<double, false, 2, 1>(
-    FOSB_GEMM_ARGS(double)) {
-  gemm_tile<double, false, 2, 1>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kc, P);
+// FP64 products.  A 3M block of 16 x 16 x 4 is three MFMAs of 32 cycles, so what
+// bounds this kernel is everything else a wave issues between them and waits for:
+//  - the tiles stay interleaved in LDS and a fragment is one 16-byte read; rows are
+//    padded by one entry, so neither the k-major store of A nor the reads conflict;
+//  - a slice's global loads are issued two slices ahead;
+//  - the loop over whole slices has no edge checks: rows and columns outside the
+//    operands read the last one inside (their results are not stored), and the
+//    last slices (K's tail) take the checked loads of the second loop;
+//  - at most 256 registers, so that the accumulators are VGPRs: with more, the
+//    compiler keeps them in AGPRs and copies them in and out on every step;
+//  - 64 x 32 and 64 x 64 tiles run at four and three waves per SIMD, which cover
+//    each other's waits; 64 x 96, the least LDS reading per MFMA, leaves room for two and
+//    reads the next step's fragments while this step's MFMAs run (PIPE).
+// Accumulation over K is in steps of 4 from the lowest, as in gemm_tile, so that
+// tiles give identical results.
+// TFLOP/s (8 per complex multiply-add) of the best tile, planar LDS tiles with checked
+// loads before -> this kernel: 30720 x 480 x 30720 71 -> 84, 7680^3 76 -> 88,
+// 7680 x 7680 x 256 66 -> 76, 7680 x 273 x 7680 51 -> 59, 7680 x 480 x 7680 61 -> 73
+// (A^H B 56 -> 73), 3840 x 96 x 3840 35 -> 40.  The MFMAs alone would allow 105.
+template <bool CONJ_A, int WM, int WN>
+__device__ __forceinline__ void gemm64_tile(int64_t M, int64_t N, int64_t K, double alpha,
+                                            const c128* __restrict__ A, int64_t lda, const c128* __restrict__ B,
+                                            int64_t ldb, double beta, c128* __restrict__ C, int64_t ldc, int64_t kc,
+                                            c128* __restrict__ P) {
+  using V4 = Mfma<double>::v4;
+  constexpr bool PIPE = WN > 2;
+  constexpr int BK = Slice<double>::BK;
+  constexpr int BM = 32 * WM, BN = 32 * WN;
+  constexpr int AE = BM * BK / 256, BE = BN * BK / 256;   // entries staged per thread
+  __shared__ __align__(16) c128 As[2][BK][BM + 1];
+  __shared__ __align__(16) c128 Bs[2][BK][BN + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wr = wave >> 1, wc = wave & 1;
+  int64_t tm, tn;
+  tile_of_block(tm, tn);
+  const int64_t m0 = tm * BM, n0 = tn * BN;
+  const int64_t kb = (int64_t)blockIdx.z * kc, ke = min(K, kb + kc);
+
+  int ak[AE], ar[AE], bk[BE], bc[BE];
+  const c128 *pa[AE], *pb[BE];
+#pragma unroll
+  for (int e = 0; e < AE; ++e) {
+    const int x = e * 256 + tid;
+    ak[e] = CONJ_A ? x / BM : x % BK;   // op(A) = A^H: its rows are contiguous in memory
+    ar[e] = CONJ_A ? x % BM : x / BK;
+    const int64_t r = min(m0 + ar[e], M - 1);
+    pa[e] = CONJ_A ? A + (kb + ak[e]) * lda + r : A + r * lda + kb + ak[e];
+  }
+#pragma unroll
+  for (int e = 0; e < BE; ++e) {
+    const int x = e * 256 + tid;
+    bk[e] = x / BN;
+    bc[e] = x % BN;
+    pb[e] = B + (kb + bk[e]) * ldb + min(n0 + bc[e], N - 1);
+  }
+  const int64_t da = CONJ_A ? BK * lda : BK, db = BK * ldb;
+  c128 ra[AE], rb[BE];
+  auto load = [&](auto whole, int64_t k0) {
+#pragma unroll
+    for (int e = 0; e < BE; ++e) {
+      rb[e] = whole || k0 + bk[e] < ke ? *pb[e] : c128{0.0, 0.0};
+      pb[e] += db;
+    }
+#pragma unroll
+    for (int e = 0; e < AE; ++e) {
+      ra[e] = whole || k0 + ak[e] < ke ? *pa[e] : c128{0.0, 0.0};
+      pa[e] += da;
+    }
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int e = 0; e < BE; ++e) Bs[buf][bk[e]][bc[e]] = rb[e];
+#pragma unroll
+    for (int e = 0; e < AE; ++e) As[buf][ak[e]][ar[e]] = c128{ra[e].re, CONJ_A ? -ra[e].im : ra[e].im};
+  };
+  V4 t1[WM][WN], t2[WM][WN], t3[WM][WN];
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) t1[i][j] = t2[i][j] = t3[i][j] = V4{0, 0, 0, 0};
+  const int r16 = lane & 15, kq = lane >> 4;
+  struct Frag {
+    c128 a[WM], b[WN];
+  } f[2];
+  auto read = [&](Frag& x, int buf, int kk) {
+#pragma unroll
+    for (int i = 0; i < WM; ++i) x.a[i] = As[buf][4 * kk + kq][wr * 16 * WM + i * 16 + r16];
+#pragma unroll
+    for (int j = 0; j < WN; ++j) x.b[j] = Bs[buf][4 * kk + kq][wc * 16 * WN + j * 16 + r16];
+  };
+  auto mul = [&](const Frag& x) {
+    double as[WM], bs[WN];
+#pragma unroll
+    for (int i = 0; i < WM; ++i) as[i] = x.a[i].re + x.a[i].im;
+#pragma unroll
+    for (int j = 0; j < WN; ++j) bs[j] = x.b[j].re + x.b[j].im;
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        t1[i][j] = Mfma<double>::op(x.a[i].re, x.b[j].re, t1[i][j]);
+        t2[i][j] = Mfma<double>::op(x.a[i].im, x.b[j].im, t2[i][j]);
+        t3[i][j] = Mfma<double>::op(as[i], bs[j], t3[i][j]);
+      }
+  };
+  constexpr std::true_type whole{};
+  constexpr std::false_type checked{};
+  // one slice; ra and rb hold the next one, with PIPE f[0] the fragments of its first step
+  auto slice = [&](auto w, int64_t k0, int buf) {
+    static_assert(BK == 8, "two steps of 4 a slice");
+    if constexpr (PIPE) {
+      read(f[1], buf, 1);
+      store(buf ^ 1);
+      load(w, k0 + 2 * BK);
+      mul(f[0]);
+      // the reads, stores and loads between the MFMAs, not before them
+#pragma unroll
+      for (int q = 0; q < 3 * WM * WN; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);   // VALU
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
+        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);   // LDS write
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // global load
+      }
+      __syncthreads();
+      read(f[0], buf ^ 1, 0);
+      mul(f[1]);
+    } else {
+      read(f[0], buf, 0);
+      mul(f[0]);
+      read(f[0], buf, 1);
+      mul(f[0]);
+      store(buf ^ 1);
+      load(w, k0 + 2 * BK);
+      __syncthreads();
+    }
+  };
+  if (ke > kb) {
+    int64_t k0 = kb;
+    int buf = 0;
+    load(checked, k0);
+    store(0);
+    load(checked, k0 + BK);
+    __syncthreads();
+    if constexpr (PIPE) read(f[0], 0, 0);
+    for (; k0 + 3 * BK <= ke; k0 += BK, buf ^= 1) slice(whole, k0, buf);
+    for (; k0 < ke; k0 += BK, buf ^= 1) slice(checked, k0, buf);
+  }
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t row = m0 + wr * 16 * WM + i * 16 + Mfma<double>::row(kq, v);
+        const int64_t col = n0 + wc * 16 * WN + j * 16 + r16;
+        store_entry<double>(M, N, row, col, t1[i][j][v], t2[i][j][v], t3[i][j][v], alpha, beta, C, ldc, P);
+      }
 }
-template <>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_gemm<double, true, 2, 1>(
-    FOSB_GEMM_ARGS(double)) {
-  gemm_tile<double, true, 2, 1>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kc, P);
+
+template <bool CONJ_A, int WM, int WN>
+__global__ __launch_bounds__(256, WN == 1 ? 4 : WN == 2 ? 3 : 2) void k_gemm64(FOSB_GEMM_ARGS(double)) {
+  gemm64_tile<CONJ_A, WM, WN>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kc, P);
 }
 #undef FOSB_GEMM_ARGS
 
@@ -368,7 +526,7 @@ template <> struct Tiles<float> {
 };
 template <> struct Tiles<double> {
   static constexpr int n = 3;
-  static constexpr int wm[3] = {2, 2, 4}, wn[3] = {1, 2, 2};
+  static constexpr int wm[3] = {2, 2, 2}, wn[3] = {1, 2, 3};
   static constexpr int lean = 0;  // 64 x 32
 };
 
@@ -377,8 +535,12 @@ static void launch_tile(hipStream_t s, int64_t M, int64_t N, int64_t K, T alpha,
                         const cplx<T>* B, int64_t ldb, T beta, cplx<T>* C, int64_t ldc, int64_t kc, cplx<T>* P,
                         int64_t nz) {
   dim3 grid((unsigned)((N + 32 * WN - 1) / (32 * WN)), (unsigned)((M + 32 * WM - 1) / (32 * WM)), (unsigned)nz);
-  hipLaunchKernelGGL((k_gemm<T, CONJ_A, WM, WN>), grid, dim3(256), 0, s, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                     kc, P);
+  if constexpr (sizeof(T) == 8)
+    hipLaunchKernelGGL((k_gemm64<CONJ_A, WM, WN>), grid, dim3(256), 0, s, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
+                       kc, P);
+  else
+    hipLaunchKernelGGL((k_gemm<T, CONJ_A, WM, WN>), grid, dim3(256), 0, s, M, N, K, alpha, A, lda, B, ldb, beta, C,
+                       ldc, kc, P);
   FOSB_LAUNCH_CHECK();
 }
 
@@ -396,7 +558,7 @@ static void launch_variant(int var, hipStream_t s, int64_t M, int64_t N, int64_t
   } else {
     switch (var) {
       case 1: return launch_tile<T, CONJ_A, 2, 2>(s, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kc, P, nz);
-      case 2: return launch_tile<T, CONJ_A, 4, 2>(s, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kc, P, nz);
+      case 2: return launch_tile<T, CONJ_A, 2, 3>(s, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kc, P, nz);
       default: return launch_tile<T, CONJ_A, 2, 1>(s, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kc, P, nz);
     }
   }
