@@ -134,11 +134,20 @@ void level_solve_inplace(Context& ctx, const Level& L, c128* B, int64_t ldb, int
       trsm_upper_inv<float>(ctx, A32, L.ldzlow, L.inv_U.as<c64>(), n, Y32, nrhs, R32, nrhs, nrhs);
       copy_c64_to_c128(s, R32, nrhs, T, nrhs, n, nrhs);
       D = T;
+    } else if (L.sym_lu) {
+      // the factors are of a symmetric matrix M without row exchanges (to the
+      // FP32 factors' accuracy, which is all that a correction needs):
+      // M^{-H} R = conj(M^{-1} conj(R)), by the forward solves' wide products
+      copy_c128_to_c64(s, R, nrhs, R32, nrhs, n, nrhs, true);
+      trsm_lower_unit_inv<float>(ctx, A32, L.ldzlow, L.inv_L.as<c64>(), n, R32, nrhs, Y32, nrhs, nrhs);
+      trsm_upper_inv<float>(ctx, A32, L.ldzlow, L.inv_U.as<c64>(), n, Y32, nrhs, R32, nrhs, nrhs);
+      if (L.sym_sign) negate_rows_c64(s, R32, nrhs, n / 2, n, nrhs);   // Z^{-H} = S (S Z)^{-H}
+      copy_c64_to_c128(s, R32, nrhs, T, nrhs, n, nrhs, true);
+      D = T;
     } else {
       copy_c128_to_c64(s, R, nrhs, R32, nrhs, n, nrhs);
       trsm_upper_ch<float>(ctx, A32, L.ldzlow, L.dinv_U.as<c64>(), 0, n, R32, nrhs, nrhs);
       trsm_lower_unit_ch<float>(ctx, A32, L.ldzlow, L.dinv_L.as<c64>(), 0, n, R32, nrhs, nrhs);
-      if (L.sym_sign) negate_rows_c64(s, R32, nrhs, n / 2, n, nrhs);   // Z^{-H} = S (S Z)^{-H}
       copy_c64_to_c128(s, R32, nrhs, T, nrhs, n, nrhs);
       permute_rows_scatter(s, perm, T, nrhs, Rw, nrhs, n, nrhs);  // R (if it was Rw) is consumed
       D = Rw;

@@ -436,10 +436,13 @@ void permute_rows_gather(hipStream_t s, const int32_t* perm, const c128* src, in
 // dst[perm[i]] = src[i]
 void permute_rows_scatter(hipStream_t s, const int32_t* perm, const c128* src, int64_t lds, c128* dst,
                           int64_t ldd, int64_t n, int64_t ncols);
-void copy_c128_to_c64(hipStream_t s, const c128* src, int64_t lds, c64* dst, int64_t ldd, int64_t rows, int64_t cols);
+// conj: the entries' conjugates
+void copy_c128_to_c64(hipStream_t s, const c128* src, int64_t lds, c64* dst, int64_t ldd, int64_t rows, int64_t cols,
+                      bool conj = false);
 // rows [r0, r1) of a complex64 matrix (row stride ld, cols columns) <- their negatives
 void negate_rows_c64(hipStream_t s, c64* p, int64_t ld, int64_t r0, int64_t r1, int64_t cols);
-void copy_c64_to_c128(hipStream_t s, const c64* src, int64_t lds, c128* dst, int64_t ldd, int64_t rows, int64_t cols);
+void copy_c64_to_c128(hipStream_t s, const c64* src, int64_t lds, c128* dst, int64_t ldd, int64_t rows, int64_t cols,
+                      bool conj = false);
 void copy_c128(hipStream_t s, const c128* src, int64_t lds, c128* dst, int64_t ldd, int64_t rows, int64_t cols);
 // dst = diag(row_scale) src^H (row_scale: device, one per dst row, or nullptr)
 void conj_transpose_c128(hipStream_t s, const c128* src, int64_t lds, c128* dst, int64_t ldd, int64_t rows,

@@ -1560,7 +1560,7 @@ template void trsm_lower_unit_ch<float>(Context&, const c64*, int64_t, const c64
                                         int64_t);
 
 // ------------------------------------------------------------------ element-wise helpers
-template <typename S, typename D>
+template <typename S, typename D, bool CONJ>
 __global__ void k_copy2d(const cplx<S>* __restrict__ src, int64_t lds, cplx<D>* __restrict__ dst, int64_t ldd,
                          int64_t rows, int64_t cols) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1568,16 +1568,19 @@ __global__ void k_copy2d(const cplx<S>* __restrict__ src, int64_t lds, cplx<D>* 
   for (int64_t rr = r; rr < rows; rr += gridDim.y)
     if (c < cols) {
       const cplx<S> v = src[rr * lds + c];
-      dst[rr * ldd + c] = cplx<D>{(D)v.re, (D)v.im};
+      dst[rr * ldd + c] = cplx<D>{(D)v.re, (D)(CONJ ? -v.im : v.im)};
     }
 }
 
 template <typename S, typename D>
 static void copy2d(hipStream_t s, const cplx<S>* src, int64_t lds, cplx<D>* dst, int64_t ldd, int64_t rows,
-                   int64_t cols) {
+                   int64_t cols, bool conj = false) {
   if (rows <= 0 || cols <= 0) return;
   dim3 g((unsigned)((cols + 255) / 256), (unsigned)std::min<int64_t>(rows, 65535));
-  hipLaunchKernelGGL((k_copy2d<S, D>), g, dim3(256), 0, s, src, lds, dst, ldd, rows, cols);
+  if (conj)
+    hipLaunchKernelGGL((k_copy2d<S, D, true>), g, dim3(256), 0, s, src, lds, dst, ldd, rows, cols);
+  else
+    hipLaunchKernelGGL((k_copy2d<S, D, false>), g, dim3(256), 0, s, src, lds, dst, ldd, rows, cols);
   FOSB_LAUNCH_CHECK();
 }
 
@@ -1599,12 +1602,12 @@ void negate_rows_c64(hipStream_t s, c64* p, int64_t ld, int64_t r0, int64_t r1, 
 }
 
 void copy_c128_to_c64(hipStream_t s, const c128* src, int64_t lds, c64* dst, int64_t ldd, int64_t rows,
-                      int64_t cols) {
-  copy2d<double, float>(s, src, lds, dst, ldd, rows, cols);
+                      int64_t cols, bool conj) {
+  copy2d<double, float>(s, src, lds, dst, ldd, rows, cols, conj);
 }
 void copy_c64_to_c128(hipStream_t s, const c64* src, int64_t lds, c128* dst, int64_t ldd, int64_t rows,
-                      int64_t cols) {
-  copy2d<float, double>(s, src, lds, dst, ldd, rows, cols);
+                      int64_t cols, bool conj) {
+  copy2d<float, double>(s, src, lds, dst, ldd, rows, cols, conj);
 }
 void copy_c128(hipStream_t s, const c128* src, int64_t lds, c128* dst, int64_t ldd, int64_t rows, int64_t cols) {
   copy2d<double, double>(s, src, lds, dst, ldd, rows, cols);

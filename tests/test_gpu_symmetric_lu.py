@@ -202,3 +202,23 @@ def test_split_products_in_wide_solves(fz, nrhs):
         worst = float((R.norm(dim=0) / (zn * X.norm(dim=0))).max())
         print(f"[gpu]   {nrhs} columns, adjoint {adjoint}: worst column residual {worst:.1e}", flush=True)
         assert worst < 1e-9   # refinement stops by the whole block's norm: small columns carry the FP32 solve's accuracy
+
+
+@pytest.mark.parametrize("nrhs", [1, 5, 65])
+def test_adjoint_solves_of_symmetric_levels(fz, nrhs):
+    """Adjoint solves through the conjugated forward factors, with the EFIE matrix
+    and with the sign-symmetrised PMCHWT one: |Z^H X - B| <= 1e-9 |Z| |X| by column
+    (refinement stops at a relative correction of 1e-10)."""
+    fosb, ctx, torch, w, m, Z = fz
+    levels = [(Z, fosb.Level(ctx, m, w.k, Z, fosb.MIXED, w.dirs, w.pols, "radial", _opts(fosb, 0)))]
+    V, F = workloads.icosphere(3)
+    mp = fosb.Mesh(ctx, V, F)   # 2N = 3840
+    Zp = fosb.assemble_pmchwt(ctx, mp, w.k, 2.1)
+    levels.append((Zp, fosb.Level.pmchwt(ctx, mp, w.k, 2.1, 1.0, Zp, fosb.MIXED, w.dirs, w.pols)))
+    for A, lv in levels:
+        assert lv.factorization() == levels[0][1].factorization()
+        B = _rhs(torch, ctx, A.shape[0], nrhs=nrhs, seed=nrhs)
+        X = B.clone()
+        lv.solve_adjoint(X)
+        R = torch.matmul(A.mH.contiguous(), X) - B
+        assert float((R.norm(dim=0) / (A.norm() * X.norm(dim=0))).max()) < 1e-9
