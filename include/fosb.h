@@ -140,7 +140,7 @@ typedef struct fosb_opts {
  * stay 0 otherwise. */
 typedef struct fosb_stats {
   int32_t ir_sweeps;        /* largest number of refinement sweeps used            */
-  int32_t n_solves;         /* level-pair solves performed                         */
+  int32_t n_solves;         /* level pairs solved, per incidence                   */
   double ir_rel_correction; /* largest final ||dX||/||X||                          */
   double backward_error;    /* largest normwise backward error of a refined solve,
                                ||B - op(Z) X||_F / (||Z||_F ||X||_F + ||B||_F), with
@@ -557,7 +557,11 @@ typedef struct fosb_batch_shape {
  * own stream (created by the library, default priority), scratch and
  * grow-only Z / Zlow / block workspaces held by the context, take shapes in
  * order from a shared queue, so several shapes are in flight on the GPU at
- * once.  Per shape the results equal fosb_second_moment(dir = -1).  The
+ * once.  Per shape the results equal fosb_second_moment(dir = -1), up to
+ * rounding (FP64) or refinement (MIXED) where a shape takes the adjoint route
+ * (as fosb_far_field_variance_adjoint: 3 n_a right-hand sides per level in place
+ * of the pair solves): finest level N >= 2048, and less than half of the pair
+ * solves' multiply-adds.  The
  * workspaces persist in the context (each worker holds its largest shape's
  * matrices).  Errors as for fosb_second_moment; on error the remaining shapes
  * are skipped and their var is unspecified. */

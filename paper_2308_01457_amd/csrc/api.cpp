@@ -708,10 +708,11 @@ static void check_far_field_args(const double* xhat, int64_t n_a, int32_t L0, in
 // var = sum over Lambda_H of sign mult Re diag(FF_l1 Sigma FF_l2^H) for nd
 // incidences dir0 .. dir0+nd-1 (blocks stacked side by side as in two_sided,
 // var[d*3 n_a ..]); mean_F (optional) = FF_L u_L per direction.  The far-field
-// maps are formed once.  Synchronises c's stream.
+// maps are formed once, or given (maps: 3 n_a x N per level).  Synchronises c's stream.
 static void far_field_impl(Context& c, const fosb_level* const* levels, int32_t L0, int32_t L, void* const* blocks,
                            const int64_t* ldb, const double* xhat, int64_t n_a, int64_t dir0, int64_t nd, double* var,
-                           void* mean_F, void* cor = nullptr, bool near = false) {
+                           void* mean_F, void* cor = nullptr, bool near = false,
+                           std::vector<DevBuf>* maps = nullptr) {
   const int32_t n_levels = L - L0 + 1;
   hipStream_t s = c.stream;
   std::vector<double> x(xhat, xhat + 3 * n_a);
@@ -719,8 +720,9 @@ static void far_field_impl(Context& c, const fosb_level* const* levels, int32_t 
   upload(dx, x, s);
   const int64_t rows = 3 * n_a;
   auto v = ct_pairs_vec(L0, L);
-  std::vector<DevBuf> FF(n_levels);
-  for (int32_t i = 0; i < n_levels; ++i) {
+  std::vector<DevBuf> own(maps ? 0 : n_levels);
+  std::vector<DevBuf>& FF = maps ? *maps : own;
+  for (int32_t i = 0; i < n_levels && !maps; ++i) {
     FF[i].alloc((size_t)rows * levels[i]->n * sizeof(c128));
     if (near)  // scattered field at field points instead of the far field at directions
       near_field_matrix_kernel(s, *levels[i]->mesh, levels[i]->k, dx.as<double>(), n_a, FF[i].as<c128>());
@@ -769,6 +771,36 @@ static void far_field_impl(Context& c, const fosb_level* const* levels, int32_t 
 }
 
 
+// Whether the variance of stacked incidences alone (no Sigma block kept) goes by
+// the adjoint route, FF Sigma FF^H = G_1 C G_2^H with G = FF Z^{-1}: 3 n_a
+// columns per level instead of nd N_l2 and nd N_l1 per pair.  By the solves' multiply-adds, with a
+// factor of two for the conjugate transposes and the products that stay; from
+// N = 2048 on, where solves are bound by products rather than launches and the
+// adjoint solves run on symmetric factors.  Six ellipsoids to N = 7680, 16 incidences, 181 angles,
+// mixed: 780 -> 243 ms.
+static bool adjoint_route_pays(const std::vector<std::array<int32_t, 4>>& pairs, const fosb_mesh* const* meshes,
+                               int32_t n_levels, int32_t L0, int64_t nd, int64_t n_a) {
+  double by_pair = 0.0, by_level = 0.0;
+  for (const auto& q : pairs) {
+    const double n1 = (double)meshes[q[0] - L0]->h.ne, n2 = (double)meshes[q[1] - L0]->h.ne;
+    by_pair += (double)nd * n1 * n2 * (n1 + n2);
+  }
+  for (int32_t i = 0; i < n_levels; ++i) by_level += 3.0 * (double)n_a * (double)meshes[i]->h.ne * (double)meshes[i]->h.ne;
+  return meshes[n_levels - 1]->h.ne >= 2048 && 2.0 * by_level <= by_pair;
+}
+
+// G = FF Z^{-1} (3 n_a x N): the adjoint solve Z^{-H} FF^H.
+static void solved_far_field(Context& c, const fosb_level& l, const double* dx, int64_t n_a, DevBuf& G,
+                             fosb_stats* st) {
+  const int64_t rows = 3 * n_a;
+  G.alloc((size_t)rows * l.n * sizeof(c128));
+  level_far_field(c.stream, l, dx, n_a, G.as<c128>());
+  DevBuf Y((size_t)rows * l.n * sizeof(c128));
+  conj_transpose_c128(c.stream, G.as<c128>(), l.n, Y.as<c128>(), rows, rows, l.n);
+  level_solve_inplace(c, l, Y.as<c128>(), rows, rows, st, true);
+  conj_transpose_c128(c.stream, Y.as<c128>(), rows, G.as<c128>(), l.n, l.n, rows);
+}
+
 // The whole pass for one ladder on c's stream alone, every incidence stacked,
 // Z / Zlow / blocks from c's grow-only workspaces; var receives n_dirs
 // consecutive 3 n_a vectors.  Used by the batch workers.
@@ -794,6 +826,14 @@ static void shape_pipeline(Context& c, const fosb_mesh* const* meshes, int32_t n
     lv[i] = level_build(c, meshes[i], k, precision, c.ws_Z[i].p, n, mixed ? c.ws_Zlow[i].p : nullptr,
                         mixed ? n : 0, dirs, pols, n_dirs, field, o, FOSB_FORM_EFIE, 1.0, 1.0, -1, false, mixed);
   }
+  const bool by_level = adjoint_route_pays(v, meshes, n_levels, L0, n_dirs, n_a);
+  std::vector<DevBuf> maps(by_level ? n_levels : 0);
+  if (by_level) {
+    std::vector<double> x(xhat, xhat + 3 * n_a);
+    DevBuf dx;
+    upload(dx, x, c.stream);
+    for (int32_t i = 0; i < n_levels; ++i) solved_far_field(c, *lv[i], dx.as<double>(), n_a, maps[i], st);
+  }
   std::vector<void*> bp(v.size());
   std::vector<int64_t> ldb(v.size());
   for (size_t p = 0; p < v.size(); ++p) {
@@ -810,14 +850,18 @@ static void shape_pipeline(Context& c, const fosb_mesh* const* meshes, int32_t n
       else
         rhs_correlation_multi(c.stream, a, b, cov, 0, n_dirs, C, ldb[p], b.n);
     }
-    two_sided(c, a, b, C, ldb[p], st, n_dirs);
+    if (!by_level)
+      two_sided(c, a, b, C, ldb[p], st, n_dirs);
+    else if (st)
+      st->n_solves += (int32_t)n_dirs;   // the pair's incidences, solved through the levels
   }
   std::vector<const fosb_level*> lp(n_levels);
   for (int32_t i = 0; i < n_levels; ++i) {
     lp[i] = lv[i].get();
     merge_level_certificate(st, *lv[i]);
   }
-  far_field_impl(c, lp.data(), L0, L, bp.data(), ldb.data(), xhat, n_a, 0, n_dirs, var, nullptr);
+  far_field_impl(c, lp.data(), L0, L, bp.data(), ldb.data(), xhat, n_a, 0, n_dirs, var, nullptr, nullptr, false,
+                 by_level ? &maps : nullptr);
 }
 
 }  // namespace fosb

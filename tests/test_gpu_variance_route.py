@@ -83,3 +83,26 @@ def test_adjoint_route_full_size_against_golden(fz, precision, tol):
     e = _rel(va, np.asarray(gold["variance"]))
     print(f"[gpu]   vs oracle golden {e:.2e} ({t1 - t0:.3f} s for 181 angles)", flush=True)
     assert e < tol
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n_a, n_dirs", [(11, 3), (700, 1)])
+def test_batch_routes(precision, n_a, n_dirs):
+    """fosb_second_moment_batch on both sides of its choice of route (finest level
+    N = 2430: 33 columns per level against 3 x 270 per pair, and 2100 against
+    270): the variance equals fosb_second_moment's to 1e-9 (refinement to 1e-10)."""
+    import torch
+    from paper_2308_01457_amd import fosb
+    ctx = fosb.Context(0)
+    prec = fosb.FP64 if precision == "fp64" else fosb.MIXED
+    w = workloads.batched_ellipsoids(n_shapes=1, n_dirs=n_dirs, seed=5)[0]
+    ms = [fosb.Mesh(ctx, *workloads.ellipsoid(nu, tuple(w.extra["axes"]))) for nu in (3, 5, 9)]
+    assert ms[-1].n_edges == 2430
+    cov = fosb.make_cov("matern32", w.sigma, w.ell)
+    xh = workloads.angles_xz(n_a)
+    item = {"meshes": ms, "L0": 0, "L": 2, "k": w.k, "dirs": w.dirs, "pols": w.pols, "cov": cov}
+    out = fosb.second_moment_batch(ctx, [item], prec, xh, n_workers=1)[0].cpu().numpy()
+    ref, _, _ = fosb.second_moment(ctx, ms, 0, 2, w.k, prec, cov, xh, w.dirs, w.pols, dir=-1)
+    ref = ref.cpu().numpy().reshape(out.shape)
+    for d in range(n_dirs):
+        assert np.linalg.norm(out[d] - ref[d]) < 1e-9 * np.linalg.norm(ref[d])
