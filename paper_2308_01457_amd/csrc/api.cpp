@@ -632,7 +632,7 @@ static void pair_rhs(Context& c, const Level& a, const Level& b, const fosb_cov*
   else if (a.form == FOSB_FORM_PMCHWT)
     sd_correlation(c, a, b, *cov, dir, C, ldc);
   else
-    rhs_correlation_kernel(c.stream, a, b, *cov, dir, C, ldc);
+    rhs_correlation(c, a, b, *cov, dir, 1, C, ldc, b.n);
 }
 
 // Sigma blocks of rank-one right-hand sides C = b_l1 b_l2^H: the two-sided solve
@@ -845,10 +845,7 @@ static void shape_pipeline(Context& c, const fosb_mesh* const* meshes, int32_t n
     c128* C = c.ws_blocks[p].as<c128>();
     {
       ProfScope prof(c, FOSB_K_RHS, 0.0, 16.0 * (double)n_dirs * (double)a.n * (double)b.n);
-      if (n_dirs == 1)
-        rhs_correlation_kernel(c.stream, a, b, cov, 0, C, ldb[p]);
-      else
-        rhs_correlation_multi(c.stream, a, b, cov, 0, n_dirs, C, ldb[p], b.n);
+      rhs_correlation(c, a, b, cov, 0, n_dirs, C, ldb[p], b.n);
     }
     if (!by_level)
       two_sided(c, a, b, C, ldb[p], st, n_dirs);
@@ -1805,10 +1802,7 @@ fosb_status fosb_second_moment(fosb_context* ctx, const fosb_mesh* const* meshes
     c128* C = static_cast<c128*>(blocks[p]);
     {
       ProfScope prof(c, FOSB_K_RHS, 0.0, 16.0 * (double)nd * (double)a.n * (double)b.n);
-      if (nd == 1)
-        rhs_correlation_kernel(c.stream, a, b, *cov, d0, C, ldb[p]);
-      else
-        rhs_correlation_multi(c.stream, a, b, *cov, d0, nd, C, ldb[p], b.n);
+      rhs_correlation(c, a, b, *cov, d0, nd, C, ldb[p], b.n);
     }
     two_sided(c, a, b, C, ldb[p], st, nd);
   };

@@ -448,23 +448,12 @@ __global__ __launch_bounds__(256) void k_assemble_singular(MeshDev md, const int
 // j0 on: block (i, j) at row 3 (i - j0), column 3 (j - j0).  The 6-point rule is
 // the same in both triangles, so block (j, i) is the transpose of block (i, j)
 // and the pairs with a row before the band come from that row's own band.
-// The RWG functions on the band's triangles are by_q[0 .. nq) (T- in the band;
-// those with T+ in it as well are skipped here) and e0, e0 + 1, ... (T+ in the
-// band: edges are numbered by their T+, and T+ < T-).
 struct Band {
   int j0, j1;
-  const int32_t* by_q;
-  int nq, e0, n;
+  BandEdges edges;
   const c128* Zc;
   int64_t ldc;
 };
-
-__device__ __forceinline__ int band_edge(const Band& b, const int32_t* __restrict__ edge_tri, int x) {
-  if (x >= b.n) return -1;
-  if (x >= b.nq) return b.e0 + x - b.nq;
-  const int e = b.by_q[x];
-  return edge_tri[e] >= b.j0 ? -1 : e;
-}
 
 __device__ __forceinline__ void add_to(c128& s, const c128& v) {
   s.re += v.re;
@@ -497,7 +486,7 @@ __global__ __launch_bounds__(256) void k_band_strip(int ne, const int32_t* __res
     mine[threadIdx.x] = on;
   }
   if (!__syncthreads_or(on)) return;
-  const int n = band_edge(B, edge_tri, blockIdx.x * TN + lane);
+  const int n = band_edge(B.edges, edge_tri, blockIdx.x * TN + lane);
   int tp = 0, tm = 0;
   bool has_p = false, has_m = false;
   int64_t cp = 0, cm = 0;
@@ -569,8 +558,8 @@ __global__ __launch_bounds__(256) void k_band_square(int ne, const int32_t* __re
                                                      const int32_t* __restrict__ edge_loc, Band B,
                                                      c128* __restrict__ Z, int64_t ldz, c64* __restrict__ Zl,
                                                      int64_t ldl) {
-  const int n = band_edge(B, edge_tri, blockIdx.x * 64 + (threadIdx.x & 63));
-  const int m = band_edge(B, edge_tri, blockIdx.y * 4 + (threadIdx.x >> 6));
+  const int n = band_edge(B.edges, edge_tri, blockIdx.x * 64 + (threadIdx.x & 63));
+  const int m = band_edge(B.edges, edge_tri, blockIdx.y * 4 + (threadIdx.x >> 6));
   if (n < 0 || m < 0) return;
   const int tm[2] = {edge_tri[m], edge_tri[ne + m]}, tn[2] = {edge_tri[n], edge_tri[ne + n]};
   const int lm[2] = {edge_loc[m], edge_loc[ne + m]}, ln[2] = {edge_loc[n], edge_loc[ne + n]};
@@ -915,8 +904,8 @@ void assemble_efie(Context& ctx, const Mesh& m, double k, int n_gauss, c128* Z, 
       FOSB_HIP(hipEventRecord(ev.e[buf], s));
       FOSB_HIP(hipStreamWaitEvent(sg, ev.e[buf], 0));
     }
-    const int nq = h.q_beg[j1] - h.q_beg[j0], n = nq + h.e_beg[j1] - h.e_beg[j0];
-    const Band B{j0, j1, m.edge_by_q.as<int32_t>() + h.q_beg[j0], nq, h.e_beg[j0], n, Zc, ldc};
+    const Band B{j0, j1, band_edges(m, j0, j1), Zc, ldc};
+    const int n = B.edges.n;
     if (n > 0) {
       const unsigned gx = (unsigned)((n + 63) / 64);
       hipLaunchKernelGGL(k_band_square, dim3(gx, (unsigned)((n + 3) / 4)), dim3(256), 0, sg, ne, md.edge_tri,

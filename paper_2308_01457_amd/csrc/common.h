@@ -279,6 +279,27 @@ struct Mesh {
   }
 };
 
+// The RWG functions on the triangles [t0, t1): by_q[0 .. nq) (T- among them;
+// those with T+ among them as well are skipped there) and e0, e0 + 1, ... (T+ among them).
+struct BandEdges {
+  const int32_t* by_q;
+  int nq, e0, n, t0;
+};
+
+inline BandEdges band_edges(const Mesh& m, int t0, int t1) {
+  const int nq = m.h.q_beg[t1] - m.h.q_beg[t0];
+  return BandEdges{m.edge_by_q.as<int32_t>() + m.h.q_beg[t0], nq, m.h.e_beg[t0], nq + m.h.e_beg[t1] - m.h.e_beg[t0],
+                   t0};
+}
+
+// x-th of them, -1 for a skipped place or past the end.
+__device__ __forceinline__ int band_edge(const BandEdges& b, const int32_t* __restrict__ edge_tri, int x) {
+  if (x >= b.n) return -1;
+  if (x >= b.nq) return b.e0 + x - b.nq;
+  const int e = b.by_q[x];
+  return edge_tri[e] >= b.t0 ? -1 : e;
+}
+
 void mesh_build_host(const double* V, int64_t nv, const int32_t* F, int64_t nt, MeshHost& out);
 void mesh_touching_pairs(MeshHost& m);
 void mesh_upload(Mesh& m);
@@ -462,11 +483,9 @@ void incident_rhs(hipStream_t s, const Mesh& m, double k, const double* dirs_dev
 void quad_nodes(hipStream_t s, const Mesh& m, double* qx);
 // u: first-moment coefficients of one direction, u[e * ustride]
 void rhs_weights(hipStream_t s, const Mesh& m, double k, int field, const c128* u, int64_t ustride, c128* W);
-void rhs_correlation_kernel(hipStream_t s, const Level& l1, const Level& l2, const fosb_cov& cov, int64_t dir,
-                            c128* C, int64_t ldc);
-// C_d = Wgt_l1(dir0 + d) K Wgt_l2(dir0 + d)^H for d < nd at C + d * dstride (row stride ldc)
-void rhs_correlation_multi(hipStream_t s, const Level& l1, const Level& l2, const fosb_cov& cov, int64_t dir0,
-                           int64_t nd, c128* C, int64_t ldc, int64_t dstride);
+// C_d = Wgt_l1(dir0 + d) K Wgt_l2(dir0 + d)^H for d < nd at C + d * dstride (row stride ldc); uses c.scratch[2]
+void rhs_correlation(Context& c, const Level& l1, const Level& l2, const fosb_cov& cov, int64_t dir0, int64_t nd,
+                     c128* C, int64_t ldc, int64_t dstride);
 // PMCHWT right-hand side b = [e; h] (2N x ndir, row stride ndir): e[m] = int phi_m . p e^{ik d.x},
 // h[m] = int phi_m . (d x p) e^{ik d.x}
 void incident_rhs_pmchwt(hipStream_t s, const Mesh& m, double k, const double* dirs_dev, const double* pols_dev,

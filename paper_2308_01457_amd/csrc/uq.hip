@@ -220,9 +220,6 @@ void rhs_weights(hipStream_t s, const Mesh& m, double k, int field, const c128* 
   FOSB_LAUNCH_CHECK();
 }
 
-// C[m][n] = sum_{q in supp m} sum_{q' in supp n} W1[m,q] K(x_q, y_q') conj(W2[n,q'])
-// one thread per entry; the 12 nodes and weights of each row/column RWG are
-// staged in LDS (16 x 16 entries per block).
 struct CovParams {
   int kind;
   double s2;       // sigma^2
@@ -242,203 +239,172 @@ __device__ __forceinline__ double cov_eval(const CovParams& cp, double r2, doubl
   }
 }
 
-struct EdgeSide {
-  const int32_t* edge_tri;
-  const int32_t* edge_loc;
+static CovParams cov_params(const fosb_cov& cov) {
+  CovParams cp;
+  cp.kind = cov.kind;
+  cp.s2 = cov.sigma * cov.sigma;
+  cp.inv2l2 = cov.ell > 0 ? 1.0 / (2.0 * cov.ell * cov.ell) : 0.0;
+  cp.s3l = cov.ell > 0 ? std::sqrt(3.0) / cov.ell : 0.0;
+  return cp;
+}
+
+// ------------------------------------------------------------------ right-hand-side correlation
+// C_d[m][n] = sum_{q in supp m} sum_{q' in supp n} W1_d[m,q] K(x_q, y_q') conj(W2_d[n,q'])
+// for each incidence d.  The covariance of the 6 x 6 nodes of a triangle pair serves
+// the nine pairs of RWG functions on it and every incidence, so it is evaluated
+// once per triangle pair: k_cov_blocks contracts it to the pair's 3 x 3 local
+// entries, k_cov_gather adds each entry's (up to) four.  One evaluation per pair of
+// functions instead, 144 nodes each, is nine times the exponentials: six
+// ellipsoids to N = 7680 with 16 incidences each took 243 ms, with this 147.
+
+// A level's geometry and weights (the first incidence's; incidences nt * 18 apart).
+struct CovSide {
   const double* nrm;
   const double* qx;
   const c128* W;
-  int ne, nt;
+  int nt;
 };
 
-__device__ void stage_edge(const EdgeSide& L, int e, double (*x)[3], c128* w, double (*nn)[3]) {
-  // 12 nodes: 6 on T+ then 6 on T-
-  const int64_t Q = 6LL * L.nt;
-  for (int side = 0; side < 2; ++side) {
-    const int t = L.edge_tri[side * L.ne + e];
-    const int a = L.edge_loc[side * L.ne + e];
-    for (int q = 0; q < 6; ++q) {
-      const int64_t id = 6LL * t + q;
-      x[side * 6 + q][0] = L.qx[id];
-      x[side * 6 + q][1] = L.qx[Q + id];
-      x[side * 6 + q][2] = L.qx[2 * Q + id];
-      w[side * 6 + q] = L.W[((int64_t)t * 3 + a) * 6 + q];
-    }
-    nn[side][0] = L.nrm[t];
-    nn[side][1] = L.nrm[L.nt + t];
-    nn[side][2] = L.nrm[2 * L.nt + t];
-  }
-}
-
-// node coordinates and triangle normals of RWG e (no weights)
-__device__ void stage_nodes(const EdgeSide& L, int e, double (*x)[3], double (*nn)[3]) {
-  const int64_t Q = 6LL * L.nt;
-  for (int side = 0; side < 2; ++side) {
-    const int t = L.edge_tri[side * L.ne + e];
-    for (int q = 0; q < 6; ++q) {
-      const int64_t id = 6LL * t + q;
-      x[side * 6 + q][0] = L.qx[id];
-      x[side * 6 + q][1] = L.qx[Q + id];
-      x[side * 6 + q][2] = L.qx[2 * Q + id];
-    }
-    nn[side][0] = L.nrm[t];
-    nn[side][1] = L.nrm[L.nt + t];
-    nn[side][2] = L.nrm[2 * L.nt + t];
-  }
-}
-
-__global__ __launch_bounds__(256) void k_rhs_correlation(EdgeSide A, EdgeSide B, CovParams cp, c128* __restrict__ C,
-                                                         int64_t ldc) {
-  __shared__ double xa[16][12][3], xb[16][12][3];
-  __shared__ c128 wa[16][12], wb[16][12];
-  __shared__ double na[16][2][3], nb[16][2][3];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
-  if (threadIdx.x < 16) {
-    const int e = m0 + threadIdx.x;
-    if (e < A.ne) stage_edge(A, e, xa[threadIdx.x], wa[threadIdx.x], na[threadIdx.x]);
-  } else if (threadIdx.x < 32) {
-    const int r = threadIdx.x - 16;
-    const int e = n0 + r;
-    if (e < B.ne) stage_edge(B, e, xb[r], wb[r], nb[r]);
-  }
-  __syncthreads();
-  const int m = m0 + ty, n = n0 + tx;
-  if (m >= A.ne || n >= B.ne) return;
-  double cr = 0, ci = 0;
-  for (int q = 0; q < 12; ++q) {
-    const double x0 = xa[ty][q][0], x1 = xa[ty][q][1], x2 = xa[ty][q][2];
-    const double* nx = na[ty][q / 6];
-    double ar = 0, ai = 0;  // sum_q' K conj(W2)
-#pragma unroll 4
-    for (int p = 0; p < 12; ++p) {
-      const double d0 = x0 - xb[tx][p][0], d1 = x1 - xb[tx][p][1], d2 = x2 - xb[tx][p][2];
-      const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-      const double* ny = nb[tx][p / 6];
-      const double kv = cov_eval(cp, r2, nx[0] * ny[0] + nx[1] * ny[1] + nx[2] * ny[2]);
-      ar += kv * wb[tx][p].re;
-      ai -= kv * wb[tx][p].im;
-    }
-    const c128 w = wa[ty][q];
-    cr += w.re * ar - w.im * ai;
-    ci += w.re * ai + w.im * ar;
-  }
-  C[(int64_t)m * ldc + n] = c128{cr, ci};
-}
-
-// Several incidences at once: the covariance between the 12 nodes of RWG m
-// and those of RWG n does not depend on the incidence, so each block of
-// kernel values is evaluated once per chunk of up to RC_DC incidences and
-// applied to all of them.  C_d (incidence dir0 + d) is written at
-// C + d * dstride with row stride ldc.
-constexpr int RC_DC = 8;
-
-__global__ __launch_bounds__(256) void k_rhs_correlation_multi(EdgeSide A, EdgeSide B, CovParams cp, int dc,
-                                                               c128* __restrict__ C, int64_t ldc, int64_t dstride) {
-  __shared__ double xa[16][12][3], xb[16][12][3];
-  __shared__ c128 wa[16][12][RC_DC], wb[16][12][RC_DC];
-  __shared__ double na[16][2][3], nb[16][2][3];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
-  if (threadIdx.x < 16) {
-    const int e = m0 + threadIdx.x;
-    if (e < A.ne) stage_nodes(A, e, xa[threadIdx.x], na[threadIdx.x]);
-  } else if (threadIdx.x < 32) {
-    const int r = threadIdx.x - 16;
-    const int e = n0 + r;
-    if (e < B.ne) stage_nodes(B, e, xb[r], nb[r]);
-  }
-  // weights of every incidence of the chunk: wa[r][q][d], wb[r][q][d] (zero past dc)
-  for (int e = threadIdx.x; e < 2 * 16 * 12 * RC_DC; e += 256) {
-    const int side = e / (16 * 12 * RC_DC);
-    const int rem = e % (16 * 12 * RC_DC);
-    const int r = rem / (12 * RC_DC), q = (rem / RC_DC) % 12, d = rem % RC_DC;
-    const EdgeSide& S = side ? B : A;
-    const int eidx = (side ? n0 : m0) + r;
-    c128 w = c128{0.0, 0.0};
-    if (eidx < S.ne && d < dc) {
-      const int t = S.edge_tri[(q / 6) * S.ne + eidx];
-      const int a = S.edge_loc[(q / 6) * S.ne + eidx];
-      w = S.W[(int64_t)d * S.nt * 18 + ((int64_t)t * 3 + a) * 6 + q % 6];  // incidences of a level: nt*18 apart
-    }
-    if (side)
-      wb[r][q][d] = w;
-    else
-      wa[r][q][d] = w;
-  }
-  __syncthreads();
-  const int m = m0 + ty, n = n0 + tx;
-  if (m >= A.ne || n >= B.ne) return;
-  double cr[RC_DC], ci[RC_DC];
+// Local entries of the triangle pairs (i0 + row, j), incidence d, at
+// P[d * dstride + (3 row + a) * ldp + 3 j + b].  One thread per pair and four rows
+// per workgroup (one per wavefront, its weights uniform): 36 covariances in registers,
+// then 432 FMAs per incidence; the 64 columns' weights pass through LDS, and the entries too, so
+// that stores are contiguous.
+__global__ __launch_bounds__(256) void k_cov_blocks(CovSide A, CovSide B, CovParams cp, int i0, int i1, int nd,
+                                                    c128* __restrict__ P, int64_t ldp, int64_t dstride) {
+  __shared__ c128 w2[18][65];
+  __shared__ c128 stage[4][3 * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + wave);
+  const int j0 = blockIdx.x * 64, jn = min(64, B.nt - j0);
+  const int i = min(i0 + row, i1 - 1), j = j0 + min(lane, jn - 1);
+  const bool act = i0 + row < i1;
+  double k[6][6];
+  {
+    const int64_t Q1 = 6LL * A.nt, Q2 = 6LL * B.nt;
+    const double nn = A.nrm[i] * B.nrm[j] + A.nrm[A.nt + i] * B.nrm[B.nt + j] +
+                      A.nrm[2 * A.nt + i] * B.nrm[2 * B.nt + j];
 #pragma unroll
-  for (int d = 0; d < RC_DC; ++d) cr[d] = ci[d] = 0.0;
-  for (int q = 0; q < 12; ++q) {
-    const double x0 = xa[ty][q][0], x1 = xa[ty][q][1], x2 = xa[ty][q][2];
-    const double* nx = na[ty][q / 6];
-    double ar[RC_DC], ai[RC_DC];  // sum_p K(q, p) conj(W2_d[p])
+    for (int p = 0; p < 6; ++p) {
+      const int64_t y = 6LL * j + p;
+      const double y0 = B.qx[y], y1 = B.qx[Q2 + y], y2 = B.qx[2 * Q2 + y];
 #pragma unroll
-    for (int d = 0; d < RC_DC; ++d) ar[d] = ai[d] = 0.0;
-#pragma unroll 1
-    for (int p = 0; p < 12; ++p) {
-      const double d0 = x0 - xb[tx][p][0], d1 = x1 - xb[tx][p][1], d2 = x2 - xb[tx][p][2];
-      const double* ny = nb[tx][p / 6];
-      const double kv = cov_eval(cp, d0 * d0 + d1 * d1 + d2 * d2, nx[0] * ny[0] + nx[1] * ny[1] + nx[2] * ny[2]);
-#pragma unroll
-      for (int d = 0; d < RC_DC; ++d) {
-        const c128 w = wb[tx][p][d];
-        ar[d] += kv * w.re;
-        ai[d] -= kv * w.im;
+      for (int q = 0; q < 6; ++q) {
+        const int64_t x = 6LL * i + q;
+        const double d0 = A.qx[x] - y0, d1 = A.qx[Q1 + x] - y1, d2 = A.qx[2 * Q1 + x] - y2;
+        k[q][p] = cov_eval(cp, d0 * d0 + d1 * d1 + d2 * d2, nn);
       }
     }
+  }
+  c128* st = stage[wave];
+  for (int d = 0; d < nd; ++d) {
+    __syncthreads();
+    const c128* Wd = B.W + ((int64_t)d * B.nt + j0) * 18;
+    for (int e = threadIdx.x; e < 18 * jn; e += 256) w2[e % 18][e / 18] = Wd[e];
+    __syncthreads();
+    if (!act) continue;
+    const c128* Wi = A.W + ((int64_t)d * A.nt + i) * 18;
+    c128 out[3][3] = {};
 #pragma unroll
-    for (int d = 0; d < RC_DC; ++d) {
-      const c128 w = wa[ty][q][d];
-      cr[d] += w.re * ar[d] - w.im * ai[d];
-      ci[d] += w.re * ai[d] + w.im * ar[d];
+    for (int b = 0; b < 3; ++b) {
+      double sr[6] = {}, si[6] = {};   // sum over the column's nodes
+#pragma unroll
+      for (int p = 0; p < 6; ++p) {
+        const c128 w = w2[6 * b + p][lane];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+          sr[q] = fma(k[q][p], w.re, sr[q]);
+          si[q] = fma(-k[q][p], w.im, si[q]);
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+          const c128 w = Wi[6 * a + q];
+          out[a][b].re += w.re * sr[q] - w.im * si[q];
+          out[a][b].im += w.re * si[q] + w.im * sr[q];
+        }
+    }
+    c128* dst = P + d * dstride + 3LL * row * ldp + 3 * j0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+#pragma unroll
+      for (int b = 0; b < 3; ++b) st[3 * lane + b] = out[a][b];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int b = 0; b < 3; ++b)
+        if (64 * b + lane < 3 * jn) dst[a * ldp + 64 * b + lane] = st[64 * b + lane];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
   }
-#pragma unroll
-  for (int d = 0; d < RC_DC; ++d)
-    if (d < dc) C[d * dstride + (int64_t)m * ldc + n] = c128{cr[d], ci[d]};
 }
 
-void rhs_correlation_multi(hipStream_t s, const Level& l1, const Level& l2, const fosb_cov& cov, int64_t dir0,
-                           int64_t nd, c128* C, int64_t ldc, int64_t dstride) {
-  const Mesh& m1 = *l1.mesh;
-  const Mesh& m2 = *l2.mesh;
-  CovParams cp;
-  cp.kind = cov.kind;
-  cp.s2 = cov.sigma * cov.sigma;
-  cp.inv2l2 = cov.ell > 0 ? 1.0 / (2.0 * cov.ell * cov.ell) : 0.0;
-  cp.s3l = cov.ell > 0 ? std::sqrt(3.0) / cov.ell : 0.0;
-  dim3 g((unsigned)((m2.h.ne + 15) / 16), (unsigned)((m1.h.ne + 15) / 16));
-  for (int64_t c0 = 0; c0 < nd; c0 += RC_DC) {
-    EdgeSide A{m1.edge_tri.as<int32_t>(), m1.edge_loc.as<int32_t>(), m1.nrm.as<double>(), l1.qx.as<double>(),
-               l1.W.as<c128>() + (dir0 + c0) * m1.h.nt * 18, (int)m1.h.ne, (int)m1.h.nt};
-    EdgeSide B{m2.edge_tri.as<int32_t>(), m2.edge_loc.as<int32_t>(), m2.nrm.as<double>(), l2.qx.as<double>(),
-               l2.W.as<c128>() + (dir0 + c0) * m2.h.nt * 18, (int)m2.h.ne, (int)m2.h.nt};
-    const int dc = (int)std::min<int64_t>(RC_DC, nd - c0);
-    hipLaunchKernelGGL(k_rhs_correlation_multi, g, dim3(256), 0, s, A, B, cp, dc, C + c0 * dstride, ldc, dstride);
-    FOSB_LAUNCH_CHECK();
+// C_d[m][n] from the local entries of the row triangles [i0, i1): stored when T+ of
+// m is among them (T+ < T-), added when only T- is.
+__global__ __launch_bounds__(256) void k_cov_gather(BandEdges rows, int i1, const int32_t* __restrict__ et1,
+                                                    const int32_t* __restrict__ el1, int ne1,
+                                                    const int32_t* __restrict__ et2,
+                                                    const int32_t* __restrict__ el2, int ne2,
+                                                    const c128* __restrict__ P, int64_t ldp, int64_t pstride,
+                                                    c128* __restrict__ C, int64_t ldc, int64_t cstride) {
+  const int n = blockIdx.x * 64 + (threadIdx.x & 63);
+  const int m = band_edge(rows, et1, blockIdx.y * 4 + (threadIdx.x >> 6));
+  if (n >= ne2 || m < 0) return;
+  const int64_t cp = 3LL * et2[n] + el2[n], cm = 3LL * et2[ne2 + n] + el2[ne2 + n];
+  const int tp = et1[m], tm = et1[ne1 + m];
+  P += blockIdx.z * pstride;
+  c128* c = C + blockIdx.z * cstride + (int64_t)m * ldc + n;
+  c128 s{0.0, 0.0};
+  if (tp >= rows.t0) {
+    const c128* r = P + (3LL * (tp - rows.t0) + el1[m]) * ldp;
+    const c128 u = r[cp], v = r[cm];
+    s = c128{u.re + v.re, u.im + v.im};
+  } else {
+    s = *c;
   }
+  if (tm < i1) {
+    const c128* r = P + (3LL * (tm - rows.t0) + el1[ne1 + m]) * ldp;
+    const c128 u = r[cp], v = r[cm];
+    s = c128{s.re + u.re + v.re, s.im + u.im + v.im};
+  }
+  *c = s;
 }
 
-void rhs_correlation_kernel(hipStream_t s, const Level& l1, const Level& l2, const fosb_cov& cov, int64_t dir,
-                            c128* C, int64_t ldc) {
-  const Mesh& m1 = *l1.mesh;
-  const Mesh& m2 = *l2.mesh;
-  EdgeSide A{m1.edge_tri.as<int32_t>(), m1.edge_loc.as<int32_t>(), m1.nrm.as<double>(), l1.qx.as<double>(),
-             l1.W.as<c128>() + dir * m1.h.nt * 18, (int)m1.h.ne, (int)m1.h.nt};
-  EdgeSide B{m2.edge_tri.as<int32_t>(), m2.edge_loc.as<int32_t>(), m2.nrm.as<double>(), l2.qx.as<double>(),
-             l2.W.as<c128>() + dir * m2.h.nt * 18, (int)m2.h.ne, (int)m2.h.nt};
-  CovParams cp;
-  cp.kind = cov.kind;
-  cp.s2 = cov.sigma * cov.sigma;
-  cp.inv2l2 = cov.ell > 0 ? 1.0 / (2.0 * cov.ell * cov.ell) : 0.0;
-  cp.s3l = cov.ell > 0 ? std::sqrt(3.0) / cov.ell : 0.0;
-  dim3 g((unsigned)((m2.h.ne + 15) / 16), (unsigned)((m1.h.ne + 15) / 16));
-  hipLaunchKernelGGL(k_rhs_correlation, g, dim3(256), 0, s, A, B, cp, C, ldc);
-  FOSB_LAUNCH_CHECK();
+// Row triangles in bands whose local entries, for up to 16 incidences, fill
+// kCovBandBytes of c's scratch[2] (free until the pair's solve).
+void rhs_correlation(Context& c, const Level& l1, const Level& l2, const fosb_cov& cov, int64_t dir0, int64_t nd,
+                     c128* C, int64_t ldc, int64_t dstride) {
+  constexpr int64_t kCovBandBytes = (int64_t)256 << 20, kChunk = 16;
+  const Mesh &m1 = *l1.mesh, &m2 = *l2.mesh;
+  const int nt1 = (int)m1.h.nt, nt2 = (int)m2.h.nt, ne1 = (int)m1.h.ne, ne2 = (int)m2.h.ne;
+  const CovParams cp = cov_params(cov);
+  hipStream_t s = c.stream;
+  for (int64_t d0 = 0; d0 < nd; d0 += kChunk) {
+    const int dn = (int)std::min(kChunk, nd - d0);
+    const int64_t row_bytes = 9LL * nt2 * dn * (int64_t)sizeof(c128);
+    const int w = (int)std::min<int64_t>({nt1, 4 * 65535, std::max<int64_t>(4, kCovBandBytes / row_bytes / 4 * 4)});
+    c.scratch[2].reserve((size_t)w * row_bytes);
+    c128* P = c.scratch[2].as<c128>();
+    const int64_t ldp = 3LL * nt2, pstride = 3LL * w * ldp;
+    const CovSide A{m1.nrm.as<double>(), l1.qx.as<double>(), l1.W.as<c128>() + (dir0 + d0) * nt1 * 18, nt1};
+    const CovSide B{m2.nrm.as<double>(), l2.qx.as<double>(), l2.W.as<c128>() + (dir0 + d0) * nt2 * 18, nt2};
+    for (int i0 = 0; i0 < nt1; i0 += w) {
+      const int i1 = std::min(nt1, i0 + w);
+      hipLaunchKernelGGL(k_cov_blocks, dim3((nt2 + 63) / 64, (i1 - i0 + 3) / 4), dim3(256), 0, s, A, B, cp, i0, i1,
+                         dn, P, ldp, pstride);
+      FOSB_LAUNCH_CHECK();
+      const BandEdges rows = band_edges(m1, i0, i1);
+      if (rows.n > 0) {
+        hipLaunchKernelGGL(k_cov_gather, dim3((ne2 + 63) / 64, (rows.n + 3) / 4, dn), dim3(256), 0, s, rows, i1,
+                           m1.edge_tri.as<int32_t>(), m1.edge_loc.as<int32_t>(), ne1, m2.edge_tri.as<int32_t>(),
+                           m2.edge_loc.as<int32_t>(), ne2, P, ldp, pstride, C + d0 * dstride, ldc, dstride);
+        FOSB_LAUNCH_CHECK();
+      }
+    }
+  }
 }
 
 // FF[(c*n_a + i)][m] = -i k [(I - x x^T) int phi_m(y) exp(-i k x.y) dy]_c
@@ -823,11 +789,7 @@ void cov_matrix(hipStream_t s, const Level& l1, const Level& l2, const fosb_cov&
   const Mesh& m1 = *l1.mesh;
   const Mesh& m2 = *l2.mesh;
   const int64_t Q1 = 6LL * m1.h.nt, Q2 = 6LL * m2.h.nt;
-  CovParams cp;
-  cp.kind = cov.kind;
-  cp.s2 = cov.sigma * cov.sigma;
-  cp.inv2l2 = cov.ell > 0 ? 1.0 / (2.0 * cov.ell * cov.ell) : 0.0;
-  cp.s3l = cov.ell > 0 ? std::sqrt(3.0) / cov.ell : 0.0;
+  const CovParams cp = cov_params(cov);
   dim3 g((unsigned)((Q2 + 255) / 256), (unsigned)std::min<int64_t>(na, 65535));
   hipLaunchKernelGGL(k_cov_matrix, g, dim3(256), 0, s, a0, na, Q2, l1.qx.as<double>(), Q1, m1.nrm.as<double>(),
                      (int)m1.h.nt, l2.qx.as<double>(), m2.nrm.as<double>(), (int)m2.h.nt, cp, Kc);

@@ -268,3 +268,27 @@ def test_batch_against_oracle_golden(fz, precision, tol):
         errs = [float(np.linalg.norm(v[d] - ref[d]) / np.linalg.norm(ref[d])) for d in range(ref.shape[0])]
         print(f"[gpu]   shape {rec['index']}: worst incidence {max(errs):.2e}", flush=True)
         assert max(errs) < tol
+
+
+def test_stacked_correlations_over_bands_and_chunks(fz):
+    """17 incidences (a chunk of 16 and one more) whose local entries take several
+    bands of row triangles (N = 1920 against itself), on shuffled triangles (T+ and
+    T- of an edge in different bands): each Sigma block equals the one of its
+    incidence alone, from one band, to rounding."""
+    fosb, ctx, torch = fz
+    rng = np.random.default_rng(3)
+    nd = 17
+    d = rng.standard_normal((nd, 3))
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+    p = np.cross(d, [0.3, 0.5, 1.0])
+    p /= np.linalg.norm(p, axis=1, keepdims=True)
+    V, F = workloads.icosphere(3)
+    meshes = [fosb.Mesh(ctx, V, F[rng.permutation(len(F))])]
+    cov = fosb.make_cov("gaussian", SIG, ELL)
+    xh = workloads.angles_xz(5)
+    _, blocks, _ = fosb.second_moment(ctx, meshes, 0, 0, K1, fosb.FP64, cov, xh, d, p, dir=-1)
+    n = meshes[0].n_edges
+    for q in (0, 7, 15, 16):
+        _, alone, _ = fosb.second_moment(ctx, meshes, 0, 0, K1, fosb.FP64, cov, xh, d, p, dir=q)
+        a, b = blocks[0][:, q * n:(q + 1) * n], alone[0]
+        assert float((a - b).norm() / b.norm()) < 1e-11, q
