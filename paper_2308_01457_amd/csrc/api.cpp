@@ -442,9 +442,13 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
       if (o.certify) matrix_certificate(true);
     }
     // the refined solves apply the factors through their diagonal-block inverses
-    const size_t bytes = (size_t)((n + kInvBlock - 1) / kInvBlock) * kInvBlock * kInvBlock * sizeof(c64);
-    L->inv_L.alloc(bytes);
-    L->inv_U.alloc(bytes);
+    const bool grow = inv_block(n) > kInvBlock;
+    const size_t small = (size_t)((n + kInvBlock - 1) / kInvBlock) * kInvBlock * kInvBlock * sizeof(c64);
+    L->inv_L.alloc((size_t)inv_bytes(n));
+    L->inv_U.alloc((size_t)inv_bytes(n));
+    DevBuf inv_small;   // kInvBlock-row inverses, from which the level's are grown
+    if (grow) inv_small.alloc(small);
+    c64* invL = (grow ? inv_small : L->inv_L).as<c64>();
     bool factored = false;
     if (o.lu_pivoting == 0 && n >= 2048) {
       // symmetric matrix: no pivoting, half the trailing-update flops; kept when no
@@ -458,7 +462,7 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
       const bool symmetric = zmax > 0 && std::isfinite(zmax) && defect <= 1e-5 * zmax;
       if (symmetric) {
         info = lu_factor<float>(c, static_cast<c64*>(Zlow), n, ldzlow, L->dinv_L.as<c64>(), L->dinv_U.as<c64>(),
-                                L->perm, L->inv_L.as<c64>(), true);
+                                L->perm, invL, true);
         const double growth = absmax_upper<float>(c, static_cast<const c64*>(Zlow), n, ldzlow) / zmax;
         factored = info == 0 && std::isfinite(growth) && growth <= 1e3;
         L->sym_lu = factored ? 1 : 0;
@@ -473,10 +477,17 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
     }
     if (!factored)
       info = lu_factor<float>(c, static_cast<c64*>(Zlow), n, ldzlow, L->dinv_L.as<c64>(), L->dinv_U.as<c64>(),
-                              L->perm, L->inv_L.as<c64>());
-    if (info == 0)
-      upper_block_inverses<float>(c, static_cast<const c64*>(Zlow), n, ldzlow, L->dinv_U.as<c64>(),
-                                  L->inv_U.as<c64>());
+                              L->perm, invL);
+    const c64* A32 = static_cast<const c64*>(Zlow);
+    if (info == 0 && grow) grow_block_inverses(c, true, A32, n, ldzlow, invL, L->inv_L.as<c64>());
+    if (info == 0 && L->sym_lu) {
+      transpose_block_inverses(c, A32, n, ldzlow, L->inv_L.as<c64>(), L->inv_U.as<c64>());
+    } else if (info == 0) {
+      c64* invU = grow ? invL : L->inv_U.as<c64>();
+      upper_block_inverses<float>(c, A32, n, ldzlow, L->dinv_U.as<c64>(), invU);
+      if (grow) grow_block_inverses(c, false, A32, n, ldzlow, invU, L->inv_U.as<c64>());
+    }
+    if (grow) FOSB_HIP(hipStreamSynchronize(s));   // inv_small is read
   }
   if (info != 0) fail(FOSB_E_SINGULAR, "exactly zero pivot at index %lld", (long long)(info - 1));
   upload(L->d_perm, L->perm, s);
@@ -553,7 +564,7 @@ static int64_t level_bytes(int64_t n, int64_t nt, int32_t precision, int64_t n_d
   const int64_t nblk = (n + kPanel - 1) / kPanel;
   const int64_t es = precision == FOSB_PREC_FP64 ? 16 : 8;
   int64_t b = 4 * n + 2 * nblk * kPanel * kPanel * es + 18 * nt * 8 + 16 * n * n_dirs + 18 * nt * n_dirs * 16;
-  if (precision == FOSB_PREC_MIXED) b += 2 * ((n + kInvBlock - 1) / kInvBlock) * kInvBlock * kInvBlock * 8;
+  if (precision == FOSB_PREC_MIXED) b += 2 * inv_bytes(n);
   return b;
 }
 

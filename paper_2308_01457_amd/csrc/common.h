@@ -329,7 +329,7 @@ struct Level {
   std::vector<int32_t> perm;   // host: row permutation (position i holds original row perm[i])
   DevBuf d_perm;               // int32 [n]
   DevBuf dinv_L, dinv_U;       // inverted nb x nb diagonal blocks of L and U (LU precision)
-  DevBuf inv_L, inv_U;         // MIXED: inverted kInvBlock x kInvBlock diagonal blocks of L and U (complex64)
+  DevBuf inv_L, inv_U;         // MIXED: inverted inv_block(n)-row diagonal blocks of L and U (complex64)
   DevBuf u;                    // c128 [n_dirs][n]
   DevBuf W;                    // c128 [n_dirs][nt][3][6] RHS weights
   DevBuf qx;                   // double [3][6*nt] quadrature nodes (component-major)
@@ -439,10 +439,28 @@ void trsm_lower_unit_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<
 // Inverses of the kInvBlock x kInvBlock diagonal blocks of the upper factor
 // (block b at inv + b kInvBlock^2, row-major, row stride kInvBlock; the last
 // block's slot is the identity outside its corner; lu_factor makes L's), and
-// out-of-place triangular solves of a whole factor that apply them at the
+// out-of-place triangular solves of a whole factor that apply inverses of inv_block(n) rows at the
 // leaves: X <- T^{-1} B, with B (n x nrhs) consumed as workspace.  Complex64
 // factors only.
 constexpr int kInvBlock = 256;
+// Rows of a leaf of those solves.  A narrow solve is a chain of launches, two
+// per leaf (N = 7680, one column: 59 products a factor with 256 rows, 15 with
+// 1024; a refined solve 2.0 -> 1.25 ms; 17 columns 11.5 -> 4.4), and a wide one runs its small products
+// far below the large ones' rate.  The inverses take 8 KB a row and factor.
+inline int64_t inv_block(int64_t n) { return n > 1024 ? 1024 : kInvBlock; }
+inline int64_t inv_bytes(int64_t n) {
+  const int64_t ib = inv_block(n);
+  return (n + ib - 1) / ib * ib * ib * (int64_t)sizeof(c64);
+}
+// W (inv_bytes(n)) <- inverses of the inv_block(n)-row diagonal blocks from those of kInvBlock rows (S):
+// halves merged by products, on ctx's stream (uses solve_tmp).  inv_block(n) > kInvBlock.
+void grow_block_inverses(Context& ctx, bool lower, const c64* A, int64_t n, int64_t lda, const c64* S, c64* W);
+// The same of U = D L^T from those of L: invU = invL^T D^{-1}, D the diagonal of A.
+void transpose_block_inverses(Context& ctx, const c64* A, int64_t n, int64_t lda, const c64* invL, c64* invU);
+// gemm.hip: one doubling of the diagonal blocks' inverses in W (blocks of ib rows) from h to 2h rows;
+// T: h^2 entries a pair
+void inverse_merge(hipStream_t s, bool lower, int64_t n, const c64* A, int64_t lda, c64* W, int64_t ib, int64_t h,
+                   c64* T);
 template <typename T>
 void upper_block_inverses(Context& ctx, const cplx<T>* A, int64_t n, int64_t lda, const cplx<T>* dinvU,
                           cplx<T>* invU);

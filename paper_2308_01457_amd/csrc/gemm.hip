@@ -68,15 +68,15 @@ __device__ __forceinline__ void tile_of_block(int64_t& tm, int64_t& tn) {
   tn = in / gs;
 }
 
-// One entry of C (or of the split-K partial product) from the three real products.
+// One entry of C, or (P given) of a split-K partial product, from the three real products.
 template <typename T>
 __device__ __forceinline__ void store_entry(int64_t M, int64_t N, int64_t row, int64_t col, T t1, T t2, T t3, T alpha,
                                             T beta, cplx<T>* __restrict__ C, int64_t ldc, cplx<T>* __restrict__ P) {
   if (row >= M || col >= N) return;
   const T cr = t1 - t2;
   const T ci = t3 - t1 - t2;
-  if (gridDim.z > 1) {
-    P[(int64_t)blockIdx.z * M * N + row * N + col] = cplx<T>{cr, ci};
+  if (P) {
+    P[row * N + col] = cplx<T>{cr, ci};
     return;
   }
   cplx<T>* p = C + row * ldc + col;
@@ -88,8 +88,8 @@ __device__ __forceinline__ void store_entry(int64_t M, int64_t N, int64_t row, i
   }
 }
 
-// Split K: workgroup z of gridDim.z covers K range [z*kc, min(K, (z+1)*kc)); with
-// gridDim.z > 1 it writes its raw partial product to P + z*M*N (row stride N)
+// Split K: workgroup z of gridDim.z covers K range [kb, ke) = [z*kc, min(K, (z+1)*kc));
+// with gridDim.z > 1 it writes its raw partial product to P + z*M*N (row stride N)
 // and k_gemm_splitk_sum forms C = beta*C + alpha*sum_z P_z in fixed z order.
 // Tile: 2 x 2 waves, each owning WM x WN blocks of 16 x 16, so the workgroup
 // covers BM = 32 WM rows and BN = 32 WN columns.  Every variant accumulates an
@@ -98,7 +98,8 @@ __device__ __forceinline__ void store_entry(int64_t M, int64_t N, int64_t row, i
 template <typename T, bool CONJ_A, int WM, int WN>
 __device__ __forceinline__ void gemm_tile(int64_t M, int64_t N, int64_t K, T alpha, const cplx<T>* __restrict__ A,
                                           int64_t lda, const cplx<T>* __restrict__ B, int64_t ldb, T beta,
-                                          cplx<T>* __restrict__ C, int64_t ldc, int64_t kc, cplx<T>* __restrict__ P) {
+                                          cplx<T>* __restrict__ C, int64_t ldc, int64_t kb, int64_t ke,
+                                          cplx<T>* __restrict__ P) {
   using V4 = typename Mfma<T>::v4;
   constexpr int BK = Slice<T>::BK;
   constexpr int BM = 32 * WM, BN = 32 * WN;
@@ -126,8 +127,6 @@ __device__ __forceinline__ void gemm_tile(int64_t M, int64_t N, int64_t K, T alp
   const int b_k = tid / (BN / BE);
   const int b_col = (tid % (BN / BE)) * BE;
 
-  const int64_t kb = (int64_t)blockIdx.z * kc;
-  const int64_t ke = min(K, kb + kc);
   cplx<T> ra[AE], rb[BE];
   const bool interior = m0 + BM <= M && n0 + BN <= N;  // no tile edge in M or N
   auto load_tiles = [&](int64_t k0) {
@@ -255,7 +254,9 @@ __device__ __forceinline__ void gemm_tile(int64_t M, int64_t N, int64_t K, T alp
 
 template <typename T, bool CONJ_A, int WM, int WN>
 __global__ __launch_bounds__(256) void k_gemm(FOSB_GEMM_ARGS(T)) {
-  gemm_tile<T, CONJ_A, WM, WN>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kc, P);
+  const int64_t kb = (int64_t)blockIdx.z * kc;
+  gemm_tile<T, CONJ_A, WM, WN>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kb, min(K, kb + kc),
+                               gridDim.z > 1 ? P + (int64_t)blockIdx.z * M * N : nullptr);
 }
 
 // FP64 products.  A 3M block of 16 x 16 x 4 is three MFMAs of 32 cycles, so what
@@ -280,8 +281,8 @@ __global__ __launch_bounds__(256) void k_gemm(FOSB_GEMM_ARGS(T)) {
 template <bool CONJ_A, int WM, int WN>
 __device__ __forceinline__ void gemm64_tile(int64_t M, int64_t N, int64_t K, double alpha,
                                             const c128* __restrict__ A, int64_t lda, const c128* __restrict__ B,
-                                            int64_t ldb, double beta, c128* __restrict__ C, int64_t ldc, int64_t kc,
-                                            c128* __restrict__ P) {
+                                            int64_t ldb, double beta, c128* __restrict__ C, int64_t ldc, int64_t kb,
+                                            int64_t ke, c128* __restrict__ P) {
   using V4 = Mfma<double>::v4;
   constexpr bool PIPE = WN > 2;
   constexpr int BK = Slice<double>::BK;
@@ -293,7 +294,6 @@ __device__ __forceinline__ void gemm64_tile(int64_t M, int64_t N, int64_t K, dou
   int64_t tm, tn;
   tile_of_block(tm, tn);
   const int64_t m0 = tm * BM, n0 = tn * BN;
-  const int64_t kb = (int64_t)blockIdx.z * kc, ke = min(K, kb + kc);
 
   int ak[AE], ar[AE], bk[BE], bc[BE];
   const c128 *pa[AE], *pb[BE];
@@ -419,9 +419,49 @@ __device__ __forceinline__ void gemm64_tile(int64_t M, int64_t N, int64_t K, dou
 
 template <bool CONJ_A, int WM, int WN>
 __global__ __launch_bounds__(256, WN == 1 ? 4 : WN == 2 ? 3 : 2) void k_gemm64(FOSB_GEMM_ARGS(double)) {
-  gemm64_tile<CONJ_A, WM, WN>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kc, P);
+  const int64_t kb = (int64_t)blockIdx.z * kc;
+  gemm64_tile<CONJ_A, WM, WN>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, kb, min(K, kb + kc),
+                              gridDim.z > 1 ? P + (int64_t)blockIdx.z * M * N : nullptr);
 }
 #undef FOSB_GEMM_ARGS
+
+// Inverse of a triangular 2h x 2h diagonal block from those of its h x h halves:
+// lower, X21 = -(A22^-1) (A21 A11^-1); upper, X12 = -(A11^-1) (A12 A22^-1).  STEP 0 forms the
+// product in parentheses in T (h x h a pair), STEP 1 the other.  Pair z is at
+// row 2hz of the factor; W holds the inverses in blocks of ib rows.  The last
+// pair's second half may be short (m rows) or missing.
+template <bool LOWER, int STEP>
+__global__ __launch_bounds__(256) void k_inverse_merge(int64_t n, const c64* __restrict__ A, int64_t lda,
+                                                       c64* __restrict__ W, int64_t ib, int64_t h,
+                                                       c64* __restrict__ T) {
+  const int64_t r = 2 * h * blockIdx.z, m = min(h, n - r - h);
+  if (m <= 0) return;
+  c64* w11 = W + r / ib * ib * ib + r % ib * (ib + 1);
+  c64* w22 = w11 + h * (ib + 1);
+  T += h * h * blockIdx.z;
+  const int64_t rows = LOWER ? m : h, cols = LOWER ? h : m;
+  if (STEP == 0)
+    gemm_tile<float, false, 2, 2>(rows, cols, cols, 1.f, LOWER ? A + (r + h) * lda + r : A + r * lda + r + h, lda,
+                                  LOWER ? w11 : w22, ib, 0.f, T, h, 0, cols, nullptr);
+  else
+    gemm_tile<float, false, 2, 2>(rows, cols, rows, -1.f, LOWER ? w22 : w11, ib, T, h, 0.f,
+                                  LOWER ? w11 + h * ib : w11 + h, ib, 0, rows, nullptr);
+}
+
+void inverse_merge(hipStream_t s, bool lower, int64_t n, const c64* A, int64_t lda, c64* W, int64_t ib, int64_t h,
+                   c64* T) {
+  const int64_t pairs = (n - h + 2 * h - 1) / (2 * h);   // pairs with a second half
+  if (n <= h) return;
+  const dim3 g((unsigned)((h + 63) / 64), (unsigned)((h + 63) / 64), (unsigned)pairs), b(256);
+  if (lower) {
+    hipLaunchKernelGGL((k_inverse_merge<true, 0>), g, b, 0, s, n, A, lda, W, ib, h, T);
+    hipLaunchKernelGGL((k_inverse_merge<true, 1>), g, b, 0, s, n, A, lda, W, ib, h, T);
+  } else {
+    hipLaunchKernelGGL((k_inverse_merge<false, 0>), g, b, 0, s, n, A, lda, W, ib, h, T);
+    hipLaunchKernelGGL((k_inverse_merge<false, 1>), g, b, 0, s, n, A, lda, W, ib, h, T);
+  }
+  FOSB_LAUNCH_CHECK();
+}
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_gemm_splitk_sum(int64_t M, int64_t N, int nz, T alpha,

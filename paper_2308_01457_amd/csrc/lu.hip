@@ -1875,6 +1875,44 @@ void upper_block_inverses(Context& ctx, const cplx<T>* A, int64_t n, int64_t lda
   if (n > 0) block_inverses<T, false>(ctx, A, n, lda, dinvU, invU, 0, (n + NL - 1) / NL);
 }
 
+// W (blocks of ib rows and columns) <- the NL-row blocks S on its diagonal, zero elsewhere.
+__global__ void k_inverse_spread(const c64* __restrict__ S, c64* __restrict__ W, int64_t ib, int64_t blocks) {
+  const int64_t b = blockIdx.z, r = blockIdx.y, c = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t q = b * (ib / NL) + r / NL;
+  const bool in = c / NL == r / NL && q < blocks;
+  W[(b * ib + r) * ib + c] = in ? S[(q * NL + r % NL) * NL + c % NL] : c64{0.f, 0.f};
+}
+
+void grow_block_inverses(Context& ctx, bool lower, const c64* A, int64_t n, int64_t lda, const c64* S, c64* W) {
+  const int64_t ib = inv_block(n), nb = (n + ib - 1) / ib;
+  hipLaunchKernelGGL(k_inverse_spread, dim3((unsigned)(ib / 256), (unsigned)ib, (unsigned)nb), dim3(256), 0, ctx.stream,
+                     S, W, ib, (n + NL - 1) / NL);
+  FOSB_LAUNCH_CHECK();
+  ctx.solve_tmp.reserve((size_t)nb * (ib / 2) * (ib / 2) * sizeof(c64) * 2);
+  for (int64_t h = NL; h < ib; h *= 2) inverse_merge(ctx.stream, lower, n, A, lda, W, ib, h, ctx.solve_tmp.as<c64>());
+}
+
+// 32 x 32 tiles through LDS; zero where d is (its factorisation has failed).
+__global__ __launch_bounds__(256) void k_inverse_transpose(const c64* __restrict__ A, int64_t lda, int64_t n,
+                                                           const c64* __restrict__ invL, c64* __restrict__ invU,
+                                                           int64_t ib) {
+  __shared__ c64 t[32][33];
+  const int64_t b = blockIdx.z, r0 = (int64_t)blockIdx.y * 32, c0 = (int64_t)blockIdx.x * 32;
+  const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+  for (int q = y; q < 32; q += 8) t[q][x] = invL[(b * ib + c0 + q) * ib + r0 + x];
+  __syncthreads();
+  const int64_t g = b * ib + c0 + x;
+  const c64 d = g < n ? cinv(A[g * lda + g]) : c64{1.f, 0.f};
+  for (int q = y; q < 32; q += 8) invU[(b * ib + r0 + q) * ib + c0 + x] = cmul(t[x][q], d);
+}
+
+void transpose_block_inverses(Context& ctx, const c64* A, int64_t n, int64_t lda, const c64* invL, c64* invU) {
+  const int64_t ib = inv_block(n), nb = (n + ib - 1) / ib;
+  hipLaunchKernelGGL(k_inverse_transpose, dim3((unsigned)(ib / 32), (unsigned)(ib / 32), (unsigned)nb), dim3(256), 0,
+                     ctx.stream, A, lda, n, invL, invU, ib);
+  FOSB_LAUNCH_CHECK();
+}
+
 // B <- T^{-1} B for rows k0 .. k0 + n of the unit lower (LOWER) or upper factor,
 // k0 a multiple of NL: halves split at multiples of NL, coupled by a GEMM; a
 // leaf block is X = inv_b B_b, a product into tmp (NL x nrhs) copied back.
@@ -1899,38 +1937,38 @@ static void trsm_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>*
   }
 }
 
-// X <- T^{-1} B out of place, same splits: B (rows k0 .. k0 + n) is consumed
+// X <- T^{-1} B out of place, halves split at multiples of ib: B (rows k0 .. k0 + n) is consumed
 // as workspace, each leaf product writes its block of X directly, and the
 // coupling products read the solved part of X.  No copies.
 template <typename T, bool LOWER>
-static void trsm_inv_oop(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* inv, int64_t k0, int64_t n,
-                         cplx<T>* B, int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
+static void trsm_inv_oop(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* inv, int64_t ib, int64_t k0,
+                         int64_t n, cplx<T>* B, int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
   if (n <= 0 || nrhs <= 0) return;
-  if (n <= NL) {
-    gemm<T>(ctx, n, nrhs, n, 1.0, inv + (k0 / NL) * NL * NL, NL, B, ldb, 0.0, X, ldx);
+  if (n <= ib) {
+    gemm<T>(ctx, n, nrhs, n, 1.0, inv + k0 * ib, ib, B, ldb, 0.0, X, ldx);
     return;
   }
-  const int64_t n1 = NL * (((n + NL - 1) / NL + 1) / 2);
+  const int64_t n1 = ib * (((n + ib - 1) / ib + 1) / 2);
   if (LOWER) {
-    trsm_inv_oop<T, true>(ctx, A, lda, inv, k0, n1, B, ldb, X, ldx, nrhs);
+    trsm_inv_oop<T, true>(ctx, A, lda, inv, ib, k0, n1, B, ldb, X, ldx, nrhs);
     gemm<T>(ctx, n - n1, nrhs, n1, -1.0, A + (k0 + n1) * lda + k0, lda, X, ldx, 1.0, B + n1 * ldb, ldb);
-    trsm_inv_oop<T, true>(ctx, A, lda, inv, k0 + n1, n - n1, B + n1 * ldb, ldb, X + n1 * ldx, ldx, nrhs);
+    trsm_inv_oop<T, true>(ctx, A, lda, inv, ib, k0 + n1, n - n1, B + n1 * ldb, ldb, X + n1 * ldx, ldx, nrhs);
   } else {
-    trsm_inv_oop<T, false>(ctx, A, lda, inv, k0 + n1, n - n1, B + n1 * ldb, ldb, X + n1 * ldx, ldx, nrhs);
+    trsm_inv_oop<T, false>(ctx, A, lda, inv, ib, k0 + n1, n - n1, B + n1 * ldb, ldb, X + n1 * ldx, ldx, nrhs);
     gemm<T>(ctx, n1, nrhs, n - n1, -1.0, A + k0 * lda + (k0 + n1), lda, X + n1 * ldx, ldx, 1.0, B, ldb);
-    trsm_inv_oop<T, false>(ctx, A, lda, inv, k0, n1, B, ldb, X, ldx, nrhs);
+    trsm_inv_oop<T, false>(ctx, A, lda, inv, ib, k0, n1, B, ldb, X, ldx, nrhs);
   }
 }
 
 template <typename T>
 void trsm_lower_unit_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t n, cplx<T>* B,
                          int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
-  trsm_inv_oop<T, true>(ctx, A, lda, invL, 0, n, B, ldb, X, ldx, nrhs);
+  trsm_inv_oop<T, true>(ctx, A, lda, invL, inv_block(n), 0, n, B, ldb, X, ldx, nrhs);
 }
 template <typename T>
 void trsm_upper_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t n, cplx<T>* B,
                     int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
-  trsm_inv_oop<T, false>(ctx, A, lda, invU, 0, n, B, ldb, X, ldx, nrhs);
+  trsm_inv_oop<T, false>(ctx, A, lda, invU, inv_block(n), 0, n, B, ldb, X, ldx, nrhs);
 }
 
 template void upper_block_inverses<float>(Context&, const c64*, int64_t, int64_t, const c64*, c64*);

@@ -222,3 +222,25 @@ def test_adjoint_solves_of_symmetric_levels(fz, nrhs):
         lv.solve_adjoint(X)
         R = torch.matmul(A.mH.contiguous(), X) - B
         assert float((R.norm(dim=0) / (A.norm() * X.norm(dim=0))).max()) < 1e-9
+
+
+@pytest.mark.parametrize("nu", [5, 6, 7, 9])
+@pytest.mark.parametrize("nrhs", [1, 33])
+def test_block_inverses_at_their_edges(nu, nrhs):
+    """Mixed solves with leaf inverses of 256 rows (N = 750) and of 1024 rows with
+    short last blocks (N = 1080: 56 rows, 1470: 446 rows; pivoted; 2430: 382 rows,
+    symmetric).  Residual as in the tests above; at most three sweeps, as a wrong
+    inverse would show in the contraction first (FP32 factors: 1e-4 or less a sweep)."""
+    import torch
+    from paper_2308_01457_amd import fosb
+    ctx = fosb.Context(0)
+    m = fosb.Mesh(ctx, *workloads.ellipsoid(nu, (0.8, 1.0, 1.2)))
+    Z = fosb.assemble(ctx, m, 2.0)
+    lv = fosb.Level(ctx, m, 2.0, Z, fosb.MIXED)
+    for adjoint in (False, True):
+        B = _rhs(torch, ctx, m.n_edges, nrhs=nrhs, seed=nu)
+        X, st = B.clone(), fosb.Stats()
+        (lv.solve_adjoint if adjoint else lv.solve)(X, st)
+        R = torch.matmul(Z.mH.contiguous() if adjoint else Z, X) - B
+        assert float((R.norm(dim=0) / (Z.norm() * X.norm(dim=0))).max()) < 1e-9
+        assert st.ir_sweeps <= 3
