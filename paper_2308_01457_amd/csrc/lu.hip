@@ -456,6 +456,7 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 template <typename FA, typename FB>
 __device__ __forceinline__ void tile_product(int K, int lane, FA fa, FB fb, f4v& re, f4v& im) {
   f4v t1{0, 0, 0, 0}, t2{0, 0, 0, 0}, t3{0, 0, 0, 0};
+#pragma unroll 4
   for (int k = 0; k < K; k += 4) {
     const c64 a = fa(lane & 15, k + (lane >> 4)), b = fb(k + (lane >> 4), lane & 15);
     t1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.re, b.re, t1, 0, 0, 0);
@@ -616,32 +617,30 @@ __global__ __launch_bounds__(512) void k_sym_diag(c64* __restrict__ A, int64_t l
 // workgroup, all 128 columns, so a row's entries are read before any is
 // written).  Uinv is upper triangular: columns 32 j .. take K = 32 (j + 1).
 // Bound by the round trip of the block column through memory.
-__global__ __launch_bounds__(256) void k_sym_mul(c64* X, int64_t ldx, int64_t m, const c64* __restrict__ Uinv) {
+__global__ __launch_bounds__(512) void k_sym_mul(c64* X, int64_t ldx, int64_t m, const c64* __restrict__ Uinv) {
   __shared__ c64 S[64 * kSymLd];
   __shared__ c64 B[kSymBlk * (NB + 1)];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   raise_wave_priority();
   const int64_t r0 = (int64_t)blockIdx.x * 64;
-  for (int e = tid; e < 64 * kSymBlk; e += 256) {
+  for (int e = tid; e < 64 * kSymBlk; e += 512) {
     const int r = e / kSymBlk, c = e % kSymBlk;
     S[r * kSymLd + c] = r0 + r < m ? X[(r0 + r) * ldx + c] : c64{0.f, 0.f};
   }
   for (int j = 0; j < kSymBlk / NB; ++j) {
     __syncthreads();   // S is loaded; the previous columns' products have read B
-    for (int e = tid; e < NB * (j + 1) * NB; e += 256)
+    for (int e = tid; e < NB * (j + 1) * NB; e += 512)
       B[e / NB * (NB + 1) + e % NB] = Uinv[e / NB * kSymBlk + NB * j + e % NB];
     __syncthreads();
+    const int q = 16 * (wave & 3), h = 16 * (wave >> 2);   // the wavefront's 16 rows and 16 of the 32 columns
+    f4v re, im;
+    tile_product(
+        NB * (j + 1), lane, [&](int mm, int kk) { return S[(q + mm) * kSymLd + kk]; },
+        [&](int kk, int n) { return B[kk * (NB + 1) + h + n]; }, re, im);
 #pragma unroll
-    for (int h = 0; h < NB; h += 16) {
-      f4v re, im;
-      tile_product(
-          NB * (j + 1), lane, [&](int mm, int kk) { return S[(16 * wave + mm) * kSymLd + kk]; },
-          [&](int kk, int n) { return B[kk * (NB + 1) + h + n]; }, re, im);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t r = r0 + 16 * wave + 4 * (lane >> 4) + v;
-        if (r < m) X[r * ldx + NB * j + h + (lane & 15)] = c64{re[v], im[v]};
-      }
+    for (int v = 0; v < 4; ++v) {
+      const int64_t r = r0 + q + 4 * (lane >> 4) + v;
+      if (r < m) X[r * ldx + NB * j + h + (lane & 15)] = c64{re[v], im[v]};
     }
   }
 }
@@ -1178,7 +1177,7 @@ static void sym_block(LuRun<float>& R, int64_t k, int64_t w) {
       FOSB_LAUNCH_CHECK();
       if (m <= 0) continue;
       // rows remain below only after a full block: the last block ends the matrix
-      hipLaunchKernelGGL(k_sym_mul, dim3((unsigned)((m + 63) / 64)), dim3(256), 0, s, A + k1 * lda + kk, lda, m, R.top);
+      hipLaunchKernelGGL(k_sym_mul, dim3((unsigned)((m + 63) / 64)), dim3(512), 0, s, A + k1 * lda + kk, lda, m, R.top);
       FOSB_LAUNCH_CHECK();
     }
     if (rest <= 0) continue;
