@@ -441,8 +441,10 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 // Panels of 16 columns: up to three wavefronts factor the 16 x 16 diagonal tile
 // in registers, one row per lane, each on its own copy, with 48 rows below it
 // in the other lanes (so the multipliers need no inverse); the lower tiles to
-// the right are updated by L D L^T on the matrix cores.  The chain of dependent
-// steps is what bounds it.  In place of four 32-column panels with their own
+// the right are updated by L D L^T on the matrix cores, those of the next panel
+// before it is factored, the rest beside it.  The chain of dependent steps is what
+// bounds it: 60 us, of which the panels' 128 columns take 33 (93 us with branches in the
+// steps, one load in flight and no overlap).  In place of four 32-column panels with their own
 // root, multiplier, triangular-leaf and product launches, a 128-column step is
 // this launch, one product for the rows below, U12 and one product for the rest
 // of the block column.
@@ -451,13 +453,13 @@ constexpr int kSymLd = kSymBlk + 1;
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
-// 16 x 16 tile of a complex product over K (a multiple of 4) on the FP32 matrix
+// 16 x 16 tile of a complex product over k0 .. k1 (a multiple of 16 apart) on the FP32 matrix
 // instruction (3M): fa(m, k), fb(k, n); lane l receives rows 4 (l / 16) + v, column l % 16.
 template <typename FA, typename FB>
-__device__ __forceinline__ void tile_product(int K, int lane, FA fa, FB fb, f4v& re, f4v& im) {
+__device__ __forceinline__ void tile_product(int k0, int k1, int lane, FA fa, FB fb, f4v& re, f4v& im) {
   f4v t1{0, 0, 0, 0}, t2{0, 0, 0, 0}, t3{0, 0, 0, 0};
 #pragma unroll 4
-  for (int k = 0; k < K; k += 4) {
+  for (int k = k0; k < k1; k += 4) {
     const c64 a = fa(lane & 15, k + (lane >> 4)), b = fb(k + (lane >> 4), lane & 15);
     t1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.re, b.re, t1, 0, 0, 0);
     t2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.im, b.im, t2, 0, 0, 0);
@@ -477,83 +479,122 @@ __global__ __launch_bounds__(512) void k_sym_diag(c64* __restrict__ A, int64_t l
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   raise_wave_priority();
   c64* Ab = A + k * lda + k;
-  // lower tiles; identity beyond w
-  for (int e = tid; e < kSymBlk * kSymBlk; e += 512) {
-    const int r = e / kSymBlk, c = e % kSymBlk;
-    if ((c >> 4) <= (r >> 4))
-      T[r * kSymLd + c] = (r < w && c < w) ? Ab[(int64_t)r * lda + c] : c64{r == c ? 1.f : 0.f, 0.f};
+  // lower tiles (the upper ones are not read); identity beyond w.  16 loads of
+  // a thread in flight: one at a time, the block's 32 round trips took 17 us.
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    c64 v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int e = (16 * h + q) * 512 + tid, r = e / kSymBlk, c = e % kSymBlk;
+      v[q] = Ab[(int64_t)min(r, w - 1) * lda + min(c, w - 1)];
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int e = (16 * h + q) * 512 + tid, r = e / kSymBlk, c = e % kSymBlk;
+      T[r * kSymLd + c] = r < w && c < w ? v[q] : c64{r == c ? 1.f : 0.f, 0.f};
+    }
   }
   if (tid == 0) szc = kSymBlk;
   if (tid < (w + NB - 1) / NB) moves[tid * (1 + 4 * NB)] = 0;
   __syncthreads();
-  for (int p = 0; p < kSymBlk / 16; ++p) {
-    const int b = 16 * p;
-    const bool works = wave < 3 && (wave == 0 || b + 16 + 48 * wave < kSymBlk);
-    const int row = lane < 16 ? b + lane : b + 48 * wave + lane;   // b + 16 + 48 wave + (lane - 16)
-    const bool live = works && row < kSymBlk;
-    c64 a[16];
+  constexpr int NP = kSymBlk / 16;   // panels
+  c64 a[16];
+  // panel p: up to three wavefronts, rows in lanes (see above); the diagonal tile's
+  // copies are taken before the first wavefront stores it
+  auto panel_row = [&](int b) { return lane < 16 ? b + lane : b + 48 * wave + lane; };
+  auto works = [&](int b) { return wave == 0 || (wave < 3 && b + 16 + 48 * wave < kSymBlk); };
+  auto fetch = [&](int b) {
+    const bool live = works(b) && panel_row(b) < kSymBlk;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) a[c] = live ? T[row * kSymLd + b + c] : c64{0.f, 0.f};
-    __syncthreads();   // every wavefront has its copy of the diagonal tile before the first one stores it
-    if (works) {
-      int zc = -1;
+    for (int c = 0; c < 16; ++c) a[c] = live ? T[panel_row(b) * kSymLd + b + c] : c64{0.f, 0.f};
+  };
+  auto factor = [&](int b) {
+    // No branch in the steps, and a step updates the next pivot's column
+    // first: the reciprocal of that pivot overlaps the other columns' updates.
+    c64 pi = cinv_panel(c64{lane_value(a[0].re, 0), lane_value(a[0].im, 0)});
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const c64 pv{lane_value(a[j].re, j), lane_value(a[j].im, j)};
-        if (zc < 0 && pv.re == 0.f && pv.im == 0.f) zc = j;
-        const c64 pi = cinv_panel(pv);
-        if (wave == 0 && lane == j) {
-          d[b + j] = pv;
-          rd[b + j] = pi;
-        }
-        // the multiplier, zero on the rows at and above the pivot
-        const bool below = lane > j;
-        const c64 l = below ? cmul(a[j], pi) : c64{0.f, 0.f};
-        if (below) a[j] = l;
+    for (int j = 0; j < 16; ++j) {
+      // the multiplier, zero on the rows at and above the pivot
+      const bool below = lane > j;
+      const c64 m = cmul(a[j], pi);
+      const float lr = below ? m.re : 0.f, li = below ? m.im : 0.f;
 #pragma unroll
-        for (int c = j + 1; c < 16; ++c) {
-          const c64 u{lane_value(a[c].re, j), lane_value(a[c].im, j)};
-          a[c].re -= l.re * u.re - l.im * u.im;
-          a[c].im -= l.re * u.im + l.im * u.re;
-        }
+      for (int c = j + 1; c < 16; ++c) {
+        const float ur = lane_value(a[c].re, j), ui = lane_value(a[c].im, j);
+        a[c].re = fmaf(-lr, ur, fmaf(li, ui, a[c].re));
+        a[c].im = fmaf(-lr, ui, fmaf(-li, ur, a[c].im));
+        if (c == j + 1) pi = cinv_panel(c64{lane_value(a[c].re, c), lane_value(a[c].im, c)});
       }
-      if (live && (lane >= 16 || wave == 0)) {   // the diagonal tile keeps the multipliers below its diagonal
-#pragma unroll
-        for (int c = 0; c < 16; ++c)
-          if (lane >= 16 || c < lane) T[row * kSymLd + b + c] = a[c];
-      }
-      if (wave == 0 && lane == 0 && zc >= 0) atomicMin(&szc, b + zc);
+      a[j].re = below ? m.re : a[j].re;
+      a[j].im = below ? m.im : a[j].im;
     }
-    __syncthreads();
-    // lower tiles (I, J), I >= J > p:  T_IJ -= L_I D L_J^T
-    const int q = kSymBlk / 16 - 1 - p;
-    for (int t = wave; t < q * (q + 1) / 2; t += 8) {
-      int i = 0, off = t;
-      while (off > i) off -= ++i;   // row i holds tiles 0 .. i
-      const int ri = b + 16 + 16 * i, rj = b + 16 + 16 * off;
-      f4v re, im;
-      tile_product(
-          16, lane, [&](int m, int kk) { return T[(ri + m) * kSymLd + b + kk]; },
-          [&](int kk, int n) { return cmul(d[b + kk], T[(rj + n) * kSymLd + b + kk]); }, re, im);
+    if (wave == 0) {   // lane j < 16 holds pivot j in its column j
+      c64 pv{1.f, 0.f};
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        c64& o = T[(ri + 4 * (lane >> 4) + v) * kSymLd + rj + (lane & 15)];
-        o.re -= re[v];
-        o.im -= im[v];
+      for (int c = 0; c < 16; ++c) {
+        pv.re = lane == c ? a[c].re : pv.re;
+        pv.im = lane == c ? a[c].im : pv.im;
+      }
+      if (lane < 16) {
+        d[b + lane] = pv;
+        rd[b + lane] = cinv_panel(pv);
+      }
+      const unsigned long long zero = __ballot(pv.re == 0.f && pv.im == 0.f);
+      if (lane == 0 && zero) atomicMin(&szc, b + __ffsll(zero) - 1);
+    }
+    if (panel_row(b) < kSymBlk && (lane >= 16 || wave == 0)) {   // the diagonal tile keeps the multipliers below its diagonal
+#pragma unroll
+      for (int c = 0; c < 16; ++c)
+        if (lane >= 16 || c < lane) T[panel_row(b) * kSymLd + b + c] = a[c];
+    }
+  };
+  // T_IJ -= L_I D L_J^T for the panel at b
+  auto update = [&](int b, int ti, int tj) {
+    const int ri = 16 * ti, rj = 16 * tj;
+    f4v re, im;
+    tile_product(
+        0, 16, lane, [&](int m, int kk) { return T[(ri + m) * kSymLd + b + kk]; },
+        [&](int kk, int n) { return cmul(d[b + kk], T[(rj + n) * kSymLd + b + kk]); }, re, im);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      c64& o = T[(ri + 4 * (lane >> 4) + v) * kSymLd + rj + (lane & 15)];
+      o.re -= re[v];
+      o.im -= im[v];
+    }
+  };
+  fetch(0);
+  __syncthreads();
+  if (works(0)) factor(0);
+  __syncthreads();
+  // Stage p: the tiles of panel p + 1 first; then three wavefronts factor it while
+  // the others update the tiles right of it.
+  for (int p = 0; p + 1 < NP; ++p) {
+    const int b = 16 * p;
+    if (wave < NP - 1 - p) update(b, p + 1 + wave, p + 1);
+    __syncthreads();
+    if (wave < 3) fetch(b + 16);
+    __syncthreads();
+    if (works(b + 16)) factor(b + 16);
+    if (wave >= 3) {
+      const int q = NP - 2 - p;
+      for (int t = wave - 3; t < q * (q + 1) / 2; t += 5) {
+        int i = 0, off = t;
+        while (off > i) off -= ++i;   // row i holds tiles 0 .. i
+        update(b, p + 2 + i, p + 2 + off);
       }
     }
     __syncthreads();
   }
   // L \ U to memory
-  for (int e = tid; e < kSymBlk * kSymBlk; e += 512) {
-    const int r = e / kSymBlk, c = e % kSymBlk;
-    if (r < w && c < w)
-      Ab[(int64_t)r * lda + c] = r > c ? T[r * kSymLd + c] : (r == c ? d[r] : cmul(d[r], T[c * kSymLd + r]));
+#pragma unroll 8
+  for (int q = 0; q < kSymBlk * kSymBlk / 512; ++q) {
+    const int e = q * 512 + tid, r = e / kSymBlk, c = e % kSymBlk;
+    const c64 v = T[max(r, c) * kSymLd + min(r, c)], dr = d[r], u = cmul(dr, v);
+    if (r < w && c < w) Ab[(int64_t)r * lda + c] = r > c ? v : (r == c ? dr : u);
   }
-  if (tid == 0 && szc < w) atomicMin(info, (int)(k + szc + 1));
-  // L^{-1} in place: the 16 x 16 diagonal tiles (wavefront t inverts tile t,
-  // lane c its column c), then pairs of blocks of 16, 32 and 64:
-  // L21 <- -L22^{-1} (L21 L11^{-1}), the inner product kept in the upper tiles
+  // L^{-1} in place: the 16 x 16 diagonal tiles (wavefront t inverts tile t, lane c
+  // its column c; the barrier keeps a step's loads from being moved before the last one's)
   {
     const int b = 16 * wave, c = lane & 15;
     c64 x[16];
@@ -563,26 +604,30 @@ __global__ __launch_bounds__(512) void k_sym_diag(c64* __restrict__ A, int64_t l
 #pragma unroll
       for (int j = 0; j < i; ++j) {
         const c64 l = T[(b + i) * kSymLd + b + j];
-        v.re -= l.re * x[j].re - l.im * x[j].im;
-        v.im -= l.re * x[j].im + l.im * x[j].re;
+        v.re = fmaf(-l.re, x[j].re, fmaf(l.im, x[j].im, v.re));
+        v.im = fmaf(-l.re, x[j].im, fmaf(-l.im, x[j].re, v.im));
       }
       x[i] = v;
+      if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
+    __syncthreads();   // the stores above have read the tiles
     if (lane < 16) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) T[(b + i) * kSymLd + b + c] = x[i];
     }
   }
   __syncthreads();
+  if (tid == 0 && szc < w) atomicMin(info, (int)(k + szc + 1));
+  // then pairs of blocks of 16, 32 and 64: L21 <- -L22^{-1} (L21 L11^{-1}), the
+  // inner product kept in the upper tiles
   for (int h = 16; h < kSymBlk; h *= 2) {   // merge blocks of h columns in pairs
     const int nt = h / 16, tiles = nt * nt, pairs = kSymBlk / (2 * h);
     for (int t = wave; t < pairs * tiles; t += 8) {   // W = L21 L11^{-1} into the pair's upper block
-      const int o = t / tiles * 2 * h, i = t % tiles / nt * 16, j = t % nt * 16;
+      const int o = t / tiles * 2 * h, i = t % tiles / nt * 16, j = (t < 8 ? t % nt : nt - 1 - t % nt) * 16;
       f4v re, im;
       tile_product(
-          h, lane, [&](int m, int kk) { return T[(o + h + i + m) * kSymLd + o + kk]; },
-          [&](int kk, int n) { return kk < j ? c64{0.f, 0.f} : T[(o + kk) * kSymLd + o + j + n]; }, re, im);
+          j, h, lane, [&](int m, int kk) { return T[(o + h + i + m) * kSymLd + o + kk]; },
+          [&](int kk, int n) { return T[(o + kk) * kSymLd + o + j + n]; }, re, im);
 #pragma unroll
       for (int v = 0; v < 4; ++v)
         T[(o + i + 4 * (lane >> 4) + v) * kSymLd + o + h + j + (lane & 15)] = c64{re[v], im[v]};
@@ -592,8 +637,7 @@ __global__ __launch_bounds__(512) void k_sym_diag(c64* __restrict__ A, int64_t l
       const int o = t / tiles * 2 * h, i = t % tiles / nt * 16, j = t % nt * 16;
       f4v re, im;
       tile_product(
-          h, lane,
-          [&](int m, int kk) { return kk >= i + 16 ? c64{0.f, 0.f} : T[(o + h + i + m) * kSymLd + o + h + kk]; },
+          0, i + 16, lane, [&](int m, int kk) { return T[(o + h + i + m) * kSymLd + o + h + kk]; },
           [&](int kk, int n) { return T[(o + kk) * kSymLd + o + h + j + n]; }, re, im);
 #pragma unroll
       for (int v = 0; v < 4; ++v)
@@ -602,13 +646,19 @@ __global__ __launch_bounds__(512) void k_sym_diag(c64* __restrict__ A, int64_t l
     __syncthreads();
   }
   // outputs: Uinv[i][j] = L^{-1}[j][i] / d_j for i <= j
-  for (int e = tid; e < kSymBlk * kSymBlk; e += 512) {
-    const int r = e / kSymBlk, c = e % kSymBlk;
-    Uinv[e] = r <= c ? cmul(T[c * kSymLd + r], rd[c]) : c64{0.f, 0.f};
-    if (r / NB == c / NB && r / NB * NB < w) {
-      const int64_t o = (int64_t)(r / NB) * NB * NB + r % NB * NB + c % NB;
-      dinvL[o] = r >= c ? T[r * kSymLd + c] : c64{0.f, 0.f};
-      dinvU[o] = r <= c ? cmul(T[c * kSymLd + r], rd[c]) : c64{0.f, 0.f};
+#pragma unroll 16
+  for (int q = 0; q < kSymBlk * kSymBlk / 512; ++q) {
+    const int e = q * 512 + tid, r = e / kSymBlk, c = e % kSymBlk;
+    const c64 u = cmul(T[max(r, c) * kSymLd + min(r, c)], rd[c]);
+    Uinv[e] = r <= c ? u : c64{0.f, 0.f};
+  }
+#pragma unroll
+  for (int q = 0; q < kSymBlk * NB / 512; ++q) {   // the 32 x 32 diagonal blocks
+    const int e = q * 512 + tid, r = e / NB, c = r / NB * NB + e % NB;
+    const c64 v = T[max(r, c) * kSymLd + min(r, c)];
+    if (r / NB * NB < w) {
+      dinvL[e] = r >= c ? v : c64{0.f, 0.f};
+      dinvU[e] = r <= c ? cmul(v, rd[c]) : c64{0.f, 0.f};
     }
   }
 }
@@ -635,7 +685,7 @@ __global__ __launch_bounds__(512) void k_sym_mul(c64* X, int64_t ldx, int64_t m,
     const int q = 16 * (wave & 3), h = 16 * (wave >> 2);   // the wavefront's 16 rows and 16 of the 32 columns
     f4v re, im;
     tile_product(
-        NB * (j + 1), lane, [&](int mm, int kk) { return S[(q + mm) * kSymLd + kk]; },
+        0, NB * (j + 1), lane, [&](int mm, int kk) { return S[(q + mm) * kSymLd + kk]; },
         [&](int kk, int n) { return B[kk * (NB + 1) + h + n]; }, re, im);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
