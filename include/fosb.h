@@ -15,10 +15,13 @@
  *     the enqueued work.  "host" pointers are read during the call only.
  *   - Handles (context, mesh, level) are owned by the library until *_destroy.
  *     The library allocates its own O(N) tables (a MIXED level also keeps the
- *     inverses of the 256 x 256 diagonal blocks of its factors, 4 KiB per
- *     unknown) and work buffers (O(N*nrhs) for solves, up to 2 GiB for the
- *     assembly's two column bands) on the context's device; O(N^2) matrices are
- *     always caller buffers.  These device blocks come from a caching pool
+ *     inverses of the 1024 x 1024 diagonal blocks of its factors, 16 KiB per
+ *     unknown, or below N = 2048 of the 256 x 256 ones, 4 KiB) and work buffers
+ *     (O(N*nrhs) for solves; about 1 GiB for the assembly's two bands, 2 GiB where a
+ *     level keeps no complex128 matrix; 256 MiB for a right-hand-side correlation;
+ *     for the packed operands of wide complex64 products 12 bytes an entry, at most
+ *     1 GiB each in solves and 9 KiB per row in a symmetric factorisation) on the
+ *     context's device; O(N^2) matrices are always caller buffers.  These device blocks come from a caching pool
  *     per context (and per stream the context creates): a released block is
  *     kept and handed out again, so once a pass has run, repeating it on
  *     shapes of the same sizes makes no device allocation and no hipFree
@@ -238,8 +241,8 @@ fosb_status fosb_assemble_pmchwt(fosb_context* ctx, const fosb_mesh* mesh, doubl
  *   precision MIXED: Z is kept read-only for FP64 refinement residuals and
  *                    must outlive the level; Zlow (device complex64, N x N,
  *                    ldzlow) receives the FP32 LU factors, which the level's
- *                    solves apply through the inverses of their 256 x 256
- *                    diagonal blocks (kept by the level).
+ *                    solves apply through the inverses of their diagonal
+ *                    blocks (kept by the level: 1024 rows, 256 below N = 2048).
  *                    Z may be NULL: the level then assembles the matrix in FP64
  *                    column bands straight into Zlow (rounded to complex64) and
  *                    re-assembles FP64 bands of Z for every refinement residual

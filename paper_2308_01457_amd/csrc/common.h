@@ -446,8 +446,9 @@ constexpr int kInvBlock = 256;
 // Rows of a leaf of those solves.  A narrow solve is a chain of launches, two
 // per leaf (N = 7680, one column: 59 products a factor with 256 rows, 15 with
 // 1024; a refined solve 2.0 -> 1.25 ms; 17 columns 11.5 -> 4.4), and a wide one runs its small products
-// far below the large ones' rate.  The inverses take 8 KB a row and factor.
-inline int64_t inv_block(int64_t n) { return n > 1024 ? 1024 : kInvBlock; }
+// far below the large ones' rate.  The inverses take 8 KB a row and factor; a level
+// below 2048 keeps the small ones (of two blocks of 1024 rows one would be mostly padding).
+inline int64_t inv_block(int64_t n) { return n >= 2048 ? 1024 : kInvBlock; }
 inline int64_t inv_bytes(int64_t n) {
   const int64_t ib = inv_block(n);
   return (n + ib - 1) / ib * ib * ib * (int64_t)sizeof(c64);
@@ -501,7 +502,7 @@ void incident_rhs(hipStream_t s, const Mesh& m, double k, const double* dirs_dev
 void quad_nodes(hipStream_t s, const Mesh& m, double* qx);
 // u: first-moment coefficients of one direction, u[e * ustride]
 void rhs_weights(hipStream_t s, const Mesh& m, double k, int field, const c128* u, int64_t ustride, c128* W);
-// C_d = Wgt_l1(dir0 + d) K Wgt_l2(dir0 + d)^H for d < nd at C + d * dstride (row stride ldc); uses c.scratch[2]
+// C_d = Wgt_l1(dir0 + d) K Wgt_l2(dir0 + d)^H for d < nd at C + d * dstride (row stride ldc)
 void rhs_correlation(Context& c, const Level& l1, const Level& l2, const fosb_cov& cov, int64_t dir0, int64_t nd,
                      c128* C, int64_t ldc, int64_t dstride);
 // PMCHWT right-hand side b = [e; h] (2N x ndir, row stride ndir): e[m] = int phi_m . p e^{ik d.x},

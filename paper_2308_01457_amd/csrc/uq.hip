@@ -374,7 +374,7 @@ __global__ __launch_bounds__(256) void k_cov_gather(BandEdges rows, int i1, cons
 }
 
 // Row triangles in bands whose local entries, for up to 16 incidences, fill
-// kCovBandBytes of c's scratch[2] (free until the pair's solve).
+// kCovBandBytes.
 void rhs_correlation(Context& c, const Level& l1, const Level& l2, const fosb_cov& cov, int64_t dir0, int64_t nd,
                      c128* C, int64_t ldc, int64_t dstride) {
   constexpr int64_t kCovBandBytes = (int64_t)256 << 20, kChunk = 16;
@@ -386,8 +386,8 @@ void rhs_correlation(Context& c, const Level& l1, const Level& l2, const fosb_co
     const int dn = (int)std::min(kChunk, nd - d0);
     const int64_t row_bytes = 9LL * nt2 * dn * (int64_t)sizeof(c128);
     const int w = (int)std::min<int64_t>({nt1, 4 * 65535, std::max<int64_t>(4, kCovBandBytes / row_bytes / 4 * 4)});
-    c.scratch[2].reserve((size_t)w * row_bytes);
-    c128* P = c.scratch[2].as<c128>();
+    DevBuf band((size_t)w * row_bytes);   // reused in the stream's order once released
+    c128* P = band.as<c128>();
     const int64_t ldp = 3LL * nt2, pstride = 3LL * w * ldp;
     const CovSide A{m1.nrm.as<double>(), l1.qx.as<double>(), l1.W.as<c128>() + (dir0 + d0) * nt1 * 18, nt1};
     const CovSide B{m2.nrm.as<double>(), l2.qx.as<double>(), l2.W.as<c128>() + (dir0 + d0) * nt2 * 18, nt2};

@@ -224,19 +224,19 @@ def test_adjoint_solves_of_symmetric_levels(fz, nrhs):
         assert float((R.norm(dim=0) / (A.norm() * X.norm(dim=0))).max()) < 1e-9
 
 
-@pytest.mark.parametrize("nu", [5, 6, 7, 9])
+@pytest.mark.parametrize("nu, pivoting", [(8, 0), (9, 0), (9, 1), (10, 0), (11, 1)])
 @pytest.mark.parametrize("nrhs", [1, 33])
-def test_block_inverses_at_their_edges(nu, nrhs):
-    """Mixed solves with leaf inverses of 256 rows (N = 750) and of 1024 rows with
-    short last blocks (N = 1080: 56 rows, 1470: 446 rows; pivoted; 2430: 382 rows,
-    symmetric).  Residual as in the tests above; at most three sweeps, as a wrong
+def test_block_inverses_at_their_edges(nu, pivoting, nrhs):
+    """Mixed solves with leaf inverses of 256 rows (N = 1920) and of 1024 rows with
+    short last blocks (N = 2430: 382 rows, 3000: 952, 3630: 558), symmetric and pivoted
+    factors.  Residual as in the tests above; at most three sweeps, as a wrong
     inverse would show in the contraction first (FP32 factors: 1e-4 or less a sweep)."""
     import torch
     from paper_2308_01457_amd import fosb
     ctx = fosb.Context(0)
     m = fosb.Mesh(ctx, *workloads.ellipsoid(nu, (0.8, 1.0, 1.2)))
     Z = fosb.assemble(ctx, m, 2.0)
-    lv = fosb.Level(ctx, m, 2.0, Z, fosb.MIXED)
+    lv = fosb.Level(ctx, m, 2.0, Z, fosb.MIXED, opts=fosb.opts_default(lu_pivoting=pivoting))
     for adjoint in (False, True):
         B = _rhs(torch, ctx, m.n_edges, nrhs=nrhs, seed=nu)
         X, st = B.clone(), fosb.Stats()
