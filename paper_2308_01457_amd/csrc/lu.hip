@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "common.h"
 
@@ -89,94 +90,130 @@ __device__ __forceinline__ unsigned pivot_key(cplx<float> v) {
 }
 __device__ __forceinline__ unsigned pivot_key(cplx<double> v) {
   const double m = cabs1(v);
-  if (m == 0.0) return 1u;
   const unsigned hi = (unsigned)((unsigned long long)__double_as_longlong(m) >> 32) & 0x7fffffffu;
-  return (hi < 1u ? 1u : hi) + 1u;
+  return m == 0.0 ? 1u : (hi < 1u ? 1u : hi) + 1u;
 }
 
-// 1/a for the panel's multipliers: FP32 through the hardware reciprocal with
-// one Newton step (within an ulp or two of the exact quotient: partial
-// pivoting needs no correctly rounded multipliers), FP64 by exact division.
+// 1/a for the panel's multipliers: through the hardware reciprocal with one
+// Newton step (FP32) or two (FP64), within an ulp or two of the exact quotient:
+// partial pivoting needs no correctly rounded multipliers.
 __device__ __forceinline__ float rcp_nr(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
   return r * (2.0f - x * r);
 }
 __device__ __forceinline__ cplx<float> cinv_panel(cplx<float> a) {
   const float s = fabsf(a.re) + fabsf(a.im);
-  if (s == 0.0f) return cplx<float>{0.0f, 0.0f};
-  const float rs = rcp_nr(s);
+  const float rs = rcp_nr(s == 0.0f ? 1.0f : s);
   const float ar = a.re * rs, ai = a.im * rs;
-  const float t = rcp_nr(ar * ar + ai * ai) * rs;
-  return cplx<float>{ar * t, -ai * t};
+  const float t = rcp_nr(s == 0.0f ? 1.0f : ar * ar + ai * ai) * rs;
+  return cplx<float>{ar * t, -ai * t};   // zero of zero
 }
-__device__ __forceinline__ cplx<double> cinv_panel(cplx<double> a) { return cinv(a); }
+__device__ __forceinline__ double rcp_nr(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ __forceinline__ cplx<double> cinv_panel(cplx<double> a) {
+  const double s = fabs(a.re) + fabs(a.im);
+  const double rs = rcp_nr(s == 0.0 ? 1.0 : s);
+  const double ar = a.re * rs, ai = a.im * rs;
+  const double t = rcp_nr(s == 0.0 ? 1.0 : ar * ar + ai * ai) * rs;
+  return cplx<double>{ar * t, -ai * t};   // zero of zero
+}
+
+// Value of lane C of each 16 lanes, by the row broadcast of the data-parallel
+// primitives (all lanes active).
+template <int C>
+__device__ __forceinline__ double row_bcast(double v) {
+  return __builtin_amdgcn_update_dpp(v, v, 0x150 + C, 0xf, 0xf, true);
+}
+template <int C>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x150 + C, 0xf, 0xf, true));
+}
+
+template <int C, int E, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (C < E) {
+    f(std::integral_constant<int, C>{});
+    static_for<C + 1, E>(f);
+  }
+}
 
 // Partial-pivoting elimination of the node's rows (one row per thread, the
 // row's NB columns in registers).  The step loop is unrolled, so column j is
 // addressed statically and every row stays in place: a row chosen at step j
 // then holds L[j][0..j) (its multipliers) followed by U[j][j..].  Per step:
 // * every candidate forms its key and, speculatively, the reciprocal of its
-//   entry in column j (off the critical path: it overlaps the reduction);
-// * a wave maximum of the keys, and a ballot for the lowest lane holding it;
-// * that lane publishes the key, its row and its reciprocal; one barrier;
-// * every thread takes the largest of the wave keys (ties to the lowest
-//   wave), reads that wave's row and reciprocal, and eliminates column j.
-// Slots alternate between two buffers, so a wave entering step j+1 never
-// overwrites a slot that another wave still reads at step j.
+//   entry in column j; a wave maximum of the keys, and a ballot for the lowest lane
+//   holding it (all of it beside step j - 1's elimination of the other columns);
+// * the wave maxima go through LDS, and the largest (ties to the lowest wave) wins;
+// * the winner stores its row and reciprocal; lane l of every 16 reads entries
+//   l and 16 + l, and the elimination broadcasts them from there.
+// A store from one lane takes the LDS as long as one from 64, and a broadcast read
+// as long as 64 different ones: with each wave's nominee storing its row, and every entry
+// read as a broadcast, these took two thirds of a step (FP64, 256 rows: 44 us a node, now 33; FP32
+// 34, now 29).  A row chosen earlier is eliminated with a multiplier of zero.
 template <typename T, int NW>
 __device__ __forceinline__ int gepp_node(cplx<T> (&a)[NB], bool valid, int nvalid, int w, int tid, int& step,
-                                         cplx<T> (*prow)[NW][NB], cplx<T> (*pinv)[NW], cplx<T> (*lu)[NB + 1],
-                                         unsigned (*skey)[NW]) {
+                                         cplx<T> (&prow)[NB], cplx<T>& pinv, cplx<T> (*lu)[NB + 1],
+                                         unsigned (&skey)[NW]) {
+  static_assert(NB == 32, "two entries of the pivot row per lane");
   int zero_col = -1;
   const int steps = min(nvalid, w);
   const int lane = tid & 63, wave = tid >> 6;
   step = -1;
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
+  cplx<T> rinv;
+  int wl;   // this wave's nominee
+  auto nominate = [&](cplx<T> v) {
+    const unsigned mine = valid && step < 0 ? pivot_key(v) : 0u;
+    rinv = cinv_panel(v);
+    const unsigned wmax = wave_max_u32(mine);
+    const unsigned long long hit = __ballot(mine != 0u && mine == wmax);
+    wl = hit ? __ffsll((unsigned long long)hit) - 1 : -1;
+    return hit ? wmax : 0u;
+  };
+  unsigned best = nominate(a[0]);
+  static_for<0, NB>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
     if (j < steps) {  // uniform over the workgroup
-      const int b = j & 1;
-      const bool cand = valid && step < 0;
-      const unsigned mine = cand ? pivot_key(a[j]) : 0u;
-      const cplx<T> rinv = cinv_panel(a[j]);
-      const unsigned wmax = wave_max_u32(mine);
-      const unsigned long long hit = __ballot(mine != 0u && mine == wmax);
-      const int wl = hit ? __ffsll((unsigned long long)hit) - 1 : -1;  // this wave's nominee
-      if (lane == wl) {
-        skey[b][wave] = wmax;
-        pinv[b][wave] = rinv;
-#pragma unroll
-        for (int c = j & ~1; c < NB; ++c) prow[b][wave][c] = a[c];  // from an even column: 16-byte stores
-      } else if (wl < 0 && lane == 0) {
-        skey[b][wave] = 0u;
-      }
+      if (lane == 0) skey[wave] = best;
       __syncthreads();
       unsigned key = 0u;
       int q = 0;
 #pragma unroll
       for (int v = 0; v < NW; ++v) {
-        const unsigned o = skey[b][v];
+        const unsigned o = skey[v];
         if (o > key) {
           key = o;
           q = v;
         }
       }
-      if (wave == q && lane == wl) step = j;
-      const cplx<T> piv = prow[b][q][j];
-      const cplx<T> pr = pinv[b][q];
-      if (piv.re == T(0) && piv.im == T(0) && zero_col < 0) zero_col = j;
-      if (cand && step < 0) {
-        const cplx<T> l = cmul(a[j], pr);
-        const T nlr = -l.re, nli = -l.im;
+      const bool cand = valid && step < 0;
+      if (wave == q && lane == wl) {
+        step = j;
+        pinv = rinv;
 #pragma unroll
-        for (int c = j + 1; c < NB; ++c) {
-          const cplx<T> u = prow[b][q][c];
-          a[c].re = fma(nlr, u.re, fma(l.im, u.im, a[c].re));  // a - (l.re u.re - l.im u.im)
-          a[c].im = fma(nlr, u.im, fma(nli, u.re, a[c].im));   // a - (l.re u.im + l.im u.re)
-        }
-        a[j] = l;
+        for (int c = j & ~1; c < NB; ++c) prow[c] = a[c];  // from an even column: 16-byte stores
       }
+      __syncthreads();
+      if (key == 1u && zero_col < 0) zero_col = j;
+      const cplx<T> pr = pinv;
+      const cplx<T> u0 = prow[lane & 15], u1 = prow[16 + (lane & 15)];
+      const bool act = cand && step < 0;
+      const cplx<T> m = cmul(a[j], pr);
+      const cplx<T> l{act ? m.re : T(0), act ? m.im : T(0)};
+      static_for<j + 1, NB>([&](auto cc) {
+        constexpr int c = decltype(cc)::value;
+        const T ur = row_bcast<(c & 15)>(c < 16 ? u0.re : u1.re), ui = row_bcast<(c & 15)>(c < 16 ? u0.im : u1.im);
+        a[c].re = fma(-l.re, ur, fma(l.im, ui, a[c].re));  // a - (l.re u.re - l.im u.im)
+        a[c].im = fma(-l.re, ui, fma(-l.im, ur, a[c].im));  // a - (l.re u.im + l.im u.re)
+        if constexpr (c == j + 1) best = nominate(a[c]);   // overlaps the other columns
+      });
+      a[j].re = act ? m.re : a[j].re;
+      a[j].im = act ? m.im : a[j].im;
     }
-  }
+  });
   if (step >= 0) {
 #pragma unroll
     for (int c = 0; c < NB; ++c) lu[step][c] = a[c];
@@ -228,8 +265,8 @@ __device__ __forceinline__ void panel_root(cplx<T> (*tb)[NB + 1], const int* win
   // FP32: one column per lane and no barrier.  Lane c of the first wavefront
   // solves L x = e_c by forward substitution while lane c of the second solves
   // U y = e_c by back substitution; the factor entries are broadcast reads of
-  // the block in LDS.  FP64 keeps the Gauss-Jordan sweeps over the whole
-  // workgroup below: its per-lane columns (128 registers of x alone) ran slower.
+  // the block in LDS.  FP64's per-lane columns (128 registers of x alone) ran
+  // slower than the tiles below.
   static_assert(Node<T>::size >= 128, "the inverses take two wavefronts");
   if constexpr (sizeof(T) == 4) {
    if ((tid & 63) < NB && tid < 128) {
@@ -272,50 +309,83 @@ __device__ __forceinline__ void panel_root(cplx<T> (*tb)[NB + 1], const int* win
     }
   }
   } else {
-  // Gauss-Jordan sweeps over the whole workgroup, one barrier per step: L X = I forward,
-  // then U Y = I backward.  At backward step r every thread forms row r's
-  // scaled entries Y[r][c] / U[r][r] (r <= c < wk) itself; the threads on row
-  // r store them to invU (they are final), the others eliminate column r from
-  // rows i < r with them.  Row r of Y is not read again after step r.
-  __shared__ cplx<T> sx[NB][NB + 1];
-  for (int e = tid; e < NB * NB; e += NODE) sx[e / NB][e % NB] = cplx<T>{(e / NB == e % NB) ? T(1) : T(0), T(0)};
-  __syncthreads();
-  for (int r = 0; r < wk; ++r) {
-    // rows i > r: X[i][c] -= L[i][r] X[r][c], c <= r
-    const int cols = r + 1, rows = wk - r - 1;
-    for (int e = tid; e < rows * cols; e += NODE) {
-      const int i = r + 1 + e / cols, c = e % cols;
-      const cplx<T> l = tb[i][r], x = sx[r][c];
-      sx[i][c].re -= l.re * x.re - l.im * x.im;
-      sx[i][c].im -= l.re * x.im + l.im * x.re;
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < NB * NB; e += NODE) {  // each thread reads, then resets, its own entries
-    invL[e] = sx[e / NB][e % NB];
-    sx[e / NB][e % NB] = cplx<T>{(e / NB == e % NB) ? T(1) : T(0), T(0)};
-  }
-  __syncthreads();
-  for (int r = wk - 1; r >= 0; --r) {
-    // rows i < r: Y[i][c] -= U[i][r] (Y[r][c] / U[r][r]), c >= r
-    const int cols = wk - r;
-    const cplx<T> inv = cinv(tb[r][r]);
-    for (int e = tid; e < (r + 1) * cols; e += NODE) {
-      const int i = e / cols, c = r + e % cols;
-      const cplx<T> x = cmul(sx[r][c], inv);
-      if (i == r) {
-        invU[r * NB + c] = x;
+  // FP64: wavefront v inverts a 16 x 16 diagonal tile (v & 1) of L (v < 2) or of
+  // U, one column per lane as above; then X21 = -L22^{-1} (L21 L11^{-1}) and
+  // X12 = -U11^{-1} (U12 U22^{-1}), an entry of each per thread, the inner
+  // products in the unused halves.  (Sweeps over the whole block, one barrier a
+  // step, took 25 us of the root's 70; the root now takes 42.)
+  static_assert(Node<T>::size == 256 && NB == 32, "an entry of a 16 x 16 tile per thread");
+  __shared__ cplx<T> sx[NB][NB + 1], sy[NB][NB + 1];
+  {
+    const int t = 16 * ((tid >> 6) & 1), c = t + (tid & 15);
+    const bool live = c < wk;
+    if ((tid & 63) < 16) {
+      cplx<T> x[16];
+      if (tid < 128) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          cplx<T> v{(t + i == c) ? T(1) : T(0), T(0)};
+#pragma unroll
+          for (int j = 0; j < i; ++j) {
+            const cplx<T> l = tb[t + i][t + j];
+            v.re -= l.re * x[j].re - l.im * x[j].im;
+            v.im -= l.re * x[j].im + l.im * x[j].re;
+          }
+          x[i] = v;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sx[t + i][c] = x[i];
       } else {
-        const cplx<T> u = tb[i][r];
-        sx[i][c].re -= u.re * x.re - u.im * x.im;
-        sx[i][c].im -= u.re * x.im + u.im * x.re;
+#pragma unroll
+        for (int i = 15; i >= 0; --i) {
+          cplx<T> v{(t + i == c) ? T(1) : T(0), T(0)};
+          if (live && t + i < wk) {
+#pragma unroll
+            for (int j = i + 1; j < 16; ++j) {   // x[j] = 0 for j > c
+              const cplx<T> u = tb[t + i][t + j];
+              v.re -= u.re * x[j].re - u.im * x[j].im;
+              v.im -= u.re * x[j].im + u.im * x[j].re;
+            }
+            v = cmul(v, udinv[t + i]);
+          }
+          x[i] = v;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sy[t + i][c] = x[i];
       }
     }
-    __syncthreads();
   }
+  __syncthreads();
+  {
+    const int r = tid >> 4, c = tid & 15;
+    cplx<T> tl{T(0), T(0)}, tu{T(0), T(0)};
+    auto mad = [](cplx<T>& s, const cplx<T>& x, const cplx<T>& y) {
+      s.re += x.re * y.re - x.im * y.im;
+      s.im += x.re * y.im + x.im * y.re;
+    };
+#pragma unroll 4
+    for (int q = 0; q < 16; ++q) {
+      if (q >= c) mad(tl, tb[16 + r][q], sx[q][c]);
+      if (q <= c) mad(tu, tb[r][16 + q], sy[16 + q][16 + c]);
+    }
+    sx[r][16 + c] = tl;
+    sy[16 + r][c] = tu;
+    __syncthreads();
+    tl = tu = cplx<T>{T(0), T(0)};
+#pragma unroll 4
+    for (int q = 0; q < 16; ++q) {
+      if (q <= r) mad(tl, sx[16 + r][16 + q], sx[q][16 + c]);
+      if (q >= r) mad(tu, sy[r][q], sy[16 + q][c]);
+    }
+    const bool live = 16 + c < wk;
+    sx[16 + r][c] = cplx<T>{-tl.re, -tl.im};
+    sy[r][16 + c] = cplx<T>{live ? -tu.re : T(0), live ? -tu.im : T(0)};
+  }
+  __syncthreads();
   for (int e = tid; e < NB * NB; e += NODE) {
     const int r = e / NB, c = e % NB;
-    if (r >= wk || c < r || c >= wk) invU[e] = cplx<T>{(r == c) ? T(1) : T(0), T(0)};  // the rest stored above
+    invL[e] = r >= c ? sx[r][c] : cplx<T>{T(0), T(0)};
+    invU[e] = r <= c ? sy[r][c] : cplx<T>{T(0), T(0)};
   }
   }
   // move list, built by the first wavefront (every thread reaches the barrier)
@@ -366,12 +436,12 @@ __global__ __launch_bounds__(Node<T>::size) void k_tslu_node(const cplx<T>* __re
                                                     cplx<T>* __restrict__ top, cplx<T>* __restrict__ invL,
                                                     cplx<T>* __restrict__ invU) {
   constexpr int NODE = Node<T>::size, NWAVE = NODE / 64, FANIN = NODE / NB;
-  __shared__ __align__(16) cplx<T> prow[2][NWAVE][NB];
+  __shared__ __align__(16) cplx<T> prow[NB];
   __shared__ cplx<T> lu[NB][NB + 1];
   __shared__ int sidx[NODE];
   __shared__ int win[NB];
-  __shared__ cplx<T> pinv[2][NWAVE];
-  __shared__ unsigned skey[2][NWAVE];
+  __shared__ cplx<T> pinv;
+  __shared__ unsigned skey[NWAVE];
   __shared__ int scnt[NWAVE];
   __shared__ int s_cnt;
   const int tid = threadIdx.x;
@@ -407,7 +477,7 @@ __global__ __launch_bounds__(Node<T>::size) void k_tslu_node(const cplx<T>* __re
   cplx<T> a[NB];
   load_row(A, lda, k, w, row, a);
   int step;
-  const int zc = gepp_node(a, valid, nvalid, w, tid, step, prow, pinv, lu, skey);
+  const int zc = gepp_node<T, NWAVE>(a, valid, nvalid, w, tid, step, prow, pinv, lu, skey);
   const int ncand = min(nvalid, w);
   if constexpr (IS_ROOT) {
     if (step >= 0) win[step] = row;
