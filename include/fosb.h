@@ -16,7 +16,8 @@
  *   - Handles (context, mesh, level) are owned by the library until *_destroy.
  *     The library allocates its own O(N) tables (a MIXED level also keeps the
  *     inverses of the 1024 x 1024 diagonal blocks of its factors, 16 KiB per
- *     unknown, or below N = 2048 of the 256 x 256 ones, 4 KiB) and work buffers
+ *     unknown, or below N = 2048 of the 256 x 256 ones, 4 KiB; an FP64 level from
+ *     N = 2048 on those of the 256 x 256 ones, 8 KiB) and work buffers
  *     (O(N*nrhs) for solves; about 1 GiB for the assembly's two bands, 2 GiB where a
  *     level keeps no complex128 matrix; 256 MiB for a right-hand-side correlation;
  *     for the packed operands of wide complex64 products 12 bytes an entry, at most

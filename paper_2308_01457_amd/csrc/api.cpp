@@ -83,7 +83,18 @@ void level_solve_inplace(Context& ctx, const Level& L, c128* B, int64_t ldb, int
   c128* T = ctx.scratch[1].as<c128>();
   if (L.precision == FOSB_PREC_FP64) {
     const c128* A = static_cast<const c128*>(L.Z);
-    if (!adjoint) {
+    const c128 *iL = L.inv_L.as<c128>(), *iU = L.inv_U.as<c128>();
+    if (iL && !adjoint) {   // B is the second buffer of the out-of-place solves
+      permute_rows_gather(s, perm, B, ldb, T, nrhs, n, nrhs);
+      trsm_lower_unit_inv<double>(ctx, A, L.ldz, iL, n, T, nrhs, B, ldb, nrhs);
+      trsm_upper_inv<double>(ctx, A, L.ldz, iU, n, B, ldb, T, nrhs, nrhs);
+      copy_c128(s, T, nrhs, B, ldb, n, nrhs);
+    } else if (iL) {
+      copy_c128(s, B, ldb, T, nrhs, n, nrhs);
+      trsm_upper_inv_ch<double>(ctx, A, L.ldz, iU, n, T, nrhs, B, ldb, nrhs);
+      trsm_lower_unit_inv_ch<double>(ctx, A, L.ldz, iL, n, B, ldb, T, nrhs, nrhs);
+      permute_rows_scatter(s, perm, T, nrhs, B, ldb, n, nrhs);
+    } else if (!adjoint) {
       permute_rows_gather(s, perm, B, ldb, T, nrhs, n, nrhs);
       trsm_lower_unit<double>(ctx, A, L.ldz, L.dinv_L.as<c128>(), 0, n, T, nrhs, nrhs);
       trsm_upper<double>(ctx, A, L.ldz, L.dinv_U.as<c128>(), 0, n, T, nrhs, nrhs);
@@ -430,7 +441,15 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
   if (precision == FOSB_PREC_FP64) {
     L->dinv_L.alloc((size_t)nblk * kPanel * kPanel * sizeof(c128));
     L->dinv_U.alloc((size_t)nblk * kPanel * kPanel * sizeof(c128));
-    info = lu_factor<double>(c, static_cast<c128*>(Z), n, ldz, L->dinv_L.as<c128>(), L->dinv_U.as<c128>(), L->perm);
+    if (inv64_bytes(n) > 0) {
+      L->inv_L.alloc((size_t)inv64_bytes(n));
+      L->inv_U.alloc((size_t)inv64_bytes(n));
+    }
+    info = lu_factor<double>(c, static_cast<c128*>(Z), n, ldz, L->dinv_L.as<c128>(), L->dinv_U.as<c128>(), L->perm,
+                             L->inv_L.as<c128>());
+    if (info == 0 && L->inv_U.p)
+      upper_block_inverses<double>(c, static_cast<const c128*>(Z), n, ldz, L->dinv_U.as<c128>(),
+                                   L->inv_U.as<c128>());
   } else {
     L->dinv_L.alloc((size_t)nblk * kPanel * kPanel * sizeof(c64));
     L->dinv_U.alloc((size_t)nblk * kPanel * kPanel * sizeof(c64));
@@ -564,7 +583,7 @@ static int64_t level_bytes(int64_t n, int64_t nt, int32_t precision, int64_t n_d
   const int64_t nblk = (n + kPanel - 1) / kPanel;
   const int64_t es = precision == FOSB_PREC_FP64 ? 16 : 8;
   int64_t b = 4 * n + 2 * nblk * kPanel * kPanel * es + 18 * nt * 8 + 16 * n * n_dirs + 18 * nt * n_dirs * 16;
-  if (precision == FOSB_PREC_MIXED) b += 2 * inv_bytes(n);
+  b += 2 * (precision == FOSB_PREC_MIXED ? inv_bytes(n) : inv64_bytes(n));
   return b;
 }
 

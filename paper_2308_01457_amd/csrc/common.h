@@ -329,7 +329,7 @@ struct Level {
   std::vector<int32_t> perm;   // host: row permutation (position i holds original row perm[i])
   DevBuf d_perm;               // int32 [n]
   DevBuf dinv_L, dinv_U;       // inverted nb x nb diagonal blocks of L and U (LU precision)
-  DevBuf inv_L, inv_U;         // MIXED: inverted inv_block(n)-row diagonal blocks of L and U (complex64)
+  DevBuf inv_L, inv_U;         // inverted diagonal blocks of L and U: MIXED inv_block(n) rows, FP64 (N >= kInv64MinN) kInvBlock
   DevBuf u;                    // c128 [n_dirs][n]
   DevBuf W;                    // c128 [n_dirs][nt][3][6] RHS weights
   DevBuf qx;                   // double [3][6*nt] quadrature nodes (component-major)
@@ -439,9 +439,9 @@ void trsm_lower_unit_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<
 // Inverses of the kInvBlock x kInvBlock diagonal blocks of the upper factor
 // (block b at inv + b kInvBlock^2, row-major, row stride kInvBlock; the last
 // block's slot is the identity outside its corner; lu_factor makes L's), and
-// out-of-place triangular solves of a whole factor that apply inverses of inv_block(n) rows at the
-// leaves: X <- T^{-1} B, with B (n x nrhs) consumed as workspace.  Complex64
-// factors only.
+// out-of-place triangular solves of a whole factor that apply inverses (complex128
+// factors: of kInvBlock rows, complex64 ones of inv_block(n)) at the leaves:
+// X <- T^{-1} B or (_ch) T^{-H} B, with B (n x nrhs) consumed as workspace.
 constexpr int kInvBlock = 256;
 // Rows of a leaf of those solves.  A narrow solve is a chain of launches, two
 // per leaf (N = 7680, one column: 59 products a factor with 256 rows, 15 with
@@ -452,6 +452,13 @@ inline int64_t inv_block(int64_t n) { return n >= 2048 ? 1024 : kInvBlock; }
 inline int64_t inv_bytes(int64_t n) {
   const int64_t ib = inv_block(n);
   return (n + ib - 1) / ib * ib * ib * (int64_t)sizeof(c64);
+}
+// An FP64 level keeps inverses of kInvBlock rows from this size on (8 KB a row; its
+// solves' leaves were 256-row substitutions against 32-row inverses, a column per
+// workgroup: N = 7680, 480 columns, 55 us each, 44% of the solve).
+constexpr int64_t kInv64MinN = 2048;
+inline int64_t inv64_bytes(int64_t n) {
+  return n < kInv64MinN ? 0 : (n + kInvBlock - 1) / kInvBlock * kInvBlock * kInvBlock * (int64_t)sizeof(c128);
 }
 // W (inv_bytes(n)) <- inverses of the inv_block(n)-row diagonal blocks from those of kInvBlock rows (S):
 // halves merged by products, on ctx's stream (uses solve_tmp).  inv_block(n) > kInvBlock.
@@ -471,6 +478,12 @@ void trsm_lower_unit_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx
 template <typename T>
 void trsm_upper_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t n, cplx<T>* B,
                     int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs);
+template <typename T>
+void trsm_lower_unit_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t n, cplx<T>* B,
+                            int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs);
+template <typename T>
+void trsm_upper_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t n, cplx<T>* B,
+                       int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs);
 void permute_rows_gather(hipStream_t s, const int32_t* perm, const c128* src, int64_t lds, c128* dst,
                          int64_t ldd, int64_t n, int64_t ncols);
 // dst[perm[i]] = src[i]

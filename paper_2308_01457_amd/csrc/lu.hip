@@ -2079,18 +2079,64 @@ static void trsm_inv_oop(Context& ctx, const cplx<T>* A, int64_t lda, const cplx
   }
 }
 
+// X <- T^{-H} B, likewise.
+template <typename T, bool LOWER>
+static void trsm_inv_ch_oop(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* inv, int64_t ib, int64_t k0,
+                            int64_t n, cplx<T>* B, int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
+  if (n <= 0 || nrhs <= 0) return;
+  if (n <= ib) {
+    gemm_ch<T>(ctx, n, nrhs, n, 1.0, inv + k0 * ib, ib, B, ldb, 0.0, X, ldx);
+    return;
+  }
+  const int64_t n1 = ib * (((n + ib - 1) / ib + 1) / 2), n2 = n - n1;
+  if (LOWER) {
+    trsm_inv_ch_oop<T, true>(ctx, A, lda, inv, ib, k0 + n1, n2, B + n1 * ldb, ldb, X + n1 * ldx, ldx, nrhs);
+    gemm_ch<T>(ctx, n1, nrhs, n2, -1.0, A + (k0 + n1) * lda + k0, lda, X + n1 * ldx, ldx, 1.0, B, ldb);
+    trsm_inv_ch_oop<T, true>(ctx, A, lda, inv, ib, k0, n1, B, ldb, X, ldx, nrhs);
+  } else {
+    trsm_inv_ch_oop<T, false>(ctx, A, lda, inv, ib, k0, n1, B, ldb, X, ldx, nrhs);
+    gemm_ch<T>(ctx, n2, nrhs, n1, -1.0, A + k0 * lda + (k0 + n1), lda, X, ldx, 1.0, B + n1 * ldb, ldb);
+    trsm_inv_ch_oop<T, false>(ctx, A, lda, inv, ib, k0 + n1, n2, B + n1 * ldb, ldb, X + n1 * ldx, ldx, nrhs);
+  }
+}
+
+template <typename T>
+static int64_t leaf_rows(int64_t n) {
+  return sizeof(T) == 8 ? kInvBlock : inv_block(n);
+}
+
 template <typename T>
 void trsm_lower_unit_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t n, cplx<T>* B,
                          int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
-  trsm_inv_oop<T, true>(ctx, A, lda, invL, inv_block(n), 0, n, B, ldb, X, ldx, nrhs);
+  trsm_inv_oop<T, true>(ctx, A, lda, invL, leaf_rows<T>(n), 0, n, B, ldb, X, ldx, nrhs);
 }
 template <typename T>
 void trsm_upper_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t n, cplx<T>* B,
                     int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
-  trsm_inv_oop<T, false>(ctx, A, lda, invU, inv_block(n), 0, n, B, ldb, X, ldx, nrhs);
+  trsm_inv_oop<T, false>(ctx, A, lda, invU, leaf_rows<T>(n), 0, n, B, ldb, X, ldx, nrhs);
+}
+
+template <typename T>
+void trsm_lower_unit_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t n, cplx<T>* B,
+                            int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
+  trsm_inv_ch_oop<T, true>(ctx, A, lda, invL, leaf_rows<T>(n), 0, n, B, ldb, X, ldx, nrhs);
+}
+template <typename T>
+void trsm_upper_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t n, cplx<T>* B,
+                       int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
+  trsm_inv_ch_oop<T, false>(ctx, A, lda, invU, leaf_rows<T>(n), 0, n, B, ldb, X, ldx, nrhs);
 }
 
 template void upper_block_inverses<float>(Context&, const c64*, int64_t, int64_t, const c64*, c64*);
+template void upper_block_inverses<double>(Context&, const c128*, int64_t, int64_t, const c128*, c128*);
+template void trsm_lower_unit_inv<double>(Context&, const c128*, int64_t, const c128*, int64_t, c128*, int64_t, c128*,
+                                          int64_t, int64_t);
+template void trsm_upper_inv<double>(Context&, const c128*, int64_t, const c128*, int64_t, c128*, int64_t, c128*,
+                                     int64_t, int64_t);
+template void trsm_lower_unit_inv_ch<double>(Context&, const c128*, int64_t, const c128*, int64_t, c128*, int64_t,
+                                             c128*, int64_t, int64_t);
+template void trsm_upper_inv_ch<double>(Context&, const c128*, int64_t, const c128*, int64_t, c128*, int64_t, c128*,
+                                        int64_t, int64_t);
 template void trsm_lower_unit_inv<float>(Context&, const c64*, int64_t, const c64*, int64_t, c64*, int64_t, c64*,
                                          int64_t, int64_t);
 template void trsm_upper_inv<float>(Context&, const c64*, int64_t, const c64*, int64_t, c64*, int64_t, c64*, int64_t,
