@@ -244,6 +244,9 @@ fosb_status fosb_assemble_pmchwt(fosb_context* ctx, const fosb_mesh* mesh, doubl
  *                    ldzlow) receives the FP32 LU factors, which the level's
  *                    solves apply through the inverses of their diagonal
  *                    blocks (kept by the level: 1024 rows, 256 below N = 2048).
+ *                    Their large products run on the fp16 matrix cores, every
+ *                    operand split into two fp16 parts (22 bits) and accumulated
+ *                    in FP32: no less accurate than FP32 products.
  *                    Z may be NULL: the level then assembles the matrix in FP64
  *                    column bands straight into Zlow (rounded to complex64) and
  *                    re-assembles FP64 bands of Z for every refinement residual
@@ -268,7 +271,7 @@ fosb_status fosb_level_create(fosb_context* ctx, const fosb_mesh* mesh, double k
  * The level keeps b: fosb_rhs_correlation and fosb_correlation on dielectric
  * levels with cov = NULL form the rank-one right-hand side C = b_l1 b_l2^H of
  * the paper's sphere validation (a second moment with M2[f] = f (x) f, whose
- * solution is u_l1 u_l2^H).
+ * solution is u_l1 u_l2^H; fosb_correlation solves one column per level for it).
  * field >= 0 (FOSB_FIELD_RADIAL or FOSB_FIELD_NORMAL; mu_r must be 1, else
  * FOSB_E_UNSUPPORTED) also builds the shape-derivative weights W (FOA section,
  * the DE shape-derivative equation), 2N x 6 nt per incidence, kept by the
@@ -575,7 +578,7 @@ fosb_status fosb_second_moment_batch(fosb_context* ctx, const fosb_batch_shape* 
 
 /* ---------------------------------------------------------------- GEMM tile autotuner */
 /* The complex GEMMs run one of several tile shapes (64x64, 64x32, 64x128,
- * 128x64 for complex64; 64x32, 64x64, 128x64 for complex128).  With tuning on
+ * 128x64 for complex64; 64x32, 64x64, 64x96 for complex128).  With tuning on
  * (the default) the first product of each size bucket (precision, operand
  * form, floor(log2) of M, N, K) times every shape on its real operands into
  * scratch output and keeps the fastest for the bucket; the table belongs to

@@ -385,12 +385,12 @@ static double inverse_norm1_estimate(Context& c, const Level& L) {
   return std::max(est, 2.0 * norm1() / (3.0 * (double)n));
 }
 
-// The first moments enter every right-hand side of their level, so their
-// refinement aims below ir_tol.  With ir_tol = 1e-10 the levels up to N = 7680
-// stop after one sweep or two depending on the last digit of the first
+// The first moments enter every right-hand side of their level, so on levels
+// whose factors come from split products their refinement aims below ir_tol.  With ir_tol = 1e-10
+// those up to N = 7680 stop after one sweep or two depending on the last digit of the first
 // correction (estimate 6e-11); one that stopped after one left 7.5e-10 in a
-// Sigma block.  The other sweep costs 0.6 ms there.
-constexpr double kFirstMomentTol = 0.1;
+// Sigma block.  The other sweep costs 0.5 ms there.
+static double first_moment_tol(const Level& L) { return L.sym_lu ? 0.1 : 1.0; }
 
 // Factorisation, first moments and RHS weights of one level, on c's stream.
 static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh, double k, int32_t precision,
@@ -529,7 +529,7 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
     L->b.alloc((size_t)n * n_dirs * sizeof(c128));
     incident_rhs_pmchwt(s, *mesh, k, ddir.as<double>(), dpol.as<double>(), (int)n_dirs, L->b.as<c128>());
     copy_c128(s, L->b.as<c128>(), n_dirs, L->u.as<c128>(), n_dirs, n, n_dirs);
-    level_solve_inplace(c, *L, L->u.as<c128>(), n_dirs, n_dirs, nullptr, false, -1, kFirstMomentTol);
+    level_solve_inplace(c, *L, L->u.as<c128>(), n_dirs, n_dirs, nullptr, false, -1, first_moment_tol(*L));
     if (sd_field >= 0) {  // shape-derivative weights per incidence, and the nodes for the covariance
       const int64_t Q = 6LL * mesh->h.nt;
       L->sd_field = sd_field;
@@ -552,7 +552,7 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
   L->qx.alloc((size_t)3 * 6 * mesh->h.nt * sizeof(double));
   quad_nodes(s, *mesh, L->qx.as<double>());
   incident_rhs(s, *mesh, k, ddir.as<double>(), dpol.as<double>(), (int)n_dirs, L->u.as<c128>());
-  level_solve_inplace(c, *L, L->u.as<c128>(), n_dirs, n_dirs, nullptr, false, -1, kFirstMomentTol);
+  level_solve_inplace(c, *L, L->u.as<c128>(), n_dirs, n_dirs, nullptr, false, -1, first_moment_tol(*L));
   L->W.alloc((size_t)n_dirs * mesh->h.nt * 18 * sizeof(c128));
   for (int64_t d = 0; d < n_dirs; ++d)
     rhs_weights(s, *mesh, k, field, L->u.as<c128>() + d, n_dirs, L->W.as<c128>() + d * mesh->h.nt * 18);
@@ -677,7 +677,7 @@ static void rank_one_blocks(Context& c, const fosb_level* const* levels, int32_t
     const fosb_level& l = *levels[i];
     x[i].alloc((size_t)l.n * sizeof(c128));
     copy_c128(c.stream, l.b.as<c128>() + dir, l.n_dirs, x[i].as<c128>(), 1, l.n, 1);
-    level_solve_inplace(c, l, x[i].as<c128>(), 1, 1, st, false, -1, kFirstMomentTol);
+    level_solve_inplace(c, l, x[i].as<c128>(), 1, 1, st, false, -1, first_moment_tol(l));
   }
   for (size_t p = 0; p < pairs.size(); ++p) {
     const int i1 = pairs[p][0] - L0, i2 = pairs[p][1] - L0;
