@@ -59,7 +59,8 @@ struct Pool {
   size_t cached_bytes = 0;                   // capacity held in free_blocks
   size_t live_bytes = 0;                     // capacity handed out and not returned
   int64_t n_device_allocs = 0;               // hipMalloc calls made
-  void* get(size_t n, size_t& cap);
+  // fresh: never a cached block
+  void* get(size_t n, size_t& cap, bool fresh = false);
   void put(void* p, size_t cap);
   void trim();
   ~Pool();
@@ -95,13 +96,13 @@ struct DevBuf {
     return *this;
   }
   ~DevBuf() { release(); }
-  void alloc(size_t n) {
+  void alloc(size_t n, bool fresh = false) {
     release();
     if (n == 0) return;
     if (thread_no_alloc()) fail(FOSB_E_DEVICE, "internal: device buffer of %zu bytes on the allocation-free path", n);
     std::shared_ptr<Pool> pool = home ? home : thread_pool();
     if (pool) {
-      p = pool->get(n, cap);
+      p = pool->get(n, cap, fresh);
       from = std::move(pool);
     } else {
       FOSB_HIP(hipMalloc(&p, n));
@@ -110,10 +111,12 @@ struct DevBuf {
     bytes = n;
   }
   // grow-only (contents are not preserved when it grows past the block's capacity)
-  void reserve(size_t n) {
+  // fresh: a buffer that a pass grows in many steps and keeps would else hold
+  // blocks that the next pass's buffers need
+  void reserve(size_t n, bool fresh = false) {
     if (n <= bytes) return;
     if (p && n <= cap) { bytes = n; return; }
-    alloc(n);
+    alloc(n, fresh);
   }
   void release() {
     if (p) {

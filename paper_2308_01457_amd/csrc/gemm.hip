@@ -711,20 +711,23 @@ static void gemm_launch(Context& ctx, int64_t M, int64_t N, int64_t K, double al
       return;
     }
   }
-  // split K when the output has too few tiles to fill the chip and K is long:
-  // about two workgroups per CU, each still streaming at least 256 of K.  The
+  // split K when the output has too few tiles to fill the chip: about two
+  // workgroups per CU, each still streaming at least 64 of K.  (With 256 instead,
+  // from K = 512 on, the solves' leaf and coupling products ran on a few dozen
+  // workgroups.  N = 7680: FP64, 480 columns 5.3 -> 4.6 ms, 16 columns 2.9 -> 1.6; mixed, 17
+  // columns 4.4 -> 2.9; adjoint gradient 15.2 -> 12.7.)  The
   // decision uses a fixed 64 x 64 reference tile, so it (and the summation
   // order) does not depend on the tile variant chosen below.
   const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
   int64_t nz = 1;
   const int64_t want = 2LL * ctx.n_cu;
-  if (tiles < want && Kp >= 512 && !ctx.no_alloc) nz = std::min<int64_t>({(want + tiles - 1) / tiles, Kp / 256, 64});
+  if (tiles < want && Kp >= 256 && !ctx.no_alloc) nz = std::min<int64_t>({(want + tiles - 1) / tiles, Kp / 64, 64});
   int64_t kc = Kp;
   cplx<T>* P = nullptr;
   if (nz > 1) {
     kc = ((Kp + nz - 1) / nz + Slice<T>::BK - 1) / Slice<T>::BK * Slice<T>::BK;
     nz = (Kp + kc - 1) / kc;
-    ctx.splitk.reserve((size_t)nz * M * N * sizeof(cplx<T>));
+    ctx.splitk.reserve((size_t)nz * M * N * sizeof(cplx<T>), true);
     P = static_cast<cplx<T>*>(ctx.splitk.p);
   }
   // The trailing update's large complex64 products (at least four 128 x 64

@@ -33,9 +33,9 @@ static size_t pool_round(size_t n) {
   return n < small ? (n + 4095) / 4096 * 4096 : (n + big - 1) / big * big;
 }
 
-void* Pool::get(size_t n, size_t& cap) {
+void* Pool::get(size_t n, size_t& cap, bool fresh) {
   const size_t want = pool_round(n);
-  {
+  if (!fresh) {
     std::lock_guard<std::mutex> lock(mu);
     auto it = free_blocks.lower_bound(want);
     // reuse the smallest cached block that fits, unless it is more than twice the request
