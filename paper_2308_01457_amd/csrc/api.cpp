@@ -445,11 +445,13 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
       L->inv_L.alloc((size_t)inv64_bytes(n));
       L->inv_U.alloc((size_t)inv64_bytes(n));
     }
-    info = lu_factor<double>(c, static_cast<c128*>(Z), n, ldz, L->dinv_L.as<c128>(), L->dinv_U.as<c128>(), L->perm,
-                             L->inv_L.as<c128>());
-    if (info == 0 && L->inv_U.p)
-      upper_block_inverses<double>(c, static_cast<const c128*>(Z), n, ldz, L->dinv_U.as<c128>(),
-                                   L->inv_U.as<c128>());
+    // no refinement follows: U12 by substitution, the block inverses for the solves after it
+    info = lu_factor<double>(c, static_cast<c128*>(Z), n, ldz, L->dinv_L.as<c128>(), L->dinv_U.as<c128>(), L->perm);
+    if (info == 0 && L->inv_U.p) {
+      diagonal_inverses<double>(c, true, static_cast<const c128*>(Z), n, ldz, L->dinv_L.as<c128>(), L->inv_L.as<c128>());
+      diagonal_inverses<double>(c, false, static_cast<const c128*>(Z), n, ldz, L->dinv_U.as<c128>(),
+                             L->inv_U.as<c128>());
+    }
   } else {
     L->dinv_L.alloc((size_t)nblk * kPanel * kPanel * sizeof(c64));
     L->dinv_U.alloc((size_t)nblk * kPanel * kPanel * sizeof(c64));
@@ -503,7 +505,7 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
       transpose_block_inverses(c, A32, n, ldzlow, L->inv_L.as<c64>(), L->inv_U.as<c64>());
     } else if (info == 0) {
       c64* invU = grow ? invL : L->inv_U.as<c64>();
-      upper_block_inverses<float>(c, A32, n, ldzlow, L->dinv_U.as<c64>(), invU);
+      diagonal_inverses<float>(c, false, A32, n, ldzlow, L->dinv_U.as<c64>(), invU);
       if (grow) grow_block_inverses(c, false, A32, n, ldzlow, invU, L->inv_U.as<c64>());
     }
     if (grow) FOSB_HIP(hipStreamSynchronize(s));   // inv_small is read

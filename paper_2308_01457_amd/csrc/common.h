@@ -410,7 +410,7 @@ void split_gemm(Context& ctx, int64_t row0, int64_t M, int64_t N, int64_t K, dou
                 int64_t ldc, int diag_nb);
 // lu.hip
 // invL (optional, complex64 factors): receives the kInvBlock x kInvBlock
-// diagonal-block inverses of L (layout as for upper_block_inverses); the
+// diagonal-block inverses of L (layout as for diagonal_inverses); the
 // blocked factorisation then also solves its block rows through them.
 // sym: the matrix is (numerically) symmetric; for n >= 2048 it is factored
 // without pivoting, A = L U with U = D L^T formed from the multipliers and the
@@ -439,9 +439,9 @@ void trsm_upper_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* d
 template <typename T>
 void trsm_lower_unit_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* dinvL, int64_t k0, int64_t n,
                         cplx<T>* B, int64_t ldb, int64_t nrhs);
-// Inverses of the kInvBlock x kInvBlock diagonal blocks of the upper factor
-// (block b at inv + b kInvBlock^2, row-major, row stride kInvBlock; the last
-// block's slot is the identity outside its corner; lu_factor makes L's), and
+// Inverses of the kInvBlock x kInvBlock diagonal blocks of the lower or the upper
+// factor (block b at inv + b kInvBlock^2, row-major, row stride kInvBlock; the
+// last block's slot is the identity outside its corner), and
 // out-of-place triangular solves of a whole factor that apply inverses (complex128
 // factors: of kInvBlock rows, complex64 ones of inv_block(n)) at the leaves:
 // X <- T^{-1} B or (_ch) T^{-H} B, with B (n x nrhs) consumed as workspace.
@@ -473,8 +473,8 @@ void transpose_block_inverses(Context& ctx, const c64* A, int64_t n, int64_t lda
 void inverse_merge(hipStream_t s, bool lower, int64_t n, const c64* A, int64_t lda, c64* W, int64_t ib, int64_t h,
                    c64* T);
 template <typename T>
-void upper_block_inverses(Context& ctx, const cplx<T>* A, int64_t n, int64_t lda, const cplx<T>* dinvU,
-                          cplx<T>* invU);
+void diagonal_inverses(Context& ctx, bool lower, const cplx<T>* A, int64_t n, int64_t lda, const cplx<T>* dinv,
+                    cplx<T>* inv);
 template <typename T>
 void trsm_lower_unit_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t n, cplx<T>* B,
                          int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs);

@@ -1203,7 +1203,7 @@ struct LuRun {
   int64_t cand_stride;
   cplx<T>* top;
   int64_t pc0, pc1;  // columns a panel permutes at once (the rest is the update stream's)
-  cplx<T>* invL = nullptr;  // optional: NL x NL diagonal-block inverses of L, filled per block
+  cplx<T>* invL = nullptr;  // optional (FP32): NL x NL diagonal-block inverses of L, filled per block
   bool sym = false;         // symmetric matrix, no pivoting: lower-triangle trailing updates, U12 = D L21^T
 };
 
@@ -1322,7 +1322,9 @@ static void trsm_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>*
 
 // B <- L_jj^{-1} B for the block row of block j (rows kj .. kj + wj): through
 // the block inverses when the run keeps them (they are final once block j's
-// panels are done), else with the leaf kernel.
+// panels are done), else with the leaf kernel.  FP64 runs keep none: a product
+// with an explicit inverse loses u |L^{-1}| |L| where substitution is backward
+// stable, and nothing refines the FP64 factors.
 template <typename T>
 static void block_row_solve(LuRun<T>& R, Context& U, int64_t kj, int64_t wj, cplx<T>* B, int64_t ncols) {
   if (R.invL) {
@@ -1989,9 +1991,13 @@ template void matrix_norms<double>(Context&, const c128*, int64_t, int64_t, bool
 static_assert(NL == kInvBlock, "inverse block size");
 
 template <typename T>
-void upper_block_inverses(Context& ctx, const cplx<T>* A, int64_t n, int64_t lda, const cplx<T>* dinvU,
-                          cplx<T>* invU) {
-  if (n > 0) block_inverses<T, false>(ctx, A, n, lda, dinvU, invU, 0, (n + NL - 1) / NL);
+void diagonal_inverses(Context& ctx, bool lower, const cplx<T>* A, int64_t n, int64_t lda, const cplx<T>* dinv,
+                    cplx<T>* inv) {
+  if (n <= 0) return;
+  if (lower)
+    block_inverses<T, true>(ctx, A, n, lda, dinv, inv, 0, (n + NL - 1) / NL);
+  else
+    block_inverses<T, false>(ctx, A, n, lda, dinv, inv, 0, (n + NL - 1) / NL);
 }
 
 // W (blocks of ib rows and columns) <- the NL-row blocks S on its diagonal, zero elsewhere.
@@ -2127,8 +2133,8 @@ void trsm_upper_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T
   trsm_inv_ch_oop<T, false>(ctx, A, lda, invU, leaf_rows<T>(n), 0, n, B, ldb, X, ldx, nrhs);
 }
 
-template void upper_block_inverses<float>(Context&, const c64*, int64_t, int64_t, const c64*, c64*);
-template void upper_block_inverses<double>(Context&, const c128*, int64_t, int64_t, const c128*, c128*);
+template void diagonal_inverses<float>(Context&, bool, const c64*, int64_t, int64_t, const c64*, c64*);
+template void diagonal_inverses<double>(Context&, bool, const c128*, int64_t, int64_t, const c128*, c128*);
 template void trsm_lower_unit_inv<double>(Context&, const c128*, int64_t, const c128*, int64_t, c128*, int64_t, c128*,
                                           int64_t, int64_t);
 template void trsm_upper_inv<double>(Context&, const c128*, int64_t, const c128*, int64_t, c128*, int64_t, c128*,

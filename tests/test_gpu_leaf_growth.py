@@ -1,0 +1,44 @@
+"""Factors with a diagonal block whose inverse is large.  The first block of L has
+ones on the diagonal and -theta below, so its inverse grows as
+(1 + theta)^(rows - 1): harmless over the 32 rows that substitution inverts
+explicitly, not over a whole leaf of 256 or 1024 rows.  Z = L U with a
+well-conditioned U and little outside that block of L, so partial pivoting
+leaves the rows in place and the elimination does not grow."""
+
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+U64 = 2.0 ** -53
+
+
+def _matrix(torch, dev, n, block, theta):
+    g = torch.Generator().manual_seed(n)
+    L = torch.randn((n, n), dtype=torch.float64, generator=g) / (4.0 * n ** 0.5)
+    L[:block, :block] = -theta
+    L = torch.tril(L, -1) + torch.eye(n, dtype=torch.float64)
+    U = torch.triu(torch.randn((n, n), dtype=torch.complex128, generator=g), 1) / (4.0 * n ** 0.5)
+    U = U + torch.eye(n, dtype=torch.complex128)
+    return torch.matmul(L.to(torch.complex128).to(dev), U.to(dev))
+
+
+def test_fp64_factors_are_backward_stable():
+    """||Z - L U||_F <= n u || |L| |U| ||_F, the bound of an elimination by
+    substitution, with (1 + theta)^255 = 1.6e8."""
+    import torch
+    from paper_2308_01457_amd import fosb
+    ctx = fosb.Context(0)
+    m = fosb.Mesh(ctx, *workloads.geodesic_sphere(9))   # N = 2430
+    Z = _matrix(torch, ctx.torch_device, m.n_edges, 256, 0.077)
+    F = Z.clone()
+    lv = fosb.Level(ctx, m, 1.0, F, fosb.FP64)
+    n = m.n_edges
+    L = torch.tril(F, -1) + torch.eye(n, dtype=F.dtype, device=F.device)
+    U = torch.triu(F)
+    err = float((Z - torch.matmul(L, U)).norm())
+    bound = n * U64 * float(torch.matmul(L.abs(), U.abs()).norm())
+    print(f"[gpu] ||Z - LU|| = {err:.2e} (bound {bound:.2e})", flush=True)
+    assert err <= bound
+    lv.close()
