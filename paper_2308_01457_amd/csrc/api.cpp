@@ -86,13 +86,13 @@ void level_solve_inplace(Context& ctx, const Level& L, c128* B, int64_t ldb, int
     const c128 *iL = L.inv_L.as<c128>(), *iU = L.inv_U.as<c128>();
     if (iL && !adjoint) {   // B is the second buffer of the out-of-place solves
       permute_rows_gather(s, perm, B, ldb, T, nrhs, n, nrhs);
-      trsm_lower_unit_inv<double>(ctx, A, L.ldz, iL, n, T, nrhs, B, ldb, nrhs);
-      trsm_upper_inv<double>(ctx, A, L.ldz, iU, n, B, ldb, T, nrhs, nrhs);
+      trsm_lower_unit_inv<double>(ctx, A, L.ldz, iL, L.leaf, n, T, nrhs, B, ldb, nrhs);
+      trsm_upper_inv<double>(ctx, A, L.ldz, iU, L.leaf, n, B, ldb, T, nrhs, nrhs);
       copy_c128(s, T, nrhs, B, ldb, n, nrhs);
     } else if (iL) {
       copy_c128(s, B, ldb, T, nrhs, n, nrhs);
-      trsm_upper_inv_ch<double>(ctx, A, L.ldz, iU, n, T, nrhs, B, ldb, nrhs);
-      trsm_lower_unit_inv_ch<double>(ctx, A, L.ldz, iL, n, B, ldb, T, nrhs, nrhs);
+      trsm_upper_inv_ch<double>(ctx, A, L.ldz, iU, L.leaf, n, T, nrhs, B, ldb, nrhs);
+      trsm_lower_unit_inv_ch<double>(ctx, A, L.ldz, iL, L.leaf, n, B, ldb, T, nrhs, nrhs);
       permute_rows_scatter(s, perm, T, nrhs, B, ldb, n, nrhs);
     } else if (!adjoint) {
       permute_rows_gather(s, perm, B, ldb, T, nrhs, n, nrhs);
@@ -141,8 +141,8 @@ void level_solve_inplace(Context& ctx, const Level& L, c128* B, int64_t ldb, int
       permute_rows_gather(s, perm, R, nrhs, T, nrhs, n, nrhs);
       copy_c128_to_c64(s, T, nrhs, R32, nrhs, n, nrhs);
       if (L.sym_sign) negate_rows_c64(s, R32, nrhs, n / 2, n, nrhs);   // (S Z)^{-1} S R
-      trsm_lower_unit_inv<float>(ctx, A32, L.ldzlow, L.inv_L.as<c64>(), n, R32, nrhs, Y32, nrhs, nrhs);
-      trsm_upper_inv<float>(ctx, A32, L.ldzlow, L.inv_U.as<c64>(), n, Y32, nrhs, R32, nrhs, nrhs);
+      trsm_lower_unit_inv<float>(ctx, A32, L.ldzlow, L.inv_L.as<c64>(), L.leaf, n, R32, nrhs, Y32, nrhs, nrhs);
+      trsm_upper_inv<float>(ctx, A32, L.ldzlow, L.inv_U.as<c64>(), L.leaf, n, Y32, nrhs, R32, nrhs, nrhs);
       copy_c64_to_c128(s, R32, nrhs, T, nrhs, n, nrhs);
       D = T;
     } else if (L.sym_lu) {
@@ -150,8 +150,8 @@ void level_solve_inplace(Context& ctx, const Level& L, c128* B, int64_t ldb, int
       // FP32 factors' accuracy, which is all that a correction needs):
       // M^{-H} R = conj(M^{-1} conj(R)), by the forward solves' wide products
       copy_c128_to_c64(s, R, nrhs, R32, nrhs, n, nrhs, true);
-      trsm_lower_unit_inv<float>(ctx, A32, L.ldzlow, L.inv_L.as<c64>(), n, R32, nrhs, Y32, nrhs, nrhs);
-      trsm_upper_inv<float>(ctx, A32, L.ldzlow, L.inv_U.as<c64>(), n, Y32, nrhs, R32, nrhs, nrhs);
+      trsm_lower_unit_inv<float>(ctx, A32, L.ldzlow, L.inv_L.as<c64>(), L.leaf, n, R32, nrhs, Y32, nrhs, nrhs);
+      trsm_upper_inv<float>(ctx, A32, L.ldzlow, L.inv_U.as<c64>(), L.leaf, n, Y32, nrhs, R32, nrhs, nrhs);
       if (L.sym_sign) negate_rows_c64(s, R32, nrhs, n / 2, n, nrhs);   // Z^{-H} = S (S Z)^{-H}
       copy_c64_to_c128(s, R32, nrhs, T, nrhs, n, nrhs, true);
       D = T;
@@ -392,6 +392,36 @@ static double inverse_norm1_estimate(Context& c, const Level& L) {
 // Sigma block.  The other sweep costs 0.5 ms there.
 static double first_moment_tol(const Level& L) { return L.sym_lu ? 0.1 : 1.0; }
 
+// Leaf inverses of a MIXED level whose factors and kInvBlock-row inverses of L
+// exist: those of U, and from N = 2048 on both grown to inv_block(n) rows, unless
+// the grown ones lose too much (kLeafGrowth).
+static void mixed_leaves(Context& c, Level& L) {
+  const int64_t n = L.n, ib = inv_block(n);
+  const c64* A = static_cast<const c64*>(L.Zlow);
+  const bool grow = ib > kInvBlock;
+  auto upper = [&] {
+    L.inv_U.alloc(L.inv_L.bytes);
+    diagonal_inverses<float>(c, false, A, n, L.ldzlow, L.dinv_U.as<c64>(), L.inv_U.as<c64>());
+  };
+  if (!grow || !L.sym_lu) upper();
+  L.leaf = kInvBlock;
+  if (!grow) return;
+  DevBuf gl((size_t)inv_bytes(n)), gu((size_t)inv_bytes(n));
+  grow_block_inverses(c, true, A, n, L.ldzlow, L.inv_L.as<c64>(), gl.as<c64>());
+  if (L.sym_lu)
+    transpose_block_inverses(c, A, n, L.ldzlow, gl.as<c64>(), gu.as<c64>());
+  else
+    grow_block_inverses(c, false, A, n, L.ldzlow, L.inv_U.as<c64>(), gu.as<c64>());
+  // synchronises, so the small inverses are read
+  if (leaf_growth<float>(c, A, n, L.ldzlow, gl.as<c64>(), gu.as<c64>(), ib) <= kLeafGrowth) {
+    L.inv_L = std::move(gl);
+    L.inv_U = std::move(gu);
+    L.leaf = ib;
+  } else if (L.sym_lu) {
+    upper();
+  }
+}
+
 // Factorisation, first moments and RHS weights of one level, on c's stream.
 static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh, double k, int32_t precision,
                                                void* Z, int64_t ldz, void* Zlow, int64_t ldzlow, const double* dirs,
@@ -441,16 +471,20 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
   if (precision == FOSB_PREC_FP64) {
     L->dinv_L.alloc((size_t)nblk * kPanel * kPanel * sizeof(c128));
     L->dinv_U.alloc((size_t)nblk * kPanel * kPanel * sizeof(c128));
-    if (inv64_bytes(n) > 0) {
-      L->inv_L.alloc((size_t)inv64_bytes(n));
-      L->inv_U.alloc((size_t)inv64_bytes(n));
-    }
     // no refinement follows: U12 by substitution, the block inverses for the solves after it
     info = lu_factor<double>(c, static_cast<c128*>(Z), n, ldz, L->dinv_L.as<c128>(), L->dinv_U.as<c128>(), L->perm);
-    if (info == 0 && L->inv_U.p) {
-      diagonal_inverses<double>(c, true, static_cast<const c128*>(Z), n, ldz, L->dinv_L.as<c128>(), L->inv_L.as<c128>());
-      diagonal_inverses<double>(c, false, static_cast<const c128*>(Z), n, ldz, L->dinv_U.as<c128>(),
-                             L->inv_U.as<c128>());
+    if (info == 0 && inv64_bytes(n) > 0) {
+      const c128* A = static_cast<const c128*>(Z);
+      L->inv_L.alloc((size_t)inv64_bytes(n));
+      L->inv_U.alloc((size_t)inv64_bytes(n));
+      diagonal_inverses<double>(c, true, A, n, ldz, L->dinv_L.as<c128>(), L->inv_L.as<c128>());
+      diagonal_inverses<double>(c, false, A, n, ldz, L->dinv_U.as<c128>(), L->inv_U.as<c128>());
+      if (leaf_growth<double>(c, A, n, ldz, L->inv_L.as<c128>(), L->inv_U.as<c128>(), kInvBlock) <= kLeafGrowth) {
+        L->leaf = kInvBlock;
+      } else {
+        L->inv_L.release();
+        L->inv_U.release();
+      }
     }
   } else {
     L->dinv_L.alloc((size_t)nblk * kPanel * kPanel * sizeof(c64));
@@ -463,13 +497,8 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
       if (o.certify) matrix_certificate(true);
     }
     // the refined solves apply the factors through their diagonal-block inverses
-    const bool grow = inv_block(n) > kInvBlock;
     const size_t small = (size_t)((n + kInvBlock - 1) / kInvBlock) * kInvBlock * kInvBlock * sizeof(c64);
-    L->inv_L.alloc((size_t)inv_bytes(n));
-    L->inv_U.alloc((size_t)inv_bytes(n));
-    DevBuf inv_small;   // kInvBlock-row inverses, from which the level's are grown
-    if (grow) inv_small.alloc(small);
-    c64* invL = (grow ? inv_small : L->inv_L).as<c64>();
+    L->inv_L.alloc(small);
     bool factored = false;
     if (o.lu_pivoting == 0 && n >= 2048) {
       // symmetric matrix: no pivoting, half the trailing-update flops; kept when no
@@ -483,7 +512,7 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
       const bool symmetric = zmax > 0 && std::isfinite(zmax) && defect <= 1e-5 * zmax;
       if (symmetric) {
         info = lu_factor<float>(c, static_cast<c64*>(Zlow), n, ldzlow, L->dinv_L.as<c64>(), L->dinv_U.as<c64>(),
-                                L->perm, invL, true);
+                                L->perm, L->inv_L.as<c64>(), true);
         const double growth = absmax_upper<float>(c, static_cast<const c64*>(Zlow), n, ldzlow) / zmax;
         factored = info == 0 && std::isfinite(growth) && growth <= 1e3;
         L->sym_lu = factored ? 1 : 0;
@@ -498,17 +527,8 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
     }
     if (!factored)
       info = lu_factor<float>(c, static_cast<c64*>(Zlow), n, ldzlow, L->dinv_L.as<c64>(), L->dinv_U.as<c64>(),
-                              L->perm, invL);
-    const c64* A32 = static_cast<const c64*>(Zlow);
-    if (info == 0 && grow) grow_block_inverses(c, true, A32, n, ldzlow, invL, L->inv_L.as<c64>());
-    if (info == 0 && L->sym_lu) {
-      transpose_block_inverses(c, A32, n, ldzlow, L->inv_L.as<c64>(), L->inv_U.as<c64>());
-    } else if (info == 0) {
-      c64* invU = grow ? invL : L->inv_U.as<c64>();
-      diagonal_inverses<float>(c, false, A32, n, ldzlow, L->dinv_U.as<c64>(), invU);
-      if (grow) grow_block_inverses(c, false, A32, n, ldzlow, invU, L->inv_U.as<c64>());
-    }
-    if (grow) FOSB_HIP(hipStreamSynchronize(s));   // inv_small is read
+                              L->perm, L->inv_L.as<c64>());
+    if (info == 0) mixed_leaves(c, *L);
   }
   if (info != 0) fail(FOSB_E_SINGULAR, "exactly zero pivot at index %lld", (long long)(info - 1));
   upload(L->d_perm, L->perm, s);

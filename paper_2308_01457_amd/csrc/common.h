@@ -332,7 +332,8 @@ struct Level {
   std::vector<int32_t> perm;   // host: row permutation (position i holds original row perm[i])
   DevBuf d_perm;               // int32 [n]
   DevBuf dinv_L, dinv_U;       // inverted nb x nb diagonal blocks of L and U (LU precision)
-  DevBuf inv_L, inv_U;         // inverted diagonal blocks of L and U: MIXED inv_block(n) rows, FP64 (N >= kInv64MinN) kInvBlock
+  DevBuf inv_L, inv_U;         // inverted diagonal blocks of L and U, of `leaf` rows
+  int64_t leaf = 0;            // MIXED: inv_block(n) or kInvBlock; FP64: kInvBlock, or 0 without block inverses
   DevBuf u;                    // c128 [n_dirs][n]
   DevBuf W;                    // c128 [n_dirs][nt][3][6] RHS weights
   DevBuf qx;                   // double [3][6*nt] quadrature nodes (component-major)
@@ -441,9 +442,8 @@ void trsm_lower_unit_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<
                         cplx<T>* B, int64_t ldb, int64_t nrhs);
 // Inverses of the kInvBlock x kInvBlock diagonal blocks of the lower or the upper
 // factor (block b at inv + b kInvBlock^2, row-major, row stride kInvBlock; the
-// last block's slot is the identity outside its corner), and
-// out-of-place triangular solves of a whole factor that apply inverses (complex128
-// factors: of kInvBlock rows, complex64 ones of inv_block(n)) at the leaves:
+// last block's slot is the identity outside its corner), and out-of-place
+// triangular solves of a whole factor that apply inverses of ib rows at the leaves:
 // X <- T^{-1} B or (_ch) T^{-H} B, with B (n x nrhs) consumed as workspace.
 constexpr int kInvBlock = 256;
 // Rows of a leaf of those solves.  A narrow solve is a chain of launches, two
@@ -463,6 +463,18 @@ constexpr int64_t kInv64MinN = 2048;
 inline int64_t inv64_bytes(int64_t n) {
   return n < kInv64MinN ? 0 : (n + kInvBlock - 1) / kInvBlock * kInvBlock * kInvBlock * (int64_t)sizeof(c128);
 }
+// A product with an inverse X of a leaf T loses up to u || |X| |T| || where
+// substitution loses u, so leaves are inverted (FP64) or grown to inv_block(n) rows
+// (MIXED) only while that norm, the largest over the leaves of both factors, is at
+// most kLeafGrowth: 2e-12 of a leaf's solution in FP64 and 1e-3 in FP32, less than
+// a refinement sweep contracts, at the very worst.  The EFIE and PMCHWT levels measured (N = 2430 and 7680, k = 0.05 .. 30,
+// at interior resonances too) have 60 .. 2500 over 256 rows and 90 .. 7500 over 1024;
+// a sphere flattened to a twentieth has 9e5 and 1e6, and takes the other leaves.
+constexpr double kLeafGrowth = 16384.0;
+// That norm for inverses of ib rows; synchronises the stream.
+template <typename T>
+double leaf_growth(Context& ctx, const cplx<T>* A, int64_t n, int64_t lda, const cplx<T>* invL, const cplx<T>* invU,
+                   int64_t ib);
 // W (inv_bytes(n)) <- inverses of the inv_block(n)-row diagonal blocks from those of kInvBlock rows (S):
 // halves merged by products, on ctx's stream (uses solve_tmp).  inv_block(n) > kInvBlock.
 void grow_block_inverses(Context& ctx, bool lower, const c64* A, int64_t n, int64_t lda, const c64* S, c64* W);
@@ -476,16 +488,16 @@ template <typename T>
 void diagonal_inverses(Context& ctx, bool lower, const cplx<T>* A, int64_t n, int64_t lda, const cplx<T>* dinv,
                     cplx<T>* inv);
 template <typename T>
-void trsm_lower_unit_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t n, cplx<T>* B,
+void trsm_lower_unit_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t ib, int64_t n, cplx<T>* B,
                          int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs);
 template <typename T>
-void trsm_upper_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t n, cplx<T>* B,
+void trsm_upper_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t ib, int64_t n, cplx<T>* B,
                     int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs);
 template <typename T>
-void trsm_lower_unit_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t n, cplx<T>* B,
+void trsm_lower_unit_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t ib, int64_t n, cplx<T>* B,
                             int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs);
 template <typename T>
-void trsm_upper_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t n, cplx<T>* B,
+void trsm_upper_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t ib, int64_t n, cplx<T>* B,
                        int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs);
 void permute_rows_gather(hipStream_t s, const int32_t* perm, const c128* src, int64_t lds, c128* dst,
                          int64_t ldd, int64_t n, int64_t ncols);

@@ -2038,6 +2038,71 @@ void transpose_block_inverses(Context& ctx, const c64* A, int64_t n, int64_t lda
   FOSB_LAUNCH_CHECK();
 }
 
+// Largest entry of |X| |T| e over the diagonal blocks T (ib rows) of both factors
+// and their inverses X, e all ones (grid y: L, U): row sums v = |T| e, then |X| v.
+// A wavefront per row.
+template <typename T>
+__global__ __launch_bounds__(256) void k_leaf_rowsum(const cplx<T>* __restrict__ A, int64_t lda, int64_t n, int64_t ib,
+                                                     double* __restrict__ v, unsigned long long* __restrict__ top) {
+  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const bool upper = blockIdx.y == 1;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *top = 0ull;
+  if (i >= n) return;
+  const int64_t b0 = i / ib * ib, j0 = upper ? i : b0, j1 = upper ? min(n, b0 + ib) : i;
+  double s = 0.0;
+  for (int64_t j = j0 + lane; j < j1; j += 64) s += (double)cabs1(A[i * lda + j]);
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (lane == 0) v[blockIdx.y * n + i] = upper ? s : s + 1.0;
+}
+
+constexpr int kGrowthRows = 32;   // rows per workgroup of the second pass: one atomic each
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_leaf_growth(const cplx<T>* __restrict__ invL, const cplx<T>* __restrict__ invU,
+                                                     int64_t n, int64_t ib, const double* __restrict__ v,
+                                                     unsigned long long* __restrict__ top) {
+  __shared__ double red[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool upper = blockIdx.y == 1;
+  const int64_t r0 = (int64_t)blockIdx.x * kGrowthRows;
+  double m = 0.0;
+  bool nan = false;
+  for (int64_t i = r0 + wave; i < min(n, r0 + kGrowthRows); i += 4) {
+    const int64_t b0 = i / ib * ib, j0 = upper ? i : b0, j1 = upper ? min(n, b0 + ib) : i + 1;
+    const cplx<T>* x = (upper ? invU : invL) + i * ib - b0;
+    double s = 0.0;
+    for (int64_t j = j0 + lane; j < j1; j += 64) s += (double)cabs1(x[j]) * v[blockIdx.y * n + j];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    nan = nan || !(s >= 0.0);
+    m = fmax(m, s);
+  }
+  if (lane == 0) red[wave] = nan ? INFINITY : m;
+  __syncthreads();
+  if (threadIdx.x == 0)   // non-negative doubles order like their bits
+    atomicMax(top, (unsigned long long)__double_as_longlong(fmax(fmax(red[0], red[1]), fmax(red[2], red[3]))));
+}
+
+template <typename T>
+double leaf_growth(Context& ctx, const cplx<T>* A, int64_t n, int64_t lda, const cplx<T>* invL, const cplx<T>* invU,
+                   int64_t ib) {
+  DevBuf buf((size_t)(2 * n + 1) * sizeof(double));
+  double* v = buf.as<double>();
+  unsigned long long* top = reinterpret_cast<unsigned long long*>(v + 2 * n);
+  hipLaunchKernelGGL(k_leaf_rowsum<T>, dim3((unsigned)((n + 3) / 4), 2), dim3(256), 0, ctx.stream, A, lda, n, ib, v,
+                     top);
+  FOSB_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_leaf_growth<T>, dim3((unsigned)((n + kGrowthRows - 1) / kGrowthRows), 2), dim3(256), 0,
+                     ctx.stream, invL, invU, n, ib, v, top);
+  FOSB_LAUNCH_CHECK();
+  double h = 0.0;
+  FOSB_HIP(hipMemcpyAsync(&h, top, sizeof(h), hipMemcpyDeviceToHost, ctx.stream));
+  FOSB_HIP(hipStreamSynchronize(ctx.stream));
+  return h;
+}
+template double leaf_growth<float>(Context&, const c64*, int64_t, int64_t, const c64*, const c64*, int64_t);
+template double leaf_growth<double>(Context&, const c128*, int64_t, int64_t, const c128*, const c128*, int64_t);
+
 // B <- T^{-1} B for rows k0 .. k0 + n of the unit lower (LOWER) or upper factor,
 // k0 a multiple of NL: halves split at multiples of NL, coupled by a GEMM; a
 // leaf block is X = inv_b B_b, a product into tmp (NL x nrhs) copied back.
@@ -2107,45 +2172,40 @@ static void trsm_inv_ch_oop(Context& ctx, const cplx<T>* A, int64_t lda, const c
 }
 
 template <typename T>
-static int64_t leaf_rows(int64_t n) {
-  return sizeof(T) == 8 ? kInvBlock : inv_block(n);
-}
-
-template <typename T>
-void trsm_lower_unit_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t n, cplx<T>* B,
+void trsm_lower_unit_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t ib, int64_t n, cplx<T>* B,
                          int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
-  trsm_inv_oop<T, true>(ctx, A, lda, invL, leaf_rows<T>(n), 0, n, B, ldb, X, ldx, nrhs);
+  trsm_inv_oop<T, true>(ctx, A, lda, invL, ib, 0, n, B, ldb, X, ldx, nrhs);
 }
 template <typename T>
-void trsm_upper_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t n, cplx<T>* B,
+void trsm_upper_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t ib, int64_t n, cplx<T>* B,
                     int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
-  trsm_inv_oop<T, false>(ctx, A, lda, invU, leaf_rows<T>(n), 0, n, B, ldb, X, ldx, nrhs);
+  trsm_inv_oop<T, false>(ctx, A, lda, invU, ib, 0, n, B, ldb, X, ldx, nrhs);
 }
 
 template <typename T>
-void trsm_lower_unit_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t n, cplx<T>* B,
+void trsm_lower_unit_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invL, int64_t ib, int64_t n, cplx<T>* B,
                             int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
-  trsm_inv_ch_oop<T, true>(ctx, A, lda, invL, leaf_rows<T>(n), 0, n, B, ldb, X, ldx, nrhs);
+  trsm_inv_ch_oop<T, true>(ctx, A, lda, invL, ib, 0, n, B, ldb, X, ldx, nrhs);
 }
 template <typename T>
-void trsm_upper_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t n, cplx<T>* B,
+void trsm_upper_inv_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* invU, int64_t ib, int64_t n, cplx<T>* B,
                        int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {
-  trsm_inv_ch_oop<T, false>(ctx, A, lda, invU, leaf_rows<T>(n), 0, n, B, ldb, X, ldx, nrhs);
+  trsm_inv_ch_oop<T, false>(ctx, A, lda, invU, ib, 0, n, B, ldb, X, ldx, nrhs);
 }
 
 template void diagonal_inverses<float>(Context&, bool, const c64*, int64_t, int64_t, const c64*, c64*);
 template void diagonal_inverses<double>(Context&, bool, const c128*, int64_t, int64_t, const c128*, c128*);
-template void trsm_lower_unit_inv<double>(Context&, const c128*, int64_t, const c128*, int64_t, c128*, int64_t, c128*,
+template void trsm_lower_unit_inv<double>(Context&, const c128*, int64_t, const c128*, int64_t, int64_t, c128*, int64_t, c128*,
                                           int64_t, int64_t);
-template void trsm_upper_inv<double>(Context&, const c128*, int64_t, const c128*, int64_t, c128*, int64_t, c128*,
+template void trsm_upper_inv<double>(Context&, const c128*, int64_t, const c128*, int64_t, int64_t, c128*, int64_t, c128*,
                                      int64_t, int64_t);
-template void trsm_lower_unit_inv_ch<double>(Context&, const c128*, int64_t, const c128*, int64_t, c128*, int64_t,
+template void trsm_lower_unit_inv_ch<double>(Context&, const c128*, int64_t, const c128*, int64_t, int64_t, c128*, int64_t,
                                              c128*, int64_t, int64_t);
-template void trsm_upper_inv_ch<double>(Context&, const c128*, int64_t, const c128*, int64_t, c128*, int64_t, c128*,
+template void trsm_upper_inv_ch<double>(Context&, const c128*, int64_t, const c128*, int64_t, int64_t, c128*, int64_t, c128*,
                                         int64_t, int64_t);
-template void trsm_lower_unit_inv<float>(Context&, const c64*, int64_t, const c64*, int64_t, c64*, int64_t, c64*,
+template void trsm_lower_unit_inv<float>(Context&, const c64*, int64_t, const c64*, int64_t, int64_t, c64*, int64_t, c64*,
                                          int64_t, int64_t);
-template void trsm_upper_inv<float>(Context&, const c64*, int64_t, const c64*, int64_t, c64*, int64_t, c64*, int64_t,
+template void trsm_upper_inv<float>(Context&, const c64*, int64_t, const c64*, int64_t, int64_t, c64*, int64_t, c64*, int64_t,
                                     int64_t);
 
 }  // namespace fosb

@@ -42,3 +42,51 @@ def test_fp64_factors_are_backward_stable():
     print(f"[gpu] ||Z - LU|| = {err:.2e} (bound {bound:.2e})", flush=True)
     assert err <= bound
     lv.close()
+
+
+@pytest.mark.parametrize("nrhs", [1, 40])
+def test_fp64_solves_are_backward_stable(nrhs):
+    """Solutions of Z X = B and Z^H X = B with B = Z Y, so that X = Y of order one
+    does not hide the loss of a leaf's inverse: |Z X - B| <= 1e-13 |Z| |X| by
+    column, the residual bound of the other FP64 solves."""
+    import torch
+    from paper_2308_01457_amd import fosb
+    ctx = fosb.Context(0)
+    m = fosb.Mesh(ctx, *workloads.geodesic_sphere(9))
+    Z = _matrix(torch, ctx.torch_device, m.n_edges, 256, 0.077)
+    lv = fosb.Level(ctx, m, 1.0, Z.clone(), fosb.FP64)
+    g = torch.Generator().manual_seed(nrhs)
+    Y = torch.randn((m.n_edges, nrhs), dtype=torch.complex128, generator=g).to(ctx.torch_device)
+    for adjoint in (False, True):
+        A = Z.mH.contiguous() if adjoint else Z
+        B = torch.matmul(A, Y)
+        X = B.clone()
+        (lv.solve_adjoint if adjoint else lv.solve)(X)
+        worst = float(((torch.matmul(A, X) - B).norm(dim=0) / (A.norm() * X.norm(dim=0))).max())
+        print(f"[gpu] FP64 solves, {nrhs} columns, adjoint {adjoint}: residual {worst:.1e}", flush=True)
+        assert worst < 1e-13
+    lv.close()
+
+
+@pytest.mark.parametrize("nrhs", [1, 40])
+def test_mixed_solves_keep_small_leaves(nrhs):
+    """A block of 1024 rows whose inverse, (1 + theta)^1023 = 5e5, is past what a
+    mixed level accepts: its leaves stay at 256 rows and the refinement converges
+    as with any well-conditioned matrix (pivoted factors; the symmetric ones
+    fall back on the graded matrices of the symmetric factorisation's tests)."""
+    import torch
+    from paper_2308_01457_amd import fosb
+    ctx = fosb.Context(0)
+    m = fosb.Mesh(ctx, *workloads.geodesic_sphere(9))
+    Z = _matrix(torch, ctx.torch_device, m.n_edges, 1024, 0.013)
+    lv = fosb.Level(ctx, m, 1.0, Z, fosb.MIXED)
+    g = torch.Generator().manual_seed(nrhs)
+    Y = torch.randn((m.n_edges, nrhs), dtype=torch.complex128, generator=g).to(ctx.torch_device)
+    for adjoint in (False, True):
+        A = Z.mH.contiguous() if adjoint else Z
+        B = torch.matmul(A, Y)
+        X, st = B.clone(), fosb.Stats()
+        (lv.solve_adjoint if adjoint else lv.solve)(X, st)
+        assert float(((torch.matmul(A, X) - B).norm(dim=0) / (A.norm() * X.norm(dim=0))).max()) < 1e-9
+        assert st.ir_sweeps <= 3
+    lv.close()
