@@ -246,7 +246,10 @@ fosb_status fosb_assemble_pmchwt(fosb_context* ctx, const fosb_mesh* mesh, doubl
  *                    blocks (kept by the level: 1024 rows, 256 below N = 2048).
  *                    Their large products run on the fp16 matrix cores, every
  *                    operand split into two fp16 parts (22 bits) and accumulated
- *                    in FP32: no less accurate than FP32 products.
+ *                    in FP32.  The error of a product's column is below that of
+ *                    FP32 products in the norm (0.6 of it on normal random
+ *                    operands), not entry by entry: an entry much smaller than
+ *                    the column's largest terms may keep fewer bits.
  *                    Z may be NULL: the level then assembles the matrix in FP64
  *                    column bands straight into Zlow (rounded to complex64) and
  *                    re-assembles FP64 bands of Z for every refinement residual

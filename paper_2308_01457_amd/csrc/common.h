@@ -402,8 +402,7 @@ void gemm_ch(Context& ctx, int64_t M, int64_t N, int64_t K, double alpha, const 
 // tiles above the diag_nb-wide diagonal blocks.
 // split_scale (or split_scale_diag, for A = L and B = D L^T with D on the
 // diagonal of the given block) sets the scaling along K before the packing.
-void split_scale(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, const c64* B, int64_t ldb,
-                 int64_t N, int64_t K);
+void split_scale(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K);
 void split_scale_diag(Context& ctx, const c64* A, int64_t lda, int64_t K);
 void split_pack_a(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K);
 void split_pack_b(Context& ctx, const c64* B, int64_t ldb, int64_t N, int64_t K);

@@ -703,7 +703,7 @@ static void gemm_launch(Context& ctx, int64_t M, int64_t N, int64_t K, double al
         const int64_t kn = std::min(kc, Kp - k0);
         const cplx<T>* Ak = CONJ_A ? A + k0 * lda : A + k0;
         const cplx<T>* Bk = B + k0 * ldb;
-        split_scale(ctx, Ak, lda, CONJ_A, M, Bk, ldb, N, kn);
+        split_scale(ctx, Ak, lda, CONJ_A, M, kn);
         split_pack_a(ctx, Ak, lda, CONJ_A, M, kn);
         split_pack_b(ctx, Bk, ldb, N, kn);
         split_gemm(ctx, 0, M, N, kn, alpha, k0 == 0 ? beta : 1.0, C, ldc, 0);

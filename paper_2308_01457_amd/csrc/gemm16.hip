@@ -3,15 +3,23 @@
 // Every FP32 operand x, scaled by powers of two, is the sum of two fp16 numbers:
 // h = fp16(x), l = fp16(x - h).  h and l carry 11 bits each, so h + l differs
 // from x by at most 2^-22 |x| (entries 2^-13 below their row's largest and
-// smaller: by 2^-25 in scaled units, 2^-35 of that largest entry).  Two exact
-// scalings keep the entries in the short range of fp16: A's column k and B's
-// row k are multiplied by 2^e_k and 2^-e_k so that their largest entries are
-// alike (a matrix whose unknowns have different units is graded along k, and
-// its small entries of A meet large ones of B), and then each row of A and
-// column of B is brought to a largest entry in [2^10, 2^11).  A real product is then the sum of three fp16 products, l h, h l and h h, accumulated
-// in FP32 by v_mfma_f32_32x32x16_f16; the complex product takes three real ones
-// (3M, as in gemm.hip), whose operand sums re + im are formed in FP32 before
-// they are split.
+// smaller: by 2^-25 in scaled units, 2^-35 of that largest entry).  Exact
+// scalings keep the entries in the short range of fp16: A's column k is
+// multiplied by 2^e_k, which brings its largest entry to [1, 2), and B's row k by
+// 2^-e_k, so that an entry of B weighs as the largest term it enters (a matrix
+// whose unknowns have different units is graded along k); then each row of A and
+// column of B is brought to a largest entry in [2^10, 2^11).  The scaling along k
+// comes from A alone: one from B too would let a large column of B take the
+// bits of the others.  In L D L^T both operands are scaled by the half exponent of
+// d_k instead.  A real product is then the sum of three fp16 products, l h, h l
+// and h h, accumulated in FP32 by v_mfma_f32_32x32x16_f16; the complex product
+// takes three real ones (3M, as in gemm.hip), whose operand sums re + im are
+// formed in FP32 before they are split.
+//
+// The error of an entry of column j is thus below about K 2^-22 times the
+// largest term |a_ik b_kj| of that column over all rows i: normwise by column,
+// not entry by entry as with FP32 products, where a row of A with small entries
+// against large ones of other rows keeps its own relative accuracy.
 //
 // Error: one rounding per 16 of K replaces one per entry of K, which more than
 // makes up for the two missing bits of the operands.  Against 64 bits on normal
@@ -46,93 +54,112 @@ struct SplitSrc {
   int conj;
 };
 
-__device__ __forceinline__ float mag(c64 v) { return fmaxf(fabsf(v.re), fabsf(v.im)); }
+// Exponents of magnitudes: floor(log2 max(|re|, |im|)), denormals included; below
+// kLowExp for zero, above kHighExp for infinities and NaN, also after a scaling.
+constexpr int kZeroExp = -(1 << 20), kLowExp = -(1 << 19);
+constexpr int kInfExp = 1 << 20, kHighExp = 1 << 19;
+// Scaling along K of a term that adds nothing (A's column is all zero).
+constexpr int kNoTerm = INT32_MIN;
 
-// Largest |re|, |im| along r for each k, as float bits: workgroup (x, y) takes
-// 64 k and 512 r; atomicMax of non-negative float bits is independent of order.
-__global__ __launch_bounds__(256) void k_split_kmax(SplitSrc s, int64_t R, int64_t K, unsigned* __restrict__ mx) {
-  __shared__ float red[4][64];
+__device__ __forceinline__ int mag_exp(c64 v) {
+  const unsigned m = max(__float_as_uint(v.re) & 0x7fffffffu, __float_as_uint(v.im) & 0x7fffffffu);
+  const int e = m >= 0x00800000u ? (int)(m >> 23) - 127 : (31 - __clz((int)m)) - 149;
+  return m == 0u ? kZeroExp : m >= 0x7f800000u ? kInfExp : e;
+}
+
+// Exponent of an entry scaled along K.  A term without effect counts nothing
+// (a large entry of B there would take the bits of its column's others),
+// unless the entry is not finite.
+__device__ __forceinline__ int scaled_exp(c64 v, int ke, int sign) {
+  const int e = mag_exp(v);
+  return ke == kNoTerm ? (e > kHighExp ? e : kZeroExp) : e + sign * ke;
+}
+
+__device__ __forceinline__ int wave_max_i32(int m) {
+  for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+  return m;
+}
+
+// Largest exponent along r for each k: workgroup (x, y) takes 64 k and 512 r;
+// the maximum is independent of order.
+__global__ __launch_bounds__(256) void k_split_kmax(SplitSrc s, int64_t R, int64_t K, int* __restrict__ mx) {
+  __shared__ int red[4][64];
   const int64_t k0 = (int64_t)blockIdx.x * 64, r0 = (int64_t)blockIdx.y * 512, r1 = min(R, r0 + 512);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (s.ks == 1) {   // neighbouring lanes along k
-    float m = 0.f;
+    int m = kZeroExp;
     if (k0 + lane < K)
-      for (int64_t r = r0 + wave; r < r1; r += 4) m = fmaxf(m, mag(s.p[r * s.rs + k0 + lane]));
+      for (int64_t r = r0 + wave; r < r1; r += 4) m = max(m, mag_exp(s.p[r * s.rs + k0 + lane]));
     red[wave][lane] = m;
     __syncthreads();
-    if (wave == 0 && k0 + lane < K) {
-      m = fmaxf(fmaxf(m, red[1][lane]), fmaxf(red[2][lane], red[3][lane]));
-      atomicMax(mx + k0 + lane, __float_as_uint(m));
-    }
+    if (wave == 0 && k0 + lane < K)
+      atomicMax(mx + k0 + lane, max(max(m, red[1][lane]), max(red[2][lane], red[3][lane])));
     return;
   }
   for (int q = wave; q < 64; q += 4) {   // neighbouring lanes along r
     const int64_t k = k0 + q;
     if (k >= K) break;
-    float m = 0.f;
-    for (int64_t r = r0 + lane; r < r1; r += 64) m = fmaxf(m, mag(s.p[r * s.rs + k * s.ks]));
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    if (lane == 0) atomicMax(mx + k, __float_as_uint(m));
+    int m = kZeroExp;
+    for (int64_t r = r0 + lane; r < r1; r += 64) m = max(m, mag_exp(s.p[r * s.rs + k * s.ks]));
+    m = wave_max_i32(m);
+    if (lane == 0) atomicMax(mx + k, m);
   }
 }
 
-// e_k from the maxima of A's column k and B's row k: half their exponents'
-// difference; 0 where either is zero, denormal or not finite.
-__global__ void k_split_kexp(const unsigned* __restrict__ ma, const unsigned* __restrict__ mb, int64_t K,
-                             int* __restrict__ ke) {
+// e_k from the largest exponent of A's column k: brings it to 0; 0 where the
+// column is not finite.
+__global__ void k_split_kexp(const int* __restrict__ ma, int64_t K, int* __restrict__ ke) {
   const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (k >= K) return;
-  const int a = (int)(ma[k] >> 23), b = (int)(mb[k] >> 23);
-  ke[k] = (a == 0 || a == 255 || b == 0 || b == 255) ? 0 : (b - a) >> 1;
+  ke[k] = ma[k] < kLowExp ? kNoTerm : ma[k] > kHighExp ? 0 : -ma[k];
 }
 
 // e_k for L times D L^T, D on a matrix's diagonal: half the exponent of d_k.
 __global__ void k_split_kexp_diag(const c64* __restrict__ A, int64_t lda, int64_t K, int* __restrict__ ke) {
   const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (k >= K) return;
-  const int e = (int)(__float_as_uint(mag(A[k * lda + k])) >> 23);
-  ke[k] = (e == 0 || e == 255) ? 0 : (e - 127) >> 1;
+  const int e = mag_exp(A[k * lda + k]);
+  ke[k] = (e < kLowExp || e > kHighExp) ? 0 : e >> 1;
 }
 
-// Largest |re|, |im| of each row, scaled by 2^(sign e_k), as float bits:
-// workgroup (x, y) takes 32 rows and 512 of K.
+// Largest exponent of each row, scaled along K by 2^(sign e_k): workgroup
+// (x, y) takes 32 rows and 512 of K.
 __global__ __launch_bounds__(256) void k_split_max(SplitSrc s, int64_t R, int64_t K, const int* __restrict__ ke,
-                                                   int sign, unsigned* __restrict__ mx) {
-  __shared__ unsigned red[8][32];
+                                                   int sign, int* __restrict__ mx) {
+  __shared__ int red[8][32];
   const int64_t r0 = (int64_t)blockIdx.x * 32, k0 = (int64_t)blockIdx.y * 512;
   if (s.ks == 1) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int q = wave; q < 32; q += 4) {
       const int64_t r = r0 + q;
-      float m = 0.f;
+      int m = kZeroExp;
       if (r < R)
         for (int64_t k = k0 + lane; k < min(K, k0 + 512); k += 64)
-          m = fmaxf(m, ldexpf(mag(s.p[r * s.rs + k]), sign * ke[k]));
-      for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-      if (lane == 0 && r < R) atomicMax(mx + r, __float_as_uint(m));
+          m = max(m, scaled_exp(s.p[r * s.rs + k], ke[k], sign));
+      m = wave_max_i32(m);
+      if (lane == 0 && r < R) atomicMax(mx + r, m);
     }
     return;
   }
   const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
   const int64_t r = r0 + c;
-  float m = 0.f;
+  int m = kZeroExp;
   if (r < R)
     for (int64_t k = k0 + g; k < min(K, k0 + 512); k += 8)
-      m = fmaxf(m, ldexpf(mag(s.p[r * s.rs + k * s.ks]), sign * ke[k]));
-  red[g][c] = __float_as_uint(m);
+      m = max(m, scaled_exp(s.p[r * s.rs + k * s.ks], ke[k], sign));
+  red[g][c] = m;
   __syncthreads();
   if (g == 0 && r < R) {
-    unsigned b = red[0][c];
+    int b = red[0][c];
     for (int q = 1; q < 8; ++q) b = max(b, red[q][c]);
     atomicMax(mx + r, b);
   }
 }
 
-// Power of two that scales a row with the largest magnitude m (float bits); a
-// zero, denormal or non-finite maximum keeps its entries as they are.
-__device__ __forceinline__ int split_exp(unsigned bits) {
-  const int e = (int)(bits >> 23);
-  return (e == 0 || e == 255) ? 0 : kTargetExp - (e - 127);
+// Power of two that scales a row with the largest exponent m; the entries of a
+// zero or a not finite row stay as they are.
+__device__ __forceinline__ int split_exp(int m) {
+  return (m < kLowExp || m > kHighExp) ? 0 : kTargetExp - m;
 }
 
 __device__ __forceinline__ void split2(float x, _Float16& h, _Float16& l) {
@@ -147,7 +174,7 @@ __device__ __forceinline__ void split2(float x, _Float16& h, _Float16& l) {
 // 256 B per k.
 __global__ __launch_bounds__(256) void k_split_pack(SplitSrc s, int64_t R, int64_t K, int64_t nkb,
                                                     const int* __restrict__ ke, int sign,
-                                                    const unsigned* __restrict__ mx, h8* __restrict__ P) {
+                                                    const int* __restrict__ mx, h8* __restrict__ P) {
   const int64_t blk = blockIdx.y, kb = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (kb >= nkb) return;
   const int lane = threadIdx.x & 63;
@@ -158,9 +185,11 @@ __global__ __launch_bounds__(256) void k_split_pack(SplitSrc s, int64_t R, int64
   for (int q = 0; q < 8; ++q) {
     c64 v{0.f, 0.f};
     int eq = e;
-    if (row < R && k0 + q < K) {
+    if (row < R && k0 + q < K) {   // both loads at once
+      const int kq = ke[k0 + q];
       v = s.p[row * s.rs + (k0 + q) * s.ks];
-      eq += sign * ke[k0 + q];
+      v = kq == kNoTerm && mag_exp(v) <= kHighExp ? c64{0.f, 0.f} : v;
+      eq += kq == kNoTerm ? 0 : sign * kq;
     }
     const float re = ldexpf(v.re, eq), im = ldexpf(s.conj ? -v.im : v.im, eq);
     _Float16 h, l;
@@ -179,9 +208,9 @@ __global__ __launch_bounds__(256) void k_split_pack(SplitSrc s, int64_t R, int64
   for (int p = 0; p < kPlanes; ++p) d[p * kChunk] = o[p];
 }
 
-__global__ void k_split_zero(unsigned* p, int64_t n) {
+__global__ void k_split_zero(int* p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0u;
+  if (i < n) p[i] = kZeroExp;
 }
 
 // One K block (16 deep) of a tile into LDS: 8 blocks of A, 4 of B, 6 planes
@@ -238,8 +267,8 @@ __device__ __forceinline__ void multiply_block(const h8* __restrict__ s, int wr,
 // With diag_nb > 0 the tiles entirely above the diag_nb-wide diagonal blocks
 // (rows and columns counted from the same origin) are left out.
 __global__ __launch_bounds__(512, 2) void k_gemm_split(int64_t M, int64_t N, int64_t nkb, float alpha,
-                                                       const h8* __restrict__ A, const unsigned* __restrict__ ma,
-                                                       const h8* __restrict__ B, const unsigned* __restrict__ mb,
+                                                       const h8* __restrict__ A, const int* __restrict__ ma,
+                                                       const h8* __restrict__ B, const int* __restrict__ mb,
                                                        float beta, c64* __restrict__ C, int64_t ldc, int nM, int nN,
                                                        int diag_nb) {
   __shared__ __align__(16) h8 s0[12 * kPlanes * kChunk];
@@ -327,32 +356,26 @@ static SplitSrc source_a(const c64* A, int64_t lda, bool conj_trans) {
   return conj_trans ? SplitSrc{A, 1, lda, 1} : SplitSrc{A, lda, 1, 0};
 }
 
-static void zero_max(hipStream_t st, unsigned* p, int64_t n) {
+static void zero_max(hipStream_t st, int* p, int64_t n) {
   hipLaunchKernelGGL(k_split_zero, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, n);
   FOSB_LAUNCH_CHECK();
 }
 
-static void kmax(hipStream_t st, const SplitSrc& s, int64_t R, int64_t K, unsigned* mx) {
-  hipLaunchKernelGGL(k_split_kmax, dim3((unsigned)((K + 63) / 64), (unsigned)((R + 511) / 512)), dim3(256), 0, st, s, R,
-                     K, mx);
-  FOSB_LAUNCH_CHECK();
-}
-
-void split_scale(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, const c64* B, int64_t ldb,
-                 int64_t N, int64_t K) {
+void split_scale(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K) {
   hipStream_t st = ctx.stream;
-  ctx.pack_ke.reserve((size_t)K * 3 * sizeof(int));
+  ctx.pack_ke.reserve((size_t)K * 2 * sizeof(int));
   int* ke = ctx.pack_ke.as<int>();
-  unsigned* ma = reinterpret_cast<unsigned*>(ke + K);
-  zero_max(st, ma, 2 * K);
-  kmax(st, source_a(A, lda, conj_trans), M, K, ma);
-  kmax(st, SplitSrc{B, 1, ldb, 0}, N, K, ma + K);
-  hipLaunchKernelGGL(k_split_kexp, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, ma, ma + K, K, ke);
+  int* ma = ke + K;
+  zero_max(st, ma, K);
+  hipLaunchKernelGGL(k_split_kmax, dim3((unsigned)((K + 63) / 64), (unsigned)((M + 511) / 512)), dim3(256), 0, st,
+                     source_a(A, lda, conj_trans), M, K, ma);
+  FOSB_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_split_kexp, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, ma, K, ke);
   FOSB_LAUNCH_CHECK();
 }
 
 void split_scale_diag(Context& ctx, const c64* A, int64_t lda, int64_t K) {
-  ctx.pack_ke.reserve((size_t)K * 3 * sizeof(int));
+  ctx.pack_ke.reserve((size_t)K * 2 * sizeof(int));
   hipLaunchKernelGGL(k_split_kexp_diag, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, ctx.stream, A, lda, K,
                      ctx.pack_ke.as<int>());
   FOSB_LAUNCH_CHECK();
@@ -363,15 +386,15 @@ static void pack(Context& ctx, const SplitSrc& s, int64_t R, int64_t K, int sign
                  DevBuf& mx) {
   const int64_t nkb = (K + 15) / 16;
   buf.reserve((size_t)(nblk * nkb) * kPlanes * kChunk * sizeof(h8));
-  mx.reserve((size_t)R * sizeof(unsigned));
+  mx.reserve((size_t)R * sizeof(int));
   hipStream_t st = ctx.stream;
   const int* ke = ctx.pack_ke.as<int>();
-  zero_max(st, mx.as<unsigned>(), R);
+  zero_max(st, mx.as<int>(), R);
   hipLaunchKernelGGL(k_split_max, dim3((unsigned)((R + 31) / 32), (unsigned)((K + 511) / 512)), dim3(256), 0, st, s, R,
-                     K, ke, sign, mx.as<unsigned>());
+                     K, ke, sign, mx.as<int>());
   FOSB_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_split_pack, dim3((unsigned)((nkb + 3) / 4), (unsigned)nblk), dim3(256), 0, st, s, R, K, nkb, ke,
-                     sign, mx.as<unsigned>(), buf.as<h8>());
+                     sign, mx.as<int>(), buf.as<h8>());
   FOSB_LAUNCH_CHECK();
 }
 
@@ -393,8 +416,8 @@ void split_gemm(Context& ctx, int64_t row0, int64_t M, int64_t N, int64_t K, dou
   if (nM * nN > INT32_MAX / 2) fail(FOSB_E_UNSUPPORTED, "product of %lld x %lld", (long long)M, (long long)N);
   const int64_t grid = std::min<int64_t>((nM * nN + 7) / 8 * 8, std::max<int64_t>(8, ctx.n_cu / 8 * 8));
   hipLaunchKernelGGL(k_gemm_split, dim3((unsigned)grid), dim3(512), 0, ctx.stream, M, N, nkb, (float)alpha,
-                     ctx.pack_a.as<h8>() + row0 / 32 * nkb * (kPlanes * kChunk), ctx.pack_ma.as<unsigned>() + row0,
-                     ctx.pack_b.as<h8>(), ctx.pack_mb.as<unsigned>(), (float)beta, C, ldc, (int)nM, (int)nN, diag_nb);
+                     ctx.pack_a.as<h8>() + row0 / 32 * nkb * (kPlanes * kChunk), ctx.pack_ma.as<int>() + row0,
+                     ctx.pack_b.as<h8>(), ctx.pack_mb.as<int>(), (float)beta, C, ldc, (int)nM, (int)nN, diag_nb);
   FOSB_LAUNCH_CHECK();
 }
 

@@ -1,0 +1,90 @@
+"""Wide mixed solves, whose coupling products run on the fp16 matrix cores: from 256
+columns and 256 of K on, once the 256 x 128 tiles cover half of the compute
+units.  At N = 7680 the largest coupling has 4096 rows (symmetric factors, leaves of
+1024) or 3840 (the pivoted adjoint, leaves of 256), so 1100 columns, which end
+inside a tile, are enough."""
+
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+NRHS = 1100
+
+
+@pytest.fixture(scope="module")
+def fz():
+    import torch
+    from paper_2308_01457_amd import fosb
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert (3840 // 256) * -(-NRHS // 128) >= cu // 2
+    ctx = fosb.Context(0)
+    return fosb, ctx, torch, fosb.Mesh(ctx, *workloads.geodesic_sphere(16))
+
+
+def _rhs(torch, dev, n, seed):
+    g = torch.Generator().manual_seed(seed)
+    return torch.randn((n, NRHS), dtype=torch.complex128, generator=g).to(dev)
+
+
+def _solve(lv, adjoint, B):
+    X = B.clone()
+    (lv.solve_adjoint if adjoint else lv.solve)(X)
+    return X
+
+
+@pytest.mark.parametrize("pivoting", [0, 1])
+def test_columns_of_any_magnitude(fz, pivoting):
+    """Right-hand sides of magnitudes 1e-12 .. 1e12 by column, with the EFIE matrix:
+    |Z X - B| <= 1e-9 |Z| |X| by column."""
+    fosb, ctx, torch, m = fz
+    Z = fosb.assemble(ctx, m, 2.0)
+    lv = fosb.Level(ctx, m, 2.0, Z, fosb.MIXED, opts=fosb.opts_default(lu_pivoting=pivoting, ir_tol=1e-12))
+    B = _rhs(torch, Z.device, m.n_edges, 1)
+    B = B * torch.logspace(-12, 12, NRHS, dtype=torch.float64, device=B.device)[None, :]
+    for adjoint in (False, True):
+        X = _solve(lv, adjoint, B)
+        R = torch.matmul(Z.mH.contiguous() if adjoint else Z, X) - B
+        worst = float((R.norm(dim=0) / (Z.norm() * X.norm(dim=0))).max())
+        print(f"[gpu] {NRHS} columns, pivoting {pivoting}, adjoint {adjoint}: residual {worst:.1e}", flush=True)
+        assert worst < 1e-9
+    lv.close()
+
+
+@pytest.mark.parametrize("pivoting", [0, 1])
+def test_unused_rows_take_no_bits(fz, pivoting):
+    """Z = diag(A, 1e-15 I): the last 2048 unknowns, 1e15 times the others, meet zero
+    columns in every coupling product.  Without refinement the others solve A x = b
+    to the rounding of an FP32 elimination: |A x - b| <= h 2^-24 |A| |x| by column."""
+    fosb, ctx, torch, m = fz
+    n, h = m.n_edges, m.n_edges - 2048
+    g = torch.Generator().manual_seed(5)
+    A = torch.randn((h, h), dtype=torch.complex128, generator=g).to(ctx.torch_device)
+    A = (A + A.T) / h ** 0.5 + 4.0 * torch.eye(h, dtype=A.dtype, device=A.device)
+    Z = 1e-15 * torch.eye(n, dtype=A.dtype, device=A.device)
+    Z[:h, :h] = A
+    lv = fosb.Level(ctx, m, 1.0, Z, fosb.MIXED, opts=fosb.opts_default(lu_pivoting=pivoting, ir_max_sweeps=0))
+    B = _rhs(torch, Z.device, n, 2)
+    for adjoint in (False, True):
+        x, b = _solve(lv, adjoint, B)[:h], B[:h]
+        R = torch.matmul(A.mH.contiguous() if adjoint else A, x) - b
+        worst = float((R.norm(dim=0) / (A.norm() * x.norm(dim=0))).max())
+        print(f"[gpu] unused rows, pivoting {pivoting}, adjoint {adjoint}: residual {worst:.1e}", flush=True)
+        assert worst <= h * 2.0 ** -24
+    lv.close()
+
+
+def test_non_finite_entries_spread(fz):
+    """A right-hand side column with an infinity or a NaN gives no finite column (or
+    no convergence), and zero columns stay zero."""
+    fosb, ctx, torch, m = fz
+    Z = fosb.assemble(ctx, m, 2.0)
+    lv = fosb.Level(ctx, m, 2.0, Z, fosb.MIXED, opts=fosb.opts_default(ir_max_sweeps=0))
+    B = _rhs(torch, Z.device, m.n_edges, 3)
+    B[7, 3], B[9, 5], B[:, 8] = float("inf"), float("nan"), 0.0
+    X = _solve(lv, False, B)
+    bad = ~torch.isfinite(torch.view_as_real(X)).all(dim=2).all(dim=0)
+    assert bool(bad[3]) and bool(bad[5]) and int(bad.sum()) == 2
+    assert float(X[:, 8].abs().max()) == 0.0
+    lv.close()
