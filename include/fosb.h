@@ -177,8 +177,8 @@ fosb_status fosb_context_synchronize(fosb_context* ctx);
  * pointer may be NULL). */
 fosb_status fosb_context_memory(fosb_context* ctx, int64_t* n_device_allocs, int64_t* bytes_cached,
                                 int64_t* bytes_in_use);
-/* Waits for the context's streams and returns every cached (unused) block to
- * the device. */
+/* Waits for the context's streams and returns every cached (unused) block, and
+ * the packed operands of wide complex64 products, to the device. */
 fosb_status fosb_context_trim(fosb_context* ctx);
 
 /* ---------------------------------------------------------------- mesh */

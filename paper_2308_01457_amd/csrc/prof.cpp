@@ -101,7 +101,9 @@ bool& thread_no_alloc() {
 Context::Context() {
   for (DevBuf& b : scratch) b.home = pool;
   for (DevBuf& b : ss) b.home = pool;
-  for (DevBuf* b : {&solve_tmp, &counters, &small, &norms, &splitk, &tune_out, &pack_a, &pack_ma, &pack_b, &pack_mb, &pack_ke}) b->home = pool;
+  for (DevBuf* b : {&solve_tmp, &counters, &small, &norms, &splitk, &tune_out, &pack_a, &pack_ma, &pack_b, &pack_mb,
+                    &pack_ke})
+    b->home = pool;
 }
 
 static void for_each_context(Context& c, const std::function<void(Context&)>& f) {
@@ -122,7 +124,10 @@ void pool_totals(Context& ctx, int64_t& n_allocs, int64_t& cached, int64_t& live
 }
 
 void pool_trim(Context& ctx) {
-  for_each_context(ctx, [&](Context& c) { c.pool->trim(); });
+  for_each_context(ctx, [&](Context& c) {
+    for (DevBuf* b : {&c.pack_a, &c.pack_ma, &c.pack_b, &c.pack_mb, &c.pack_ke}) b->release();
+    c.pool->trim();
+  });
 }
 
 // ------------------------------------------------------------------ child contexts

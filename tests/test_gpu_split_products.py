@@ -75,6 +75,22 @@ def test_unused_rows_take_no_bits(fz, pivoting):
     lv.close()
 
 
+def test_trim_returns_packed_operands(fz):
+    """The coupling of 3584 by 4096 packs at least 12 * 3584 * 4096 bytes, which a
+    trim gives back; solves go on afterwards with the same result."""
+    fosb, ctx, torch, m = fz
+    Z = fosb.assemble(ctx, m, 2.0)
+    lv = fosb.Level(ctx, m, 2.0, Z, fosb.MIXED)
+    B = _rhs(torch, Z.device, m.n_edges, 4)
+    X = _solve(lv, False, B)
+    before = ctx.memory()["bytes_in_use"]
+    ctx.trim()
+    after = ctx.memory()
+    assert after["bytes_in_use"] <= before - 12 * 3584 * 4096 and after["bytes_cached"] == 0
+    assert torch.equal(X, _solve(lv, False, B))
+    lv.close()
+
+
 def test_non_finite_entries_spread(fz):
     """A right-hand side column with an infinity or a NaN gives no finite column (or
     no convergence), and zero columns stay zero."""
