@@ -394,7 +394,7 @@ static double first_moment_tol(const Level& L) { return L.sym_lu ? 0.1 : 1.0; }
 
 // Leaf inverses of a MIXED level whose factors and kInvBlock-row inverses of L
 // exist: those of U, and from N = 2048 on both grown to inv_block(n) rows, unless
-// the grown ones lose too much (kLeafGrowth).
+// the grown ones lose too much (kLeafGrowth) or the device has no room for them.
 static void mixed_leaves(Context& c, Level& L) {
   const int64_t n = L.n, ib = inv_block(n);
   const c64* A = static_cast<const c64*>(L.Zlow);
@@ -403,15 +403,17 @@ static void mixed_leaves(Context& c, Level& L) {
     L.inv_U.alloc(L.inv_L.bytes);
     diagonal_inverses<float>(c, false, A, n, L.ldzlow, L.dinv_U.as<c64>(), L.inv_U.as<c64>());
   };
-  if (!grow || !L.sym_lu) upper();
+  DevBuf gl, gu, tmp;
+  const bool room = grow && gl.try_reserve((size_t)inv_bytes(n)) && gu.try_reserve((size_t)inv_bytes(n)) &&
+                    tmp.try_reserve((size_t)grow_scratch_bytes(n));
+  if (!room || !L.sym_lu) upper();
   L.leaf = kInvBlock;
-  if (!grow) return;
-  DevBuf gl((size_t)inv_bytes(n)), gu((size_t)inv_bytes(n));
-  grow_block_inverses(c, true, A, n, L.ldzlow, L.inv_L.as<c64>(), gl.as<c64>());
+  if (!room) return;
+  grow_block_inverses(c, true, A, n, L.ldzlow, L.inv_L.as<c64>(), gl.as<c64>(), tmp.as<c64>());
   if (L.sym_lu)
     transpose_block_inverses(c, A, n, L.ldzlow, gl.as<c64>(), gu.as<c64>());
   else
-    grow_block_inverses(c, false, A, n, L.ldzlow, L.inv_U.as<c64>(), gu.as<c64>());
+    grow_block_inverses(c, false, A, n, L.ldzlow, L.inv_U.as<c64>(), gu.as<c64>(), tmp.as<c64>());
   // synchronises, so the small inverses are read
   if (leaf_growth<float>(c, A, n, L.ldzlow, gl.as<c64>(), gu.as<c64>(), ib) <= kLeafGrowth) {
     L.inv_L = std::move(gl);
@@ -473,18 +475,17 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
     L->dinv_U.alloc((size_t)nblk * kPanel * kPanel * sizeof(c128));
     // no refinement follows: U12 by substitution, the block inverses for the solves after it
     info = lu_factor<double>(c, static_cast<c128*>(Z), n, ldz, L->dinv_L.as<c128>(), L->dinv_U.as<c128>(), L->perm);
-    if (info == 0 && inv64_bytes(n) > 0) {
+    if (info == 0 && inv64_bytes(n) > 0 && L->inv_L.try_reserve((size_t)inv64_bytes(n)) &&
+        L->inv_U.try_reserve((size_t)inv64_bytes(n))) {
       const c128* A = static_cast<const c128*>(Z);
-      L->inv_L.alloc((size_t)inv64_bytes(n));
-      L->inv_U.alloc((size_t)inv64_bytes(n));
       diagonal_inverses<double>(c, true, A, n, ldz, L->dinv_L.as<c128>(), L->inv_L.as<c128>());
       diagonal_inverses<double>(c, false, A, n, ldz, L->dinv_U.as<c128>(), L->inv_U.as<c128>());
-      if (leaf_growth<double>(c, A, n, ldz, L->inv_L.as<c128>(), L->inv_U.as<c128>(), kInvBlock) <= kLeafGrowth) {
+      if (leaf_growth<double>(c, A, n, ldz, L->inv_L.as<c128>(), L->inv_U.as<c128>(), kInvBlock) <= kLeafGrowth)
         L->leaf = kInvBlock;
-      } else {
-        L->inv_L.release();
-        L->inv_U.release();
-      }
+    }
+    if (L->leaf == 0) {
+      L->inv_L.release();
+      L->inv_U.release();
     }
   } else {
     L->dinv_L.alloc((size_t)nblk * kPanel * kPanel * sizeof(c64));
@@ -600,12 +601,17 @@ static void adjoint_node_rows(Context& c, const Level& l, const double* dx, int6
   adjoint_nodes(s, *l.mesh, l.W.as<c128>() + dir * l.mesh->h.nt * 18, Y.as<c128>(), R, Hn.as<c128>());
 }
 
-// Device bytes a level keeps for its lifetime.
-static int64_t level_bytes(int64_t n, int64_t nt, int32_t precision, int64_t n_dirs) {
+// Device bytes a level keeps for its lifetime; least: without the leaf inverses
+// that it does without when the device has no room.
+static int64_t level_bytes(int64_t n, int64_t nt, int32_t precision, int64_t n_dirs, bool least = false) {
   const int64_t nblk = (n + kPanel - 1) / kPanel;
   const int64_t es = precision == FOSB_PREC_FP64 ? 16 : 8;
   int64_t b = 4 * n + 2 * nblk * kPanel * kPanel * es + 18 * nt * 8 + 16 * n * n_dirs + 18 * nt * n_dirs * 16;
-  b += 2 * (precision == FOSB_PREC_MIXED ? inv_bytes(n) : inv64_bytes(n));
+  const int64_t small = (n + kInvBlock - 1) / kInvBlock * kInvBlock * kInvBlock * (int64_t)sizeof(c64);
+  if (precision == FOSB_PREC_MIXED)
+    b += 2 * (least ? small : inv_bytes(n));
+  else if (!least)
+    b += 2 * inv64_bytes(n);
   return b;
 }
 
@@ -1069,7 +1075,7 @@ fosb_status fosb_level_create(fosb_context* ctx, const fosb_mesh* mesh, double k
   fosb_opts o = opts_or_default(opts);
   bind(*ctx);
   check_device_memory(*ctx,
-                      level_bytes(mesh->h.ne, mesh->h.nt, precision, n_dirs) +
+                      level_bytes(mesh->h.ne, mesh->h.nt, precision, n_dirs, true) +
                           solve_work_bytes(mesh->h.ne, precision, std::max<int64_t>(n_dirs, 256)),
                       "the level");
   auto L = level_build(*ctx, mesh, k, precision, Z, ldz, Zlow, ldzlow, dirs, pols, n_dirs, field, o);
@@ -1143,7 +1149,7 @@ fosb_status fosb_level_create_pmchwt(fosb_context* ctx, const fosb_mesh* mesh, d
   fosb_opts o = opts_or_default(opts);
   bind(*ctx);
   const int64_t sd_bytes = field >= 0 ? (streamed ? 0 : n_dirs * n * 6LL * mesh->h.nt * 16) + 24LL * mesh->h.nt : 0;
-  check_device_memory(*ctx, level_bytes(n, 0, precision, n_dirs) + solve_work_bytes(n, precision, n_dirs) + sd_bytes,
+  check_device_memory(*ctx, level_bytes(n, 0, precision, n_dirs, true) + solve_work_bytes(n, precision, n_dirs) + sd_bytes,
                       "the level");
   auto L = level_build(*ctx, mesh, k0, precision, Z, ldz, Zlow, ldzlow, dirs, pols, n_dirs, FOSB_FIELD_NORMAL, o,
                        FOSB_FORM_PMCHWT, eps_r, mu_r, field, streamed);
@@ -1821,7 +1827,7 @@ fosb_status fosb_second_moment(fosb_context* ctx, const fosb_mesh* const* meshes
   {
     int64_t need = (int64_t)2 << 30;  // the assembly's two band buffers
     for (int32_t i = 0; i < n_levels; ++i) {
-      need += level_bytes(meshes[i]->h.ne, meshes[i]->h.nt, precision, n_dirs);
+      need += level_bytes(meshes[i]->h.ne, meshes[i]->h.nt, precision, n_dirs, true);
       if (!Z[i]) need += (int64_t)8 << 30;  // bands of the re-assembled residual
     }
     int64_t pair_max = 0;

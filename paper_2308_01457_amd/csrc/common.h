@@ -59,8 +59,8 @@ struct Pool {
   size_t cached_bytes = 0;                   // capacity held in free_blocks
   size_t live_bytes = 0;                     // capacity handed out and not returned
   int64_t n_device_allocs = 0;               // hipMalloc calls made
-  // fresh: never a cached block
-  void* get(size_t n, size_t& cap, bool fresh = false);
+  // fresh: never a cached block; optional: null when the device has no room
+  void* get(size_t n, size_t& cap, bool fresh = false, bool optional = false);
   void put(void* p, size_t cap);
   void trim();
   ~Pool();
@@ -117,6 +117,21 @@ struct DevBuf {
     if (n <= bytes) return;
     if (p && n <= cap) { bytes = n; return; }
     alloc(n, fresh);
+  }
+  // For buffers that only make a call faster: false, and nothing held, when the
+  // device has no room.  The pool's cached blocks stay (other calls need them).
+  bool try_reserve(size_t n) {
+    if (n <= cap) {
+      bytes = n;
+      return true;
+    }
+    release();
+    if (thread_no_alloc()) return false;
+    std::shared_ptr<Pool> pool = home ? home : thread_pool();
+    if (!pool || !(p = pool->get(n, cap, false, true))) return false;
+    from = std::move(pool);
+    bytes = n;
+    return true;
   }
   void release() {
     if (p) {
@@ -402,6 +417,9 @@ void gemm_ch(Context& ctx, int64_t M, int64_t N, int64_t K, double alpha, const 
 // tiles above the diag_nb-wide diagonal blocks.
 // split_scale (or split_scale_diag, for A = L and B = D L^T with D on the
 // diagonal of the given block) sets the scaling along K before the packing.
+// split_reserve makes room for products up to M x N x K; false when the device has
+// none, and the product then takes the FP32 instruction, which needs no buffers.
+bool split_reserve(Context& ctx, int64_t M, int64_t N, int64_t K);
 void split_scale(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K);
 void split_scale_diag(Context& ctx, const c64* A, int64_t lda, int64_t K);
 void split_pack_a(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K);
@@ -475,8 +493,12 @@ template <typename T>
 double leaf_growth(Context& ctx, const cplx<T>* A, int64_t n, int64_t lda, const cplx<T>* invL, const cplx<T>* invU,
                    int64_t ib);
 // W (inv_bytes(n)) <- inverses of the inv_block(n)-row diagonal blocks from those of kInvBlock rows (S):
-// halves merged by products, on ctx's stream (uses solve_tmp).  inv_block(n) > kInvBlock.
-void grow_block_inverses(Context& ctx, bool lower, const c64* A, int64_t n, int64_t lda, const c64* S, c64* W);
+// halves merged by products, on ctx's stream.  T: grow_scratch_bytes(n).  inv_block(n) > kInvBlock.
+inline int64_t grow_scratch_bytes(int64_t n) {
+  const int64_t ib = inv_block(n);
+  return (n + ib - 1) / ib * (ib / 2) * (ib / 2) * (int64_t)sizeof(c64);
+}
+void grow_block_inverses(Context& ctx, bool lower, const c64* A, int64_t n, int64_t lda, const c64* S, c64* W, c64* T);
 // The same of U = D L^T from those of L: invU = invL^T D^{-1}, D the diagonal of A.
 void transpose_block_inverses(Context& ctx, const c64* A, int64_t n, int64_t lda, const c64* invL, c64* invU);
 // gemm.hip: one doubling of the diagonal blocks' inverses in W (blocks of ib rows) from h to 2h rows;

@@ -694,11 +694,11 @@ static void gemm_launch(Context& ctx, int64_t M, int64_t N, int64_t K, double al
   }
   const int64_t Kp = std::max<int64_t>(K, 0);
   if constexpr (sizeof(T) == 4) {
-    if (split_pays(ctx, M, N, Kp)) {
+    // K in chunks, so that a packed operand (12 bytes an entry) stays within
+    // kSplitPackBytes; the later chunks add to C
+    const int64_t kc = std::max<int64_t>(256, kSplitPackBytes / (12 * std::max(M, N)) / 256 * 256);
+    if (split_pays(ctx, M, N, Kp) && split_reserve(ctx, M, N, std::min(kc, Kp))) {
       ProfScope prof(ctx, FOSB_K_GEMM_F32, flops, bytes);
-      // K in chunks, so that a packed operand (12 bytes an entry) stays within
-      // kSplitPackBytes; the later chunks add to C
-      const int64_t kc = std::max<int64_t>(256, kSplitPackBytes / (12 * std::max(M, N)) / 256 * 256);
       for (int64_t k0 = 0; k0 < Kp; k0 += kc) {
         const int64_t kn = std::min(kc, Kp - k0);
         const cplx<T>* Ak = CONJ_A ? A + k0 * lda : A + k0;

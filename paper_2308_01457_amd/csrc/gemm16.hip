@@ -361,9 +361,27 @@ static void zero_max(hipStream_t st, int* p, int64_t n) {
   FOSB_LAUNCH_CHECK();
 }
 
+// 32-row blocks of a packed A, one tile more than M needs (a product may start at
+// any multiple of 32 rows), and of a packed B.
+static int64_t blocks_a(int64_t M) { return ((M + kTileM - 1) / kTileM + 1) * (kTileM / 32); }
+static int64_t blocks_b(int64_t N) { return (N + kTileN - 1) / kTileN * (kTileN / 32); }
+static int64_t pack_bytes(int64_t nblk, int64_t K) {
+  return nblk * ((K + 15) / 16) * kPlanes * kChunk * (int64_t)sizeof(h8);
+}
+
+bool split_reserve(Context& ctx, int64_t M, int64_t N, int64_t K) {
+  if (ctx.pack_a.try_reserve((size_t)pack_bytes(blocks_a(M), K)) &&
+      ctx.pack_b.try_reserve((size_t)pack_bytes(blocks_b(N), K)) &&
+      ctx.pack_ma.try_reserve((size_t)M * sizeof(int)) && ctx.pack_mb.try_reserve((size_t)N * sizeof(int)) &&
+      ctx.pack_ke.try_reserve((size_t)K * 2 * sizeof(int)))
+    return true;
+  ctx.pack_a.release();   // the room is needed elsewhere
+  ctx.pack_b.release();
+  return false;
+}
+
 void split_scale(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K) {
   hipStream_t st = ctx.stream;
-  ctx.pack_ke.reserve((size_t)K * 2 * sizeof(int));
   int* ke = ctx.pack_ke.as<int>();
   int* ma = ke + K;
   zero_max(st, ma, K);
@@ -375,7 +393,6 @@ void split_scale(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64
 }
 
 void split_scale_diag(Context& ctx, const c64* A, int64_t lda, int64_t K) {
-  ctx.pack_ke.reserve((size_t)K * 2 * sizeof(int));
   hipLaunchKernelGGL(k_split_kexp_diag, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, ctx.stream, A, lda, K,
                      ctx.pack_ke.as<int>());
   FOSB_LAUNCH_CHECK();
@@ -385,8 +402,8 @@ void split_scale_diag(Context& ctx, const c64* A, int64_t lda, int64_t K) {
 static void pack(Context& ctx, const SplitSrc& s, int64_t R, int64_t K, int sign, int64_t nblk, DevBuf& buf,
                  DevBuf& mx) {
   const int64_t nkb = (K + 15) / 16;
-  buf.reserve((size_t)(nblk * nkb) * kPlanes * kChunk * sizeof(h8));
-  mx.reserve((size_t)R * sizeof(int));
+  if (buf.cap < (size_t)pack_bytes(nblk, K) || mx.cap < (size_t)R * sizeof(int))
+    fail(FOSB_E_DEVICE, "internal: packed operand without room");
   hipStream_t st = ctx.stream;
   const int* ke = ctx.pack_ke.as<int>();
   zero_max(st, mx.as<int>(), R);
@@ -399,12 +416,10 @@ static void pack(Context& ctx, const SplitSrc& s, int64_t R, int64_t K, int sign
 }
 
 void split_pack_a(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K) {
-  // one tile more than M needs: a product may start at any multiple of 32 rows
-  const int64_t nblk = ((M + kTileM - 1) / kTileM + 1) * (kTileM / 32);
-  pack(ctx, source_a(A, lda, conj_trans), M, K, 1, nblk, ctx.pack_a, ctx.pack_ma);
+  pack(ctx, source_a(A, lda, conj_trans), M, K, 1, blocks_a(M), ctx.pack_a, ctx.pack_ma);
 }
 void split_pack_b(Context& ctx, const c64* B, int64_t ldb, int64_t N, int64_t K) {
-  pack(ctx, SplitSrc{B, 1, ldb, 0}, N, K, -1, (N + kTileN - 1) / kTileN * (kTileN / 32), ctx.pack_b, ctx.pack_mb);
+  pack(ctx, SplitSrc{B, 1, ldb, 0}, N, K, -1, blocks_b(N), ctx.pack_b, ctx.pack_mb);
 }
 
 void split_gemm(Context& ctx, int64_t row0, int64_t M, int64_t N, int64_t K, double alpha, double beta, c64* C,

@@ -1397,7 +1397,8 @@ static void blocked_lu(LuRun<T>& R, Context& U, int64_t nb) {
     if (j + 1 == nblk) break;
     const int64_t k1 = kj + wj, w1 = std::min(nb, n - k1);
     if constexpr (sizeof(T) == 4) {
-      if (R.sym && n - k1 >= kSplitMinRows) {  // as below, the products on the fp16 matrix cores
+      // as below, the products on the fp16 matrix cores (the first step needs the most room)
+      if (R.sym && n - k1 >= kSplitMinRows && split_reserve(U, n - k1, std::min(kSplitChunk * nb, n - k1), wj)) {
         split_scale_diag(U, A + kj * lda + kj, lda, wj);
         split_pack_a(U, A + k1 * lda + kj, lda, false, n - k1, wj);
         auto update = [&](int64_t c0, int64_t cn) {
@@ -2008,13 +2009,13 @@ __global__ void k_inverse_spread(const c64* __restrict__ S, c64* __restrict__ W,
   W[(b * ib + r) * ib + c] = in ? S[(q * NL + r % NL) * NL + c % NL] : c64{0.f, 0.f};
 }
 
-void grow_block_inverses(Context& ctx, bool lower, const c64* A, int64_t n, int64_t lda, const c64* S, c64* W) {
+void grow_block_inverses(Context& ctx, bool lower, const c64* A, int64_t n, int64_t lda, const c64* S, c64* W,
+                         c64* T) {
   const int64_t ib = inv_block(n), nb = (n + ib - 1) / ib;
   hipLaunchKernelGGL(k_inverse_spread, dim3((unsigned)(ib / 256), (unsigned)ib, (unsigned)nb), dim3(256), 0, ctx.stream,
                      S, W, ib, (n + NL - 1) / NL);
   FOSB_LAUNCH_CHECK();
-  ctx.solve_tmp.reserve((size_t)nb * (ib / 2) * (ib / 2) * sizeof(c64) * 2);
-  for (int64_t h = NL; h < ib; h *= 2) inverse_merge(ctx.stream, lower, n, A, lda, W, ib, h, ctx.solve_tmp.as<c64>());
+  for (int64_t h = NL; h < ib; h *= 2) inverse_merge(ctx.stream, lower, n, A, lda, W, ib, h, T);
 }
 
 // 32 x 32 tiles through LDS; zero where d is (its factorisation has failed).

@@ -33,7 +33,7 @@ static size_t pool_round(size_t n) {
   return n < small ? (n + 4095) / 4096 * 4096 : (n + big - 1) / big * big;
 }
 
-void* Pool::get(size_t n, size_t& cap, bool fresh) {
+void* Pool::get(size_t n, size_t& cap, bool fresh, bool optional) {
   const size_t want = pool_round(n);
   if (!fresh) {
     std::lock_guard<std::mutex> lock(mu);
@@ -50,6 +50,10 @@ void* Pool::get(size_t n, size_t& cap, bool fresh) {
   }
   void* p = nullptr;
   hipError_t e = hipMalloc(&p, want);
+  if (e == hipErrorOutOfMemory && optional) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
     trim();  // give the cached blocks back and try once more

@@ -91,6 +91,55 @@ def test_trim_returns_packed_operands(fz):
     lv.close()
 
 
+def _fill(torch, dev, leave):
+    """Blocks that leave about that many bytes of the device free."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    blocks = []
+    for _ in range(8):
+        room = torch.cuda.mem_get_info()[0] - leave
+        if room < 4 << 20:
+            break
+        blocks.append(torch.empty(room, dtype=torch.uint8, device=dev))
+    free = torch.cuda.mem_get_info()[0]
+    print(f"[gpu] {free / 2 ** 20:.0f} MiB free (asked for {leave / 2 ** 20:.0f})", flush=True)
+    assert abs(free - leave) < 8 << 20
+    return blocks
+
+
+def test_calls_fit_without_the_optional_buffers(fz):
+    """The packed operands and the 1024-row leaf inverses are not asked of a device
+    that has no room for them: beside a block that leaves 230 MB (the level check
+    asks for 200, its grown inverses and packed panels would take 230 beside the 35
+    of the rest), then the work buffers of a wide solve (80 bytes an entry) and
+    100 MB, less than the packed coupling's 188, level and solve succeed."""
+    fosb, ctx, torch, m_ = fz
+    dev, n = ctx.torch_device, m_.n_edges
+    low = fosb.Context(0)
+    fosb.autotune(low, 0)   # no scratch output for timing either
+    m = fosb.Mesh(low, *workloads.geodesic_sphere(16))
+    Z = fosb.assemble(low, m, 2.0)
+    Zlow = torch.empty((n, n), dtype=torch.complex64, device=dev)
+    fosb.Level(low, m, 2.0, Z, fosb.MIXED, Zlow=Zlow).close()   # the streams and kernels exist before the device fills up
+    low.trim()
+    ctx.trim()
+    B = _rhs(torch, dev, n, 4)
+    X = B.clone()
+    ballast = _fill(torch, dev, 230 << 20)
+    lv = fosb.Level(low, m, 2.0, Z, fosb.MIXED, Zlow=Zlow)
+    del ballast
+    low.trim()
+    ballast = _fill(torch, dev, 80 * n * NRHS + (100 << 20))
+    X.copy_(B)
+    lv.solve(X)
+    del ballast
+    torch.cuda.empty_cache()
+    R = torch.matmul(Z, X) - B
+    assert float((R.norm(dim=0) / (Z.norm() * X.norm(dim=0))).max()) < 1e-9
+    lv.close()
+    low.close()
+
+
 def test_non_finite_entries_spread(fz):
     """A right-hand side column with an infinity or a NaN gives no finite column (or
     no convergence), and zero columns stay zero."""
