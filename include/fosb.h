@@ -321,7 +321,10 @@ fosb_status fosb_level_info(const fosb_level* level, int64_t* n, int32_t* precis
  * incidences keeps for its lifetime (permutation, diagonal-block inverses,
  * first moments, RHS weights, quadrature nodes), and the largest work buffer
  * bytes its construction and a refined solve with nrhs right-hand sides take
- * from the context's pool (nrhs <= 0: n_dirs).  Host-only. */
+ * from the context's pool (nrhs <= 0: n_dirs), with everything that makes them
+ * fast: on a device without that room, FP64 levels go without the 256-row inverses,
+ * MIXED ones keep the 256-row inverses at every size, and wide products go without
+ * packed operands.  Host-only. */
 fosb_status fosb_level_workspace_size(const fosb_mesh* mesh, int32_t precision, int64_t n_dirs, int64_t nrhs,
                                       int64_t* level_bytes, int64_t* work_bytes);
 /* The level's certificate from construction with opts.certify = 1 (0 otherwise):

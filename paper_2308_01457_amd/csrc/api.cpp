@@ -124,6 +124,8 @@ void level_solve_inplace(Context& ctx, const Level& L, c128* B, int64_t ldb, int
   c128* Rw = ctx.scratch[5].as<c128>();
   ctx.solve_tmp.reserve((size_t)n * nrhs * sizeof(c64));
   c64* Y32 = ctx.solve_tmp.as<c64>();  // L^{-1} P R between the two triangular solves
+  // once, instead of growing from product to product; without room each product sees for itself
+  (void)split_reserve(ctx, solve_pack_bytes(ctx.n_cu, n, nrhs, L.leaf));
   const c64* A32 = static_cast<const c64*>(L.Zlow);
   const c128* Z64 = static_cast<const c128*>(L.Z);
   copy_c128(s, B, ldb, Bo, nrhs, n, nrhs);
@@ -498,8 +500,7 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
       if (o.certify) matrix_certificate(true);
     }
     // the refined solves apply the factors through their diagonal-block inverses
-    const size_t small = (size_t)((n + kInvBlock - 1) / kInvBlock) * kInvBlock * kInvBlock * sizeof(c64);
-    L->inv_L.alloc(small);
+    L->inv_L.alloc((size_t)small_inv_bytes(n));
     bool factored = false;
     if (o.lu_pivoting == 0 && n >= 2048) {
       // symmetric matrix: no pivoting, half the trailing-update flops; kept when no
@@ -607,9 +608,8 @@ static int64_t level_bytes(int64_t n, int64_t nt, int32_t precision, int64_t n_d
   const int64_t nblk = (n + kPanel - 1) / kPanel;
   const int64_t es = precision == FOSB_PREC_FP64 ? 16 : 8;
   int64_t b = 4 * n + 2 * nblk * kPanel * kPanel * es + 18 * nt * 8 + 16 * n * n_dirs + 18 * nt * n_dirs * 16;
-  const int64_t small = (n + kInvBlock - 1) / kInvBlock * kInvBlock * kInvBlock * (int64_t)sizeof(c64);
   if (precision == FOSB_PREC_MIXED)
-    b += 2 * (least ? small : inv_bytes(n));
+    b += 2 * (least ? small_inv_bytes(n) : inv_bytes(n));
   else if (!least)
     b += 2 * inv64_bytes(n);
   return b;
@@ -1212,7 +1212,23 @@ fosb_status fosb_level_workspace_size(const fosb_mesh* mesh, int32_t precision, 
   REQUIRE(n_dirs >= 1 && n_dirs <= 4096, "need 1..4096 incidence directions");
   if (nrhs <= 0) nrhs = n_dirs;
   if (level_b) *level_b = level_bytes(mesh->h.ne, mesh->h.nt, precision, n_dirs);
-  if (work_b) *work_b = std::max<int64_t>((int64_t)2 << 30, solve_work_bytes(mesh->h.ne, precision, nrhs));
+  if (work_b) {
+    const int64_t n = mesh->h.ne;
+    const int n_cu = mesh->ctx ? mesh->ctx->n_cu : 256;
+    // beside the vectors: scratch output of tuning runs, partial products of split K (at most
+    // 64 MiB, and the smaller buffers they grew from)
+    int64_t solve = solve_work_bytes(n, precision, nrhs) + 16 * n * nrhs + ((int64_t)128 << 20), packs = 0, build = 0;
+    if (precision == FOSB_PREC_MIXED) {
+      // packed operands of the wide products; the inverses from which the leaves' are grown
+      const PackBytes f = factor_pack_bytes(n);
+      for (const int64_t ib : {inv_block(n), (int64_t)kInvBlock}) {
+        const PackBytes p = solve_pack_bytes(n_cu, n, nrhs, ib);
+        packs = std::max(packs, p.a + p.b);
+      }
+      if (inv_block(n) > kInvBlock) build = f.a + f.b + grow_scratch_bytes(n) + 2 * small_inv_bytes(n);
+    }
+    *work_b = std::max<int64_t>((int64_t)2 << 30, solve + packs) + build;
+  }
   API_END
 }
 

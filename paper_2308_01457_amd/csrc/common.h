@@ -417,9 +417,18 @@ void gemm_ch(Context& ctx, int64_t M, int64_t N, int64_t K, double alpha, const 
 // tiles above the diag_nb-wide diagonal blocks.
 // split_scale (or split_scale_diag, for A = L and B = D L^T with D on the
 // diagonal of the given block) sets the scaling along K before the packing.
-// split_reserve makes room for products up to M x N x K; false when the device has
-// none, and the product then takes the FP32 instruction, which needs no buffers.
+// split_reserve makes room for a product; false when the device has none, and the
+// product then takes the FP32 instruction, which needs no buffers.
+struct PackBytes {   // of the packed operands A and B
+  int64_t a = 0, b = 0;
+};
+PackBytes split_pack_bytes(int64_t M, int64_t N, int64_t K);
+bool split_reserve(Context& ctx, const PackBytes& p);
 bool split_reserve(Context& ctx, int64_t M, int64_t N, int64_t K);
+// The most that the products of a refined solve with leaves of ib rows take
+// (gemm.hip), and the updates of a factorisation (lu.hip; the update stream's).
+PackBytes solve_pack_bytes(int n_cu, int64_t n, int64_t nrhs, int64_t ib);
+PackBytes factor_pack_bytes(int64_t n);
 void split_scale(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K);
 void split_scale_diag(Context& ctx, const c64* A, int64_t lda, int64_t K);
 void split_pack_a(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K);
@@ -472,6 +481,9 @@ inline int64_t inv_block(int64_t n) { return n >= 2048 ? 1024 : kInvBlock; }
 inline int64_t inv_bytes(int64_t n) {
   const int64_t ib = inv_block(n);
   return (n + ib - 1) / ib * ib * ib * (int64_t)sizeof(c64);
+}
+inline int64_t small_inv_bytes(int64_t n) {   // of kInvBlock rows
+  return (n + kInvBlock - 1) / kInvBlock * kInvBlock * kInvBlock * (int64_t)sizeof(c64);
 }
 // An FP64 level keeps inverses of kInvBlock rows from this size on (8 KB a row; its
 // solves' leaves were 256-row substitutions against 32-row inverses, a column per

@@ -14,6 +14,7 @@
 // lane l is D[row][l%16] with row = 4*(l/16) + v for the FP32 instruction and
 // row = l/16 + 4*v for the FP64 one.
 #include <algorithm>
+#include <functional>
 #include <map>
 #include <type_traits>
 
@@ -668,9 +669,36 @@ constexpr int64_t kSplitPackBytes = (int64_t)1 << 30;
 // Complex64 products worth packing for the fp16 matrix cores (gemm16.hip): at
 // least 256 columns and 256 of K, so that reading and packing A (28 bytes an
 // entry) stays below the products saved, and tiles for half the compute units.
+static bool split_size(int n_cu, int64_t M, int64_t N, int64_t K) {
+  return N >= 256 && K >= 256 && ((M + 255) / 256) * ((N + 127) / 128) >= n_cu / 2;
+}
 static bool split_pays(const Context& ctx, int64_t M, int64_t N, int64_t K) {
   if (ctx.no_alloc || ctx.lean_tiles > 0) return false;
-  return N >= 256 && K >= 256 && ((M + 255) / 256) * ((N + 127) / 128) >= ctx.n_cu / 2;
+  return split_size(ctx.n_cu, M, N, K);
+}
+// K in chunks, so that a packed operand stays within kSplitPackBytes
+static int64_t split_chunk(int64_t M, int64_t N) {
+  return std::max<int64_t>(256, kSplitPackBytes / (12 * std::max(M, N)) / 256 * 256);
+}
+
+PackBytes solve_pack_bytes(int n_cu, int64_t n, int64_t nrhs, int64_t ib) {
+  PackBytes p;
+  auto product = [&](int64_t M, int64_t K) {
+    if (!split_size(n_cu, M, nrhs, K)) return;
+    const PackBytes q = split_pack_bytes(M, nrhs, std::min(split_chunk(M, nrhs), K));
+    p.a = std::max(p.a, q.a);
+    p.b = std::max(p.b, q.b);
+  };
+  std::function<void(int64_t)> solve = [&](int64_t m) {   // the splits of the triangular solves
+    if (m <= ib) return product(m, m);
+    const int64_t m1 = ib * (((m + ib - 1) / ib + 1) / 2);
+    product(m - m1, m1);
+    product(m1, m - m1);
+    solve(m1);
+    solve(m - m1);
+  };
+  if (nrhs >= 256) solve(n);
+  return p;
 }
 
 template <typename T, bool CONJ_A>
@@ -694,9 +722,7 @@ static void gemm_launch(Context& ctx, int64_t M, int64_t N, int64_t K, double al
   }
   const int64_t Kp = std::max<int64_t>(K, 0);
   if constexpr (sizeof(T) == 4) {
-    // K in chunks, so that a packed operand (12 bytes an entry) stays within
-    // kSplitPackBytes; the later chunks add to C
-    const int64_t kc = std::max<int64_t>(256, kSplitPackBytes / (12 * std::max(M, N)) / 256 * 256);
+    const int64_t kc = split_chunk(M, N);   // the later chunks add to C
     if (split_pays(ctx, M, N, Kp) && split_reserve(ctx, M, N, std::min(kc, Kp))) {
       ProfScope prof(ctx, FOSB_K_GEMM_F32, flops, bytes);
       for (int64_t k0 = 0; k0 < Kp; k0 += kc) {

@@ -369,15 +369,20 @@ static int64_t pack_bytes(int64_t nblk, int64_t K) {
   return nblk * ((K + 15) / 16) * kPlanes * kChunk * (int64_t)sizeof(h8);
 }
 
-bool split_reserve(Context& ctx, int64_t M, int64_t N, int64_t K) {
-  if (ctx.pack_a.try_reserve((size_t)pack_bytes(blocks_a(M), K)) &&
-      ctx.pack_b.try_reserve((size_t)pack_bytes(blocks_b(N), K)) &&
-      ctx.pack_ma.try_reserve((size_t)M * sizeof(int)) && ctx.pack_mb.try_reserve((size_t)N * sizeof(int)) &&
-      ctx.pack_ke.try_reserve((size_t)K * 2 * sizeof(int)))
-    return true;
+PackBytes split_pack_bytes(int64_t M, int64_t N, int64_t K) {
+  return PackBytes{pack_bytes(blocks_a(M), K), pack_bytes(blocks_b(N), K)};
+}
+
+bool split_reserve(Context& ctx, const PackBytes& p) {
+  if (ctx.pack_a.try_reserve((size_t)p.a) && ctx.pack_b.try_reserve((size_t)p.b)) return true;
   ctx.pack_a.release();   // the room is needed elsewhere
   ctx.pack_b.release();
   return false;
+}
+
+bool split_reserve(Context& ctx, int64_t M, int64_t N, int64_t K) {
+  return split_reserve(ctx, split_pack_bytes(M, N, K)) && ctx.pack_ma.try_reserve((size_t)M * sizeof(int)) &&
+         ctx.pack_mb.try_reserve((size_t)N * sizeof(int)) && ctx.pack_ke.try_reserve((size_t)K * 2 * sizeof(int));
 }
 
 void split_scale(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K) {

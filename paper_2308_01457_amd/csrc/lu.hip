@@ -1221,6 +1221,22 @@ constexpr int64_t kSymChunk = 2048;        // symmetric form: its rows start at 
 constexpr int64_t kSplitMinRows = 1024;
 constexpr int64_t kSplitChunk = 3;
 
+// Columns of a block, measured at N = 30720: pivoted FP64 1.300 -> 1.293 s with 768
+// against 512.  The symmetric form takes 768 at every size: its block column
+// costs one launch chain per 128 columns, and a wider block halves the passes
+// over the trailing matrix (N = 7680: level build 16.1 / 14.9 / 14.6 ms at 256 / 512 /
+// 768; 15870: 77 / 53 / 50; 1024 gained 4% at 7680 and lost 2% at 30720).
+static inline int64_t block_width(int64_t n, bool sym) { return sym || n >= 16384 ? 768 : 256; }
+
+// The larger of the symmetric form's updates and the pivoted one's.
+PackBytes factor_pack_bytes(int64_t n) {
+  if (n < kLookaheadMinN) return PackBytes{};
+  const int64_t ws = block_width(n, true), wp = block_width(n, false);
+  const PackBytes p = split_pack_bytes(n, std::min(n, kSplitChunk * ws), ws),
+                  q = split_pack_bytes(n, std::min(n, kTrailChunk), wp);
+  return PackBytes{std::max(p.a, q.a), std::max(p.b, q.b)};
+}
+
 static inline int64_t split_half(int64_t w) { return (int64_t)NB * (((w / NB) + 1) / 2); }
 
 template <typename T>
@@ -1494,14 +1510,7 @@ int64_t lu_factor(Context& ctx, cplx<T>* A, int64_t n, int64_t lda, cplx<T>* din
     }
     FOSB_HIP(hipEventRecord(ctx.lu_ev[1], s));
     FOSB_HIP(hipStreamWaitEvent(U.stream, ctx.lu_ev[1], 0));
-    // block width: 768 from N = 16384 (measured at N = 30720: symmetric FP32
-    // factorisation 0.325 -> 0.319 s, pivoted FP64 1.300 -> 1.293 s against 512;
-    // 1024 gained nothing for the symmetric form)
-    // The symmetric form takes 768 at every size: its block column costs one
-    // launch chain per 128 columns, and a wider block halves the passes over
-    // the trailing matrix (N = 7680: level build 16.1 / 14.9 / 14.6 ms at 256 /
-    // 512 / 768; 15870: 77 / 53 / 50; 1024 gained 4% at 7680 and lost 2% at 30720).
-    blocked_lu(R, U, R.sym || n >= 16384 ? 768 : 256);
+    blocked_lu(R, U, block_width(n, R.sym));
     if (R.sym && invL) block_inverses<T, true>(ctx, A, n, lda, dinvL, invL, 0, (n + NL - 1) / NL);
   } else {
     rec_lu(R, 0, n);
