@@ -19,7 +19,8 @@
  *     unknown, or below N = 2048 of the 256 x 256 ones, 4 KiB; an FP64 level from
  *     N = 2048 on those of the 256 x 256 ones, 8 KiB) and work buffers
  *     (O(N*nrhs) for solves; about 1 GiB for the assembly's two bands, 2 GiB where a
- *     level keeps no complex128 matrix; 256 MiB for a right-hand-side correlation;
+ *     level keeps no complex128 matrix; 256 MiB for a right-hand-side correlation
+ *     that is not being captured;
  *     for the packed operands of wide complex64 products 12 bytes an entry, at most
  *     1 GiB each in solves and 9 KiB per row in a symmetric factorisation) on the
  *     context's device; O(N^2) matrices are always caller buffers.  These device blocks come from a caching pool

@@ -373,8 +373,99 @@ __global__ __launch_bounds__(256) void k_cov_gather(BandEdges rows, int i1, cons
   *c = s;
 }
 
+// Without scratch, an entry per thread: the 12 nodes and weights of each RWG function of
+// 16 x 16 entries are staged in LDS and every pair of functions evaluates its 144
+// covariances.  For calls that cannot have the band above (see rhs_correlation).
+struct EdgeSide {
+  const int32_t* edge_tri;
+  const int32_t* edge_loc;
+  const double* nrm;
+  const double* qx;
+  const c128* W;
+  int ne, nt;
+};
+
+__device__ void stage_edge(const EdgeSide& L, int e, double (*x)[3], c128* w, double (*nn)[3]) {
+  // 12 nodes: 6 on T+ then 6 on T-
+  const int64_t Q = 6LL * L.nt;
+  for (int side = 0; side < 2; ++side) {
+    const int t = L.edge_tri[side * L.ne + e];
+    const int a = L.edge_loc[side * L.ne + e];
+    for (int q = 0; q < 6; ++q) {
+      const int64_t id = 6LL * t + q;
+      x[side * 6 + q][0] = L.qx[id];
+      x[side * 6 + q][1] = L.qx[Q + id];
+      x[side * 6 + q][2] = L.qx[2 * Q + id];
+      w[side * 6 + q] = L.W[((int64_t)t * 3 + a) * 6 + q];
+    }
+    nn[side][0] = L.nrm[t];
+    nn[side][1] = L.nrm[L.nt + t];
+    nn[side][2] = L.nrm[2 * L.nt + t];
+  }
+}
+
+__global__ __launch_bounds__(256) void k_rhs_correlation(EdgeSide A, EdgeSide B, CovParams cp, c128* __restrict__ C,
+                                                         int64_t ldc) {
+  __shared__ double xa[16][12][3], xb[16][12][3];
+  __shared__ c128 wa[16][12], wb[16][12];
+  __shared__ double na[16][2][3], nb[16][2][3];
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
+  if (threadIdx.x < 16) {
+    const int e = m0 + threadIdx.x;
+    if (e < A.ne) stage_edge(A, e, xa[threadIdx.x], wa[threadIdx.x], na[threadIdx.x]);
+  } else if (threadIdx.x < 32) {
+    const int r = threadIdx.x - 16;
+    const int e = n0 + r;
+    if (e < B.ne) stage_edge(B, e, xb[r], wb[r], nb[r]);
+  }
+  __syncthreads();
+  const int m = m0 + ty, n = n0 + tx;
+  if (m >= A.ne || n >= B.ne) return;
+  double cr = 0, ci = 0;
+  for (int q = 0; q < 12; ++q) {
+    const double x0 = xa[ty][q][0], x1 = xa[ty][q][1], x2 = xa[ty][q][2];
+    const double* nx = na[ty][q / 6];
+    double ar = 0, ai = 0;  // sum_q' K conj(W2)
+#pragma unroll 4
+    for (int p = 0; p < 12; ++p) {
+      const double d0 = x0 - xb[tx][p][0], d1 = x1 - xb[tx][p][1], d2 = x2 - xb[tx][p][2];
+      const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+      const double* ny = nb[tx][p / 6];
+      const double kv = cov_eval(cp, r2, nx[0] * ny[0] + nx[1] * ny[1] + nx[2] * ny[2]);
+      ar += kv * wb[tx][p].re;
+      ai -= kv * wb[tx][p].im;
+    }
+    const c128 w = wa[ty][q];
+    cr += w.re * ar - w.im * ai;
+    ci += w.re * ai + w.im * ar;
+  }
+  C[(int64_t)m * ldc + n] = c128{cr, ci};
+}
+
+static void correlation_without_scratch(hipStream_t s, const Level& l1, const Level& l2, const CovParams& cp,
+                                        int64_t dir, c128* C, int64_t ldc) {
+  const Mesh &m1 = *l1.mesh, &m2 = *l2.mesh;
+  const EdgeSide A{m1.edge_tri.as<int32_t>(), m1.edge_loc.as<int32_t>(), m1.nrm.as<double>(), l1.qx.as<double>(),
+                   l1.W.as<c128>() + dir * m1.h.nt * 18, (int)m1.h.ne, (int)m1.h.nt};
+  const EdgeSide B{m2.edge_tri.as<int32_t>(), m2.edge_loc.as<int32_t>(), m2.nrm.as<double>(), l2.qx.as<double>(),
+                   l2.W.as<c128>() + dir * m2.h.nt * 18, (int)m2.h.ne, (int)m2.h.nt};
+  const dim3 g((unsigned)((m2.h.ne + 15) / 16), (unsigned)((m1.h.ne + 15) / 16));
+  hipLaunchKernelGGL(k_rhs_correlation, g, dim3(256), 0, s, A, B, cp, C, ldc);
+  FOSB_LAUNCH_CHECK();
+}
+
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
+
 // Row triangles in bands whose local entries, for up to 16 incidences, fill
-// kCovBandBytes.
+// kCovBandBytes.  The band is the pool's, to be handed on after the call, so a
+// captured call, whose replays would write it later, does without; so does one
+// that the device has no room for.
 void rhs_correlation(Context& c, const Level& l1, const Level& l2, const fosb_cov& cov, int64_t dir0, int64_t nd,
                      c128* C, int64_t ldc, int64_t dstride) {
   constexpr int64_t kCovBandBytes = (int64_t)256 << 20, kChunk = 16;
@@ -382,11 +473,17 @@ void rhs_correlation(Context& c, const Level& l1, const Level& l2, const fosb_co
   const int nt1 = (int)m1.h.nt, nt2 = (int)m2.h.nt, ne1 = (int)m1.h.ne, ne2 = (int)m2.h.ne;
   const CovParams cp = cov_params(cov);
   hipStream_t s = c.stream;
+  const bool scratch = !capturing(s);
   for (int64_t d0 = 0; d0 < nd; d0 += kChunk) {
     const int dn = (int)std::min(kChunk, nd - d0);
     const int64_t row_bytes = 9LL * nt2 * dn * (int64_t)sizeof(c128);
     const int w = (int)std::min<int64_t>({nt1, 4 * 65535, std::max<int64_t>(4, kCovBandBytes / row_bytes / 4 * 4)});
-    DevBuf band((size_t)w * row_bytes);   // reused in the stream's order once released
+    DevBuf band;   // reused in the stream's order once released
+    if (!scratch || !band.try_reserve((size_t)w * row_bytes)) {
+      for (int d = 0; d < dn; ++d)
+        correlation_without_scratch(s, l1, l2, cp, dir0 + d0 + d, C + (d0 + d) * dstride, ldc);
+      continue;
+    }
     c128* P = band.as<c128>();
     const int64_t ldp = 3LL * nt2, pstride = 3LL * w * ldp;
     const CovSide A{m1.nrm.as<double>(), l1.qx.as<double>(), l1.W.as<c128>() + (dir0 + d0) * nt1 * 18, nt1};

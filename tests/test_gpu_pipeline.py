@@ -292,3 +292,38 @@ def test_stacked_correlations_over_bands_and_chunks(fz):
         _, alone, _ = fosb.second_moment(ctx, meshes, 0, 0, K1, fosb.FP64, cov, xh, d, p, dir=q)
         a, b = blocks[0][:, q * n:(q + 1) * n], alone[0]
         assert float((a - b).norm() / b.norm()) < 1e-11, q
+
+
+def test_captured_correlation_keeps_to_its_output(fz):
+    """fosb_rhs_correlation under stream capture, on a context that holds no cached
+    block: nothing is allocated, and replays with other work of the context between
+    them (a level that takes the pool's blocks) give the eager result and
+    leave that level as it was.  The replayed kernel sums in another order than the
+    eager one: 1e-13 of the block's norm."""
+    fosb, _, torch = fz
+    stream = torch.cuda.Stream()
+    cov = fosb.make_cov("gaussian", SIG, ELL)
+    with torch.cuda.stream(stream):
+        ctx = fosb.Context(0, stream)
+        m = fosb.Mesh(ctx, *workloads.icosphere(2))
+        lv = fosb.Level(ctx, m, K1, fosb.assemble(ctx, m, K1), fosb.FP64)
+        ref = fosb.rhs_correlation(ctx, lv, lv, cov)
+        out = torch.zeros_like(ref)
+        ctx.trim()
+        allocs = ctx.memory()["n_device_allocs"]
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            fosb.rhs_correlation(ctx, lv, lv, cov, C_out=out)
+        assert ctx.memory()["n_device_allocs"] == allocs
+        for _ in range(3):
+            out.zero_()
+            other = fosb.Level(ctx, m, K1, fosb.assemble(ctx, m, K1), fosb.FP64)
+            u = other.first_moment(0).clone()
+            graph.replay()
+            stream.synchronize()
+            assert float((out - ref).norm() / ref.norm()) < 1e-13
+            assert torch.equal(other.first_moment(0), u)
+            other.close()
+        lv.close()
+        ctx.close()
