@@ -700,17 +700,25 @@ static void pair_rhs(Context& c, const Level& a, const Level& b, const fosb_cov*
 static void rank_one_blocks(Context& c, const fosb_level* const* levels, int32_t n_levels, int32_t L0,
                             const std::vector<std::array<int32_t, 4>>& pairs, int64_t dir, void* const* blocks,
                             const int64_t* ldb, fosb_stats* st) {
-  std::vector<DevBuf> x(n_levels);
+  // the columns in the buffer that the two-sided solves transpose into: the context's, so
+  // that a captured call's replays find it
+  int64_t total = 0;
+  std::vector<int64_t> at(n_levels);
+  for (int32_t i = 0; i < n_levels; ++i) {
+    at[i] = total;
+    total += levels[i]->n;
+  }
+  c.scratch[0].reserve((size_t)total * sizeof(c128));
+  c128* x = c.scratch[0].as<c128>();
   for (int32_t i = 0; i < n_levels; ++i) {
     const fosb_level& l = *levels[i];
-    x[i].alloc((size_t)l.n * sizeof(c128));
-    copy_c128(c.stream, l.b.as<c128>() + dir, l.n_dirs, x[i].as<c128>(), 1, l.n, 1);
-    level_solve_inplace(c, l, x[i].as<c128>(), 1, 1, st, false, -1, first_moment_tol(l));
+    copy_c128(c.stream, l.b.as<c128>() + dir, l.n_dirs, x + at[i], 1, l.n, 1);
+    level_solve_inplace(c, l, x + at[i], 1, 1, st, false, -1, first_moment_tol(l));
   }
   for (size_t p = 0; p < pairs.size(); ++p) {
     const int i1 = pairs[p][0] - L0, i2 = pairs[p][1] - L0;
     ProfScope prof(c, FOSB_K_RHS, 0.0, 16.0 * (double)levels[i1]->n * (double)levels[i2]->n);
-    rank_one_correlation(c.stream, x[i1].as<c128>(), levels[i1]->n, x[i2].as<c128>(), levels[i2]->n, 1, 0,
+    rank_one_correlation(c.stream, x + at[i1], levels[i1]->n, x + at[i2], levels[i2]->n, 1, 0,
                          static_cast<c128*>(blocks[p]), ldb[p]);
     if (st) st->n_solves += 1;
   }

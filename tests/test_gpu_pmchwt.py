@@ -338,3 +338,39 @@ def test_rank_one_blocks_equal_two_sided_solves(fz, precision, tol):
         e = float((W[:, :n2] - S).norm() / S.norm())
         print(f"[gpu] rank-one block ({a},{b}) {precision}: separated vs two-sided {e:.1e}", flush=True)
         assert e < tol and float(W[:, n2:].abs().max()) == 0.0
+
+
+def test_captured_rank_one_blocks(fz):
+    """A captured fosb_correlation with rank-one data (FP64), replayed with a new level of the
+    context between capture and replay: the eager blocks, and that level's own
+    first moment as it was."""
+    fosb, _, torch = fz
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = fosb.Context(0, stream)
+        m = fosb.Mesh(ctx, *workloads.icosphere(1))
+
+        def level():
+            Z = fosb.assemble_pmchwt(ctx, m, 1.3, 2.1)
+            return fosb.Level.pmchwt(ctx, m, 1.3, 2.1, 1.0, Z, fosb.FP64)
+
+        lv = level()
+        ref = fosb.correlation(ctx, [lv], 1, 1, None, 0)[0].clone()
+        out = torch.zeros_like(ref)
+        fosb.correlation(ctx, [lv], 1, 1, None, 0, blocks=[out])
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            fosb.correlation(ctx, [lv], 1, 1, None, 0, blocks=[out])
+        others = [level() for _ in range(3)]   # their first moments have the columns' size
+        u = [o.first_moment(0).clone() for o in others]
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            stream.synchronize()
+            assert torch.equal(out, ref)
+            for o, v in zip(others, u):
+                assert torch.equal(o.first_moment(0), v)
+        for l in (lv, *others):
+            l.close()
+        ctx.close()
