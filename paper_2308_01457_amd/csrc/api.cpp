@@ -894,9 +894,9 @@ static void shape_pipeline(Context& c, const fosb_mesh* const* meshes, int32_t n
   }
   const bool by_level = adjoint_route_pays(v, meshes, n_levels, L0, n_dirs, n_a);
   std::vector<DevBuf> maps(by_level ? n_levels : 0);
+  std::vector<double> x(xhat, xhat + 3 * n_a);   // lives until far_field_impl has synchronised
+  DevBuf dx;
   if (by_level) {
-    std::vector<double> x(xhat, xhat + 3 * n_a);
-    DevBuf dx;
     upload(dx, x, c.stream);
     for (int32_t i = 0; i < n_levels; ++i) solved_far_field(c, *lv[i], dx.as<double>(), n_a, maps[i], st);
   }
