@@ -161,7 +161,9 @@ struct Orbits6 {
 // pairs, whose blocks come from the singular kernel.
 //
 // Bound by FP64 VALU issue, so it is written for few instructions per point
-// pair.  Lengths are in units of 1/k (the phase is the distance).  With
+// pair.  Lengths are in units of 1/unit, and unit = k (the phase is the distance)
+// unless OWN_UNIT: a k so small that squared distances in units of 1/k would
+// underflow.  With
 // R0 the distance of the centroids, e^{ir} = e^{iR0} e^{i(r - R0)}: for
 // NT > 0 the second factor has |r - R0| <= k (h_i + h_j) (h: largest distance
 // of a vertex from its centroid) and is a short series without range reduction,
@@ -178,9 +180,11 @@ struct Orbits6 {
 // moments of the coordinates).  Alone, on all pairs of nt = 5120: 1.8 ms (issue
 // alone would take 1.2, the blocks' 3.8 GB 0.9); 140 registers leave three
 // wavefronts per SIMD, and four (spilling 52 bytes) are slower.
-template <int NT>
-__global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Orbits6 R, double k, int i0, int j0,
+template <int NT, bool OWN_UNIT = false>
+__global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Orbits6 R, double k, double unit, int i0, int j0,
                                                           int jc, c128* __restrict__ Zc, int64_t ldc) {
+  static_assert(NT > 0 || !OWN_UNIT, "a small k has a short phase series");
+  const double ku = OWN_UNIT ? k / unit : 1.0;   // phase of a unit length
   __shared__ c128 stage[4][3 * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + wave);
@@ -204,11 +208,11 @@ __global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Orbits6 R,
       load_tri(md, j, Lj, cj);
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        dc[c] = k * (ci[c] - cj[c]);
+        dc[c] = unit * (ci[c] - cj[c]);
 #pragma unroll
         for (int v = 0; v < 3; ++v) {
-          Li[v][c] = k * (Li[v][c] - ci[c]);
-          Lj[v][c] = k * (Lj[v][c] - cj[c]);
+          Li[v][c] = unit * (Li[v][c] - ci[c]);
+          Lj[v][c] = unit * (Lj[v][c] - cj[c]);
         }
       }
     }
@@ -238,7 +242,7 @@ __global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Orbits6 R,
             const double ir = rsqrt_pos(r2);
             double sn, cs;
             if constexpr (NT > 0)
-              sincos_short<NT>(fma(r2, ir, -R0), &sn, &cs);
+              sincos_short<NT>(OWN_UNIT ? ku * fma(r2, ir, -R0) : fma(r2, ir, -R0), &sn, &cs);
             else
               sincos_phase(r2 * ir, &sn, &cs);
             const double gr = cs * ir, gi = sn * ir;
@@ -283,7 +287,8 @@ __global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Orbits6 R,
       const double rr = Nr[a][0] + Nr[a][1] + Nr[a][2], ri = Ni[a][0] + Ni[a][1] + Ni[a][2];
 #pragma unroll
       for (int b = 0; b < 3; ++b) {
-        D[a][b] = 0.25 * (Li[a][0] * Lj[b][0] + Li[a][1] * Lj[b][1] + Li[a][2] * Lj[b][2]);
+        const double q = OWN_UNIT ? 0.25 * ku * ku : 0.25;
+        D[a][b] = q * (Li[a][0] * Lj[b][0] + Li[a][1] * Lj[b][1] + Li[a][2] * Lj[b][2]);
         Ur[b] = fma(rr, D[a][b], Ur[b]);
         Ui[b] = fma(ri, D[a][b], Ui[b]);
         Vr[a] = fma(cr[b], D[a][b], Vr[a]);
@@ -294,10 +299,10 @@ __global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Orbits6 R,
     }
     // i / (4 pi) e^{iR0} times the areas
     double fr, fi;
-    const double sc = md.area[i] * md.area[j] * kInv4Pi;
+    const double sc = md.area[i] * md.area[j] * kInv4Pi * (OWN_UNIT ? 1.0 / ku : 1.0);
     if constexpr (NT > 0) {
       double sn, cs;
-      sincos_phase(R0, &sn, &cs);
+      sincos_phase(OWN_UNIT ? ku * R0 : R0, &sn, &cs);
       fr = -sc * sn;
       fi = sc * cs;
     } else {
@@ -717,16 +722,22 @@ namespace {
 // the general reduction is the cheaper one.
 constexpr double kShortPhase6 = 0.43, kShortPhase8 = 0.95;
 
+// Below this phase over the mesh's diameter the diameter is the unit of length:
+// distances of 1e-30 of it still have squares of 1e-300 in units of 1/k.
+constexpr double kOwnUnitPhase = 1e-120;
+
 // phase: bound of k |r - R0| over the mesh's pairs.
-void launch_regular(hipStream_t s, const MeshDev& md, const Orbits6& R, double k, double phase, int i0, int j0,
-                    int w, c128* Zc, int64_t ldc) {
+void launch_regular(hipStream_t s, const MeshDev& md, const Orbits6& R, double k, double diag, double phase, int i0,
+                    int j0, int w, c128* Zc, int64_t ldc) {
   const dim3 g((w + 63) / 64, (md.nt - i0 + 3) / 4), b(256);
-  if (phase <= kShortPhase6)
-    hipLaunchKernelGGL(k_assemble_regular<6>, g, b, 0, s, md, R, k, i0, j0, w, Zc, ldc);
+  if (k * diag < kOwnUnitPhase)
+    hipLaunchKernelGGL((k_assemble_regular<6, true>), g, b, 0, s, md, R, k, 1.0 / diag, i0, j0, w, Zc, ldc);
+  else if (phase <= kShortPhase6)
+    hipLaunchKernelGGL(k_assemble_regular<6>, g, b, 0, s, md, R, k, k, i0, j0, w, Zc, ldc);
   else if (phase <= kShortPhase8)
-    hipLaunchKernelGGL(k_assemble_regular<8>, g, b, 0, s, md, R, k, i0, j0, w, Zc, ldc);
+    hipLaunchKernelGGL(k_assemble_regular<8>, g, b, 0, s, md, R, k, k, i0, j0, w, Zc, ldc);
   else
-    hipLaunchKernelGGL(k_assemble_regular<0>, g, b, 0, s, md, R, k, i0, j0, w, Zc, ldc);
+    hipLaunchKernelGGL(k_assemble_regular<0>, g, b, 0, s, md, R, k, k, i0, j0, w, Zc, ldc);
   FOSB_LAUNCH_CHECK();
 }
 
@@ -832,7 +843,7 @@ void assemble_bands(Context& ctx, const Mesh& m, double k, int n_gauss, int64_t 
     const int buf = two ? (bi & 1) : 0;
     c128* Zc = Zbuf[buf];
     if (two && bi >= 2) FOSB_HIP(hipStreamWaitEvent(s, ev.e[2 + buf], 0));   // band bi - 2 consumed
-    launch_regular(s, md, R, k, phase, 0, j0, w, Zc, ldc);
+    launch_regular(s, md, R, k, h.diag, phase, 0, j0, w, Zc, ldc);
     launch_singular(ctx, m, k, n_gauss, h.tp_beg[j0], h.tp_beg[j1], j0, Zc, ldc);
     const int32_t* bc = dcols.as<int32_t>() + cbeg[bi];
     const int nbc = (int)(cbeg[bi + 1] - cbeg[bi]);
@@ -897,7 +908,7 @@ void assemble_efie(Context& ctx, const Mesh& m, double k, int n_gauss, c128* Z, 
     const int64_t ldc = 3LL * w;
     c128* Zc = band[buf].as<c128>();
     if (bi >= 2) FOSB_HIP(hipStreamWaitEvent(s, ev.e[2 + buf], 0));   // band bi - 2 gathered
-    launch_regular(s, md, R, k, phase, j0, j0, w, Zc, ldc);
+    launch_regular(s, md, R, k, h.diag, phase, j0, j0, w, Zc, ldc);
     if (one) {
       launch_singular(ctx, m, k, n_gauss, 0, (int)h.tp_i.size(), 0, Zc, ldc);
     } else {

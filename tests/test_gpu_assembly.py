@@ -57,3 +57,16 @@ def test_bands_from_the_diagonal_on(s, shuffled):
     at = np.array(corners + far + near)
     Zo = efie.entries(m, k, at[:, 0], at[:, 1])
     assert np.abs(Z[at[:, 0], at[:, 1]] - Zo).max() / np.abs(Z).max() < 1e-12
+
+
+@pytest.mark.parametrize("k", [1e-100, 1e-119, 1e-122, 1e-160])
+def test_wavenumbers_without_squares(k):
+    """Wavenumbers on both sides of the one below which the mesh's diameter is the
+    unit of length (1e-120 over the diameter); the square of 1e-160 underflows."""
+    from oracle import efie, mesh
+    from paper_2308_01457_amd import fosb
+    V, F = _stretched(1)
+    ctx = fosb.Context(0)
+    Z = fosb.assemble(ctx, fosb.Mesh(ctx, V, F), k).cpu().numpy()
+    Zo = efie.assemble(mesh.build(V, F), k)
+    assert np.abs(Z - Zo).max() / np.abs(Zo).max() < 1e-12
