@@ -417,7 +417,7 @@ static void mixed_leaves(Context& c, Level& L) {
   else
     grow_block_inverses(c, false, A, n, L.ldzlow, L.inv_U.as<c64>(), gu.as<c64>(), tmp.as<c64>());
   // synchronises, so the small inverses are read
-  if (leaf_growth<float>(c, A, n, L.ldzlow, gl.as<c64>(), gu.as<c64>(), ib) <= kLeafGrowth) {
+  if (leaf_growth<float>(c, A, n, L.ldzlow, gl.as<c64>(), gu.as<c64>(), ib) <= kLeafGrowth<float>) {
     L.inv_L = std::move(gl);
     L.inv_U = std::move(gu);
     L.leaf = ib;
@@ -482,7 +482,7 @@ static std::unique_ptr<fosb_level> level_build(Context& c, const fosb_mesh* mesh
       const c128* A = static_cast<const c128*>(Z);
       diagonal_inverses<double>(c, true, A, n, ldz, L->dinv_L.as<c128>(), L->inv_L.as<c128>());
       diagonal_inverses<double>(c, false, A, n, ldz, L->dinv_U.as<c128>(), L->inv_U.as<c128>());
-      if (leaf_growth<double>(c, A, n, ldz, L->inv_L.as<c128>(), L->inv_U.as<c128>(), kInvBlock) <= kLeafGrowth)
+      if (leaf_growth<double>(c, A, n, ldz, L->inv_L.as<c128>(), L->inv_U.as<c128>(), kInvBlock) <= kLeafGrowth<double>)
         L->leaf = kInvBlock;
     }
     if (L->leaf == 0) {

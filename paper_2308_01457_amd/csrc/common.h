@@ -495,11 +495,14 @@ inline int64_t inv64_bytes(int64_t n) {
 // A product with an inverse X of a leaf T loses up to u || |X| |T| || where
 // substitution loses u, so leaves are inverted (FP64) or grown to inv_block(n) rows
 // (MIXED) only while that norm, the largest over the leaves of both factors, is at
-// most kLeafGrowth: 2e-12 of a leaf's solution in FP64 and 1e-3 in FP32, less than
-// a refinement sweep contracts, at the very worst.  The EFIE and PMCHWT levels measured (N = 2430 and 7680, k = 0.05 .. 30,
-// at interior resonances too) have 60 .. 2500 over 256 rows and 90 .. 7500 over 1024;
-// a sphere flattened to a twentieth has 9e5 and 1e6, and takes the other leaves.
-constexpr double kLeafGrowth = 16384.0;
+// most this: at the very worst 2e-12 of a leaf's solution in FP64, and in FP32 8e-3,
+// by which a refinement sweep multiplies the error.  EFIE and PMCHWT levels of spheres,
+// ellipsoids of axes 0.7 .. 1.3 and superquadrics (N = 2430 .. 61440, k = 0.05 .. 30,
+// interior resonances among them) have 60 .. 4700 over 256 rows and 90 .. 19000 over
+// 1024.  A sphere flattened to a fifth has 4e4 and 4e5, and takes the other leaves;
+// one to a tenth 3e5 and 2e6.
+template <typename T>
+constexpr double kLeafGrowth = sizeof(T) == 8 ? 16384.0 : 131072.0;
 // That norm for inverses of ib rows; synchronises the stream.
 template <typename T>
 double leaf_growth(Context& ctx, const cplx<T>* A, int64_t n, int64_t lda, const cplx<T>* invL, const cplx<T>* invU,
