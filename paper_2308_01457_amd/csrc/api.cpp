@@ -387,11 +387,11 @@ static double inverse_norm1_estimate(Context& c, const Level& L) {
   return std::max(est, 2.0 * norm1() / (3.0 * (double)n));
 }
 
-// The first moments enter every right-hand side of their level, so on levels
-// whose factors come from split products their refinement aims below ir_tol.  With ir_tol = 1e-10
-// those up to N = 7680 stop after one sweep or two depending on the last digit of the first
-// correction (estimate 6e-11); one that stopped after one left 7.5e-10 in a
-// Sigma block.  The other sweep costs 0.5 ms there.
+// The first moments enter every right-hand side of their level, so on levels whose
+// factors come from split products their refinement aims below ir_tol.  With ir_tol
+// = 1e-10 those up to N = 7680 stop after one sweep or two depending on the last
+// digit of the first correction (estimate 6e-11); one that stopped after one left
+// 7.5e-10 in a Sigma block.  The other sweep costs 0.5 ms there.
 static double first_moment_tol(const Level& L) { return L.sym_lu ? 0.1 : 1.0; }
 
 // Leaf inverses of a MIXED level whose factors and kInvBlock-row inverses of L
@@ -838,12 +838,14 @@ static void far_field_impl(Context& c, const fosb_level* const* levels, int32_t 
 
 
 // Whether the variance of stacked incidences alone (no Sigma block kept) goes by
-// the adjoint route, FF Sigma FF^H = G_1 C G_2^H with G = FF Z^{-1}: 3 n_a
-// columns per level instead of nd N_l2 and nd N_l1 per pair.  By the solves' multiply-adds, with a
-// factor of two for the conjugate transposes and the products that stay; from
-// N = 2048 on, where solves are bound by products rather than launches and the
-// adjoint solves run on symmetric factors.  Six ellipsoids to N = 7680, 16 incidences, 181 angles,
-// mixed: 780 -> 243 ms.
+// the adjoint route, FF Sigma FF^H = G_1 C G_2^H with G = FF Z^{-1}: 3 n_a columns
+// per level instead of nd N_l2 and nd N_l1 per pair.  By the solves' multiply-adds,
+// with a factor of two for the conjugate transposes and the products that stay;
+// from N = 2048 on, where solves are bound by products rather than launches.  Six
+// ellipsoids to N = 7680, 16 incidences, 181 angles, mixed: 780 -> 243 ms.  Two of
+// them, 16 and 2 incidences, by pair and now: symmetric factors 769 -> 99 and
+// 174 -> 72 ms, pivoted 793 -> 138 and 207 -> 111, FP64 436 -> 122 and 204 -> 99
+// (other changes of the same build included).
 static bool adjoint_route_pays(const std::vector<std::array<int32_t, 4>>& pairs, const fosb_mesh* const* meshes,
                                int32_t n_levels, int32_t L0, int64_t nd, int64_t n_a) {
   double by_pair = 0.0, by_level = 0.0;

@@ -160,26 +160,25 @@ struct Orbits6 {
 // One thread per ordered triangle pair (i0 + row, j0 + jj); zeros for touching
 // pairs, whose blocks come from the singular kernel.
 //
-// Bound by FP64 VALU issue, so it is written for few instructions per point
-// pair.  Lengths are in units of 1/unit, and unit = k (the phase is the distance)
-// unless OWN_UNIT: a k so small that squared distances in units of 1/k would
-// underflow.  With
-// R0 the distance of the centroids, e^{ir} = e^{iR0} e^{i(r - R0)}: for
-// NT > 0 the second factor has |r - R0| <= k (h_i + h_j) (h: largest distance
-// of a vertex from its centroid) and is a short series without range reduction,
-// and the first is applied once per pair; NT = 0 takes the general sincos_phase of
-// r.  The centred nodes are d_o times a vertex (the centred vertices add to
-// zero), and the moments are kept barycentric, N[a][b] = sum w w' G lambda_a
-// lambda'_b: per orbit a plain sum and one term more, with the weights applied
-// after it.  The block then needs the dot products of the centred vertices only:
+// Bound by FP64 VALU issue, so it is written for few instructions per point pair.
+// Lengths are in units of 1/unit, and unit = k (the phase is the distance) unless
+// OWN_UNIT: a k so small that squared distances in units of 1/k would underflow.
+// With R0 the distance of the centroids, e^{ir} = e^{iR0} e^{i(r - R0)}: for NT > 0
+// the second factor has |r - R0| <= k (h_i + h_j) (h: largest distance of a vertex
+// from its centroid) and is a short series without range reduction, and the first
+// is applied once per pair; NT = 0 takes the general sincos_phase of r.  The
+// centred nodes are d_o times a vertex (the centred vertices add to zero), and the
+// moments are kept barycentric, N[a][b] = sum w w' G lambda_a lambda'_b: per orbit
+// a plain sum and one term more, with the weights applied after it.  The block then
+// needs the dot products of the centred vertices only:
 //   (i/k) alpha_a beta_b (I0 - k^2 M / 4),  M = Ixy - U_b - V_a + D_ab I0,
 //   D_ab = P~_a . Q~_b,  U_b = sum_a' (sum_b' N) D_a'b,  V_a = sum_b' (sum_a' N) D_ab',
 //   Ixy = sum N D,  I0 = sum N.
-// Vector instructions per point pair, all included: 48.7 with NT = 6, 52.6 with
-// NT = 8, 70.1 with NT = 0 (78.6 with sincos_phase on every point pair and
-// moments of the coordinates).  Alone, on all pairs of nt = 5120: 1.8 ms (issue
-// alone would take 1.2, the blocks' 3.8 GB 0.9); 140 registers leave three
-// wavefronts per SIMD, and four (spilling 52 bytes) are slower.
+// Vector instructions per point pair, all included: 48.7 with NT = 6, 52.6 with NT
+// = 8, 70.1 with NT = 0 (78.6 with sincos_phase on every point pair and moments of
+// the coordinates).  Alone, on all pairs of nt = 5120: 1.8 ms (issue alone would
+// take 1.2, the blocks' 3.8 GB 0.9); 140 registers leave three wavefronts per SIMD,
+// and four (spilling 52 bytes) are slower.
 template <int NT, bool OWN_UNIT = false>
 __global__ __launch_bounds__(256) void k_assemble_regular(MeshDev md, Orbits6 R, double k, double unit, int i0, int j0,
                                                           int jc, c128* __restrict__ Zc, int64_t ldc) {
@@ -862,14 +861,14 @@ void assemble_bands(Context& ctx, const Mesh& m, double k, int n_gauss, int64_t 
 }
 }  // namespace
 
-// Bands of column triangles with rows from the band on (struct Band): half of
-// the triangle pairs, and of the band buffer's traffic, of whole columns.  The
-// width follows the rows left, so that a band holds about kBandBytes; a mesh
-// whose blocks fit one band takes whole columns and its touching pairs'
-// blocks directly.  Two band buffers in turn: band b + 1 is integrated (bound by
-// the vector units) while band b is gathered (bound by memory) on the update stream.
-// N = 30720: 29.2 ms with 512 MiB bands (whole columns in 1 GiB bands: 49.4), 35 with
-// 128, 28.6 with 1024, the same order at N = 7680 (2.9, 2.9 and 3.0; 4.0).
+// Bands of column triangles with rows from the band on (struct Band): half of the
+// triangle pairs, and of the band buffer's traffic, of whole columns.  The width
+// follows the rows left, so that a band holds about kBandBytes; a mesh whose blocks
+// fit one band takes whole columns and its touching pairs' blocks directly.  Two
+// band buffers in turn: band b + 1 is integrated (bound by the vector units) while
+// band b is gathered (bound by memory) on the update stream. N = 30720: 29.2 ms
+// with 512 MiB bands (whole columns in 1 GiB bands: 49.4), 35 with 128, 28.6 with
+// 1024, the same order at N = 7680 (2.9, 2.9 and 3.0; 4.0).
 static constexpr int64_t kBandBytes = (int64_t)512 << 20;
 
 void assemble_efie(Context& ctx, const Mesh& m, double k, int n_gauss, c128* Z, int64_t ldz, c64* Zl,

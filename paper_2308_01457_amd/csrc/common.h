@@ -467,16 +467,17 @@ template <typename T>
 void trsm_lower_unit_ch(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* dinvL, int64_t k0, int64_t n,
                         cplx<T>* B, int64_t ldb, int64_t nrhs);
 // Inverses of the kInvBlock x kInvBlock diagonal blocks of the lower or the upper
-// factor (block b at inv + b kInvBlock^2, row-major, row stride kInvBlock; the
-// last block's slot is the identity outside its corner), and out-of-place
-// triangular solves of a whole factor that apply inverses of ib rows at the leaves:
-// X <- T^{-1} B or (_ch) T^{-H} B, with B (n x nrhs) consumed as workspace.
+// factor (block b at inv + b kInvBlock^2, row-major, row stride kInvBlock; the last
+// block's slot is the identity outside its corner), and out-of-place triangular
+// solves of a whole factor that apply inverses of ib rows at the leaves: X <-
+// T^{-1} B or (_ch) T^{-H} B, with B (n x nrhs) consumed as workspace.
 constexpr int kInvBlock = 256;
-// Rows of a leaf of those solves.  A narrow solve is a chain of launches, two
-// per leaf (N = 7680, one column: 59 products a factor with 256 rows, 15 with
-// 1024; a refined solve 2.0 -> 1.25 ms; 17 columns 11.5 -> 4.4), and a wide one runs its small products
-// far below the large ones' rate.  The inverses take 8 KB a row and factor; a level
-// below 2048 keeps the small ones (of two blocks of 1024 rows one would be mostly padding).
+// Rows of a leaf of those solves.  A narrow solve is a chain of launches, two per
+// leaf (N = 7680, one column: 59 products a factor with 256 rows, 15 with 1024; a
+// refined solve 2.0 -> 1.25 ms; 17 columns 11.5 -> 4.4), and a wide one runs its
+// small products far below the large ones' rate.  The inverses take 8 KB a row and
+// factor; a level below 2048 keeps the small ones (of two blocks of 1024 rows one
+// would be mostly padding).
 inline int64_t inv_block(int64_t n) { return n >= 2048 ? 1024 : kInvBlock; }
 inline int64_t inv_bytes(int64_t n) {
   const int64_t ib = inv_block(n);
@@ -495,20 +496,21 @@ inline int64_t inv64_bytes(int64_t n) {
 // A product with an inverse X of a leaf T loses up to u || |X| |T| || where
 // substitution loses u, so leaves are inverted (FP64) or grown to inv_block(n) rows
 // (MIXED) only while that norm, the largest over the leaves of both factors, is at
-// most this: at the very worst 2e-12 of a leaf's solution in FP64, and in FP32 8e-3,
-// by which a refinement sweep multiplies the error.  EFIE and PMCHWT levels of spheres,
-// ellipsoids of axes 0.7 .. 1.3 and superquadrics (N = 2430 .. 61440, k = 0.05 .. 30,
-// interior resonances among them) have 60 .. 4700 over 256 rows and 90 .. 19000 over
-// 1024.  A sphere flattened to a fifth has 4e4 and 4e5, and takes the other leaves;
-// one to a tenth 3e5 and 2e6.
+// most this: at the very worst 2e-12 of a leaf's solution in FP64, and in FP32
+// 8e-3, by which a refinement sweep multiplies the error.  EFIE and PMCHWT levels
+// of spheres, ellipsoids of axes 0.7 .. 1.3 and superquadrics (N = 2430 .. 61440, k
+// = 0.05 .. 30, interior resonances among them) have 60 .. 4700 over 256 rows and
+// 90 .. 19000 over 1024.  A sphere flattened to a fifth has 4e4 and 4e5, and takes
+// the other leaves; one to a tenth 3e5 and 2e6.
 template <typename T>
 constexpr double kLeafGrowth = sizeof(T) == 8 ? 16384.0 : 131072.0;
 // That norm for inverses of ib rows; synchronises the stream.
 template <typename T>
 double leaf_growth(Context& ctx, const cplx<T>* A, int64_t n, int64_t lda, const cplx<T>* invL, const cplx<T>* invU,
                    int64_t ib);
-// W (inv_bytes(n)) <- inverses of the inv_block(n)-row diagonal blocks from those of kInvBlock rows (S):
-// halves merged by products, on ctx's stream.  T: grow_scratch_bytes(n).  inv_block(n) > kInvBlock.
+// W (inv_bytes(n)) <- inverses of the inv_block(n)-row diagonal blocks from those
+// of kInvBlock rows (S): halves merged by products, on ctx's stream.  T:
+// grow_scratch_bytes(n).  inv_block(n) > kInvBlock.
 inline int64_t grow_scratch_bytes(int64_t n) {
   const int64_t ib = inv_block(n);
   return (n + ib - 1) / ib * (ib / 2) * (ib / 2) * (int64_t)sizeof(c64);
@@ -516,8 +518,8 @@ inline int64_t grow_scratch_bytes(int64_t n) {
 void grow_block_inverses(Context& ctx, bool lower, const c64* A, int64_t n, int64_t lda, const c64* S, c64* W, c64* T);
 // The same of U = D L^T from those of L: invU = invL^T D^{-1}, D the diagonal of A.
 void transpose_block_inverses(Context& ctx, const c64* A, int64_t n, int64_t lda, const c64* invL, c64* invU);
-// gemm.hip: one doubling of the diagonal blocks' inverses in W (blocks of ib rows) from h to 2h rows;
-// T: h^2 entries a pair
+// gemm.hip: one doubling of the diagonal blocks' inverses in W (blocks of ib rows)
+// from h to 2h rows; T: h^2 entries a pair
 void inverse_merge(hipStream_t s, bool lower, int64_t n, const c64* A, int64_t lda, c64* W, int64_t ib, int64_t h,
                    c64* T);
 template <typename T>

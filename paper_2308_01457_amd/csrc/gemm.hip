@@ -274,11 +274,11 @@ __global__ __launch_bounds__(256) void k_gemm(FOSB_GEMM_ARGS(T)) {
 //    each other's waits; 64 x 96, the least LDS reading per MFMA, leaves room for two and
 //    reads the next step's fragments while this step's MFMAs run (PIPE).
 // Accumulation over K is in steps of 4 from the lowest, as in gemm_tile, so that
-// tiles give identical results.
-// TFLOP/s (8 per complex multiply-add) of the best tile, planar LDS tiles with checked
-// loads before -> this kernel: 30720 x 480 x 30720 71 -> 84, 7680^3 76 -> 88,
-// 7680 x 7680 x 256 66 -> 76, 7680 x 273 x 7680 51 -> 59, 7680 x 480 x 7680 61 -> 73
-// (A^H B 56 -> 73), 3840 x 96 x 3840 35 -> 40.  The MFMAs alone would allow 105.
+// tiles give identical results. TFLOP/s (8 per complex multiply-add) of the best
+// tile, planar LDS tiles with checked loads before -> this kernel: 30720 x 480 x
+// 30720 71 -> 84, 7680^3 76 -> 88, 7680 x 7680 x 256 66 -> 76, 7680 x 273 x 7680 51
+// -> 59, 7680 x 480 x 7680 61 -> 73 (A^H B 56 -> 73), 3840 x 96 x 3840 35 -> 40.
+// The MFMAs alone would allow 105.
 template <bool CONJ_A, int WM, int WN>
 __device__ __forceinline__ void gemm64_tile(int64_t M, int64_t N, int64_t K, double alpha,
                                             const c128* __restrict__ A, int64_t lda, const c128* __restrict__ B,
@@ -661,14 +661,14 @@ static int pick_variant(Context& ctx, int64_t M, int64_t N, int64_t K, const cpl
   return best;
 }
 
-// A packed operand of a split product takes 12 bytes an entry.  1 GiB: solves
-// with 480 columns at N = 30720 took 196 ms; bounds of 384, 192 and 96 MiB, whose
+// A packed operand of a split product takes 12 bytes an entry.  1 GiB: solves with
+// 480 columns at N = 30720 took 196 ms; bounds of 384, 192 and 96 MiB, whose
 // shorter K chunks add more passes over C, 199, 213 and 231 ms.
 constexpr int64_t kSplitPackBytes = (int64_t)1 << 30;
 
-// Complex64 products worth packing for the fp16 matrix cores (gemm16.hip): at
-// least 256 columns and 256 of K, so that reading and packing A (28 bytes an
-// entry) stays below the products saved, and tiles for half the compute units.
+// Complex64 products worth packing for the fp16 matrix cores (gemm16.hip): at least
+// 256 columns and 256 of K, so that reading and packing A (28 bytes an entry) stays
+// below the products saved, and tiles for half the compute units.
 static bool split_size(int n_cu, int64_t M, int64_t N, int64_t K) {
   return N >= 256 && K >= 256 && ((M + 255) / 256) * ((N + 127) / 128) >= n_cu / 2;
 }
@@ -740,10 +740,10 @@ static void gemm_launch(Context& ctx, int64_t M, int64_t N, int64_t K, double al
   // split K when the output has too few tiles to fill the chip: about two
   // workgroups per CU, each still streaming at least 64 of K.  (With 256 instead,
   // from K = 512 on, the solves' leaf and coupling products ran on a few dozen
-  // workgroups.  N = 7680: FP64, 480 columns 5.3 -> 4.6 ms, 16 columns 2.9 -> 1.6; mixed, 17
-  // columns 4.4 -> 2.9; adjoint gradient 15.2 -> 12.7.)  The
-  // decision uses a fixed 64 x 64 reference tile, so it (and the summation
-  // order) does not depend on the tile variant chosen below.
+  // workgroups.  N = 7680: FP64, 480 columns 5.3 -> 4.6 ms, 16 columns 2.9 ->
+  // 1.6; mixed, 17 columns 4.4 -> 2.9; adjoint gradient 15.2 -> 12.7.)  The
+  // decision uses a fixed 64 x 64 reference tile, so it (and the summation order)
+  // does not depend on the tile variant chosen below.
   const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
   int64_t nz = 1;
   const int64_t want = 2LL * ctx.n_cu;

@@ -14,7 +14,8 @@
 // d_k instead.  A real product is then the sum of three fp16 products, l h, h l
 // and h h, accumulated in FP32 by v_mfma_f32_32x32x16_f16; the complex product
 // takes three real ones (3M, as in gemm.hip), whose operand sums re + im are
-// formed in FP32 before they are split.
+// formed in FP32 before they are split.  (Splitting into two half-precision parts:
+// Markidis et al., IPDPSW 2018; Ootomo and Yokota, IJHPCA 36, 2022.)
 //
 // The error of an entry of column j is thus below about K 2^-22 times the
 // largest term |a_ik b_kj| of that column over all rows i: normwise by column,

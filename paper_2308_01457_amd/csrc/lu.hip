@@ -140,10 +140,10 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// Partial-pivoting elimination of the node's rows (one row per thread, the
-// row's NB columns in registers).  The step loop is unrolled, so column j is
-// addressed statically and every row stays in place: a row chosen at step j
-// then holds L[j][0..j) (its multipliers) followed by U[j][j..].  Per step:
+// Partial-pivoting elimination of the node's rows (one row per thread, the row's NB
+// columns in registers).  The step loop is unrolled, so column j is addressed
+// statically and every row stays in place: a row chosen at step j then holds
+// L[j][0..j) (its multipliers) followed by U[j][j..].  Per step:
 // * every candidate forms its key and, speculatively, the reciprocal of its
 //   entry in column j; a wave maximum of the keys, and a ballot for the lowest lane
 //   holding it (all of it beside step j - 1's elimination of the other columns);
@@ -151,9 +151,10 @@ __device__ __forceinline__ void static_for(F&& f) {
 // * the winner stores its row and reciprocal; lane l of every 16 reads entries
 //   l and 16 + l, and the elimination broadcasts them from there.
 // A store from one lane takes the LDS as long as one from 64, and a broadcast read
-// as long as 64 different ones: with each wave's nominee storing its row, and every entry
-// read as a broadcast, these took two thirds of a step (FP64, 256 rows: 44 us a node, now 33; FP32
-// 34, now 29).  A row chosen earlier is eliminated with a multiplier of zero.
+// as long as 64 different ones: with each wave's nominee storing its row, and every
+// entry read as a broadcast, these took two thirds of a step (FP64, 256 rows: 44 us
+// a node, now 33; FP32 34, now 29).  A row chosen earlier is eliminated with a
+// multiplier of zero.
 template <typename T, int NW>
 __device__ __forceinline__ int gepp_node(cplx<T> (&a)[NB], bool valid, int nvalid, int w, int tid, int& step,
                                          cplx<T> (&prow)[NB], cplx<T>& pinv, cplx<T> (*lu)[NB + 1],
@@ -310,10 +311,10 @@ __device__ __forceinline__ void panel_root(cplx<T> (*tb)[NB + 1], const int* win
   }
   } else {
   // FP64: wavefront v inverts a 16 x 16 diagonal tile (v & 1) of L (v < 2) or of
-  // U, one column per lane as above; then X21 = -L22^{-1} (L21 L11^{-1}) and
-  // X12 = -U11^{-1} (U12 U22^{-1}), an entry of each per thread, the inner
-  // products in the unused halves.  (Sweeps over the whole block, one barrier a
-  // step, took 25 us of the root's 70; the root now takes 42.)
+  // U, one column per lane as above; then X21 = -L22^{-1} (L21 L11^{-1}) and X12
+  // = -U11^{-1} (U12 U22^{-1}), an entry of each per thread, the inner products
+  // in the unused halves.  (Sweeps over the whole block, one barrier a step, took
+  // 25 us of the root's 70; the root now takes 42.)
   static_assert(Node<T>::size == 256 && NB == 32, "an entry of a 16 x 16 tile per thread");
   __shared__ cplx<T> sx[NB][NB + 1], sy[NB][NB + 1];
   {
@@ -494,30 +495,24 @@ __global__ __launch_bounds__(Node<T>::size) void k_tslu_node(const cplx<T>* __re
 __device__ __forceinline__ float lane_value(float v, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
-__device__ __forceinline__ double lane_value(double v, int l) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b & 0xffffffffll), l);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)((unsigned long long)b >> 32), l);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
 
-// Symmetric factorisation without pivoting of a diagonal block of up to
-// kSymBlk = 128 columns, by one workgroup with the block in LDS (FP32):
-// A = L D L^T, U = D L^T.  Writes L \ U over the block, the inverses of the
-// 32 x 32 diagonal blocks of both factors, the inverse of the whole upper factor
-// (Uinv, 128 x 128 row-major: U^{-1} = L^{-T} D^{-1}, so one inversion serves
-// both factors), empty row-move lists and the first exactly zero pivot.
+// Symmetric factorisation without pivoting of a diagonal block of up to kSymBlk =
+// 128 columns, by one workgroup with the block in LDS (FP32): A = L D L^T, U = D
+// L^T.  Writes L \ U over the block, the inverses of the 32 x 32 diagonal blocks of
+// both factors, the inverse of the whole upper factor (Uinv, 128 x 128 row-major:
+// U^{-1} = L^{-T} D^{-1}, so one inversion serves both factors), empty row-move
+// lists and the first exactly zero pivot.
 //
-// Panels of 16 columns: up to three wavefronts factor the 16 x 16 diagonal tile
-// in registers, one row per lane, each on its own copy, with 48 rows below it
-// in the other lanes (so the multipliers need no inverse); the lower tiles to
-// the right are updated by L D L^T on the matrix cores, those of the next panel
-// before it is factored, the rest beside it.  The chain of dependent steps is what
-// bounds it: 60 us, of which the panels' 128 columns take 33 (93 us with branches in the
-// steps, one load in flight and no overlap).  In place of four 32-column panels with their own
-// root, multiplier, triangular-leaf and product launches, a 128-column step is
-// this launch, one product for the rows below, U12 and one product for the rest
-// of the block column.
+// Panels of 16 columns: up to three wavefronts factor the 16 x 16 diagonal tile in
+// registers, one row per lane, each on its own copy, with 48 rows below it in the
+// other lanes (so the multipliers need no inverse); the lower tiles to the right
+// are updated by L D L^T on the matrix cores, those of the next panel before it is
+// factored, the rest beside it.  The chain of dependent steps is what bounds it: 60
+// us, of which the panels' 128 columns take 33 (93 us with branches in the steps,
+// one load in flight and no overlap).  In place of four 32-column panels with their
+// own root, multiplier, triangular-leaf and product launches, a 128-column step is
+// this launch, one product for the rows below, U12 and one product for the rest of
+// the block column.
 constexpr int kSymBlk = 128;
 constexpr int kSymLd = kSymBlk + 1;
 
@@ -663,8 +658,9 @@ __global__ __launch_bounds__(512) void k_sym_diag(c64* __restrict__ A, int64_t l
     const c64 v = T[max(r, c) * kSymLd + min(r, c)], dr = d[r], u = cmul(dr, v);
     if (r < w && c < w) Ab[(int64_t)r * lda + c] = r > c ? v : (r == c ? dr : u);
   }
-  // L^{-1} in place: the 16 x 16 diagonal tiles (wavefront t inverts tile t, lane c
-  // its column c; the barrier keeps a step's loads from being moved before the last one's)
+  // L^{-1} in place: the 16 x 16 diagonal tiles (wavefront t inverts tile t, lane
+  // c its column c; the barrier keeps a step's loads from being moved before the
+  // last one's)
   {
     const int b = 16 * wave, c = lane & 15;
     c64 x[16];
@@ -734,9 +730,9 @@ __global__ __launch_bounds__(512) void k_sym_diag(c64* __restrict__ A, int64_t l
 }
 
 // Rows below a diagonal block of 128 columns: X <- X Uinv, in place (64 rows per
-// workgroup, all 128 columns, so a row's entries are read before any is
-// written).  Uinv is upper triangular: columns 32 j .. take K = 32 (j + 1).
-// Bound by the round trip of the block column through memory.
+// workgroup, all 128 columns, so a row's entries are read before any is written).
+// Uinv is upper triangular: columns 32 j .. take K = 32 (j + 1). Bound by the round
+// trip of the block column through memory.
 __global__ __launch_bounds__(512) void k_sym_mul(c64* X, int64_t ldx, int64_t m, const c64* __restrict__ Uinv) {
   __shared__ c64 S[64 * kSymLd];
   __shared__ c64 B[kSymBlk * (NB + 1)];
@@ -1211,7 +1207,7 @@ constexpr int kMoveStride = 1 + 4 * NB;
 static_assert(kMoveStride == kMoveStrideDev, "row-move list stride");
 constexpr int64_t kLookaheadMinN = 2048;  // smaller matrices: plain recursion on one stream
 constexpr int64_t kTrailChunk = 16384;     // columns per trailing-update launch (measured: 2048..16384)
-constexpr int64_t kSymChunk = 2048;        // symmetric form: its rows start at the chunk, so narrower chunks waste less
+constexpr int64_t kSymChunk = 2048;        // symmetric form in FP32: its rows start at the chunk, so narrower chunks waste less
 
 // Symmetric form on the fp16 matrix cores: fewer trailing rows than this keep
 // the FP32 instruction (under 24 tiles, each a chain of 48 K blocks), and an
@@ -2137,9 +2133,9 @@ static void trsm_inv(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>*
   }
 }
 
-// X <- T^{-1} B out of place, halves split at multiples of ib: B (rows k0 .. k0 + n) is consumed
-// as workspace, each leaf product writes its block of X directly, and the
-// coupling products read the solved part of X.  No copies.
+// X <- T^{-1} B out of place, halves split at multiples of ib: B (rows k0 .. k0 +
+// n) is consumed as workspace, each leaf product writes its block of X directly,
+// and the coupling products read the solved part of X.  No copies.
 template <typename T, bool LOWER>
 static void trsm_inv_oop(Context& ctx, const cplx<T>* A, int64_t lda, const cplx<T>* inv, int64_t ib, int64_t k0,
                          int64_t n, cplx<T>* B, int64_t ldb, cplx<T>* X, int64_t ldx, int64_t nrhs) {

@@ -250,12 +250,12 @@ static CovParams cov_params(const fosb_cov& cov) {
 
 // ------------------------------------------------------------------ right-hand-side correlation
 // C_d[m][n] = sum_{q in supp m} sum_{q' in supp n} W1_d[m,q] K(x_q, y_q') conj(W2_d[n,q'])
-// for each incidence d.  The covariance of the 6 x 6 nodes of a triangle pair serves
-// the nine pairs of RWG functions on it and every incidence, so it is evaluated
-// once per triangle pair: k_cov_blocks contracts it to the pair's 3 x 3 local
-// entries, k_cov_gather adds each entry's (up to) four.  One evaluation per pair of
-// functions instead, 144 nodes each, is nine times the exponentials: six
-// ellipsoids to N = 7680 with 16 incidences each took 243 ms, with this 147.
+// for each incidence d.  The covariance of the 6 x 6 nodes of a triangle pair
+// serves the nine pairs of RWG functions on it and every incidence, so it is
+// evaluated once per triangle pair: k_cov_blocks contracts it to the pair's 3 x 3
+// local entries, k_cov_gather adds each entry's (up to) four.  One evaluation per pair of functions instead, 144 nodes each, is
+// nine times the exponentials: six ellipsoids to N = 7680 with 16 incidences each
+// took 243 ms, with this 147.
 
 // A level's geometry and weights (the first incidence's; incidences nt * 18 apart).
 struct CovSide {
@@ -265,11 +265,11 @@ struct CovSide {
   int nt;
 };
 
-// Local entries of the triangle pairs (i0 + row, j), incidence d, at
-// P[d * dstride + (3 row + a) * ldp + 3 j + b].  One thread per pair and four rows
-// per workgroup (one per wavefront, its weights uniform): 36 covariances in registers,
-// then 432 FMAs per incidence; the 64 columns' weights pass through LDS, and the entries too, so
-// that stores are contiguous.
+// Local entries of the triangle pairs (i0 + row, j), incidence d, at P[d * dstride
+// + (3 row + a) * ldp + 3 j + b].  One thread per pair and four rows per workgroup
+// (one per wavefront, its weights uniform): 36 covariances in registers, then 432
+// FMAs per incidence; the 64 columns' weights pass through LDS, and the entries
+// too, so that stores are contiguous.
 __global__ __launch_bounds__(256) void k_cov_blocks(CovSide A, CovSide B, CovParams cp, int i0, int i1, int nd,
                                                     c128* __restrict__ P, int64_t ldp, int64_t dstride) {
   __shared__ c128 w2[18][65];
@@ -373,9 +373,10 @@ __global__ __launch_bounds__(256) void k_cov_gather(BandEdges rows, int i1, cons
   *c = s;
 }
 
-// Without scratch, an entry per thread: the 12 nodes and weights of each RWG function of
-// 16 x 16 entries are staged in LDS and every pair of functions evaluates its 144
-// covariances.  For calls that cannot have the band above (see rhs_correlation).
+// Without scratch, an entry per thread: the 12 nodes and weights of each RWG
+// function of 16 x 16 entries are staged in LDS and every pair of functions
+// evaluates its 144 covariances.  For calls that cannot have the band above (see
+// rhs_correlation).
 struct EdgeSide {
   const int32_t* edge_tri;
   const int32_t* edge_loc;
