@@ -57,24 +57,21 @@ struct SplitSrc {
 
 // Exponents of magnitudes: floor(log2 max(|re|, |im|)), denormals included; below
 // kLowExp for zero, above kHighExp for infinities and NaN, also after a scaling.
-constexpr int kZeroExp = -(1 << 20), kLowExp = -(1 << 19);
-constexpr int kInfExp = 1 << 20, kHighExp = 1 << 19;
-// Scaling along K of a term that adds nothing (A's column is all zero).
-constexpr int kNoTerm = INT32_MIN;
+constexpr int kZeroExp = -(1 << 23), kLowExp = -(1 << 19);
+constexpr int kInfExp = 1 << 23, kHighExp = 1 << 19;
+// Scaling along K of a term that adds nothing (A's column is all zero): B's
+// entries there count nothing (a large one would take the bits of its column's
+// others) and are scaled to zero, unless they are not finite.
+constexpr int kNoTerm = 1 << 21;
 
 __device__ __forceinline__ int mag_exp(c64 v) {
   const unsigned m = max(__float_as_uint(v.re) & 0x7fffffffu, __float_as_uint(v.im) & 0x7fffffffu);
-  const int e = m >= 0x00800000u ? (int)(m >> 23) - 127 : (31 - __clz((int)m)) - 149;
+  const int e = __builtin_amdgcn_frexp_expf(__uint_as_float(m)) - 1;
   return m == 0u ? kZeroExp : m >= 0x7f800000u ? kInfExp : e;
 }
 
-// Exponent of an entry scaled along K.  A term without effect counts nothing
-// (a large entry of B there would take the bits of its column's others),
-// unless the entry is not finite.
-__device__ __forceinline__ int scaled_exp(c64 v, int ke, int sign) {
-  const int e = mag_exp(v);
-  return ke == kNoTerm ? (e > kHighExp ? e : kZeroExp) : e + sign * ke;
-}
+// ke or, with flip = -1, -ke
+__device__ __forceinline__ int turned(int ke, int flip) { return (ke ^ flip) - flip; }
 
 __device__ __forceinline__ int wave_max_i32(int m) {
   for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
@@ -123,10 +120,10 @@ __global__ void k_split_kexp_diag(const c64* __restrict__ A, int64_t lda, int64_
   ke[k] = (e < kLowExp || e > kHighExp) ? 0 : e >> 1;
 }
 
-// Largest exponent of each row, scaled along K by 2^(sign e_k): workgroup
-// (x, y) takes 32 rows and 512 of K.
+// Largest exponent of each row, scaled along K by 2^e_k (2^-e_k with flip = -1):
+// workgroup (x, y) takes 32 rows and 512 of K.
 __global__ __launch_bounds__(256) void k_split_max(SplitSrc s, int64_t R, int64_t K, const int* __restrict__ ke,
-                                                   int sign, int* __restrict__ mx) {
+                                                   int flip, int* __restrict__ mx) {
   __shared__ int red[8][32];
   const int64_t r0 = (int64_t)blockIdx.x * 32, k0 = (int64_t)blockIdx.y * 512;
   if (s.ks == 1) {
@@ -136,7 +133,7 @@ __global__ __launch_bounds__(256) void k_split_max(SplitSrc s, int64_t R, int64_
       int m = kZeroExp;
       if (r < R)
         for (int64_t k = k0 + lane; k < min(K, k0 + 512); k += 64)
-          m = max(m, scaled_exp(s.p[r * s.rs + k], ke[k], sign));
+          m = max(m, mag_exp(s.p[r * s.rs + k]) + turned(ke[k], flip));
       m = wave_max_i32(m);
       if (lane == 0 && r < R) atomicMax(mx + r, m);
     }
@@ -147,7 +144,7 @@ __global__ __launch_bounds__(256) void k_split_max(SplitSrc s, int64_t R, int64_
   int m = kZeroExp;
   if (r < R)
     for (int64_t k = k0 + g; k < min(K, k0 + 512); k += 8)
-      m = max(m, scaled_exp(s.p[r * s.rs + k * s.ks], ke[k], sign));
+      m = max(m, mag_exp(s.p[r * s.rs + k * s.ks]) + turned(ke[k], flip));
   red[g][c] = m;
   __syncthreads();
   if (g == 0 && r < R) {
@@ -174,7 +171,7 @@ __device__ __forceinline__ void split2(float x, _Float16& h, _Float16& l) {
 // are contiguous along k are read 64 B per lane; columns of a row-major matrix
 // 256 B per k.
 __global__ __launch_bounds__(256) void k_split_pack(SplitSrc s, int64_t R, int64_t K, int64_t nkb,
-                                                    const int* __restrict__ ke, int sign,
+                                                    const int* __restrict__ ke, int flip,
                                                     const int* __restrict__ mx, h8* __restrict__ P) {
   const int64_t blk = blockIdx.y, kb = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (kb >= nkb) return;
@@ -186,11 +183,9 @@ __global__ __launch_bounds__(256) void k_split_pack(SplitSrc s, int64_t R, int64
   for (int q = 0; q < 8; ++q) {
     c64 v{0.f, 0.f};
     int eq = e;
-    if (row < R && k0 + q < K) {   // both loads at once
-      const int kq = ke[k0 + q];
+    if (row < R && k0 + q < K) {
       v = s.p[row * s.rs + (k0 + q) * s.ks];
-      v = kq == kNoTerm && mag_exp(v) <= kHighExp ? c64{0.f, 0.f} : v;
-      eq += kq == kNoTerm ? 0 : sign * kq;
+      eq += turned(ke[k0 + q], flip);
     }
     const float re = ldexpf(v.re, eq), im = ldexpf(s.conj ? -v.im : v.im, eq);
     _Float16 h, l;
@@ -405,7 +400,7 @@ void split_scale_diag(Context& ctx, const c64* A, int64_t lda, int64_t K) {
 }
 
 // nblk: 32-row blocks written, those past R with zeros
-static void pack(Context& ctx, const SplitSrc& s, int64_t R, int64_t K, int sign, int64_t nblk, DevBuf& buf,
+static void pack(Context& ctx, const SplitSrc& s, int64_t R, int64_t K, int flip, int64_t nblk, DevBuf& buf,
                  DevBuf& mx) {
   const int64_t nkb = (K + 15) / 16;
   if (buf.cap < (size_t)pack_bytes(nblk, K) || mx.cap < (size_t)R * sizeof(int))
@@ -414,15 +409,15 @@ static void pack(Context& ctx, const SplitSrc& s, int64_t R, int64_t K, int sign
   const int* ke = ctx.pack_ke.as<int>();
   zero_max(st, mx.as<int>(), R);
   hipLaunchKernelGGL(k_split_max, dim3((unsigned)((R + 31) / 32), (unsigned)((K + 511) / 512)), dim3(256), 0, st, s, R,
-                     K, ke, sign, mx.as<int>());
+                     K, ke, flip, mx.as<int>());
   FOSB_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_split_pack, dim3((unsigned)((nkb + 3) / 4), (unsigned)nblk), dim3(256), 0, st, s, R, K, nkb, ke,
-                     sign, mx.as<int>(), buf.as<h8>());
+                     flip, mx.as<int>(), buf.as<h8>());
   FOSB_LAUNCH_CHECK();
 }
 
 void split_pack_a(Context& ctx, const c64* A, int64_t lda, bool conj_trans, int64_t M, int64_t K) {
-  pack(ctx, source_a(A, lda, conj_trans), M, K, 1, blocks_a(M), ctx.pack_a, ctx.pack_ma);
+  pack(ctx, source_a(A, lda, conj_trans), M, K, 0, blocks_a(M), ctx.pack_a, ctx.pack_ma);
 }
 void split_pack_b(Context& ctx, const c64* B, int64_t ldb, int64_t N, int64_t K) {
   pack(ctx, SplitSrc{B, 1, ldb, 0}, N, K, -1, blocks_b(N), ctx.pack_b, ctx.pack_mb);
