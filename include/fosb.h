@@ -16,14 +16,15 @@
  *   - Handles (context, mesh, level) are owned by the library until *_destroy.
  *     The library allocates its own O(N) tables (a MIXED level also keeps the
  *     inverses of the 1024 x 1024 diagonal blocks of its factors, 16 KiB per
- *     unknown, or below N = 2048 of the 256 x 256 ones, 4 KiB; an FP64 level from
- *     N = 2048 on those of the 256 x 256 ones, 8 KiB) and work buffers
- *     (O(N*nrhs) for solves; about 1 GiB for the assembly's two bands, 2 GiB where a
- *     level keeps no complex128 matrix; 256 MiB for a right-hand-side correlation
- *     that is not being captured;
- *     for the packed operands of wide complex64 products 12 bytes an entry, at most
- *     1 GiB each in solves and 9 KiB per row in a symmetric factorisation) on the
- *     context's device; O(N^2) matrices are always caller buffers.  These device blocks come from a caching pool
+ *     unknown, or of the 256 x 256 ones, 4 KiB: below N = 2048, where the larger
+ *     ones would cost accuracy, or without room; an FP64 level from N = 2048 on
+ *     those of the 256 x 256 ones, 8 KiB, or none) and work buffers (O(N*nrhs)
+ *     for solves; about 1 GiB for the assembly's two bands, 2 GiB where a level
+ *     keeps no complex128 matrix; 256 MiB for a right-hand-side correlation that
+ *     is not being captured; for the packed operands of wide complex64 products
+ *     12 bytes an entry, at most 1 GiB each in solves and 9 KiB per row in a
+ *     symmetric factorisation) on the context's device; O(N^2) matrices are
+ *     always caller buffers.  These device blocks come from a caching pool
  *     per context (and per stream the context creates): a released block is
  *     kept and handed out again, so once a pass has run, repeating it on
  *     shapes of the same sizes makes no device allocation and no hipFree
@@ -592,8 +593,8 @@ fosb_status fosb_second_moment_batch(fosb_context* ctx, const fosb_batch_shape* 
  * the context and its auxiliary and worker streams.  The trailing update of
  * the blocked LU takes the 64x64 shape for its large complex64 products
  * without tuning.  All shapes give identical results, so tuning never changes
- * outputs.  mode: 0 off (built-in
- * shape: the first listed), 1 on, 2 on and forget the table, -1 query only.
+ * outputs.  mode: 0 off (built-in shape: the first listed), 1 on, 2 on and
+ * forget the table, -1 query only.
  * n_entries (may be NULL) receives the number of tuned buckets. */
 fosb_status fosb_autotune(fosb_context* ctx, int32_t mode, int32_t* n_entries);
 /* Export of the tuned table, in increasing key order: up to capacity entries
@@ -606,7 +607,9 @@ fosb_status fosb_autotune_table(fosb_context* ctx, int64_t* keys, int32_t* varia
                                 int64_t* n_entries);
 /* Adds n entries (host arrays) to the table, replacing entries with equal
  * keys, so that a table exported from one run settles the same buckets in
- * another without timing.  A variant out of range for its key's precision,
+ * another without timing.  Variants index this build's shapes, which a table
+ * from another build may have meant differently: results are the same, the
+ * speed need not be.  A variant out of range for its key's precision,
  * or a key with bits above 40 set, gives FOSB_E_INVALID and loads nothing. */
 fosb_status fosb_autotune_load(fosb_context* ctx, const int64_t* keys, const int32_t* variants, int64_t n);
 
