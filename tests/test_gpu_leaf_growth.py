@@ -90,3 +90,27 @@ def test_mixed_solves_keep_small_leaves(nrhs):
         assert float(((torch.matmul(A, X) - B).norm(dim=0) / (A.norm() * X.norm(dim=0))).max()) < 1e-9
         assert st.ir_sweeps <= 3
     lv.close()
+
+
+@pytest.mark.parametrize("surface, k", [("sphere", 2.7437), ("sphere", 4.4934), ("superquadric", 8.0)])
+def test_levels_near_resonances_and_with_edges(surface, k):
+    """N = 7680 at the first interior resonances of the sphere and on the superquadric:
+    FP64 residuals below 1e-13 |Z| |X| by column, mixed ones below 1e-9 after at most
+    five sweeps (a contraction of 1e-2, FP32 rounding times a condition of 1e5)."""
+    import torch
+    from paper_2308_01457_amd import fosb
+    ctx = fosb.Context(0)
+    m = fosb.Mesh(ctx, *(workloads.icosphere(4) if surface == "sphere" else workloads.superquadric(4)))
+    Z = fosb.assemble(ctx, m, k)
+    g = torch.Generator().manual_seed(1)
+    B = torch.randn((m.n_edges, 5), dtype=torch.complex128, generator=g).to(ctx.torch_device)
+    for precision, tol in ((fosb.FP64, 1e-13), (fosb.MIXED, 1e-9)):
+        lv = fosb.Level(ctx, m, k, Z.clone(), precision)
+        for adjoint in (False, True):
+            A = Z.mH.contiguous() if adjoint else Z
+            X, st = B.clone(), fosb.Stats()
+            (lv.solve_adjoint if adjoint else lv.solve)(X, st)
+            worst = float(((torch.matmul(A, X) - B).norm(dim=0) / (A.norm() * X.norm(dim=0))).max())
+            print(f"[gpu] {surface} k={k} {precision} adjoint {adjoint}: {worst:.1e}, {st.ir_sweeps} sweeps", flush=True)
+            assert worst < tol and st.ir_sweeps <= 5
+        lv.close()
